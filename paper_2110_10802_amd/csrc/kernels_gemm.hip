@@ -224,11 +224,6 @@ hipError_t launch_bf_wgrad(int N, int Ma, int Mb, int HW, const Operand &U, cons
                            float *partial, int *splits_out, hipStream_t st);
 
 // kernels_x3.hip
-bool x3_conv_plan(int N, int M, int K, int HW, int *qtiles, int *splits);
-size_t x3_conv_splitk_floats(int N, int M, int K, int HW);
-hipError_t launch_x3_conv1x1(int N, int M, int K, int HW, const void *wimg, const Operand &B,
-                             void *out, int epi, const void *res, float *psum, float *psq,
-                             float *splitk_ws, hipStream_t st);
 bool x3_wgrad_plan(int Ma, int Mb, int N, int HW, int *splits);
 hipError_t launch_x3_wgrad(int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
                            float *partial, int *splits_out, hipStream_t st);
@@ -247,12 +242,10 @@ hipError_t launch_big_wgrad_pair(bool bf16, int N, int MaA, int MbA, int HWA, co
 bool xw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt);
 hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *wimg, const Operand &B,
                              void *out, int epi, float *psum, float *psq, hipStream_t st);
-#ifndef MBK_X3
-#define MBK_X3 1
-#endif
-#ifndef MBK_XW
-#define MBK_XW 1
-#endif
+// kernels_xk.hip
+bool xk_conv_plan(bool bf16, int N, int M, int K, int HW, int pro, int *chunks);
+hipError_t launch_xk_conv1x1(bool bf16, int N, int M, int K, int HW, const void *wimg, const Operand &B,
+                             void *out, int epi, const void *res, float *psum, float *psq, hipStream_t st);
 #ifndef MBK_X3W
 #define MBK_X3W 1
 #endif
@@ -261,33 +254,32 @@ hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *wimg, cons
 static bool xw_applies(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi,
                        int *nt)
 {
-    return MBK_XW && !bf16 && !stores_operand && pro >= 0 && epi >= 0 && !wave_conv_kind(M, K, HW) &&
+    return !bf16 && !stores_operand && pro >= 0 && epi >= 0 && !wave_conv_kind(M, K, HW) &&
            xw_conv_plan(N, M, K, HW, pro, epi, nt);
 }
+// the other wide shapes: the contraction split over a workgroup's wavefronts (conv_xk)
+static bool xk_applies(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi,
+                       int *nt)
+{
+    return !stores_operand && pro >= 0 && epi >= 0 && !wave_conv_kind(M, K, HW) &&
+           !xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, nt) &&
+           xk_conv_plan(bf16, N, M, K, HW, pro, nt);
+}
 
-// fp32 convolutions of the wide blocks run on the bf16 matrix cores from a weight image
+// convolutions of the wide blocks that run on the bf16 matrix cores from a weight image
 bool conv1x1_uses_weight_image(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro,
                                int epi)
 {
-    int qtiles, splits;
-    if (xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
-        return true;
-    return MBK_X3 && !bf16 && !stores_operand && !wave_conv_kind(M, K, HW) &&
-           x3_conv_plan(N, M, K, HW, &qtiles, &splits);
-}
-
-int conv1x1_image_lane_order(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro,
-                             int epi)
-{
     int nt;
-    return xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt) ? 1 : 0;
+    return xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt) ||
+           xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt);
 }
 
 // which matrix-core instruction family serves a launch (values of mbconv_engine in mbconv.h)
 int conv1x1_engine(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi)
 {
     if (conv1x1_uses_weight_image(bf16, N, M, K, HW, stores_operand, pro, epi))
-        return 3;
+        return bf16 ? 2 : 3;
     int qtiles, splits;
     if (bf16 && !stores_operand && !wave_conv_kind(M, K, HW) && bf_conv_plan(N, M, K, HW, &qtiles, &splits))
         return 2;
@@ -313,28 +305,25 @@ int conv1x1_num_partials(bool bf16, int N, int M, int K, int HW, bool stores_ope
     if (kind)
         return wave_conv_num_partials(kind, N, M, HW);
     int wt, qtiles, splits;
-    if (xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
+    if (xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
+        xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
         return qtiles;
     if (bf16 && !stores_operand && bf_conv_plan(N, M, K, HW, &qtiles, &splits))
         return qtiles;
-    if (conv1x1_uses_weight_image(bf16, N, M, K, HW, stores_operand)) {
-        x3_conv_plan(N, M, K, HW, &qtiles, &splits);
-        return qtiles;
-    }
     if (!stores_operand && big_conv_plan(N, M, K, HW, &wt, &qtiles, &splits))
         return qtiles;
     return conv1x1_num_qtiles(N, HW);
 }
 
-size_t conv1x1_splitk_floats(bool bf16, int N, int M, int K, int HW, bool stores_operand)
+size_t conv1x1_splitk_floats(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi)
 {
-    if (stores_operand || wave_conv_kind(M, K, HW))
-        return 0;
     int qtiles, splits;
+    if (stores_operand || wave_conv_kind(M, K, HW) ||
+        xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
+        xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
+        return 0;
     if (bf16 && bf_conv_plan(N, M, K, HW, &qtiles, &splits))
         return bf_conv_splitk_floats(N, M, K, HW);
-    if (conv1x1_uses_weight_image(bf16, N, M, K, HW, stores_operand))
-        return x3_conv_splitk_floats(N, M, K, HW);
     return big_conv_splitk_floats(N, M, K, HW);
 }
 
@@ -350,11 +339,11 @@ hipError_t launch_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w,
                 return hipErrorInvalidValue;
             return launch_xw_conv1x1(N, M, K, HW, wimg, B, out, epi, psum, psq, st);
         }
-    }
-    if (conv1x1_uses_weight_image(bf16, N, M, K, HW, sc_store != nullptr)) {
-        if (!wimg)
-            return hipErrorInvalidValue;
-        return launch_x3_conv1x1(N, M, K, HW, wimg, B, out, epi, res, psum, psq, splitk_ws, st);
+        if (xk_applies(bf16, N, M, K, HW, sc_store != nullptr, B.pro, epi, &nt)) {
+            if (!wimg)
+                return hipErrorInvalidValue;
+            return launch_xk_conv1x1(bf16, N, M, K, HW, wimg, B, out, epi, res, psum, psq, st);
+        }
     }
     const int kind = sc_store ? 0 : wave_conv_kind(M, K, HW);
     if (kind)
@@ -403,6 +392,13 @@ hipError_t launch_conv1x1_affine(bool bf16, int N, int M, int K, int HW, const v
     if (wave_conv_kind(M, K, HW) == 2)
         return launch_wave_conv1x1(bf16, 2, N, M, K, HW, w, sAm, sAk, B, out, EPI_AFFINE, res, sc, sh,
                                    st);
+    {
+        // (the image is that of the training-mode role, whose kernel this one shares)
+        int nt;
+        if (xk_applies(bf16, N, M, K, HW, false, B.pro, EPI_STATS, &nt))
+            return wimg ? launch_xk_conv1x1(bf16, N, M, K, HW, wimg, B, out, EPI_AFFINE, res, sc, sh, st)
+                        : hipErrorNotSupported;
+    }
     if (wave_conv_kind(M, K, HW) || (sAm != 1 && sAk != 1) || HW % 4 != 0)
         return hipErrorNotSupported;
     int wt, qtiles, splits;
@@ -410,12 +406,6 @@ hipError_t launch_conv1x1_affine(bool bf16, int N, int M, int K, int HW, const v
         return splits == 1 ? launch_bf_conv1x1(N, M, K, HW, w, sAm, sAk, B, out, EPI_AFFINE, res, sc,
                                                sh, nullptr, st)
                            : hipErrorNotSupported;
-    if (conv1x1_uses_weight_image(bf16, N, M, K, HW, false)) {
-        x3_conv_plan(N, M, K, HW, &qtiles, &splits);
-        if (splits != 1 || !wimg)
-            return hipErrorNotSupported;
-        return launch_x3_conv1x1(N, M, K, HW, wimg, B, out, EPI_AFFINE, res, sc, sh, nullptr, st);
-    }
     if (big_conv_plan(N, M, K, HW, &wt, &qtiles, &splits) && splits == 1)
         return launch_big_conv1x1(bf16, N, M, K, HW, w, sAm, sAk, B, out, EPI_AFFINE, res, sc, sh,
                                   nullptr, st);

@@ -9,52 +9,13 @@
 // six bf16 MFMAs with fp32 accumulation reproduce the fp32 contraction to fp32 rounding level
 // (the dropped terms are of the size of one fp32 rounding of the product) at 6/16 of the fp32
 // MFMA's matrix-core time, and that time overlaps with the staging arithmetic.  Storage stays
-// fp32 in HBM; the three planes of an activation exist in LDS only, those of the conv weights
-// are written once per forward pass (x3_prep_kernel) in the order the kernels keep them in LDS.
-//
-// Same decomposition as kernels_big.hip / kernels_bf.hip: flattened batch (column q = n*HW +
-// pixel), 64 x 64 output tiles per workgroup of four wavefronts, the contraction 32 at a time
-// through two LDS buffers fed from a two-slot register ring, fixed-order split reductions.
-// Operand layout of the instruction: lane l holds, of A, row l%32 and the contraction indices
-// 8*(l/32)..+7; of B, column l%32 and the same indices; so both LDS tiles are [row or column][k]
-// with k contiguous (pitch BK+8 halfwords = 80 bytes: 16-byte reads of a quarter wavefront fall
-// on distinct banks), one such tile per plane.
+// fp32 in HBM; the three planes of an activation exist in LDS and registers only, those of the conv
+// weights are written once per forward pass (x3_prep_kernel) in the order the kernels read them.
 #include <algorithm>
-#include "mbconv_dev.h"
-#include "mbconv_launch.h"
+#include "mbconv_x3.h"
 
 
 namespace mbk {
-
-typedef float float16v __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-struct X3Operand {
-    const float *p0, *p1;
-    const float *c0, *c1, *c2, *gate;
-};
-
-// (x0, x1) -> three words, each the bf16 pair (plane value of x0 in bits 0-15, of x1 in 16-31)
-__device__ __forceinline__ void x3_split2(float x0, float x1, uint32_t (&w)[3])
-{
-    w[0] = bf16_pack2(x0, x1);
-    float r0 = x0 - __uint_as_float(w[0] << 16), r1 = x1 - __uint_as_float(w[0] & 0xffff0000u);
-    w[1] = bf16_pack2(r0, r1);
-    r0 -= __uint_as_float(w[1] << 16);
-    r1 -= __uint_as_float(w[1] & 0xffff0000u);
-    w[2] = bf16_pack2(r0, r1);
-}
-
-template <int PRO>
-__device__ __forceinline__ float x3_apply(float v0, float v1, float k0, float k1, float k2)
-{
-    if (PRO == PRO_NONE)
-        return v0;
-    if (PRO == PRO_BNSWISH_GATE)
-        return actf(fmaf(v0, k0, k1)) * k2;
-    return fmaf(k0, v0, fmaf(k1, v1, k2));
-}
 
 __device__ __forceinline__ void x3_ld4(const float *p, size_t i, float (&v)[4])
 {
@@ -64,33 +25,6 @@ __device__ __forceinline__ void x3_ld4(const float *p, size_t i, float (&v)[4])
     v[2] = t.z;
     v[3] = t.w;
 }
-// four consecutive floats at an address that is only 4-byte aligned (pixel runs of planes whose
-// size is not a multiple of four)
-typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ void x3_ld4u(const float *p, size_t i, float (&v)[4])
-{
-    const float4u t = *reinterpret_cast<const float4u *>(p + i);
-    v[0] = t[0];
-    v[1] = t[1];
-    v[2] = t[2];
-    v[3] = t[3];
-}
-
-// Halfword offset of element (row, k) in a [rows][BK = 32] plane of pitch 40 halfwords (80 bytes).
-// The four 16-byte groups of a row are permuted by bits 4-5 of the row: the transposing stores
-// (a wavefront writes one 32-bit k pair to each of 16 rows that are four apart, or to 64
-// consecutive rows) then fall on 64 distinct banks instead of 16, and the 16-byte reads of 16
-// consecutive rows stay conflict-free.
-__device__ __forceinline__ int x3_at(int row, int k)
-{
-    return row * 40 + ((((k >> 3) ^ (row >> 4)) & 3) << 3) + (k & 7);
-}
-
-__device__ __forceinline__ bf16x8 x3_lds8(const uint16_t *p)
-{
-    return *reinterpret_cast<const bf16x8 *>(p);
-}
-
 // acc += a*b for the three-plane operands (small terms first)
 __device__ __forceinline__ float16v x3_mfma6(const bf16x8 (&a)[3], const bf16x8 (&b)[3], float16v acc)
 {
@@ -103,28 +37,29 @@ __device__ __forceinline__ float16v x3_mfma6(const bf16x8 (&a)[3], const bf16x8 
     return acc;
 }
 
-// ---- weight images -------------------------------------------------------------------------
-// The A operand of a convolution (rows m, contraction index k) as bf16 planes, cut into tiles
-// of 64 rows x 32 k: tile (mt, ch), plane pl starts at halfword ((mt*CH + ch)*3 + pl)*2048 and
-// holds element (row, k) at x3_img_at(row, k): rows of 64 bytes whose four 16-byte groups are
-// permuted by bits 2-3 of the row, which keeps the 16-byte fragment reads of 16 consecutive
-// rows on distinct banks without padding.  A workgroup copies a tile to LDS as it is (one 16-byte
-// piece per thread and plane).  Rows and k past the end are zeros.
+// Halfword offset of element (row, k) in a plane of rows of 64 bytes (32 k) whose four 16-byte groups
+// are permuted by bits 2-3 of the row: the 16-byte reads of 16 consecutive rows fall on distinct banks
+// without padding.
 __device__ __forceinline__ int x3_img_at(int row, int k)
 {
     return row * 32 + ((((k >> 3) ^ (row >> 2)) & 3) << 3) + (k & 7);
 }
 
+// ---- weight images -------------------------------------------------------------------------
+// The A operand of a convolution (rows m, contraction index k) as bf16 planes (three for fp32 weights,
+// one for bf16), cut into tiles of 64 rows x 32 k in the lane order of v_mfma_f32_16x16x32_bf16:
+// tile (mt, ch) is [row tile of 16][plane][lane][8 k] with lane = row % 16 + 16 * (k / 8), so that a
+// wavefront reads an operand as 64 consecutive 16-byte pieces.  Rows and k past the end are zeros.
 struct X3PrepSet {
-    const float *w; // A(m, k) = w[m*sm + k*sk]
+    const void *w; // A(m, k) = w[m*sm + k*sk]
     int M, K, sm, sk;
     uint16_t *img;
     int CH, firstTile;
-    int lane_order; // the tile's arrangement: 0 as described above (conv_x3), 1 for conv_xw
 };
 struct X3PrepArgs {
     X3PrepSet s[4];
     int nsets;
+    int bf16; // the weights are stored as bf16: one plane
 };
 
 // one workgroup per tile: thread -> (row tid/4, eight k at 8*(tid%4))
@@ -143,34 +78,39 @@ __global__ __launch_bounds__(256) void x3_prep_kernel(X3PrepArgs a)
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int k = k0 + j;
-        v[j] = (m < S.M && k < S.K) ? S.w[(size_t)m * S.sm + (size_t)k * S.sk] : 0.f;
+        const size_t at = (size_t)m * S.sm + (size_t)k * S.sk;
+        v[j] = (m < S.M && k < S.K) ? (a.bf16 ? ld<bf16_t>((const bf16_t *)S.w, at) : ((const float *)S.w)[at])
+                                    : 0.f;
+    }
+    if (a.bf16) { // (uniform) the values are bf16 already: packing them rounds nothing
+        *reinterpret_cast<uint4 *>(S.img + ((size_t)mt * S.CH + ch) * 2048 + ((r >> 4) * 64 + (r & 15) + 16 * g) * 8) =
+            make_uint4(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]), bf16_pack2(v[4], v[5]),
+                       bf16_pack2(v[6], v[7]));
+        return;
     }
     uint32_t w[4][3];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
         x3_split2(v[2 * j], v[2 * j + 1], w[j]);
-    uint16_t *tile = S.img + ((size_t)mt * S.CH + ch) * 3 * 2048;
-    // lane order: the tile as four 16-row MFMA operands, [row tile][plane][lane] with lane =
-    // row % 16 + 16 * (k / 8): a wavefront reads an operand as 64 consecutive 16-byte pieces
-    const int at1 = (((r >> 4) * 3) * 64 + (r & 15) + 16 * g) * 8;
+    uint16_t *tile = S.img + ((size_t)mt * S.CH + ch) * 3 * 2048 + ((r >> 4) * 3 * 64 + (r & 15) + 16 * g) * 8;
 #pragma unroll
     for (int pl = 0; pl < 3; ++pl)
-        *reinterpret_cast<uint4 *>(tile + (S.lane_order ? at1 + pl * 512 : pl * 2048 + x3_img_at(r, 8 * g))) =
-            make_uint4(w[0][pl], w[1][pl], w[2][pl], w[3][pl]);
+        *reinterpret_cast<uint4 *>(tile + pl * 512) = make_uint4(w[0][pl], w[1][pl], w[2][pl], w[3][pl]);
 }
 
-size_t x3_weight_image_bytes(int M, int K)
+size_t x3_weight_image_bytes(bool bf16, int M, int K)
 {
-    return (size_t)((M + 63) / 64) * ((K + 31) / 32) * 3 * 2048 * sizeof(uint16_t);
+    return (size_t)((M + 63) / 64) * ((K + 31) / 32) * (bf16 ? 1 : 3) * 2048 * sizeof(uint16_t);
 }
 
 // Writes up to four images in one launch; set i: A(m,k) = w[i][m*sm[i] + k*sk[i]], M[i] x K[i].
-hipError_t launch_x3_prep(int nsets, const float *const *w, const int *M, const int *K, const int *sm,
-                          const int *sk, void *const *img, const int *lane_order, hipStream_t st)
+hipError_t launch_x3_prep(bool bf16, int nsets, const void *const *w, const int *M, const int *K, const int *sm,
+                          const int *sk, void *const *img, hipStream_t st)
 {
     if (nsets < 1 || nsets > 4)
         return hipErrorInvalidValue;
     X3PrepArgs a = {};
+    a.bf16 = bf16;
     int tiles = 0;
     for (int i = 0; i < nsets; ++i) {
         a.s[i].w = w[i];
@@ -179,7 +119,6 @@ hipError_t launch_x3_prep(int nsets, const float *const *w, const int *M, const 
         a.s[i].sm = sm[i];
         a.s[i].sk = sk[i];
         a.s[i].img = (uint16_t *)img[i];
-        a.s[i].lane_order = lane_order[i];
         a.s[i].CH = (K[i] + 31) / 32;
         a.s[i].firstTile = tiles;
         tiles += ((M[i] + 63) / 64) * a.s[i].CH;
@@ -187,435 +126,6 @@ hipError_t launch_x3_prep(int nsets, const float *const *w, const int *M, const 
     a.nsets = nsets;
     hipLaunchKernelGGL(x3_prep_kernel, dim3((unsigned)tiles), dim3(256), 0, st, a);
     return hipGetLastError();
-}
-
-// ---- convolution ---------------------------------------------------------------------------
-struct X3ConvArgs {
-    int M, K, HW;
-    uint32_t Q;
-    FastDiv divHW;
-    const uint16_t *img; // weight image of this convolution's A operand
-    int CH;              // its chunks of 32 along k
-    X3Operand B;
-    float *out;
-    const float *res;
-    float *psum, *psq;
-    int QT, MT;
-    float *partial;
-    int chunksPerSplit;
-};
-
-// out[n,m,pix] = sum_k A(m,k) * op(B)[n,k,pix], A given as a weight image.  Requirements
-// (checked by the host): K % 8 == 0, M % 4 == 0, HW % 4 == 0.
-//
-// PT (plane tiles, for planes of at most 64 pixels whose size is not a multiple of four: the
-// 7x7 stages): a tile's 64 columns are the pixels of ONE image (QT = N), columns past the plane
-// are zeros.  Pixel runs then never straddle an image; the last, partial run of a plane is read
-// and written four pixels wide starting at HW-4, overlapping the run before it with identical
-// values, so every access stays 16 bytes wide (4-byte aligned) and inside its plane.
-//
-// Persistent workgroups.  Output tiles are dealt out per XCD (blockIdx.x mod 8): XCD x owns the
-// pixel tiles qt = x, x+8, ... with all their row tiles, so the workgroups that read the same
-// activation tile share an L2; workgroup i of the XCD's Gx takes that list's tiles i, i+Gx, ...
-// The (tile, chunk) items of a workgroup form one stream: the register ring prefetches two
-// items ahead across tile boundaries, so the first chunks of the next tile are in flight while
-// the current tile's results leave, and the start-up latency is paid once per workgroup.
-template <int PRO, int EPI, bool PT>
-__global__ __launch_bounds__(256) void conv_x3_kernel(X3ConvArgs a)
-{
-    constexpr int BM = 64, BP = 64, BK = 32, PK = BK + 8, PC = BP + 4;
-    static_assert(PK == 40, "x3_at assumes a pitch of 40 halfwords");
-    constexpr int kPlaneA = BM * BK, kPlaneB = BP * PK; // halfwords
-    constexpr int kBuf = 3 * (kPlaneA + kPlaneB);
-    // one operand buffer during the contraction, the fp32 output tile after it
-    __shared__ __attribute__((aligned(16))) uint16_t smem[kBuf];
-    static_assert(kBuf * 2 >= 64 * PC * 4, "output tile must fit into the operand buffer");
-    float(*Ct)[PC] = reinterpret_cast<float(*)[PC]>(smem);
-    auto As = [&](int pl) __attribute__((always_inline)) { return smem + pl * kPlaneA; };
-    auto Bs = [&](int pl) __attribute__((always_inline)) { return smem + 3 * kPlaneA + pl * kPlaneB; };
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wp = wave & 1;
-    const int xcd = blockIdx.x & 7, wi = blockIdx.x >> 3, Gx = gridDim.x >> 3;
-    const int nTx = a.QT > xcd ? ((a.QT - xcd + 7) >> 3) * a.MT : 0; // tiles of this XCD
-    if (wi >= nTx)
-        return;
-    const int nT = (nTx - wi + Gx - 1) / Gx; // tiles of this workgroup
-    int cbeg = 0, cend = (a.K + BK - 1) / BK;
-    if (EPI == EPI_PARTIAL) {
-        cbeg = blockIdx.y * a.chunksPerSplit;
-        cend = min(cbeg + a.chunksPerSplit, cend);
-    }
-    const int nch = cend - cbeg, total = nT * nch;
-    if (nch <= 0) // cannot happen with the host's split plan; keeps every image access in bounds
-        return;
-
-    // ---- prefetch cursor: the item the next load takes, and what depends on its tile ----
-    // this thread's pixel run (tile columns brow .. brow+3) and k pair of a B chunk
-    const int c0 = 4 * (tid & 15), kp = tid >> 4;
-    const bool runIn = !PT || c0 < a.HW;                            // the run holds pixels of the plane
-    const int brow = (PT && runIn && c0 + 4 > a.HW) ? a.HW - 4 : c0; // the partial run starts at HW-4
-    int pk = 0, pc = cbeg, pmt = 0;
-    bool bvalid = false;
-    uint32_t bn = 0;
-    size_t bbase = 0;
-    auto set_ptile = [&](int k) __attribute__((always_inline)) {
-        const int t = wi + min(k, nT - 1) * Gx; // past the last tile: the last one again (never consumed)
-        const int qt = xcd + 8 * (t / a.MT);
-        pmt = t - (t / a.MT) * a.MT;
-        if (PT) {
-            bvalid = runIn;
-            bn = (uint32_t)qt;
-            bbase = (size_t)bn * a.K * a.HW + (runIn ? brow : 0);
-        } else {
-            const uint32_t qb = (uint32_t)qt * BP + (uint32_t)c0;
-            bvalid = qb < a.Q;
-            bn = bvalid ? fdiv(qb, a.divHW) : 0u;
-            bbase = (size_t)bn * a.K * a.HW + (bvalid ? qb - bn * (uint32_t)a.HW : 0u);
-        }
-    };
-    auto advance = [&]() __attribute__((always_inline)) {
-        if (++pc == cend) { // uniform over the workgroup; no memory access inside
-            pc = cbeg;
-            set_ptile(++pk);
-        }
-    };
-
-    // Staged items live in a ring of two register slots: item j is loaded during iteration j-2
-    // and written to LDS at the end of iteration j-1.  All loads are unconditional (indices
-    // clamped into the tensor) and validity is an AND mask applied on the way into LDS, so no
-    // branch and no use of loaded data sits between a load and the MFMAs it should overlap.
-    //
-    // A: the tile's three planes are copied as they are, 16 bytes per thread and plane.
-    u32x4 ra[2][3];
-    // B: thread -> (four pixels at 4*(tid%16), k pair tid/16); the pair of a pixel is one 32-bit
-    // LDS store per plane.
-    float rb0[2][2][4], rb1[2][2][PRO == PRO_BNBWD ? 4 : 1];
-    float bk0[2][2], bk1[2][2], bk2[2][2];
-    uint32_t rbok[2][2];
-    auto load = [&](int s) __attribute__((always_inline)) {
-        const uint16_t *tile = a.img + ((size_t)pmt * a.CH + pc) * 3 * kPlaneA;
-#pragma unroll
-        for (int pl = 0; pl < 3; ++pl)
-            ra[s][pl] = *reinterpret_cast<const u32x4 *>(tile + pl * kPlaneA + 8 * tid);
-        const int k0 = pc * BK;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int k = k0 + 2 * kp + j, kc = min(k, a.K - 1);
-            rbok[s][j] = (bvalid && k < a.K) ? 0xffffffffu : 0u;
-            if (PT)
-                x3_ld4u(a.B.p0, bbase + (size_t)kc * a.HW, rb0[s][j]);
-            else
-                x3_ld4(a.B.p0, bbase + (size_t)kc * a.HW, rb0[s][j]);
-            if constexpr (PRO == PRO_BNBWD) {
-                if (PT)
-                    x3_ld4u(a.B.p1, bbase + (size_t)kc * a.HW, rb1[s][j]);
-                else
-                    x3_ld4(a.B.p1, bbase + (size_t)kc * a.HW, rb1[s][j]);
-            }
-            if (PRO != PRO_NONE) {
-                bk0[s][j] = a.B.c0[kc];
-                bk1[s][j] = a.B.c1[kc];
-                bk2[s][j] = PRO == PRO_BNBWD ? a.B.c2[kc] : a.B.gate[(size_t)bn * a.K + kc];
-            }
-        }
-    };
-    auto store = [&](int s) __attribute__((always_inline)) {
-#pragma unroll
-        for (int pl = 0; pl < 3; ++pl)
-            *reinterpret_cast<u32x4 *>(As(pl) + 8 * tid) = ra[s][pl];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float v[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                v[j] = and_mask(x3_apply<PRO>(rb0[s][j][r], rb1[s][j][PRO == PRO_BNBWD ? r : 0], bk0[s][j],
-                                              bk1[s][j], bk2[s][j]),
-                                rbok[s][j]);
-            uint32_t w[3];
-            x3_split2(v[0], v[1], w);
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl)
-                *reinterpret_cast<uint32_t *>(Bs(pl) + x3_at(brow + r, 2 * kp)) = w[pl];
-        }
-    };
-
-    float16v acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-        acc[r] = 0.f;
-
-    // ---- results of the current tile; register r of lane l is row 8*(r/4)+4*(l/32)+r%4, column l%32 ----
-    auto epilogue = [&](int ck) __attribute__((always_inline)) {
-        const int t = wi + ck * Gx;
-        const int qt = xcd + 8 * (t / a.MT), m0 = (t - (t / a.MT) * a.MT) * BM;
-        const uint32_t q0 = PT ? (uint32_t)qt * (uint32_t)a.HW : (uint32_t)qt * BP; // first pixel of the tile
-        if constexpr (EPI != EPI_PARTIAL) {
-            // Through LDS, so that 16 lanes own the pixels of one output row: 16-byte accesses, one
-            // pixel-index division per thread, and a row's BN statistics summed inside those 16
-            // lanes.  (The chunk's barrier has passed: the operand buffer is free.)
-            const int pg = tid & 15;
-            bool valid;
-            uint32_t n, pix;
-            int fresh = 0; // first element of the run that no other run covers
-            if (PT) {
-                valid = runIn;
-                n = (uint32_t)qt;
-                pix = runIn ? (uint32_t)brow : 0u;
-                fresh = runIn ? c0 - brow : 0;
-            } else {
-                const uint32_t q = q0 + 4u * pg;
-                valid = q < a.Q;
-                n = valid ? fdiv(q, a.divHW) : 0u;
-                pix = valid ? q - n * (uint32_t)a.HW : 0u;
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                Ct[wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)][wp * 32 + (lane & 31)] = acc[r];
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int row = (tid >> 4) + 16 * i, m = m0 + row;
-                const bool ok = valid && m < a.M;
-                float v[4];
-                if (PT) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        v[j] = Ct[row][(runIn ? brow : 0) + j];
-                } else {
-                    const float4 c = *reinterpret_cast<const float4 *>(&Ct[row][4 * pg]);
-                    v[0] = c.x;
-                    v[1] = c.y;
-                    v[2] = c.z;
-                    v[3] = c.w;
-                }
-                const size_t idx = ((size_t)n * a.M + min(m, a.M - 1)) * a.HW + pix;
-                float rr[4] = {0.f, 0.f, 0.f, 0.f};
-                if (EPI == EPI_RES || (EPI == EPI_AFFINE && a.res)) {
-                    if (PT)
-                        x3_ld4u(a.res, idx, rr);
-                    else
-                        x3_ld4(a.res, idx, rr);
-                }
-                if (EPI == EPI_RES) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        v[j] += rr[j];
-                }
-                if (EPI == EPI_AFFINE) { // psum / psq carry the row's scale and shift
-                    const float osc = a.psum[min(m, a.M - 1)], osh = a.psq[min(m, a.M - 1)];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        v[j] = fmaf(v[j], osc, osh) + rr[j];
-                }
-                if (ok) {
-                    if (PT) {
-                        float4u o;
-                        o[0] = v[0];
-                        o[1] = v[1];
-                        o[2] = v[2];
-                        o[3] = v[3];
-                        *reinterpret_cast<float4u *>(a.out + idx) = o;
-                    } else {
-                        *reinterpret_cast<float4 *>(a.out + idx) = make_float4(v[0], v[1], v[2], v[3]);
-                    }
-                }
-                if (EPI == EPI_STATS) {
-                    float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float sv = (ok && j >= fresh) ? v[j] : 0.f;
-                        s1 += sv;
-                        s2 = fmaf(sv, sv, s2);
-                    }
-                    s1 = row16_sum(s1);
-                    s2 = row16_sum(s2);
-                    if (pg == 0 && m < a.M) {
-                        a.psum[(size_t)m * a.QT + qt] = s1;
-                        a.psq[(size_t)m * a.QT + qt] = s2;
-                    }
-                }
-            }
-        } else {
-            // a split contraction: the raw partial tile, lanes along the pixels
-            const int col = wp * 32 + (lane & 31);
-            const uint32_t q = q0 + (uint32_t)col;
-            const bool valid = PT ? col < a.HW : q < a.Q;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int m = m0 + wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                if (valid && m < a.M)
-                    a.partial[((size_t)blockIdx.y * a.M + m) * a.Q + q] = acc[r];
-            }
-        }
-    };
-
-    // PT: tile columns past the plane must read as zeros, and the pixel runs do not cover all of
-    // them (the partial run starts early); they are cleared before the first item and again after
-    // every output tile, which passes through the same LDS.  (A store and a barrier follow.)
-    auto zero_pad = [&]() __attribute__((always_inline)) {
-        if (PT) {
-            for (int i = tid; i < 3 * BP * 4; i += 256) {
-                const int pl = i / (BP * 4), row = (i >> 2) & (BP - 1), g = i & 3;
-                if (row >= a.HW)
-                    *reinterpret_cast<uint4 *>(Bs(pl) + row * PK + 8 * g) = make_uint4(0u, 0u, 0u, 0u);
-            }
-        }
-    };
-    zero_pad();
-    set_ptile(0);
-    load(0);
-    advance();
-    load(1);
-    advance();
-    store(0);
-    __syncthreads();
-    int ck = 0, cj = 0; // current tile of this workgroup, chunk within it
-    auto body = [&](int u) __attribute__((always_inline)) {
-        load(u); // slot u is free: its item went to LDS last iteration
-        advance();
-        __builtin_amdgcn_sched_barrier(0); // loads first, then the MFMAs, then the staging arithmetic
-#pragma unroll
-        for (int s = 0; s < BK / 16; ++s) {
-            bf16x8 av[3], bv[3];
-            const int ko = 16 * s + 8 * (lane >> 5);
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl) {
-                av[pl] = x3_lds8(As(pl) + x3_img_at(wm * 32 + (lane & 31), ko));
-                bv[pl] = x3_lds8(Bs(pl) + x3_at(wp * 32 + (lane & 31), ko));
-            }
-            acc = x3_mfma6(av, bv, acc);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads(); // every wavefront has read the chunk
-        if (++cj == nch) { // uniform: the tile is complete
-            epilogue(ck);
-            __syncthreads(); // the output tile has left LDS
-            zero_pad();
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                acc[r] = 0.f;
-            cj = 0;
-            ++ck;
-        }
-        store(u ^ 1); // past the last item: a repeated item that is never consumed
-        __syncthreads();
-    };
-    int it = 0;
-    for (; it + 1 < total; it += 2) {
-        body(0);
-        body(1);
-    }
-    if (it < total)
-        body(0);
-}
-
-// Plan: 64 x 64 tiles; the contraction is split when the tiles alone cannot fill the chip
-// (`qtiles` is then the second stage's count of statistics partials per row).
-bool x3_conv_plan(int N, int M, int K, int HW, int *qtiles, int *splits)
-{
-    const long long Q = (long long)N * HW;
-    if (K % 8 != 0 || M % 4 != 0 || Q >= (1ll << 31) || K < 32 || M < 32)
-        return false;
-    // planes whose size is not a multiple of four: one image per tile if a plane fits (the 7x7
-    // stages); larger ones stay with kernels_big.hip
-    const bool pt = HW % 4 != 0;
-    if (pt && (HW > 64 || HW < 4))
-        return false;
-    *qtiles = pt ? N : (int)((Q + 63) / 64);
-    *splits = 1;
-    const long long tiles = (long long)*qtiles * ((M + 63) / 64);
-    const int chunks = (K + 31) / 32;
-    if (tiles < 384 && chunks >= 8) {
-        long long s = (768 + tiles - 1) / tiles;
-        if (s > chunks / 2)
-            s = chunks / 2;
-        if (s > 16)
-            s = 16;
-        const int per = (int)((chunks + s - 1) / s);
-        *splits = (chunks + per - 1) / per;
-        if (*splits > 1)
-            *qtiles = (int)((Q + 1023) / 1024);
-    }
-    return true;
-}
-
-size_t x3_conv_splitk_floats(int N, int M, int K, int HW)
-{
-    int qtiles, splits;
-    if (!x3_conv_plan(N, M, K, HW, &qtiles, &splits) || splits == 1)
-        return 0;
-    return (size_t)splits * M * N * HW;
-}
-
-// kernels_big.hip
-hipError_t launch_splitk_finish_f32(const float *partial, int S, int M, uint32_t Q, int HW, void *out,
-                                    const void *res, int epi, float *psum, float *psq, int NT,
-                                    hipStream_t st);
-
-hipError_t launch_x3_conv1x1(int N, int M, int K, int HW, const void *wimg, const Operand &B,
-                             void *out, int epi, const void *res, float *psum, float *psq,
-                             float *splitk_ws, hipStream_t st)
-{
-    int qtiles, splits;
-    if (!x3_conv_plan(N, M, K, HW, &qtiles, &splits) || !wimg)
-        return hipErrorInvalidValue;
-    if (splits > 1 && (!splitk_ws || epi == EPI_AFFINE))
-        return hipErrorInvalidValue;
-    X3ConvArgs a;
-    a.M = M;
-    a.K = K;
-    a.HW = HW;
-    a.Q = (uint32_t)((long long)N * HW);
-    a.divHW = make_div((uint32_t)HW);
-    a.img = (const uint16_t *)wimg;
-    a.CH = (K + 31) / 32;
-    a.B.p0 = (const float *)B.p0;
-    a.B.p1 = (const float *)B.p1;
-    a.B.c0 = B.c0;
-    a.B.c1 = B.c1;
-    a.B.c2 = B.c2;
-    a.B.gate = B.gate;
-    a.out = (float *)out;
-    a.res = (const float *)res;
-    a.psum = psum;
-    a.psq = psq;
-    const bool pt = HW % 4 != 0; // one image per tile
-    a.QT = pt ? N : (int)((a.Q + 63u) / 64u);
-    a.MT = (M + 63) / 64;
-    a.partial = splitk_ws;
-    const int chunks = (K + 31) / 32;
-    a.chunksPerSplit = (chunks + splits - 1) / splits;
-    // workgroups per XCD: every workgroup gets the same number of tiles (or one fewer), at most
-    // about four workgroups per compute unit in all
-    const int tilesPerXcd = ((a.QT + 7) / 8) * a.MT;
-    const int cap = std::max(1, 128 / splits);
-    const int rounds = (tilesPerXcd + cap - 1) / cap;
-    const int gx = (tilesPerXcd + rounds - 1) / rounds;
-    dim3 grid((unsigned)(8 * gx), (unsigned)splits);
-    const int kepi = splits > 1 ? EPI_PARTIAL : epi;
-    hipError_t e = hipErrorInvalidValue;
-#define MBK_CASE(P, E)                                                                            \
-    if (B.pro == P && kepi == E) {                                                                \
-        if (pt)                                                                                   \
-            hipLaunchKernelGGL((conv_x3_kernel<P, E, true>), grid, dim3(256), 0, st, a);          \
-        else                                                                                      \
-            hipLaunchKernelGGL((conv_x3_kernel<P, E, false>), grid, dim3(256), 0, st, a);         \
-        e = hipGetLastError();                                                                    \
-    }
-    MBK_CASE(PRO_NONE, EPI_STATS)
-    MBK_CASE(PRO_BNSWISH_GATE, EPI_STATS)
-    MBK_CASE(PRO_BNBWD, EPI_NONE)
-    MBK_CASE(PRO_BNBWD, EPI_RES)
-    MBK_CASE(PRO_BNSWISH_GATE, EPI_AFFINE)
-    MBK_CASE(PRO_NONE, EPI_PARTIAL)
-    MBK_CASE(PRO_BNSWISH_GATE, EPI_PARTIAL)
-    MBK_CASE(PRO_BNBWD, EPI_PARTIAL)
-#undef MBK_CASE
-    if (e != hipSuccess || splits == 1)
-        return e;
-    return launch_splitk_finish_f32(splitk_ws, splits, M, a.Q, HW, out, res, epi, psum, psq, qtiles, st);
 }
 
 // ---- weight gradient -------------------------------------------------------------------------
@@ -1013,9 +523,6 @@ hipError_t launch_x3_wgrad_pair(int N, int MaA, int MbA, int HWA, const Operand 
 // fp32 operands are split into three bf16 planes as everywhere in this file.  The four
 // wavefronts' weight-gradient tiles are added in wavefront order at the end, the workgroups'
 // partial tiles by reduce_splits: fixed order, no atomics.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
 struct X3Bwd1x1Args {
     int Cn, Cw, HW;
     uint32_t Q;
@@ -1028,31 +535,6 @@ struct X3Bwd1x1Args {
     const float *res;          // optional, added to dx
     float *partial;            // [grid][Cw][Cn]
 };
-
-__device__ __forceinline__ f32x4 x3_mfma6_16(const bf16x8 (&a)[3], const bf16x8 (&b)[3], f32x4 acc)
-{
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc, 0, 0, 0);
-    return acc;
-}
-
-// eight values -> the three planes of an MFMA operand (value t in halfword t); p keeps the
-// packed pairs (values 2t and 2t+1 of plane pl in p[t][pl])
-__device__ __forceinline__ void x3_split8(const float (&v)[8], uint32_t (&p)[4][3], bf16x8 (&o)[3])
-{
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-        x3_split2(v[2 * t], v[2 * t + 1], p[t]);
-#pragma unroll
-    for (int pl = 0; pl < 3; ++pl) {
-        const u32x4 q = {p[0][pl], p[1][pl], p[2][pl], p[3][pl]};
-        o[pl] = __builtin_bit_cast(bf16x8, q);
-    }
-}
 
 __device__ __forceinline__ void x3_wave_lds_fence()
 {
@@ -1334,8 +816,8 @@ hipError_t launch_bwd1x1_x3(int N, int Cw, int Cn, int HW, const Operand &de, co
 
 // ---- 1x1 convolution with a short contraction: weights resident in LDS, a wavefront per chunk ----
 // out[n][m][q] = sum_k W[m][k] * op(B)[n][k][q] for K <= 192 and many rows (the expansion conv,
-// K = Cin, and the projection conv's data gradient, K = Cout, of the wide blocks).  In conv_x3
-// every 64 x 64 output tile stages its own copy of the B operand (load, split into planes, LDS
+// K = Cin, and the projection conv's data gradient, K = Cout, of the wide blocks).  With
+// 64 x 64 output tiles every tile stages its own copy of the B operand (load, split into planes, LDS
 // stores, two barriers per 32 values of k) and lasts 2-3 us per 32 values of k for 0.2 us of
 // matrix-core time; with a short contraction the tile's prologue and epilogue are most of it.
 // Here the roles are turned round:

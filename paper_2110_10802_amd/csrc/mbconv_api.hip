@@ -30,7 +30,6 @@ struct Plan {
     // the shape reads the weights themselves): expansion conv, projection conv, projection data
     // gradient, expansion data gradient; written by forward, read again by backward
     size_t o_wimg[4];
-    int wimg_lane_order[4]; // how the kernel that reads image i wants its tiles arranged
     // scratch workspace (byte offsets)
     size_t o_part;  // partial sums: 2 arrays of part_floats
     size_t o_wg2;   // projection weight gradient's partials while their reduction is deferred
@@ -160,10 +159,7 @@ Plan make_plan(const mbconv_desc *d)
         for (int i = 0; i < 4; ++i) {
             const bool use = ro[i].present && conv1x1_uses_weight_image(P.bf16, P.N, ro[i].M, ro[i].K, ro[i].HW,
                                                                           ro[i].stores, ro[i].pro, ro[i].epi);
-            P.o_wimg[i] = use ? take(x3_weight_image_bytes(ro[i].M, ro[i].K)) : kAbsent;
-            P.wimg_lane_order[i] = use ? conv1x1_image_lane_order(P.bf16, P.N, ro[i].M, ro[i].K, ro[i].HW,
-                                                                  ro[i].stores, ro[i].pro, ro[i].epi)
-                                       : 0;
+            P.o_wimg[i] = use ? take(x3_weight_image_bytes(P.bf16, ro[i].M, ro[i].K)) : kAbsent;
         }
     }
     P.saved_bytes = o;
@@ -195,11 +191,11 @@ Plan make_plan(const mbconv_desc *d)
     if (P.expand)
         wg = std::max(wg, (size_t)wgrad_splits(P.bf16, P.Cexp, P.Cin, P.N, P.HW) * P.Cexp * P.Cin);
     P.o_wg = take(wg * f);
-    size_t sk = conv1x1_splitk_floats(P.bf16, P.N, P.Cout, P.Cexp, P.HWo, P.store);
-    sk = std::max(sk, conv1x1_splitk_floats(P.bf16, P.N, P.Cexp, P.Cout, P.HWo, false));
-    if (P.expand) {
-        sk = std::max(sk, conv1x1_splitk_floats(P.bf16, P.N, P.Cexp, P.Cin, P.HW, false));
-        sk = std::max(sk, conv1x1_splitk_floats(P.bf16, P.N, P.Cin, P.Cexp, P.HW, false));
+    size_t sk = 0;
+    for (int i = 0; i < 4; ++i) {
+        const ConvRole r = conv_role(P, i);
+        if (r.present)
+            sk = std::max(sk, conv1x1_splitk_floats(P.bf16, P.N, r.M, r.K, r.HW, r.stores, r.pro, r.epi));
     }
     P.o_splitk = take(sk * f);
     P.o_wg2 = P.expand ? take((size_t)wgrad_splits(P.bf16, P.Cout, P.Cexp, P.N, P.HWo) * P.Cout * P.Cexp * f)
@@ -323,11 +319,11 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
         return P.o_wimg[i] == kAbsent ? nullptr : at<char>(saved, P.o_wimg[i]);
     };
     const auto prep_images = [&]() -> hipError_t {
-        const float *w[4];
-        int M[4], K[4], sm[4], sk[4], lo[4], n = 0;
+        const void *w[4];
+        int M[4], K[4], sm[4], sk[4], n = 0;
         void *img[4];
-        const float *we = (const float *)prm->w_expand, *wp = (const float *)prm->w_proj;
-        const auto add = [&](int i, const float *src, int m, int k, int s_m, int s_k) {
+        const void *we = prm->w_expand, *wp = prm->w_proj;
+        const auto add = [&](int i, const void *src, int m, int k, int s_m, int s_k) {
             if (P.o_wimg[i] == kAbsent)
                 return;
             w[n] = src;
@@ -336,7 +332,6 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
             sm[n] = s_m;
             sk[n] = s_k;
             img[n] = at<char>(saved, P.o_wimg[i]);
-            lo[n] = P.wimg_lane_order[i];
             ++n;
         };
         add(0, we, P.Cexp, P.Cin, P.Cin, 1);
@@ -345,7 +340,7 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
             add(2, wp, P.Cexp, P.Cout, 1, P.Cexp);
             add(3, we, P.Cin, P.Cexp, 1, P.Cin);
         }
-        return n ? launch_x3_prep(n, w, M, K, sm, sk, img, lo, st) : hipSuccess;
+        return n ? launch_x3_prep(bf, n, w, M, K, sm, sk, img, st) : hipSuccess;
     };
     bool images_ready = false;
     // expansion conv + BN1 statistics
@@ -690,6 +685,13 @@ mbconv_status backward_impl(const mbconv_desc *desc, const mbconv_params *prm, c
 
 namespace {
 bool relu6(const mbconv_desc *d) { return d && d->activation == MBCONV_ACT_RELU6; }
+// evaluation mode saves nothing: the policy is ignored
+mbconv_desc eval_desc(const mbconv_desc *desc)
+{
+    mbconv_desc d = *desc;
+    d.policy = MBCONV_RECOMPUTE;
+    return d;
+}
 } // namespace
 
 extern "C" {
@@ -711,7 +713,7 @@ mbconv_status mbconv_step_engine(const mbconv_desc *desc, int32_t step, int32_t 
             e = conv1x1_engine(P.bf16, P.N, P.Cexp, P.Cin, P.HW, false, PRO_NONE, EPI_STATS);
         break;
     case MBCONV_STEP_PROJ_CONV:
-        e = conv1x1_engine(P.bf16, P.N, P.Cout, P.Cexp, P.HWo, P.store);
+        e = conv1x1_engine(P.bf16, P.N, P.Cout, P.Cexp, P.HWo, P.store, PRO_BNSWISH_GATE, EPI_STATS);
         break;
     case MBCONV_STEP_PROJ_DGRAD:
     case MBCONV_STEP_PROJ_WGRAD: {
@@ -730,7 +732,8 @@ mbconv_status mbconv_step_engine(const mbconv_desc *desc, int32_t step, int32_t 
             const bool fused = bwd1x1_fused_plan(P.N, P.Cexp, P.Cin, P.HW, &fs);
             if (step == MBCONV_STEP_EXPAND_DGRAD)
                 e = fused ? bwd1x1_fused_engine(P.bf16, P.N, P.Cexp, P.Cin, P.HW)
-                          : conv1x1_engine(P.bf16, P.N, P.Cin, P.Cexp, P.HW, false);
+                          : conv1x1_engine(P.bf16, P.N, P.Cin, P.Cexp, P.HW, false, PRO_BNBWD,
+                                           P.res ? EPI_RES : EPI_NONE);
             else
                 e = fused ? MBCONV_ENGINE_VECTOR : wgrad1x1_engine(P.bf16, P.Cexp, P.Cin, P.N, P.HW);
         }
@@ -819,7 +822,8 @@ mbconv_status mbconv_eval_workspace_size(const mbconv_desc *desc, size_t *worksp
         return s;
     if (!workspace_bytes)
         return MBCONV_EINVAL;
-    const Plan P = make_plan(desc);
+    const mbconv_desc d = eval_desc(desc);
+    const Plan P = make_plan(&d);
     *workspace_bytes = align_up(P.saved_bytes) + P.scratch_bytes;
     return MBCONV_OK;
 }
@@ -843,13 +847,14 @@ mbconv_status mbconv_forward_eval_probed(const mbconv_desc *desc, const mbconv_p
         return MBCONV_EINVAL;
     if (misaligned(workspace))
         return MBCONV_EALIGN;
-    const Plan P = make_plan(desc);
+    const mbconv_desc d = eval_desc(desc);
+    const Plan P = make_plan(&d);
     // the intermediates a training call would save, then its scratch region
     char *saved = static_cast<char *>(workspace);
     char *scratch = saved + align_up(P.saved_bytes);
     mbconv_bn_state *run = const_cast<mbconv_bn_state *>(running); // read only in evaluation mode
-    return relu6(desc) ? mbk_r6::forward_impl(desc, prm, run, true, x, out, saved, scratch, hip_stream, probe)
-                       : mbk::forward_impl(desc, prm, run, true, x, out, saved, scratch, hip_stream, probe);
+    return relu6(&d) ? mbk_r6::forward_impl(&d, prm, run, true, x, out, saved, scratch, hip_stream, probe)
+                     : mbk::forward_impl(&d, prm, run, true, x, out, saved, scratch, hip_stream, probe);
 }
 
 mbconv_status mbconv_backward(const mbconv_desc *desc, const mbconv_params *prm, const void *x,

@@ -1,0 +1,66 @@
+"""The 1x1 convolutions whose contraction is split over a workgroup's wavefronts (conv_xk): block
+shapes at the edges of its tiles, against the oracle at the tolerances of parity_util."""
+import numpy as np
+import pytest
+
+from mbconv_inputs import BlockShape, make_block_inputs
+from oracle import oracle as orc
+from parity_util import TOL, compare_block, metric_for, run_gpu_block
+
+pytestmark = pytest.mark.gpu
+
+
+def _s(**kw):
+    base = dict(N=2, Cin=48, H=8, W=8, Cexp=288, Cse=12, Cout=48, k=3, stride=1, residual=True)
+    base.update(kw)
+    return BlockShape(**base)
+
+
+SHAPES = {
+    # contraction and rows that are no multiple of eight; an odd plane; a last chunk of 13 pixels
+    "ragged_channels": _s(Cin=43, Cexp=259, Cout=43, H=5, W=9),
+    # several images in one 32-pixel chunk (their gates wait in LDS), even and odd planes
+    "images_per_chunk": _s(N=9, H=2, W=3),
+    "images_per_chunk_odd": _s(N=11, H=1, W=3, residual=False, Cout=40),
+    # one image of few pixels: two row tiles per workgroup, eight wavefronts along the contraction
+    "one_image": _s(N=1, Cin=192, Cexp=1152, Cout=200, H=7, W=7, residual=False, k=5),
+    # one 32-deep step for a single wavefront; rows past the weight image's last tile
+    "short_contraction": _s(Cin=24, Cexp=56, Cout=33, H=7, W=9, residual=False),
+    # eight, seven and five row tiles per slab, more than one slab
+    "slab_8": _s(N=3, Cin=40, Cexp=240, Cout=128, H=14, W=14, residual=False),
+    "slab_7": _s(N=70, Cin=56, Cexp=224, Cout=112, H=12, W=16, residual=False),
+    "slab_5": _s(N=41, Cin=80, Cexp=320, Cout=320, H=9, W=9, residual=False),
+    "many_workgroups": _s(N=40, Cin=40, Cexp=160, Cout=40, H=24, W=24),
+    "relu6": _s(N=3, H=7, W=7, activation="relu6", has_se=False, Cse=1),
+    "bf16": _s(N=16, Cin=64, Cexp=384, Cse=16, Cout=96, H=10, W=10, dtype="bf16", residual=False),
+}
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_block_matches_oracle(name):
+    s = SHAPES[name]
+    t = make_block_inputs(s, seed=17)
+    print(f"[conv_xk] {name} {s}", flush=True)
+    res, blk = run_gpu_block(s, t)
+    f, b = orc.mbconv_step(s, t)
+    compare_block(s, t, res, f, b, blk)
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("name", ["one_image", "images_per_chunk", "slab_8", "bf16"])
+def test_eval_matches_oracle(name, policy):
+    """BN3 and the residual in the epilogue; evaluation mode ignores the policy."""
+    import torch
+    from paper_2110_10802_amd.harness import DeviceBlock, to_numpy
+
+    s = SHAPES[name]
+    t = make_block_inputs(s, seed=18)
+    rng = np.random.default_rng(19)
+    for i, c in ((1, s.Cexp), (2, s.Cexp), (3, s.Cout)):
+        t[f"bn{i}_mean"] = (0.3 * rng.standard_normal(c)).astype(np.float32)
+        t[f"bn{i}_var"] = (0.5 + rng.random(c)).astype(np.float32)
+    print(f"[conv_xk/eval] {name} policy={policy}", flush=True)
+    blk = DeviceBlock(s, t, policy=policy)
+    out = to_numpy(blk.forward_eval(blk.to_device(t["x"])))
+    torch.cuda.synchronize()
+    assert metric_for(s)(out, orc.mbconv_forward_eval(s, t)) <= TOL[s.dtype]["fwd"]
