@@ -305,84 +305,97 @@ __global__ __launch_bounds__(256) void se_fwd_kernel(int C, int Cse, const float
     }
 }
 
-// The same for wide blocks (hundreds of channels): a workgroup per (image, channel slice).
-// Every workgroup of an image recomputes the whole of q (Cse dot products of length C: cheap,
-// and it keeps the kernel free of a grid-wide dependency), then produces g for its slice.
-// A dependent global load costs about a microsecond here, so every phase issues all of its
-// loads before it consumes any: loops are unrolled over compile-time bounds (CI*256 >= C,
-// Cse <= 64) with guards.  Requires Cse % 4 == 0.
-template <int CI>
-__global__ __launch_bounds__(256) void se_fwd_wide_kernel(int C, int Cse, int slice,
-                                                          const float *__restrict__ z,
-                                                          const float *__restrict__ w1,
-                                                          const float *__restrict__ b1,
-                                                          const float *__restrict__ w2,
-                                                          const float *__restrict__ b2, float *q,
-                                                          float *g)
+// The same for 128 to 2048 channels and 4 to 64 squeezed ones: a workgroup of 1024 threads per (image,
+// channel slice).  What bounds it is the chain of memory round trips (about a microsecond each), so a
+// wavefront owns at most four rows of W1 and every load of the kernel - z, the wavefront's rows of W1
+// (16*CI bytes per lane and row), the thread's part of its channel's row of W2 - is requested before
+// the first one is used.  Every workgroup of an image recomputes the whole of q, which keeps the
+// kernel free of a grid-wide dependency.  (One image: 480 -> 20 channels 4.1 us, 1152 -> 48 6.3; with
+// 256 threads and 16 rows of W1 at a time 6.6 and 11.  Batch 64: 4.2 and 11.4 against 4.7 and 12.3.
+// The same form of the backward kernel measured no faster, 6.8 and 11.4 against 6.8 and 11, and is not
+// used.)
+// Rows whose length is no multiple of four are read in pieces of four that are clamped to the row's
+// end; the elements a piece shares with the one before it are masked.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int CI, int JR>
+__global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int slice,
+                                                           const float *__restrict__ z,
+                                                           const float *__restrict__ w1,
+                                                           const float *__restrict__ b1,
+                                                           const float *__restrict__ w2,
+                                                           const float *__restrict__ b2, float *q,
+                                                           float *g)
 {
-    __shared__ float part[4][64];
+    constexpr int RU = JR * CI <= 15 ? JR : 10 / CI > 1 ? 10 / CI : 1; // rows of W1 in flight (128 registers)
     __shared__ float rs[64];
     const int n = blockIdx.x, sl = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float zv[CI];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    f32x4u zv[CI], wv[RU][CI], w2v[JR];
+    const auto fetch_w1 = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < CI; ++i) {
-        const int c = tid + 256 * i;
-        zv[i] = c < C ? z[(size_t)n * C + c] : 0.f;
-    }
-    for (int jb = 0; jb < Cse; jb += 16) {
-        float wv[16][CI];
-        // unconditional loads from clamped indices: rows past Cse repeat the last row (their
-        // sums are never read), columns past C meet zv = 0
+        for (int i = 0; i < CI; ++i)
+            wv[u % RU][i] = *reinterpret_cast<const f32x4u *>(w1 + (size_t)min(wave + 16 * u, Cse - 1) * C +
+                                                              min(4 * (lane + 64 * i), C - 4));
+    };
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
+    for (int i = 0; i < CI; ++i)
+        zv[i] = *reinterpret_cast<const f32x4u *>(z + (size_t)n * C + min(4 * (lane + 64 * i), C - 4));
 #pragma unroll
-            for (int i = 0; i < CI; ++i) {
-                const int c = min(tid + 256 * i, C - 1);
-                wv[u][i] = w1[(size_t)min(jb + u, Cse - 1) * C + c];
-            }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int u = 0; u < RU; ++u)
+        fetch_w1(u);
+    // W2: four threads per channel, thread t%4 takes the pieces t%4, t%4 + 4, ...
+    const int part = tid & 3, cend = min(C, (sl + 1) * slice);
+    int c = sl * slice + (tid >> 2);
+    const auto fetch_w2 = [&](int ch) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            float acc = 0.f;
+        for (int v = 0; v < JR; ++v)
+            w2v[v] = *reinterpret_cast<const f32x4u *>(w2 + (size_t)min(ch, C - 1) * Cse +
+                                                       min(4 * (part + 4 * v), Cse - 4));
+    };
+    fetch_w2(c);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < CI; ++i)
-                acc = fmaf(wv[u][i], zv[i], acc);
-            acc = wave_sum(acc);
-            if (lane == 0)
-                part[wave][jb + u] = acc;
+    for (int i = 0; i < CI; ++i) // (a piece past the end, or the part of one that another lane has)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            zv[i][e] = min(4 * (lane + 64 * i), C - 4) + e >= 4 * (lane + 64 * i) ? zv[i][e] : 0.f;
+#pragma unroll
+    for (int u = 0; u < JR; ++u) {
+        const int j = wave + 16 * u;
+        float acc = 0.f;
+#pragma unroll
+        for (int i = 0; i < CI; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc = fmaf(wv[u % RU][i][e], zv[i][e], acc);
+        if (u + RU < JR)
+            fetch_w1(u + RU);
+        acc = wave_sum(acc);
+        if (lane == 0) {
+            const float qv = acc + b1[min(j, Cse - 1)];
+            if (sl == 0 && j < Cse)
+                q[(size_t)n * Cse + j] = qv;
+            rs[j] = j < Cse ? swishf(qv) : 0.f;
         }
+        if (RU < JR)
+            __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
-    if (tid < Cse) {
-        const float qv = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]) + b1[tid];
-        if (sl == 0)
-            q[(size_t)n * Cse + tid] = qv;
-        rs[tid] = swishf(qv);
-    }
-    __syncthreads();
-    const int cend = min(C, (sl + 1) * slice);
-    for (int c = sl * slice + tid; c < cend; c += 256) {
-        const float4 *row = reinterpret_cast<const float4 *>(w2 + (size_t)c * Cse);
-        // unconditional loads (a quad past the end re-reads the last one and is masked): a
-        // branch around each load would make every load wait for the previous one
-        const int lastq = (Cse >> 2) - 1;
-        float4 w[16];
+    for (; c < cend; c += 256) {
+        float acc = 0.f;
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj)
-            w[jj] = row[min(jj, lastq)];
-        float acc = b2[c];
-        __builtin_amdgcn_sched_barrier(0);
+        for (int v = 0; v < JR; ++v) {
+            const int want = 4 * (part + 4 * v), at = min(want, Cse - 4);
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const bool ok = jj <= lastq;
-            const int j4 = 4 * min(jj, lastq);
-            acc = fmaf(ok ? w[jj].x : 0.f, rs[j4], acc);
-            acc = fmaf(ok ? w[jj].y : 0.f, rs[j4 + 1], acc);
-            acc = fmaf(ok ? w[jj].z : 0.f, rs[j4 + 2], acc);
-            acc = fmaf(ok ? w[jj].w : 0.f, rs[j4 + 3], acc);
+            for (int e = 0; e < 4; ++e)
+                acc = fmaf(at + e >= want ? w2v[v][e] : 0.f, rs[at + e], acc);
         }
-        g[(size_t)n * C + c] = sigmoidf_fast(acc);
+        fetch_w2(c + 256);
+        acc += __shfl_xor(acc, 1, kWave);
+        acc += __shfl_xor(acc, 2, kWave);
+        if (part == 0)
+            g[(size_t)n * C + c] = sigmoidf_fast(acc + b2[c]);
     }
 }
 
@@ -405,18 +418,27 @@ static bool se_wide(int C, int Cse)
 hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, const float *w1, const float *b1,
                          const float *w2, const float *b2, float *q, float *g, hipStream_t st)
 {
-    if (se_wide(C, Cse)) {
-        const int G = se_slices(N, C), slice = (C + G - 1) / G;
-        if (C <= 768)
-            hipLaunchKernelGGL(se_fwd_wide_kernel<3>, dim3(N, G), dim3(256), 0, st, C, Cse, slice, z,
-                               w1, b1, w2, b2, q, g);
-        else if (C <= 1280)
-            hipLaunchKernelGGL(se_fwd_wide_kernel<5>, dim3(N, G), dim3(256), 0, st, C, Cse, slice, z,
-                               w1, b1, w2, b2, q, g);
-        else
-            hipLaunchKernelGGL(se_fwd_wide_kernel<8>, dim3(N, G), dim3(256), 0, st, C, Cse, slice, z,
-                               w1, b1, w2, b2, q, g);
-        return hipGetLastError();
+    // (128 channels and more: 240 -> 10, batch 64, 7.8 -> 4.8 us; 96 -> 4, two images, no faster)
+    if (C >= 128 && C <= 2048 && Cse >= 4 && Cse <= 64) {
+        // channel slices per image: at most 256 channels each (a thread then owns one), about 256
+        // workgroups
+        const int G = std::max((C + 255) / 256, std::min(8, std::min(256 / N, (C + 63) / 64)));
+        const int slice = (C + G - 1) / G, ci = (C + 255) / 256, jr = (Cse + 15) / 16;
+#define MBK_CASE(CI_, JR_)                                                                        \
+    if (ci <= CI_ && jr == JR_) {                                                                 \
+        hipLaunchKernelGGL((se_fwd_wide_kernel<CI_, JR_>), dim3(N, G), dim3(1024), 0, st, C, Cse, \
+                           slice, z, w1, b1, w2, b2, q, g);                                       \
+        return hipGetLastError();                                                                 \
+    }
+#define MBK_CI(CI_) MBK_CASE(CI_, 1) MBK_CASE(CI_, 2) MBK_CASE(CI_, 3) MBK_CASE(CI_, 4)
+        MBK_CI(1)
+        MBK_CI(2)
+        MBK_CI(3)
+        MBK_CI(5)
+        MBK_CI(6)
+        MBK_CI(8)
+#undef MBK_CI
+#undef MBK_CASE
     }
     hipLaunchKernelGGL(se_fwd_kernel, dim3(N), dim3(256), sizeof(float) * (C + Cse), st, C, Cse, z,
                        w1, b1, w2, b2, q, g);
