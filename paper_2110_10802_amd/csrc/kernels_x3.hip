@@ -25,6 +25,18 @@ __device__ __forceinline__ void x3_ld4(const float *p, size_t i, float (&v)[4])
     v[2] = t.z;
     v[3] = t.w;
 }
+// four consecutive floats at an address that is only 4-byte aligned (pixel runs of planes whose
+// size is not a multiple of four)
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void x3_ld4u(const float *p, size_t i, float (&v)[4])
+{
+    const float4u t = *reinterpret_cast<const float4u *>(p + i);
+    v[0] = t[0];
+    v[1] = t[1];
+    v[2] = t[2];
+    v[3] = t[3];
+}
+
 // acc += a*b for the three-plane operands (small terms first)
 __device__ __forceinline__ float16v x3_mfma6(const bf16x8 (&a)[3], const bf16x8 (&b)[3], float16v acc)
 {
@@ -139,10 +151,10 @@ hipError_t launch_x3_prep(bool bf16, int nsets, const void *const *w, const int 
 // splits' partial tiles are added by a fixed-order second stage.
 struct X3WgradArgs {
     int Ma, Mb, HW;
-    uint32_t Q;
-    int chunksPerSplit; // chunks of 32 pixels
+    uint32_t runs;      // runs of four pixels: (HW + 3)/4 per image
+    int chunksPerSplit; // chunks of eight runs
     int tilesA, tilesB, splits;
-    FastDiv divHW;
+    FastDiv divRuns; // by the runs of an image
     X3Operand U, V;
     float *partial;
 };
@@ -173,9 +185,10 @@ template <int PRO, int NP>
 struct X3RowData {
     float v0[NP][4], v1[NP][PRO == PRO_BNBWD ? 4 : 1];
     float g[NP];
-    // n, pix: image and first pixel of the run (it lies inside one plane: HW % 4 == 0).  Both rows
-    // load, also past the last row (clamped, masked on the way into LDS): a branch around a load
-    // would make the loads behind it wait.
+    // n, pix: image and first pixel of the run (it lies inside one plane).  Both rows load, also past
+    // the last row (clamped, masked on the way into LDS): a branch around a load would make the loads
+    // behind it wait.
+    template <bool RAG>
     __device__ __forceinline__ void load(const X3Operand &o, int row0, int rr, int M, int HW, uint32_t n,
                                          uint32_t pix)
     {
@@ -183,16 +196,25 @@ struct X3RowData {
         for (int i = 0; i < NP; ++i) {
             const int r = min(row0 + rr + 64 * i, M - 1);
             const size_t idx = ((size_t)n * M + r) * HW + pix;
-            x3_ld4(o.p0, idx, v0[i]);
-            if constexpr (PRO == PRO_BNBWD)
-                x3_ld4(o.p1, idx, v1[i]);
+            if (RAG)
+                x3_ld4u(o.p0, idx, v0[i]);
+            else
+                x3_ld4(o.p0, idx, v0[i]);
+            if constexpr (PRO == PRO_BNBWD) {
+                if (RAG)
+                    x3_ld4u(o.p1, idx, v1[i]);
+                else
+                    x3_ld4(o.p1, idx, v1[i]);
+            }
             if constexpr (PRO == PRO_BNSWISH_GATE)
                 g[i] = o.gate[(size_t)n * M + r];
         }
     }
-    // prologue, split, three 8-byte LDS stores per row
+    // prologue, split, three 8-byte LDS stores per row.  fresh: the run's pixels before this one are
+    // zeros (RAG: the last run of an image, moved back to the plane's last four pixels)
+    template <bool RAG>
     __device__ __forceinline__ void store(const X3RowConst<PRO, NP> &c, uint16_t *planes, int rr, int qg,
-                                          uint32_t qmask) const
+                                          uint32_t qmask, int fresh) const
     {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
@@ -201,7 +223,7 @@ struct X3RowData {
             for (int j = 0; j < 4; ++j)
                 y[j] = and_mask(x3_apply<PRO>(v0[i][j], v1[i][PRO == PRO_BNBWD ? j : 0], c.k0[i], c.k1[i],
                                               PRO == PRO_BNSWISH_GATE ? g[i] : c.k2[i]),
-                                qmask & c.rmask[i]);
+                                (RAG && j < fresh) ? 0u : qmask & c.rmask[i]);
             uint32_t w0[3], w1[3];
             x3_split2(y[0], y[1], w0);
             x3_split2(y[2], y[3], w1);
@@ -218,7 +240,11 @@ struct X3RowData {
 // the narrow one).
 // (`bid`: the workgroup's index within this weight gradient's grid; Us, Vs: LDS for three planes
 // of 128 and of VB rows)
-template <int PROU, int PROV, int VB, bool TR>
+// RAG: the plane size is no multiple of four.  The contraction runs over runs of four pixels, image by
+// image; the last run of an image starts at HW - 4 and its pixels that the run before has are masked, so
+// a 7x7 plane takes 13 runs (52 of its 49 pixels), every access stays 16 bytes wide (4-byte aligned)
+// inside its plane, and both operands see the same order.
+template <int PROU, int PROV, int VB, bool TR, bool RAG>
 __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uint16_t *Us, uint16_t *Vs)
 {
     constexpr int BQ = 32, kPlane = 128 * 32, kPlaneV = VB * 32; // planes in the layout of x3_img_at
@@ -236,7 +262,7 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
     if (split >= a.splits)
         return;
     const int a0 = (tile % a.tilesA) * 128, b0 = (tile / a.tilesA) * VB;
-    const int numChunks = (int)((a.Q + BQ - 1) / BQ);
+    const int numChunks = (int)((a.runs + BQ / 4 - 1) / (BQ / 4));
     const int cbeg = split * a.chunksPerSplit;
     const int cend = min(cbeg + a.chunksPerSplit, numChunks);
     const int qg = tid & 7, rr = tid >> 3;
@@ -247,18 +273,21 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
     X3RowData<PROU, 2> du[2];
     X3RowData<PROV, VB / 64> dv[2];
     uint32_t qmask[2] = {0u, 0u};
+    int fresh[2] = {0, 0};
     // unconditional clamped loads, validity as an AND mask on the way into LDS
     auto load = [&](int s, int chunk) __attribute__((always_inline)) {
-        const uint32_t q = (uint32_t)chunk * BQ + 4u * qg;
-        qmask[s] = q < a.Q ? 0xffffffffu : 0u; // HW % 4 == 0: the run of four lies in one image
-        const uint32_t qc = qmask[s] ? q : 0u;
-        const uint32_t n = fdiv(qc, a.divHW), pix = qc - n * (uint32_t)a.HW;
-        du[s].load(a.U, a0, rr, a.Ma, a.HW, n, pix);
-        dv[s].load(a.V, b0, rr, a.Mb, a.HW, n, pix);
+        const uint32_t run = (uint32_t)chunk * (BQ / 4) + (uint32_t)qg;
+        qmask[s] = run < a.runs ? 0xffffffffu : 0u;
+        const uint32_t rc = qmask[s] ? run : 0u;
+        const uint32_t n = fdiv(rc, a.divRuns);
+        const uint32_t want = 4u * (rc - n * a.divRuns.d), pix = RAG ? min(want, (uint32_t)a.HW - 4u) : want;
+        fresh[s] = (int)(want - pix);
+        du[s].template load<RAG>(a.U, a0, rr, a.Ma, a.HW, n, pix);
+        dv[s].template load<RAG>(a.V, b0, rr, a.Mb, a.HW, n, pix);
     };
     auto store = [&](int s) __attribute__((always_inline)) {
-        du[s].store(cu, Us, rr, qg, qmask[s]);
-        dv[s].store(cv, Vs, rr, qg, qmask[s]);
+        du[s].template store<RAG>(cu, Us, rr, qg, qmask[s], fresh[s]);
+        dv[s].template store<RAG>(cv, Vs, rr, qg, qmask[s], fresh[s]);
     };
 
     float16v acc[NA];
@@ -317,45 +346,45 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
         }
 }
 
-template <int PROU, int PROV, int VB, bool TR>
+template <int PROU, int PROV, int VB, bool TR, bool RAG>
 __global__ __launch_bounds__(512) void wgrad_x3_kernel(X3WgradArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint16_t Us[3 * 128 * 32];
     __shared__ __attribute__((aligned(16))) uint16_t Vs[3 * VB * 32];
-    wgrad_x3_body<PROU, PROV, VB, TR>(a, (int)blockIdx.x, Us, Vs);
+    wgrad_x3_body<PROU, PROV, VB, TR, RAG>(a, (int)blockIdx.x, Us, Vs);
 }
 
 // The six forms of the kernel above, by number (x3_wgrad_variant).
-template <int VAR>
+template <int VAR, bool RAG>
 __device__ __forceinline__ void wgrad_x3_variant(const X3WgradArgs &a, int bid, uint16_t *Us, uint16_t *Vs)
 {
     if (VAR == 0)
-        wgrad_x3_body<PRO_BNBWD, PRO_NONE, 128, false>(a, bid, Us, Vs);
+        wgrad_x3_body<PRO_BNBWD, PRO_NONE, 128, false, RAG>(a, bid, Us, Vs);
     else if (VAR == 1)
-        wgrad_x3_body<PRO_BNBWD, PRO_BNSWISH_GATE, 128, false>(a, bid, Us, Vs);
+        wgrad_x3_body<PRO_BNBWD, PRO_BNSWISH_GATE, 128, false, RAG>(a, bid, Us, Vs);
     else if (VAR == 2)
-        wgrad_x3_body<PRO_BNBWD, PRO_NONE, 64, false>(a, bid, Us, Vs);
+        wgrad_x3_body<PRO_BNBWD, PRO_NONE, 64, false, RAG>(a, bid, Us, Vs);
     else if (VAR == 3)
-        wgrad_x3_body<PRO_BNBWD, PRO_BNSWISH_GATE, 64, false>(a, bid, Us, Vs);
+        wgrad_x3_body<PRO_BNBWD, PRO_BNSWISH_GATE, 64, false, RAG>(a, bid, Us, Vs);
     else if (VAR == 4)
-        wgrad_x3_body<PRO_NONE, PRO_BNBWD, 64, true>(a, bid, Us, Vs);
+        wgrad_x3_body<PRO_NONE, PRO_BNBWD, 64, true, RAG>(a, bid, Us, Vs);
     else
-        wgrad_x3_body<PRO_BNSWISH_GATE, PRO_BNBWD, 64, true>(a, bid, Us, Vs);
+        wgrad_x3_body<PRO_BNSWISH_GATE, PRO_BNBWD, 64, true, RAG>(a, bid, Us, Vs);
 }
 
 // Two weight gradients in one launch (a block's projection and expansion conv: independent of
 // each other, each about one workgroup per compute unit and bound by the latency of its own
 // load-stage-multiply chain): the first gridA workgroups work on `a`, the others on `b`, and
 // with at most 128 registers two workgroups, one of each, share a compute unit.
-template <int VARA, int VARB>
+template <int VARA, int VARB, bool RAG>
 __global__ __launch_bounds__(512, 4) void wgrad_x3_pair_kernel(X3WgradArgs a, X3WgradArgs b, int gridA)
 {
     __shared__ __attribute__((aligned(16))) uint16_t Us[3 * 128 * 32];
     __shared__ __attribute__((aligned(16))) uint16_t Vs[3 * 128 * 32];
     if ((int)blockIdx.x < gridA) // uniform over the workgroup
-        wgrad_x3_variant<VARA>(a, (int)blockIdx.x, Us, Vs);
+        wgrad_x3_variant<VARA, RAG>(a, (int)blockIdx.x, Us, Vs);
     else
-        wgrad_x3_variant<VARB>(b, (int)blockIdx.x - gridA, Us, Vs);
+        wgrad_x3_variant<VARB, RAG>(b, (int)blockIdx.x - gridA, Us, Vs);
 }
 
 // Tile and splits.  The wider operand gets 128-row tiles; the other one 128-row tiles, or one
@@ -364,15 +393,13 @@ __global__ __launch_bounds__(512, 4) void wgrad_x3_pair_kernel(X3WgradArgs a, X3
 bool x3_wgrad_plan(int Ma, int Mb, int N, int HW, int *splits)
 {
     const long long Q = (long long)N * HW;
-    // (planes whose size is not a multiple of four stay with kernels_big.hip: one-image chunks with
-    // a shifted partial run measured slower there, 41 -> 52 us on 1152 x 192 channels at 7x7)
     // (a side of at most 32 channels belongs to the fused backward kernels of kernels_wave.hip,
     // which size their partial tiles by the plan of that file)
-    if (Q >= (1ll << 31) || HW % 4 != 0 || std::min(Ma, Mb) <= 32 || std::max(Ma, Mb) < 64)
+    if (Q >= (1ll << 31) || HW < 4 || std::min(Ma, Mb) <= 32 || std::max(Ma, Mb) < 64)
         return false;
     const int wide = std::max(Ma, Mb), narrow = std::min(Ma, Mb), vb = narrow <= 64 ? 64 : 128;
     const long long tiles = (long long)((wide + 127) / 128) * ((narrow + vb - 1) / vb);
-    const long long chunks = (Q + 31) / 32;
+    const long long chunks = ((long long)N * ((HW + 3) / 4) + 7) / 8;
     long long s = (256 + tiles - 1) / tiles; // 512 workgroups measured slower (twice the partial tiles)
     const long long smax = (chunks + 1) / 2;
     if (s > smax)
@@ -410,10 +437,11 @@ static bool x3_wgrad_setup(int N, int Ma, int Mb, int HW, const Operand &U, cons
     a.Ma = swap ? Mb : Ma;
     a.Mb = swap ? Ma : Mb;
     a.HW = HW;
-    a.Q = (uint32_t)((long long)N * HW);
-    const int chunks = (int)((a.Q + 31u) / 32u);
+    const int perImage = (HW + 3) / 4;
+    a.runs = (uint32_t)((long long)N * perImage);
+    const int chunks = (int)((a.runs + 7u) / 8u);
     a.chunksPerSplit = (chunks + splits - 1) / splits;
-    a.divHW = make_div((uint32_t)HW);
+    a.divRuns = make_div((uint32_t)perImage);
     a.U = to_x3(swap ? V : U);
     a.V = to_x3(swap ? U : V);
     a.partial = partial;
@@ -449,7 +477,10 @@ hipError_t launch_x3_wgrad(int N, int Ma, int Mb, int HW, const Operand &U, cons
         return hipErrorInvalidValue;
 #define MBK_CASE(VAR, PU, PV, VB_, TR_)                                                           \
     if (var == VAR) {                                                                             \
-        hipLaunchKernelGGL((wgrad_x3_kernel<PU, PV, VB_, TR_>), dim3(grid), dim3(512), 0, st, a); \
+        if (HW % 4 != 0)                                                                          \
+            hipLaunchKernelGGL((wgrad_x3_kernel<PU, PV, VB_, TR_, true>), dim3(grid), dim3(512), 0, st, a);  \
+        else                                                                                      \
+            hipLaunchKernelGGL((wgrad_x3_kernel<PU, PV, VB_, TR_, false>), dim3(grid), dim3(512), 0, st, a); \
         return hipGetLastError();                                                                 \
     }
     MBK_CASE(0, PRO_BNBWD, PRO_NONE, 128, false)
@@ -478,8 +509,12 @@ hipError_t launch_x3_wgrad_pair(int N, int MaA, int MbA, int HWA, const Operand 
         return hipErrorNotSupported;
 #define MBK_CASE(VA_, VB_)                                                                        \
     if (va == VA_ && vb == VB_) {                                                                 \
-        hipLaunchKernelGGL((wgrad_x3_pair_kernel<VA_, VB_>), dim3(ga + gb), dim3(512), 0, st, a, b, \
-                           (int)ga);                                                              \
+        if (HWA % 4 != 0 || HWB % 4 != 0)                                                         \
+            hipLaunchKernelGGL((wgrad_x3_pair_kernel<VA_, VB_, true>), dim3(ga + gb), dim3(512), 0, st, a, b,  \
+                               (int)ga);                                                          \
+        else                                                                                      \
+            hipLaunchKernelGGL((wgrad_x3_pair_kernel<VA_, VB_, false>), dim3(ga + gb), dim3(512), 0, st, a, b, \
+                               (int)ga);                                                          \
         return hipGetLastError();                                                                 \
     }
     // projection side: dp (BN backward) with the gated activation, 128- or 64-row tile, or
