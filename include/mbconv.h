@@ -166,8 +166,8 @@ mbconv_status mbconv_forward_eval(const mbconv_desc *desc, const mbconv_params *
                                   void *workspace, void *hip_stream);
 
 /* Backward of the forward call that wrote saved_ws (same desc, params and x; the parameter VALUES
- * must be those forward saw as well: for fp32 wide blocks saved_ws holds a re-encoded copy of the
- * two 1x1 conv weights, which the data-gradient kernels read instead of params).
+ * must be those forward saw as well: for wide blocks saved_ws holds a re-encoded copy of 1x1 conv
+ * weights, which data-gradient kernels read instead of params).
  *   dout [N,Cout,Ho,Wo] dtype, read-only.   dx [N,Cin,H,W] dtype, written.
  *   grads: every non-NULL member is overwritten with the gradient of sum(out*dout).
  * Every reduction runs in a fixed order without floating-point atomics, so results are
@@ -185,18 +185,18 @@ mbconv_status mbconv_backward(const mbconv_desc *desc, const mbconv_params *para
 typedef enum {
     MBCONV_STEP_NONE = 0,
     /* forward */
-    MBCONV_STEP_EXPAND_CONV = 1,   /* 1x1 expansion conv + BN1 partial statistics; for fp32 wide blocks also the
-                                      launch that re-encodes the 1x1 conv weights (in PROJ_CONV when
-                                      has_expand == 0) */
+    MBCONV_STEP_EXPAND_CONV = 1,   /* 1x1 expansion conv + BN1 partial statistics (and, where that conv reads
+                                      re-encoded weights, the launch that writes them) */
     MBCONV_STEP_BN1_FINALIZE = 2,  /* BN1_FINALIZE and BN3_FINALIZE do not occur where the kernel
                                       that consumes the statistics finalises them itself: DW_FWD
                                       and BN3_APPLY do for planes of 1024 elements or more (DW_FWD:
                                       stride 1, W % 4 == 0, recompute policy) */
     MBCONV_STEP_DW_FWD = 3,        /* BN1 + Swish + depthwise conv + BN2 partial statistics */
-    MBCONV_STEP_BN2_FINALIZE = 4,  /* when no_se, in training: also fills the gate with ones */
+    MBCONV_STEP_BN2_FINALIZE = 4,  /* also re-encodes the 1x1 conv weights for the wide blocks' kernels and,
+                                      when no_se, fills the gate with ones (in evaluation mode the launch
+                                      of the coefficient blocks does both) */
     MBCONV_STEP_SE_POOL = 5,       /* BN2 + Swish + plane means; does not occur when no_se */
-    MBCONV_STEP_SE_FC = 6,         /* when no_se: fills the gate with ones in evaluation mode and does not
-                                      occur in training */
+    MBCONV_STEP_SE_FC = 6,         /* does not occur when no_se */
     MBCONV_STEP_PROJ_CONV = 7,     /* (BN2 + Swish)*gate + 1x1 projection conv + BN3 partials */
     MBCONV_STEP_BN3_FINALIZE = 8,
     MBCONV_STEP_BN3_APPLY = 9,     /* BN3 (+ residual) */

@@ -240,7 +240,7 @@ hipError_t launch_big_wgrad_pair(bool bf16, int N, int MaA, int MbA, int HWA, co
                                  int HWB, const Operand &UB, const Operand &VB, float *partialB,
                                  int *splitsB, hipStream_t st);
 bool xw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt);
-hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *wimg, const Operand &B,
+hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm, int sAk, const Operand &B,
                              void *out, int epi, float *psum, float *psq, hipStream_t st);
 // kernels_xk.hip
 bool xk_conv_plan(bool bf16, int N, int M, int K, int HW, int pro, int *chunks);
@@ -271,16 +271,16 @@ bool conv1x1_uses_weight_image(bool bf16, int N, int M, int K, int HW, bool stor
                                int epi)
 {
     int nt;
-    return xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt) ||
-           xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt);
+    return xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt);
 }
 
 // which matrix-core instruction family serves a launch (values of mbconv_engine in mbconv.h)
 int conv1x1_engine(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi)
 {
-    if (conv1x1_uses_weight_image(bf16, N, M, K, HW, stores_operand, pro, epi))
-        return bf16 ? 2 : 3;
     int qtiles, splits;
+    if (xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
+        xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
+        return bf16 ? 2 : 3;
     if (bf16 && !stores_operand && !wave_conv_kind(M, K, HW) && bf_conv_plan(N, M, K, HW, &qtiles, &splits))
         return 2;
     return 1;
@@ -335,9 +335,7 @@ hipError_t launch_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w,
     {
         int nt;
         if (xw_applies(bf16, N, M, K, HW, sc_store != nullptr, B.pro, epi, &nt)) {
-            if (!wimg)
-                return hipErrorInvalidValue;
-            return launch_xw_conv1x1(N, M, K, HW, wimg, B, out, epi, psum, psq, st);
+            return launch_xw_conv1x1(N, M, K, HW, w, sAm, sAk, B, out, epi, psum, psq, st);
         }
         if (xk_applies(bf16, N, M, K, HW, sc_store != nullptr, B.pro, epi, &nt)) {
             if (!wimg)

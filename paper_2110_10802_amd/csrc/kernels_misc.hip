@@ -1,8 +1,8 @@
 // Small kernels: batch-norm statistics finalisation (forward and backward), the
 // squeeze-and-excitation fully connected layers and their gradients, and the fixed-order
 // second stage of the split reductions.  All of them touch O(N*C) values.
-#include "mbconv_dev.h"
-#include "mbconv_launch.h"
+#include <algorithm>
+#include "mbconv_x3.h"
 
 namespace mbk {
 
@@ -17,6 +17,9 @@ __device__ __forceinline__ double wave_sum_d(double v)
 // One wavefront per channel.  Partials are fp32 sums over at most a plane or a GEMM tile;
 // they are combined in fp64 so that var = E[x^2]-E[x]^2 loses nothing in this stage.
 // BN formula and running statistics: section "Statistical Normalization".
+// PREP: the workgroups past the channels' write the weight images of convolutions later in the
+// sequence (a launch of their own cost 4 to 5 us; this one's few workgroups leave the chip empty).
+template <bool PREP>
 __global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double m,
                                                           const float *__restrict__ psum,
                                                           const float *__restrict__ psq,
@@ -24,11 +27,15 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double 
                                                           const float *__restrict__ beta, float eps,
                                                           float momentum, float *run_mean,
                                                           float *run_var, float *bn, float *ones,
-                                                          size_t ones_count)
+                                                          size_t ones_count, X3PrepArgs prep)
 {
+    if (PREP && (int)blockIdx.x >= (C + 3) / 4) {
+        x3_prep_tile(prep, blockIdx.x - (C + 3) / 4);
+        return;
+    }
     // a block without squeeze-and-excitation has its gate buffer set to one here, by the launch
     // that precedes the gate's first reader anyway
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < ones_count; i += (size_t)gridDim.x * 256)
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < ones_count; i += (size_t)((C + 3) / 4) * 256)
         ones[i] = 1.0f;
     const int c = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (c >= C)
@@ -82,10 +89,15 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double 
 hipError_t launch_bn_finalize(int C, int NP, double m, const float *psum, const float *psq,
                               const float *gamma, const float *beta, float eps, float momentum,
                               float *run_mean, float *run_var, float *bn, hipStream_t st,
-                              float *ones, size_t ones_count)
+                              float *ones, size_t ones_count, const X3PrepArgs *prep)
 {
-    hipLaunchKernelGGL(bn_finalize_kernel, dim3((C + 3) / 4), dim3(256), 0, st, C, NP, m, psum, psq,
-                       gamma, beta, eps, momentum, run_mean, run_var, bn, ones, ones ? ones_count : 0);
+    const unsigned own = (unsigned)((C + 3) / 4);
+    if (prep && prep->tiles)
+        hipLaunchKernelGGL(bn_finalize_kernel<true>, dim3(own + prep->tiles), dim3(256), 0, st, C, NP, m, psum, psq,
+                           gamma, beta, eps, momentum, run_mean, run_var, bn, ones, ones ? ones_count : 0, *prep);
+    else
+        hipLaunchKernelGGL(bn_finalize_kernel<false>, dim3(own), dim3(256), 0, st, C, NP, m, psum, psq, gamma, beta,
+                           eps, momentum, run_mean, run_var, bn, ones, ones ? ones_count : 0, X3PrepArgs());
     return hipGetLastError();
 }
 
@@ -101,9 +113,19 @@ struct BnEvalOne {
 struct BnEvalArgs {
     BnEvalOne b[3];
     float eps;
+    int blocks;       // workgroups of the coefficients; those past them write the weight images
+    float *ones;      // gate of a block without squeeze-and-excitation, set to one
+    size_t ones_count;
+    X3PrepArgs prep;
 };
 __global__ __launch_bounds__(256) void bn_eval_coef_kernel(BnEvalArgs a)
 {
+    if ((int)blockIdx.x >= a.blocks) {
+        x3_prep_tile(a.prep, blockIdx.x - a.blocks);
+        return;
+    }
+    for (size_t j = (size_t)blockIdx.x * 256 + threadIdx.x; j < a.ones_count; j += (size_t)a.blocks * 256)
+        a.ones[j] = 1.0f;
     int i = blockIdx.x * 256 + threadIdx.x;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -125,29 +147,22 @@ hipError_t launch_bn_eval_coef(int C1, const float *gamma1, const float *beta1, 
                                const float *rv1, float *bn1, int C2, const float *gamma2,
                                const float *beta2, const float *rm2, const float *rv2, float *bn2,
                                int C3, const float *gamma3, const float *beta3, const float *rm3,
-                               const float *rv3, float *bn3, float eps, hipStream_t st)
+                               const float *rv3, float *bn3, float eps, hipStream_t st, float *ones,
+                               size_t ones_count, const X3PrepArgs *prep)
 {
-    BnEvalArgs a;
+    BnEvalArgs a = {};
     a.b[0] = {C1, gamma1, beta1, rm1, rv1, bn1};
     a.b[1] = {C2, gamma2, beta2, rm2, rv2, bn2};
     a.b[2] = {C3, gamma3, beta3, rm3, rv3, bn3};
     a.eps = eps;
-    const int total = C1 + C2 + C3;
-    hipLaunchKernelGGL(bn_eval_coef_kernel, dim3((total + 255) / 256), dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void fill_kernel(float *out, float value, size_t count)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < count)
-        out[i] = value;
-}
-
-hipError_t launch_fill(float *out, float value, size_t count, hipStream_t st)
-{
-    hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, out,
-                       value, count);
+    a.ones = ones;
+    a.ones_count = ones ? ones_count : 0;
+    if (prep)
+        a.prep = *prep;
+    // (the coefficients need a thread each; the ones, where there are any, eight to a thread)
+    const size_t want = std::max((size_t)(C1 + C2 + C3), (a.ones_count + 7) / 8);
+    a.blocks = (int)std::max<size_t>((C1 + C2 + C3 + 255) / 256, std::min<size_t>((want + 255) / 256, 1024));
+    hipLaunchKernelGGL(bn_eval_coef_kernel, dim3((unsigned)(a.blocks + a.prep.tiles)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

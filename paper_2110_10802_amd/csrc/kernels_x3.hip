@@ -62,81 +62,16 @@ __device__ __forceinline__ int x3_img_at(int row, int k)
 // one for bf16), cut into tiles of 64 rows x 32 k in the lane order of v_mfma_f32_16x16x32_bf16:
 // tile (mt, ch) is [row tile of 16][plane][lane][8 k] with lane = row % 16 + 16 * (k / 8), so that a
 // wavefront reads an operand as 64 consecutive 16-byte pieces.  Rows and k past the end are zeros.
-struct X3PrepSet {
-    const void *w; // A(m, k) = w[m*sm + k*sk]
-    int M, K, sm, sk;
-    uint16_t *img;
-    int CH, firstTile;
-};
-struct X3PrepArgs {
-    X3PrepSet s[4];
-    int nsets;
-    int bf16; // the weights are stored as bf16: one plane
-};
-
-// one workgroup per tile: thread -> (row tid/4, eight k at 8*(tid%4))
-__global__ __launch_bounds__(256) void x3_prep_kernel(X3PrepArgs a)
-{
-    int si = 0;
-#pragma unroll
-    for (int i = 1; i < 4; ++i)
-        if (i < a.nsets && (int)blockIdx.x >= a.s[i].firstTile)
-            si = i;
-    const X3PrepSet S = a.s[si];
-    const int local = blockIdx.x - S.firstTile, mt = local / S.CH, ch = local % S.CH;
-    const int tid = threadIdx.x, r = tid >> 2, g = tid & 3;
-    const int m = mt * 64 + r, k0 = ch * 32 + 8 * g;
-    float v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int k = k0 + j;
-        const size_t at = (size_t)m * S.sm + (size_t)k * S.sk;
-        v[j] = (m < S.M && k < S.K) ? (a.bf16 ? ld<bf16_t>((const bf16_t *)S.w, at) : ((const float *)S.w)[at])
-                                    : 0.f;
-    }
-    if (a.bf16) { // (uniform) the values are bf16 already: packing them rounds nothing
-        *reinterpret_cast<uint4 *>(S.img + ((size_t)mt * S.CH + ch) * 2048 + ((r >> 4) * 64 + (r & 15) + 16 * g) * 8) =
-            make_uint4(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]), bf16_pack2(v[4], v[5]),
-                       bf16_pack2(v[6], v[7]));
-        return;
-    }
-    uint32_t w[4][3];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        x3_split2(v[2 * j], v[2 * j + 1], w[j]);
-    uint16_t *tile = S.img + ((size_t)mt * S.CH + ch) * 3 * 2048 + ((r >> 4) * 3 * 64 + (r & 15) + 16 * g) * 8;
-#pragma unroll
-    for (int pl = 0; pl < 3; ++pl)
-        *reinterpret_cast<uint4 *>(tile + pl * 512) = make_uint4(w[0][pl], w[1][pl], w[2][pl], w[3][pl]);
-}
+__global__ __launch_bounds__(256) void x3_prep_kernel(X3PrepArgs a) { x3_prep_tile(a, blockIdx.x); }
 
 size_t x3_weight_image_bytes(bool bf16, int M, int K)
 {
     return (size_t)((M + 63) / 64) * ((K + 31) / 32) * (bf16 ? 1 : 3) * 2048 * sizeof(uint16_t);
 }
 
-// Writes up to four images in one launch; set i: A(m,k) = w[i][m*sm[i] + k*sk[i]], M[i] x K[i].
-hipError_t launch_x3_prep(bool bf16, int nsets, const void *const *w, const int *M, const int *K, const int *sm,
-                          const int *sk, void *const *img, hipStream_t st)
+hipError_t launch_x3_prep(const X3PrepArgs &a, hipStream_t st)
 {
-    if (nsets < 1 || nsets > 4)
-        return hipErrorInvalidValue;
-    X3PrepArgs a = {};
-    a.bf16 = bf16;
-    int tiles = 0;
-    for (int i = 0; i < nsets; ++i) {
-        a.s[i].w = w[i];
-        a.s[i].M = M[i];
-        a.s[i].K = K[i];
-        a.s[i].sm = sm[i];
-        a.s[i].sk = sk[i];
-        a.s[i].img = (uint16_t *)img[i];
-        a.s[i].CH = (K[i] + 31) / 32;
-        a.s[i].firstTile = tiles;
-        tiles += ((M[i] + 63) / 64) * a.s[i].CH;
-    }
-    a.nsets = nsets;
-    hipLaunchKernelGGL(x3_prep_kernel, dim3((unsigned)tiles), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(x3_prep_kernel, dim3((unsigned)a.tiles), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -856,9 +791,10 @@ hipError_t launch_bwd1x1_x3(int N, int Cw, int Cn, int HW, const Operand &de, co
 // stores, two barriers per 32 values of k) and lasts 2-3 us per 32 values of k for 0.2 us of
 // matrix-core time; with a short contraction the tile's prologue and epilogue are most of it.
 // Here the roles are turned round:
-//   - a workgroup owns a slab of 64 output rows; the slab's weights, all of K, are copied once
-//     from the weight image into LDS (at most 72 KB) in the lane order of the MFMA's A operand,
-//     so an operand is one 16-byte LDS read per lane and plane, conflict-free;
+//   - a workgroup owns a slab of 64 output rows; the slab's weights, all of K, are read once, split
+//     into planes and kept in LDS (at most 72 KB) in the lane order of the MFMA's A operand, so an
+//     operand is one 16-byte LDS read per lane and plane, conflict-free (24 to 48 values to split
+//     per thread: no weight image, and no launch ahead of the expansion conv to write one);
 //   - a wavefront owns whole chunks of 32 pixels: lane (r, g) loads, for every 32 values of k,
 //     the values k = 8g .. 8g+7 of its two pixels (2r and 2r+1 of the chunk when the plane size
 //     is even: eight-byte loads, sixteen lanes cover a 128-byte line; r and 16+r otherwise),
@@ -877,7 +813,8 @@ struct X3WArgs {
     uint32_t Q;
     int numChunks;
     FastDiv divHW;
-    const uint16_t *img; // weight image in lane order
+    const float *w; // A(m, k) = w[m*sm + k*sk], sm or sk = 1
+    int sm, sk;
     X3Operand B;
     float *out;
     float *psum, *psq; // EPI_STATS: [M][NT]
@@ -900,14 +837,30 @@ __global__ __launch_bounds__(256, 2) void conv_xw_kernel(X3WArgs a)
     const int die = blockIdx.x & 7, bi = blockIdx.x >> 3;
     const int slab = bi % a.slabs, cs = (bi / a.slabs) * 8 + die;
 
-    // the slab's weights: KS * 12 KB, copied as they lie in the image (requested here, parked in
-    // LDS below, after the first chunk's values have been requested as well)
-    u32x4 slabv[KS * 3];
+    // the slab's weights: thread -> (row r16, k group) pieces of eight k, of every 32-deep step one;
+    // requested here, split into planes and parked in LDS below, after the first chunk's values have
+    // been requested as well.  (Rows and k past the end: clamped loads, masked to zero.)
+    float slabv[KS][8];
+    const int sr = 16 * (tid >> 6) + (tid & 15), sg = (tid >> 4) & 3; // row of the slab, k group
     {
-        const u32x4 *src = reinterpret_cast<const u32x4 *>(a.img + (size_t)slab * KS * STEP_HW);
+        const float *wr = a.w + (size_t)min(64 * slab + sr, M - 1) * a.sm;
+        if (a.sk == 1) { // (uniform) rows of the matrix: 16-byte loads, K and every k group multiples of 8
 #pragma unroll
-        for (int i = 0; i < KS * 3; ++i)
-            slabv[i] = src[tid + 256 * i];
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(wr + min(32 * s + 8 * sg, K - 8) + 4 * h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        slabv[s][4 * h + e] = v[e];
+                }
+        } else { // columns: sixteen lanes read sixteen consecutive rows
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    slabv[s][t] = wr[(size_t)min(32 * s + 8 * sg + t, K - 1) * a.sk];
+        }
     }
     // BN-backward coefficients per contraction index, {c0, c1, c2, -} (zero past K)
     f32x4 *Cl = reinterpret_cast<f32x4 *>(lds16 + KS * STEP_HW); // [32*KS] (PRO_BNBWD)
@@ -980,9 +933,21 @@ __global__ __launch_bounds__(256, 2) void conv_xw_kernel(X3WArgs a)
     for (int s = 0; s < KS; ++s)
         fetch_step(s, bo);
     __builtin_amdgcn_sched_barrier(0);
+    {
+        const bool mok = 64 * slab + sr < M;
 #pragma unroll
-    for (int i = 0; i < KS * 3; ++i)
-        reinterpret_cast<u32x4 *>(lds16)[tid + 256 * i] = slabv[i];
+        for (int s = 0; s < KS; ++s) {
+            uint32_t p[4][3];
+            bf16x8 o[3];
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                slabv[s][t] = and_mask(slabv[s][t], mok && 32 * s + 8 * sg + t < K ? 0xffffffffu : 0u);
+            x3_split8(slabv[s], p, o);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                *reinterpret_cast<bf16x8 *>(lds16 + s * STEP_HW + (((tid >> 6) * 3 + pl) * 64 + lane) * 8) = o[pl];
+        }
+    }
     __syncthreads(); // the slab, Cl
 
     for (; ch < a.numChunks; ch += cStep) {
@@ -1107,11 +1072,11 @@ bool xw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt)
     return true;
 }
 
-hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *wimg, const Operand &B,
+hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm, int sAk, const Operand &B,
                              void *out, int epi, float *psum, float *psq, hipStream_t st)
 {
     int nt;
-    if (!xw_conv_plan(N, M, K, HW, B.pro, epi, &nt) || !wimg)
+    if (!xw_conv_plan(N, M, K, HW, B.pro, epi, &nt))
         return hipErrorInvalidValue;
     X3WArgs a;
     a.M = M;
@@ -1120,7 +1085,9 @@ hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *wimg, cons
     a.Q = (uint32_t)((long long)N * HW);
     a.numChunks = (int)((a.Q + 31u) / 32u);
     a.divHW = make_div((uint32_t)HW);
-    a.img = (const uint16_t *)wimg;
+    a.w = (const float *)w;
+    a.sm = sAm;
+    a.sk = sAk;
     a.B = to_x3(B);
     a.out = (float *)out;
     a.psum = psum;

@@ -305,44 +305,42 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     void *d = at<char>(saved, P.o_d), *p = at<char>(saved, P.o_p);
     const float eps = desc->bn_eps, mom = desc->bn_momentum;
 
+    // Weight images of the convolutions that want them (the two data-gradient images only in
+    // training mode).  They are written by a launch that precedes their first reader anyway: the BN
+    // coefficients' in evaluation mode, BN2's finalise step in training mode, unless the expansion
+    // conv itself reads one.
+    const auto wimg = [&](int i) -> const void * {
+        return P.o_wimg[i] == kAbsent ? nullptr : at<char>(saved, P.o_wimg[i]);
+    };
+    X3PrepArgs prep = {};
+    prep.bf16 = bf;
+    {
+        const auto add = [&](int i, const void *w, int M, int K, int sm, int sk) {
+            if (P.o_wimg[i] != kAbsent)
+                x3_prep_add(prep, w, M, K, sm, sk, at<char>(saved, P.o_wimg[i]));
+        };
+        add(0, prm->w_expand, P.Cexp, P.Cin, P.Cin, 1);
+        add(1, prm->w_proj, P.Cout, P.Cexp, P.Cexp, 1);
+        if (!eval) {
+            add(2, prm->w_proj, P.Cexp, P.Cout, 1, P.Cexp);
+            add(3, prm->w_expand, P.Cin, P.Cexp, 1, P.Cin);
+        }
+    }
+    const bool prep_first = !eval && P.o_wimg[0] != kAbsent;
+    float *z = at<float>(saved, P.o_z), *g = at<float>(saved, P.o_g), *q = at<float>(saved, P.o_q);
+    // no squeeze-and-excitation stage: the gate every later prologue multiplies by is one, written by
+    // the same launches
+    float *ones = P.se ? nullptr : g;
+    const size_t ones_count = (size_t)P.N * P.Cexp;
     const auto eval_coefs = [&]() {
         return launch_bn_eval_coef(P.expand ? P.Cexp : 0, prm->bn1_gamma, prm->bn1_beta, run->bn1_mean,
                                    run->bn1_var, bn1, P.Cexp, prm->bn2_gamma, prm->bn2_beta,
                                    run->bn2_mean, run->bn2_var, bn2, P.Cout, prm->bn3_gamma,
-                                   prm->bn3_beta, run->bn3_mean, run->bn3_var, bn3, eps, st);
+                                   prm->bn3_beta, run->bn3_mean, run->bn3_var, bn3, eps, st, ones, ones_count,
+                                   &prep);
     };
     if (eval)
         MBK_STEP(P.expand ? MBCONV_STEP_BN1_FINALIZE : MBCONV_STEP_BN2_FINALIZE, eval_coefs());
-    // Weight images of the convolutions that want them (one launch; the two data-gradient images
-    // only in training mode).  The launch belongs to the step of the first convolution.
-    const auto wimg = [&](int i) -> const void * {
-        return P.o_wimg[i] == kAbsent ? nullptr : at<char>(saved, P.o_wimg[i]);
-    };
-    const auto prep_images = [&]() -> hipError_t {
-        const void *w[4];
-        int M[4], K[4], sm[4], sk[4], n = 0;
-        void *img[4];
-        const void *we = prm->w_expand, *wp = prm->w_proj;
-        const auto add = [&](int i, const void *src, int m, int k, int s_m, int s_k) {
-            if (P.o_wimg[i] == kAbsent)
-                return;
-            w[n] = src;
-            M[n] = m;
-            K[n] = k;
-            sm[n] = s_m;
-            sk[n] = s_k;
-            img[n] = at<char>(saved, P.o_wimg[i]);
-            ++n;
-        };
-        add(0, we, P.Cexp, P.Cin, P.Cin, 1);
-        add(1, wp, P.Cout, P.Cexp, P.Cexp, 1);
-        if (!eval) {
-            add(2, wp, P.Cexp, P.Cout, 1, P.Cexp);
-            add(3, we, P.Cin, P.Cexp, 1, P.Cin);
-        }
-        return n ? launch_x3_prep(bf, n, w, M, K, sm, sk, img, st) : hipSuccess;
-    };
-    bool images_ready = false;
     // expansion conv + BN1 statistics
     const void *dw_in = x;
     if (P.expand) {
@@ -351,14 +349,13 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
         B.p0 = x;
         B.pro = PRO_NONE;
         const auto conv = [&]() -> hipError_t {
-            const hipError_t pe = prep_images();
+            const hipError_t pe = prep_first ? launch_x3_prep(prep, st) : hipSuccess;
             if (pe != hipSuccess)
                 return pe;
             return launch_conv1x1(bf, P.N, P.Cexp, P.Cin, P.HW, prm->w_expand, P.Cin, 1, B, e, EPI_STATS,
                                   nullptr, psum, psq, nullptr, splitk, st, wimg(0));
         };
         MBK_STEP(MBCONV_STEP_EXPAND_CONV, conv());
-        images_ready = true;
         dw_in = e;
     }
     // A normalisation's finalise step (partial sums -> scale, shift, mean, rstd, running
@@ -381,21 +378,16 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     MBK_STEP(MBCONV_STEP_DW_FWD, launch_dw_fwd(bf, ds, dw_in, bn1, prm->w_dw, d, psum2, psq2, a1_store,
                                                fuse1 ? &fin1 : nullptr, st));
     // BN2 + Swish + SE squeeze, SE excite
-    float *z = at<float>(saved, P.o_z), *g = at<float>(saved, P.o_g), *q = at<float>(saved, P.o_q);
-    // no squeeze-and-excitation stage: the gate every later prologue multiplies by is one; in
-    // training BN2's finalisation writes it
     if (!eval)
         MBK_STEP(MBCONV_STEP_BN2_FINALIZE, launch_bn_finalize(P.Cexp, P.NPdw, m2, psum2, psq2, prm->bn2_gamma,
                                    prm->bn2_beta, eps, mom, run ? run->bn2_mean : nullptr,
-                                   run ? run->bn2_var : nullptr, bn2, st, P.se ? nullptr : g,
-                                   (size_t)P.N * P.Cexp));
+                                   run ? run->bn2_var : nullptr, bn2, st, ones, ones_count,
+                                   prep_first ? nullptr : &prep));
     if (P.se) {
         MBK_STEP(MBCONV_STEP_SE_POOL, launch_pool(bf, P.N, P.Cexp, P.HWo, d, bn2, z, at<float>(saved, P.o_s3),
                             at<float>(saved, P.o_s4), st));
         MBK_STEP(MBCONV_STEP_SE_FC, launch_se_fwd(P.N, P.Cexp, P.Cse, z, prm->se_w1, prm->se_b1, prm->se_w2, prm->se_b2, q,
                               g, st));
-    } else if (eval) {
-        MBK_STEP(MBCONV_STEP_SE_FC, launch_fill(g, 1.0f, (size_t)P.N * P.Cexp, st));
     }
     // projection conv on Swish(BN2(d))*g + BN3 statistics
     {
@@ -410,12 +402,6 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
             // go into the convolution's epilogue where the kernel family has one
             hipError_t fused = hipSuccess;
             const auto try_fused = [&]() {
-                if (!images_ready) { // a block without expansion conv
-                    const hipError_t pe = prep_images();
-                    if (pe != hipSuccess)
-                        return pe;
-                    images_ready = true;
-                }
                 fused = launch_conv1x1_affine(bf, P.N, P.Cout, P.Cexp, P.HWo, prm->w_proj, P.Cexp, 1, B,
                                               out, P.res ? x : nullptr, bn3, bn3 + P.Cout, st, wimg(1));
                 return fused == hipErrorNotSupported ? hipSuccess : fused;
@@ -426,12 +412,6 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
         }
         void *sc_store = (P.store && !eval) ? at<char>(saved, P.o_sc) : nullptr;
         const auto conv = [&]() -> hipError_t {
-            if (!images_ready) { // a block without expansion conv
-                const hipError_t pe = prep_images();
-                if (pe != hipSuccess)
-                    return pe;
-                images_ready = true;
-            }
             return launch_conv1x1(bf, P.N, P.Cout, P.Cexp, P.HWo, prm->w_proj, P.Cexp, 1, B, p, EPI_STATS,
                                   nullptr, psum, psq, sc_store, splitk, st, wimg(1));
         };

@@ -57,9 +57,27 @@ size_t conv1x1_splitk_floats(bool bf16, int N, int M, int K, int HW, bool stores
 bool conv1x1_uses_weight_image(bool bf16, int N, int M, int K, int HW, bool stores_operand,
                                int pro = -1, int epi = -1);
 size_t x3_weight_image_bytes(bool bf16, int M, int K);
-// Writes up to four images in one launch; image i is of A(m,k) = w[i][m*sm[i] + k*sk[i]], M[i] x K[i].
-hipError_t launch_x3_prep(bool bf16, int nsets, const void *const *w, const int *M, const int *K, const int *sm,
-                          const int *sk, void *const *img, hipStream_t st);
+// Up to four images: set i is of A(m,k) = w[m*sm + k*sk], M x K (w in the activation dtype).  They are
+// written by a launch of their own, or by extra workgroups of a launch that precedes their first
+// reader anyway (launch_bn_finalize, launch_bn_eval_coef).
+struct X3PrepSet {
+    const void *w;
+    int M, K, sm, sk;
+    uint16_t *img;
+    int CH, firstTile;
+};
+struct X3PrepArgs {
+    X3PrepSet s[4];
+    int nsets, tiles; // tiles: workgroups of 256 threads it takes
+    int bf16;         // the weights are stored as bf16: one plane
+};
+inline void x3_prep_add(X3PrepArgs &a, const void *w, int M, int K, int sm, int sk, void *img)
+{
+    const int CH = (K + 31) / 32;
+    a.s[a.nsets++] = {w, M, K, sm, sk, (uint16_t *)img, CH, a.tiles};
+    a.tiles += (M + 63) / 64 * CH;
+}
+hipError_t launch_x3_prep(const X3PrepArgs &a, hipStream_t st);
 hipError_t launch_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w, int sAm, int sAk,
                           const Operand &B, void *out, int epi, const void *res, float *psum,
                           float *psq, void *sc_store, float *splitk_ws, hipStream_t st,
@@ -150,22 +168,21 @@ inline BnFin make_bn_fin(const float *psum, const float *psq, const float *gamma
 
 // psum/psq: [C][NP] partial sums.  Writes bn = {scale[C], shift[C], mean[C], rstd[C]} and
 // updates running statistics (if non-null) with momentum.  If ones is non-null the same launch
-// also sets ones[0..ones_count) to 1.
+// also sets ones[0..ones_count) to 1; if prep is non-null it also writes those weight images.
 hipError_t launch_bn_finalize(int C, int NP, double m, const float *psum, const float *psq,
                               const float *gamma, const float *beta, float eps, float momentum,
                               float *run_mean, float *run_var, float *bn, hipStream_t st,
-                              float *ones = nullptr, size_t ones_count = 0);
+                              float *ones = nullptr, size_t ones_count = 0,
+                              const X3PrepArgs *prep = nullptr);
 
 // Evaluation mode: the same blocks from running statistics, three normalisations per launch
-// (C1 = 0 skips the first).
+// (C1 = 0 skips the first); ones and prep as above.
 hipError_t launch_bn_eval_coef(int C1, const float *gamma1, const float *beta1, const float *rm1,
                                const float *rv1, float *bn1, int C2, const float *gamma2,
                                const float *beta2, const float *rm2, const float *rv2, float *bn2,
                                int C3, const float *gamma3, const float *beta3, const float *rm3,
-                               const float *rv3, float *bn3, float eps, hipStream_t st);
-
-// out[i] = value, i < count.
-hipError_t launch_fill(float *out, float value, size_t count, hipStream_t st);
+                               const float *rv3, float *bn3, float eps, hipStream_t st, float *ones,
+                               size_t ones_count, const X3PrepArgs *prep);
 
 // Block without a squeeze-and-excitation stage (gate = 1, dz = 0): BN2's backward from the
 // plane sums A1 = sum G*act'(y2), A2 = sum G*act'(y2)*dhat, both [N][C]:

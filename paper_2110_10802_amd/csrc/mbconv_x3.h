@@ -1,5 +1,5 @@
-// fp32 contractions on the bf16 matrix cores: the three-plane operand split and its MFMA, shared by
-// kernels_x3.hip (which derives it) and kernels_xk.hip.
+// fp32 contractions on the bf16 matrix cores: the three-plane operand split and its MFMA, and the
+// weight images; shared by kernels_x3.hip (which derives them), kernels_xk.hip and kernels_misc.hip.
 #pragma once
 #include "mbconv_dev.h"
 #include "mbconv_launch.h"
@@ -66,6 +66,44 @@ __device__ __forceinline__ void x3_split8(const float (&v)[8], uint32_t (&p)[4][
         const u32x4 q = {p[0][pl], p[1][pl], p[2][pl], p[3][pl]};
         o[pl] = __builtin_bit_cast(bf16x8, q);
     }
+}
+
+// One tile (64 rows x 32 k) of a weight image, by a workgroup of 256 threads: thread -> (row tid/4,
+// eight k at 8*(tid%4)).  The layout: kernels_x3.hip.
+__device__ __forceinline__ void x3_prep_tile(const X3PrepArgs &a, int tile)
+{
+    int si = 0;
+#pragma unroll
+    for (int i = 1; i < 4; ++i)
+        if (i < a.nsets && tile >= a.s[i].firstTile)
+            si = i;
+    const X3PrepSet S = a.s[si];
+    const int local = tile - S.firstTile, mt = local / S.CH, ch = local % S.CH;
+    const int tid = threadIdx.x, r = tid >> 2, g = tid & 3;
+    const int m = mt * 64 + r, k0 = ch * 32 + 8 * g;
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int k = k0 + j;
+        const size_t at = (size_t)m * S.sm + (size_t)k * S.sk;
+        v[j] = (m < S.M && k < S.K) ? (a.bf16 ? ld<bf16_t>((const bf16_t *)S.w, at) : ((const float *)S.w)[at])
+                                    : 0.f;
+    }
+    const int lane = (r & 15) + 16 * g;
+    if (a.bf16) { // (uniform) the values are bf16 already: packing them rounds nothing
+        *reinterpret_cast<uint4 *>(S.img + ((size_t)mt * S.CH + ch) * 2048 + ((r >> 4) * 64 + lane) * 8) =
+            make_uint4(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]), bf16_pack2(v[4], v[5]),
+                       bf16_pack2(v[6], v[7]));
+        return;
+    }
+    uint32_t w[4][3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        x3_split2(v[2 * j], v[2 * j + 1], w[j]);
+    uint16_t *dst = S.img + ((size_t)mt * S.CH + ch) * 3 * 2048 + ((r >> 4) * 3 * 64 + lane) * 8;
+#pragma unroll
+    for (int pl = 0; pl < 3; ++pl)
+        *reinterpret_cast<uint4 *>(dst + pl * 512) = make_uint4(w[0][pl], w[1][pl], w[2][pl], w[3][pl]);
 }
 
 } // namespace mbk
