@@ -5,7 +5,7 @@
 // register pass plus a DPP wavefront reduction and the row is read from HBM exactly once (the
 // paper's warp tiling with warp-level reductions, section "Softmax"; what depends on a
 // reduction is recomputed from registers instead of being written out).  Rows longer than 2048
-// take a workgroup per row with the row in LDS.  The weight gradients of layer normalisation
+// take a workgroup per row, rows of one to three columns a thread.  The weight gradients of layer normalisation
 // are accumulated per lane over the rows a wavefront walks (a lane owns the same columns in
 // every row), combined over the four wavefronts of a workgroup in LDS, written once per
 // workgroup and added in a fixed order by a second stage: no atomics.
@@ -17,6 +17,7 @@
 #include "mbconv_dev.h"
 #include "mbconv_launch.h"
 
+#include <algorithm>
 #include <mutex>
 
 namespace mbk {
@@ -92,201 +93,64 @@ __global__ __launch_bounds__(256) void mish_kernel(const float *__restrict__ x, 
 }
 
 // ---- rows in registers ------------------------------------------------------------------------
-// Lane l, vector j covers columns 4*(l + 64*j) .. +3.  cols % 4 == 0, cols <= 256*NV.
-template <int NV>
+// TPR threads own a row (a DPP row of 16 lanes up to 128 columns, a wavefront up to 2048, else the whole
+// workgroup): thread t, vector j covers columns 4*(t + TPR*j) .. +3, cols >= 4, cols <= 4*TPR*NV.  Rows
+// whose length is no multiple of four start at any 4-byte boundary (the 16-byte accesses of this chip
+// may) and end in a partial vector: it is moved back to the row's last four columns, `own` tells the
+// columns that no other thread covers, and both threads write the same values to the others.  Softmax
+// of 48768 x 381, forward and backward: 63.5 us (5.9 TB/s); with a workgroup per row, the row in LDS and
+// 4-byte accesses 112.6.  4000 x 8192: 112 us against 270.  The 16 lanes: 65536 x 45 10.9 us against 21.6
+// with a wavefront per row.  RAG: cols % 4 != 0 (the masks cost 4096 x 1024 five per cent forward).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int NV, int TPR, bool RAG>
 struct RowRegs {
     float v[NV][4];
-    __device__ __forceinline__ void load(const float *row, int cols, int lane, float fill)
+    static __device__ __forceinline__ int start(int cols, int t, int j) { return min(4 * (t + TPR * j), cols - 4); }
+    static __device__ __forceinline__ bool own(int cols, int t, int j, int k)
+    {
+        const int c = 4 * (t + TPR * j);
+        return c < cols && (!RAG || min(c, cols - 4) + k >= c);
+    }
+    __device__ __forceinline__ void load(const float *row, int cols, int t)
     {
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            const int c = 4 * (lane + 64 * j);
-            const float4 t = *reinterpret_cast<const float4 *>(row + min(c, cols - 4));
-            const bool ok = c < cols;
-            v[j][0] = ok ? t.x : fill;
-            v[j][1] = ok ? t.y : fill;
-            v[j][2] = ok ? t.z : fill;
-            v[j][3] = ok ? t.w : fill;
+            const f32x4u x = *reinterpret_cast<const f32x4u *>(row + start(cols, t, j));
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                v[j][k] = x[k];
         }
     }
-    __device__ __forceinline__ void store(float *row, int cols, int lane) const
+    __device__ __forceinline__ void store(float *row, int cols, int t) const
     {
 #pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            const int c = 4 * (lane + 64 * j);
-            if (c < cols)
-                *reinterpret_cast<float4 *>(row + c) = make_float4(v[j][0], v[j][1], v[j][2], v[j][3]);
-        }
+        for (int j = 0; j < NV; ++j)
+            if (4 * (t + TPR * j) < cols)
+                *reinterpret_cast<f32x4u *>(row + start(cols, t, j)) = (f32x4u){v[j][0], v[j][1], v[j][2], v[j][3]};
     }
 };
 
-template <int NV>
-__global__ __launch_bounds__(256) void layernorm_fwd_kernel(const float *__restrict__ x,
-                                                            const float *__restrict__ gamma,
-                                                            const float *__restrict__ beta, float eps,
-                                                            int rows, int cols, float *y, float *mean,
-                                                            float *rstd)
+__device__ __forceinline__ float row16_max(float v)
 {
-    const int lane = threadIdx.x & 63;
-    const int wave = blockIdx.x * 4 + (threadIdx.x >> 6), nwaves = gridDim.x * 4;
-    RowRegs<NV> g, b;
-    g.load(gamma, cols, lane, 0.f);
-    b.load(beta, cols, lane, 0.f);
-    const float inv = 1.0f / (float)cols;
-    for (int r = wave; r < rows; r += nwaves) {
-        RowRegs<NV> a;
-        a.load(x + (size_t)r * cols, cols, lane, 0.f);
-        float s = 0.f;
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                s += a.v[j][k];
-        const float mu = wave_sum(s) * inv;
-        float s2 = 0.f;
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float d = (4 * (lane + 64 * j) < cols) ? a.v[j][k] - mu : 0.f;
-                s2 = fmaf(d, d, s2);
-            }
-        const float rs = 1.0f / sqrtf(wave_sum(s2) * inv + eps);
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                a.v[j][k] = fmaf(g.v[j][k], (a.v[j][k] - mu) * rs, b.v[j][k]);
-        a.store(y + (size_t)r * cols, cols, lane);
-        if (lane == 0) {
-            mean[r] = mu;
-            rstd[r] = rs;
-        }
-    }
+#define MBK_STEP(ctrl)                                                                            \
+    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xf, 0xf, false)));
+    MBK_STEP(0x128) // row_ror:8
+    MBK_STEP(0x124)
+    MBK_STEP(0x122)
+    MBK_STEP(0x121)
+#undef MBK_STEP
+    return v;
 }
 
-template <int NV>
-__global__ __launch_bounds__(256) void layernorm_bwd_kernel(const float *__restrict__ x,
-                                                            const float *__restrict__ dy,
-                                                            const float *__restrict__ gamma,
-                                                            const float *__restrict__ mean,
-                                                            const float *__restrict__ rstd, int rows,
-                                                            int cols, float *dx, float *pgamma,
-                                                            float *pbeta)
+// Sum (or maximum) over the TPR threads of a row, the same bits in all of them.
+template <int TPR>
+__device__ __forceinline__ float row_reduce(float v, float *red, bool is_max)
 {
-    const int lane = threadIdx.x & 63;
-    const int wave = blockIdx.x * 4 + (threadIdx.x >> 6), nwaves = gridDim.x * 4;
-    RowRegs<NV> g, ag, ab;
-    g.load(gamma, cols, lane, 0.f);
-#pragma unroll
-    for (int j = 0; j < NV; ++j)
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            ag.v[j][k] = ab.v[j][k] = 0.f;
-    const float inv = 1.0f / (float)cols;
-    for (int r = wave; r < rows; r += nwaves) {
-        RowRegs<NV> a, d;
-        a.load(x + (size_t)r * cols, cols, lane, 0.f);
-        d.load(dy + (size_t)r * cols, cols, lane, 0.f);
-        const float mu = mean[r], rs = rstd[r];
-        float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float xh = (a.v[j][k] - mu) * rs; // padded columns: dy = 0 there
-                const float gg = d.v[j][k] * g.v[j][k];
-                ag.v[j][k] = fmaf(d.v[j][k], xh, ag.v[j][k]);
-                ab.v[j][k] += d.v[j][k];
-                a.v[j][k] = xh;
-                d.v[j][k] = gg;
-                s1 += gg;
-                s2 = fmaf(gg, xh, s2);
-            }
-        const float m1 = wave_sum(s1) * inv, m2 = wave_sum(s2) * inv;
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                d.v[j][k] = rs * (d.v[j][k] - m1 - a.v[j][k] * m2);
-        d.store(dx + (size_t)r * cols, cols, lane);
-    }
-    // one partial row per workgroup: the four wavefronts are added in a fixed order through LDS
-    __shared__ float part[2][4][256 * NV];
-    const int wv = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < NV; ++j)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            part[0][wv][4 * (lane + 64 * j) + k] = ag.v[j][k];
-            part[1][wv][4 * (lane + 64 * j) + k] = ab.v[j][k];
-        }
-    __syncthreads();
-    for (int c = threadIdx.x; c < cols; c += 256) {
-        pgamma[(size_t)blockIdx.x * cols + c] = (part[0][0][c] + part[0][1][c]) + (part[0][2][c] + part[0][3][c]);
-        pbeta[(size_t)blockIdx.x * cols + c] = (part[1][0][c] + part[1][1][c]) + (part[1][2][c] + part[1][3][c]);
-    }
-}
-
-template <int NV, bool BWD>
-__global__ __launch_bounds__(256) void softmax_kernel(const float *__restrict__ in0,
-                                                      const float *__restrict__ in1, float *out,
-                                                      int rows, int cols)
-{
-    const int lane = threadIdx.x & 63;
-    const int wave = blockIdx.x * 4 + (threadIdx.x >> 6), nwaves = gridDim.x * 4;
-    for (int r = wave; r < rows; r += nwaves) {
-        RowRegs<NV> a;
-        if (!BWD) {
-            a.load(in0 + (size_t)r * cols, cols, lane, -INFINITY);
-            float m = -INFINITY;
-#pragma unroll
-            for (int j = 0; j < NV; ++j)
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    m = fmaxf(m, a.v[j][k]);
-            m = wave_max(m);
-            float s = 0.f;
-#pragma unroll
-            for (int j = 0; j < NV; ++j)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    a.v[j][k] = __expf(a.v[j][k] - m); // padded columns: exp(-inf) = 0
-                    s += a.v[j][k];
-                }
-            const float is = 1.0f / wave_sum(s);
-#pragma unroll
-            for (int j = 0; j < NV; ++j)
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    a.v[j][k] *= is;
-        } else {
-            RowRegs<NV> d;
-            a.load(in0 + (size_t)r * cols, cols, lane, 0.f); // y
-            d.load(in1 + (size_t)r * cols, cols, lane, 0.f); // dy
-            float s = 0.f;
-#pragma unroll
-            for (int j = 0; j < NV; ++j)
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    s = fmaf(d.v[j][k], a.v[j][k], s);
-            s = wave_sum(s);
-#pragma unroll
-            for (int j = 0; j < NV; ++j)
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    a.v[j][k] *= d.v[j][k] - s;
-        }
-        a.store(out + (size_t)r * cols, cols, lane);
-    }
-}
-
-// ---- long or ragged rows: a workgroup per row, the row staged in LDS ----------------------------
-// mode 0: layer-norm forward, 1: layer-norm backward (dx only; the column sums are taken by
-// colsum_kernel), 2: softmax forward, 3: softmax backward.
-__device__ __forceinline__ float block_reduce(float v, float *red, bool is_max)
-{
+    if (TPR == 16)
+        return is_max ? row16_max(v) : row16_sum(v);
     v = is_max ? wave_max(v) : wave_sum(v);
+    if (TPR == kWave)
+        return v;
     __syncthreads(); // red may still be read from the previous reduction
     if ((threadIdx.x & 63) == 0)
         red[threadIdx.x >> 6] = v;
@@ -298,80 +162,260 @@ __device__ __forceinline__ float block_reduce(float v, float *red, bool is_max)
     return r;
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void row_generic_kernel(const float *__restrict__ in0,
-                                                          const float *__restrict__ in1,
-                                                          const float *__restrict__ gamma,
-                                                          const float *__restrict__ beta, float eps,
-                                                          int rows, int cols, float *out, float *mean,
-                                                          float *rstd)
+template <int NV, int TPR, bool RAG>
+__global__ __launch_bounds__(256) void layernorm_fwd_kernel(const float *__restrict__ x,
+                                                            const float *__restrict__ gamma,
+                                                            const float *__restrict__ beta, float eps,
+                                                            int rows, int cols, float *y, float *mean,
+                                                            float *rstd)
 {
-    extern __shared__ float rowbuf[]; // [cols] (+ [cols] for the two-input modes)
     __shared__ float red[4];
-    const int tid = threadIdx.x;
+    const int t = threadIdx.x % TPR;
+    const int first = blockIdx.x * (256 / TPR) + threadIdx.x / TPR, step = gridDim.x * (256 / TPR);
+    RowRegs<NV, TPR, RAG> g, b;
+    g.load(gamma, cols, t);
+    b.load(beta, cols, t);
     const float inv = 1.0f / (float)cols;
-    for (int r = blockIdx.x; r < rows; r += gridDim.x) {
-        const size_t o = (size_t)r * cols;
-        __syncthreads(); // the previous row's buffer has been consumed
-        for (int c = tid; c < cols; c += 256) {
-            rowbuf[c] = in0[o + c];
-            if (MODE == 1 || MODE == 3)
-                rowbuf[cols + c] = in1[o + c];
-        }
-        __syncthreads();
-        if (MODE == 0) {
-            float s = 0.f;
-            for (int c = tid; c < cols; c += 256)
-                s += rowbuf[c];
-            const float mu = block_reduce(s, red, false) * inv;
-            float s2 = 0.f;
-            for (int c = tid; c < cols; c += 256)
-                s2 = fmaf(rowbuf[c] - mu, rowbuf[c] - mu, s2);
-            const float rs = 1.0f / sqrtf(block_reduce(s2, red, false) * inv + eps);
-            for (int c = tid; c < cols; c += 256)
-                out[o + c] = fmaf(gamma[c], (rowbuf[c] - mu) * rs, beta[c]);
-            if (tid == 0) {
-                mean[r] = mu;
-                rstd[r] = rs;
+    for (int r = first; r < rows; r += step) {
+        RowRegs<NV, TPR, RAG> a;
+        a.load(x + (size_t)r * cols, cols, t);
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                s += a.own(cols, t, j, k) ? a.v[j][k] : 0.f;
+        const float mu = row_reduce<TPR>(s, red, false) * inv;
+        float s2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float d = a.own(cols, t, j, k) ? a.v[j][k] - mu : 0.f;
+                s2 = fmaf(d, d, s2);
             }
-        } else if (MODE == 1) { // in0 = x, in1 = dy
-            const float mu = mean[r], rs = rstd[r];
-            float s1 = 0.f, s2 = 0.f;
-            for (int c = tid; c < cols; c += 256) {
-                const float gg = rowbuf[cols + c] * gamma[c];
-                s1 += gg;
-                s2 = fmaf(gg, (rowbuf[c] - mu) * rs, s2);
-            }
-            const float m1 = block_reduce(s1, red, false) * inv;
-            const float m2 = block_reduce(s2, red, false) * inv;
-            for (int c = tid; c < cols; c += 256)
-                out[o + c] = rs * (rowbuf[cols + c] * gamma[c] - m1 - (rowbuf[c] - mu) * rs * m2);
-        } else if (MODE == 2) {
-            float m = -INFINITY;
-            for (int c = tid; c < cols; c += 256)
-                m = fmaxf(m, rowbuf[c]);
-            m = block_reduce(m, red, true);
-            float s = 0.f;
-            for (int c = tid; c < cols; c += 256) {
-                const float e = __expf(rowbuf[c] - m);
-                rowbuf[c] = e; // each thread rewrites only its own columns
-                s += e;
-            }
-            const float is = 1.0f / block_reduce(s, red, false);
-            for (int c = tid; c < cols; c += 256)
-                out[o + c] = rowbuf[c] * is;
-        } else { // in0 = y, in1 = dy
-            float s = 0.f;
-            for (int c = tid; c < cols; c += 256)
-                s = fmaf(rowbuf[cols + c], rowbuf[c], s);
-            s = block_reduce(s, red, false);
-            for (int c = tid; c < cols; c += 256)
-                out[o + c] = rowbuf[c] * (rowbuf[cols + c] - s);
+        const float rs = 1.0f / sqrtf(row_reduce<TPR>(s2, red, false) * inv + eps);
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                a.v[j][k] = fmaf(g.v[j][k], (a.v[j][k] - mu) * rs, b.v[j][k]);
+        a.store(y + (size_t)r * cols, cols, t);
+        if (t == 0) {
+            mean[r] = mu;
+            rstd[r] = rs;
         }
     }
 }
 
-// Column sums for the generic layer-norm backward: workgroup (column block of 64, row slice)
+// Rows of up to 1024 (4096): the next row is requested before this one is reduced.  With 16 rows per
+// workgroup there are few wavefronts, and their loads have to overlap the reductions (4096 x 1024:
+// 10.5 us; 11.5 without).  Longer rows have no registers for it.
+template <int NV, int TPR, bool RAG>
+__global__ __launch_bounds__(256) void layernorm_bwd_kernel(const float *__restrict__ x,
+                                                            const float *__restrict__ dy,
+                                                            const float *__restrict__ gamma,
+                                                            const float *__restrict__ mean,
+                                                            const float *__restrict__ rstd, int rows,
+                                                            int cols, float *dx, float *pgamma,
+                                                            float *pbeta)
+{
+    __shared__ float red[4];
+    const int t = threadIdx.x % TPR;
+    const int first = blockIdx.x * (256 / TPR) + threadIdx.x / TPR, step = gridDim.x * (256 / TPR);
+    RowRegs<NV, TPR, RAG> g, ag, ab, na, nd;
+    g.load(gamma, cols, t);
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            ag.v[j][k] = ab.v[j][k] = 0.f;
+    const float inv = 1.0f / (float)cols;
+    constexpr bool AHEAD = NV <= 4;
+    const auto fetch = [&](int r) __attribute__((always_inline)) {
+        na.load(x + (size_t)r * cols, cols, t);
+        nd.load(dy + (size_t)r * cols, cols, t);
+    };
+    if (AHEAD && first < rows)
+        fetch(first);
+    for (int r = first; r < rows; r += step) {
+        if (!AHEAD)
+            fetch(r);
+        RowRegs<NV, TPR, RAG> a = na, d = nd;
+        const float mu = mean[r], rs = rstd[r];
+        if (AHEAD)
+            fetch(min(r + step, rows - 1)); // (past the end the last row again, never used)
+        float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float xh = (a.v[j][k] - mu) * rs;
+                const float gg = d.v[j][k] * g.v[j][k];
+                ag.v[j][k] = fmaf(d.v[j][k], xh, ag.v[j][k]);
+                ab.v[j][k] += d.v[j][k];
+                a.v[j][k] = xh;
+                d.v[j][k] = gg;
+                const float gm = a.own(cols, t, j, k) ? gg : 0.f;
+                s1 += gm;
+                s2 = fmaf(gm, xh, s2);
+            }
+        const float m1 = row_reduce<TPR>(s1, red, false) * inv, m2 = row_reduce<TPR>(s2, red, false) * inv;
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                d.v[j][k] = rs * (d.v[j][k] - m1 - a.v[j][k] * m2);
+        d.store(dx + (size_t)r * cols, cols, t);
+    }
+    // one partial row per workgroup: the thread groups of different rows are added in a fixed order
+    // through LDS (a workgroup per row: every column has one thread)
+    if (TPR == 256) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (ag.own(cols, t, j, k)) {
+                    const int c = ag.start(cols, t, j) + k;
+                    pgamma[(size_t)blockIdx.x * cols + c] = ag.v[j][k];
+                    pbeta[(size_t)blockIdx.x * cols + c] = ab.v[j][k];
+                }
+        return;
+    }
+    constexpr int G = 256 / TPR, GC = TPR == 256 ? 1 : 4 * TPR * NV;
+    __shared__ float part[2][G][GC];
+    const int grp = threadIdx.x / TPR;
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (ag.own(cols, t, j, k)) {
+                const int c = (ag.start(cols, t, j) + k) % GC;
+                part[0][grp][c] = ag.v[j][k];
+                part[1][grp][c] = ab.v[j][k];
+            }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * cols; i += 256) {
+        const int w = i >= cols, c = i - w * cols;
+        float s = 0.f;
+#pragma unroll
+        for (int u = 0; u < G; u += 4)
+            s += (part[w][u][c % GC] + part[w][(u + 1) % G][c % GC]) + (part[w][(u + 2) % G][c % GC] + part[w][(u + 3) % G][c % GC]);
+        (w ? pbeta : pgamma)[(size_t)blockIdx.x * cols + c] = s;
+    }
+}
+
+template <int NV, int TPR, bool RAG, bool BWD>
+__global__ __launch_bounds__(256) void softmax_kernel(const float *__restrict__ in0, const float *in1, float *out,
+                                                      int rows, int cols)
+{
+    __shared__ float red[4];
+    const int t = threadIdx.x % TPR;
+    const int first = blockIdx.x * (256 / TPR) + threadIdx.x / TPR, step = gridDim.x * (256 / TPR);
+    for (int r = first; r < rows; r += step) {
+        RowRegs<NV, TPR, RAG> a;
+        a.load(in0 + (size_t)r * cols, cols, t);
+        if (!BWD) {
+            float m = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) // (columns read twice, or past the end: another thread's as well)
+                    m = fmaxf(m, a.v[j][k]);
+            m = row_reduce<TPR>(m, red, true);
+            float s = 0.f;
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    a.v[j][k] = __expf(a.v[j][k] - m);
+                    s += a.own(cols, t, j, k) ? a.v[j][k] : 0.f;
+                }
+            const float is = 1.0f / row_reduce<TPR>(s, red, false);
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    a.v[j][k] *= is;
+        } else {
+            RowRegs<NV, TPR, RAG> d;
+            d.load(in1 + (size_t)r * cols, cols, t); // dy (in0 is y)
+            float s = 0.f;
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    s = fmaf(d.v[j][k], a.own(cols, t, j, k) ? a.v[j][k] : 0.f, s);
+            s = row_reduce<TPR>(s, red, false);
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    a.v[j][k] *= d.v[j][k] - s;
+        }
+        a.store(out + (size_t)r * cols, cols, t);
+    }
+}
+
+// ---- rows of one to three columns: a thread per row ------------------------------------------------
+// mode 0: layer-norm forward, 1: layer-norm backward (dx only; the column sums are taken by
+// ln_colsum_kernel), 2: softmax forward, 3: softmax backward.
+template <int MODE>
+__global__ __launch_bounds__(256) void row_short_kernel(const float *__restrict__ in0, const float *in1,
+                                                        const float *__restrict__ gamma,
+                                                        const float *__restrict__ beta, float eps,
+                                                        int rows, int cols, float *out, float *mean,
+                                                        float *rstd)
+{
+    const float inv = 1.0f / (float)cols;
+    for (int r = blockIdx.x * 256 + threadIdx.x; r < rows; r += gridDim.x * 256) {
+        const size_t o = (size_t)r * cols;
+        float a[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 0.f};
+        for (int c = 0; c < cols; ++c) {
+            a[c] = in0[o + c];
+            if (MODE == 1 || MODE == 3)
+                d[c] = in1[o + c];
+        }
+        if (MODE == 0) {
+            const float mu = (a[0] + a[1] + a[2]) * inv;
+            float s2 = 0.f;
+            for (int c = 0; c < cols; ++c)
+                s2 = fmaf(a[c] - mu, a[c] - mu, s2);
+            const float rs = 1.0f / sqrtf(s2 * inv + eps);
+            for (int c = 0; c < cols; ++c)
+                out[o + c] = fmaf(gamma[c], (a[c] - mu) * rs, beta[c]);
+            mean[r] = mu;
+            rstd[r] = rs;
+        } else if (MODE == 1) { // in0 = x, in1 = dy
+            const float mu = mean[r], rs = rstd[r];
+            float s1 = 0.f, s2 = 0.f;
+            for (int c = 0; c < cols; ++c) {
+                const float gg = d[c] * gamma[c];
+                s1 += gg;
+                s2 = fmaf(gg, (a[c] - mu) * rs, s2);
+            }
+            for (int c = 0; c < cols; ++c)
+                out[o + c] = rs * (d[c] * gamma[c] - s1 * inv - (a[c] - mu) * rs * (s2 * inv));
+        } else if (MODE == 2) {
+            float m = -INFINITY, s = 0.f;
+            for (int c = 0; c < cols; ++c)
+                m = fmaxf(m, a[c]);
+            for (int c = 0; c < cols; ++c) {
+                a[c] = __expf(a[c] - m);
+                s += a[c];
+            }
+            const float is = 1.0f / s;
+            for (int c = 0; c < cols; ++c)
+                out[o + c] = a[c] * is;
+        } else { // in0 = y, in1 = dy
+            const float s = fmaf(a[0], d[0], fmaf(a[1], d[1], a[2] * d[2]));
+            for (int c = 0; c < cols; ++c)
+                out[o + c] = a[c] * (d[c] - s);
+        }
+    }
+}
+
+// Column sums for the layer-norm backward of such rows: workgroup (column block of 64, row slice)
 // writes partial[slice][cols] for dgamma and dbeta; rows are added in ascending order.
 __global__ __launch_bounds__(256) void ln_colsum_kernel(const float *__restrict__ x,
                                                         const float *__restrict__ dy,
@@ -403,16 +447,22 @@ __global__ __launch_bounds__(256) void ln_colsum_kernel(const float *__restrict_
 // ---- host side ----------------------------------------------------------------------------------
 bool bad_align(const void *p) { return ((uintptr_t)p & 15u) != 0; }
 
-// rows in registers: cols % 4 == 0 and cols <= 2048
+// form of the row kernels: 1, 2, 4, 8: that many vectors per thread with a wavefront per row (129 to
+// 2048 columns); -1, -2: one and two with 16 lanes per row; 16, 32: four and eight with a workgroup per
+// row; 0: rows of less than four columns
 int row_nv(int cols)
 {
-    if (cols % 4 != 0 || cols > 2048)
+    if (cols < 4)
         return 0;
+    if (cols <= 128)
+        return cols <= 64 ? -1 : -2;
+    if (cols > 2048)
+        return cols <= 4096 ? 16 : 32;
     return cols <= 256 ? 1 : cols <= 512 ? 2 : cols <= 1024 ? 4 : 8;
 }
-int row_grid(int rows) // four rows per workgroup in flight, at most 2048 workgroups
+int row_grid(int rows, int nv) // a workgroup's rows (16, four, or one) in flight, at most 2048 workgroups
 {
-    const int g = (rows + 3) / 4;
+    const int g = nv >= 16 ? rows : nv < 0 ? (rows + 15) / 16 : (rows + 3) / 4;
     return g < 1 ? 1 : (g > 2048 ? 2048 : g);
 }
 int row_grid_bwd(int rows) // sixteen rows per workgroup, at most 512 partial rows
@@ -420,11 +470,24 @@ int row_grid_bwd(int rows) // sixteen rows per workgroup, at most 512 partial ro
     const int g = (rows + 15) / 16;
     return g < 1 ? 1 : (g > 512 ? 512 : g);
 }
-int generic_grid(int rows) { return rows > 4096 ? 4096 : rows; }
-int ln_slices(int rows) // row slices of the generic column sums
+int short_grid(int rows) { return std::min((rows + 255) / 256, 4096); }
+int ln_slices(int rows) // row slices of the column sums of rows of less than four columns
 {
     const int s = (rows + 63) / 64;
     return s > 256 ? 256 : (s < 1 ? 1 : s);
+}
+// Partial rows of the layer-norm weight gradients (one per workgroup of the backward kernel).  Rows
+// longer than 2048: a workgroup per row up to 256, and no more than the 8 MiB of the static scratch
+// hold wherever one per 64 rows fits into them (the shapes the entry point without scratch takes).
+int ln_parts(int rows, int cols)
+{
+    const int nv = row_nv(cols);
+    if (!nv)
+        return ln_slices(rows);
+    if (nv < 16)
+        return row_grid_bwd(rows);
+    const int fits = (1 << 20) / cols;
+    return ln_slices(rows) > fits ? ln_slices(rows) : std::min(rows, std::min(fits, 256));
 }
 
 } // namespace
@@ -493,12 +556,27 @@ dnnops_status dnnops_mish_backward(const float *x, const float *dy, float *dx, s
     return hipGetLastError() == hipSuccess ? DNNOPS_OK : DNNOPS_EHIP;
 }
 
-#define DNNOPS_NV_SWITCH(nv, CALL)                                                                \
+#define DNNOPS_FORM(n, v, tpr, ...)                                                               \
+    case n: {                                                                                     \
+        constexpr int NV = v, TPR = tpr;                                                          \
+        if (cols % 4 != 0) {                                                                      \
+            constexpr bool RAG = true;                                                            \
+            __VA_ARGS__;                                                                          \
+        } else {                                                                                  \
+            constexpr bool RAG = false;                                                           \
+            __VA_ARGS__;                                                                          \
+        }                                                                                         \
+    } break;
+#define DNNOPS_NV_SWITCH(nv, ...)                                                                 \
     switch (nv) {                                                                                 \
-    case 1: { constexpr int NV = 1; CALL; } break;                                                \
-    case 2: { constexpr int NV = 2; CALL; } break;                                                \
-    case 4: { constexpr int NV = 4; CALL; } break;                                                \
-    default: { constexpr int NV = 8; CALL; } break;                                               \
+        DNNOPS_FORM(-1, 1, 16, __VA_ARGS__)                                                       \
+        DNNOPS_FORM(-2, 2, 16, __VA_ARGS__)                                                       \
+        DNNOPS_FORM(1, 1, 64, __VA_ARGS__)                                                        \
+        DNNOPS_FORM(2, 2, 64, __VA_ARGS__)                                                        \
+        DNNOPS_FORM(4, 4, 64, __VA_ARGS__)                                                        \
+        DNNOPS_FORM(8, 8, 64, __VA_ARGS__)                                                        \
+        DNNOPS_FORM(16, 4, 256, __VA_ARGS__)                                                      \
+        DNNOPS_FORM(32, 8, 256, __VA_ARGS__)                                                      \
     }
 
 dnnops_status dnnops_layernorm_forward(const float *x, const float *gamma, const float *beta,
@@ -514,11 +592,10 @@ dnnops_status dnnops_layernorm_forward(const float *x, const float *gamma, const
     hipStream_t st = (hipStream_t)hip_stream;
     const int nv = row_nv(cols);
     if (nv) {
-        DNNOPS_NV_SWITCH(nv, hipLaunchKernelGGL((layernorm_fwd_kernel<NV>), dim3(row_grid(rows)), dim3(256),
+        DNNOPS_NV_SWITCH(nv, hipLaunchKernelGGL((layernorm_fwd_kernel<NV, TPR, RAG>), dim3(row_grid(rows, nv)), dim3(256),
                                                 0, st, x, gamma, beta, eps, rows, cols, y, mean, rstd));
     } else {
-        hipLaunchKernelGGL((row_generic_kernel<0>), dim3(generic_grid(rows)), dim3(256),
-                           sizeof(float) * cols, st, x, (const float *)nullptr, gamma, beta, eps, rows,
+        hipLaunchKernelGGL((row_short_kernel<0>), dim3(short_grid(rows)), dim3(256), 0, st, x, (const float *)nullptr, gamma, beta, eps, rows,
                            cols, y, mean, rstd);
     }
     return hipGetLastError() == hipSuccess ? DNNOPS_OK : DNNOPS_EHIP;
@@ -528,7 +605,7 @@ size_t dnnops_layernorm_backward_scratch_bytes(int32_t rows, int32_t cols)
 {
     if (rows < 1 || cols < 1 || cols > DNNOPS_MAX_COLS)
         return 0;
-    const size_t parts = row_nv(cols) ? (size_t)row_grid_bwd(rows) : (size_t)ln_slices(rows);
+    const size_t parts = (size_t)ln_parts(rows, cols);
     return 2 * parts * (size_t)cols * sizeof(float);
 }
 
@@ -553,18 +630,15 @@ static dnnops_status layernorm_backward_launch(const float *x, const float *dy, 
                                                void *scratch, hipStream_t st)
 {
     const int nv = row_nv(cols);
-    int parts;
+    const int parts = ln_parts(rows, cols);
     float *pg = (float *)scratch;
     if (nv) {
-        parts = row_grid_bwd(rows);
         float *pb = pg + (size_t)parts * cols;
-        DNNOPS_NV_SWITCH(nv, hipLaunchKernelGGL((layernorm_bwd_kernel<NV>), dim3(parts), dim3(256),
+        DNNOPS_NV_SWITCH(nv, hipLaunchKernelGGL((layernorm_bwd_kernel<NV, TPR, RAG>), dim3(parts), dim3(256),
                                                 0, st, x, dy, gamma, mean, rstd, rows, cols, dx, pg, pb));
     } else {
-        parts = ln_slices(rows);
         float *pb = pg + (size_t)parts * cols;
-        hipLaunchKernelGGL((row_generic_kernel<1>), dim3(generic_grid(rows)), dim3(256),
-                           2 * sizeof(float) * cols, st, x, dy, gamma, (const float *)nullptr, 0.f,
+        hipLaunchKernelGGL((row_short_kernel<1>), dim3(short_grid(rows)), dim3(256), 0, st, x, dy, gamma, (const float *)nullptr, 0.f,
                            rows, cols, dx, const_cast<float *>(mean), const_cast<float *>(rstd));
         const int per = (rows + parts - 1) / parts;
         hipLaunchKernelGGL(ln_colsum_kernel, dim3((cols + 63) / 64, parts), dim3(256), 0, st, x, dy,
@@ -628,20 +702,18 @@ static dnnops_status softmax_launch(bool bwd, const float *in0, const float *in1
     const int nv = row_nv(cols);
     if (nv) {
         if (bwd) {
-            DNNOPS_NV_SWITCH(nv, hipLaunchKernelGGL((softmax_kernel<NV, true>), dim3(row_grid(rows)),
+            DNNOPS_NV_SWITCH(nv, hipLaunchKernelGGL((softmax_kernel<NV, TPR, RAG, true>), dim3(row_grid(rows, nv)),
                                                     dim3(256), 0, st, in0, in1, out, rows, cols));
         } else {
-            DNNOPS_NV_SWITCH(nv, hipLaunchKernelGGL((softmax_kernel<NV, false>), dim3(row_grid(rows)),
+            DNNOPS_NV_SWITCH(nv, hipLaunchKernelGGL((softmax_kernel<NV, TPR, RAG, false>), dim3(row_grid(rows, nv)),
                                                     dim3(256), 0, st, in0, in1, out, rows, cols));
         }
     } else if (bwd) {
-        hipLaunchKernelGGL((row_generic_kernel<3>), dim3(generic_grid(rows)), dim3(256),
-                           2 * sizeof(float) * cols, st, in0, in1, (const float *)nullptr,
+        hipLaunchKernelGGL((row_short_kernel<3>), dim3(short_grid(rows)), dim3(256), 0, st, in0, in1, (const float *)nullptr,
                            (const float *)nullptr, 0.f, rows, cols, out, (float *)nullptr,
                            (float *)nullptr);
     } else {
-        hipLaunchKernelGGL((row_generic_kernel<2>), dim3(generic_grid(rows)), dim3(256),
-                           sizeof(float) * cols, st, in0, in1, (const float *)nullptr,
+        hipLaunchKernelGGL((row_short_kernel<2>), dim3(short_grid(rows)), dim3(256), 0, st, in0, in1, (const float *)nullptr,
                            (const float *)nullptr, 0.f, rows, cols, out, (float *)nullptr,
                            (float *)nullptr);
     }
