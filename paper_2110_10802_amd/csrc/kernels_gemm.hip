@@ -588,11 +588,14 @@ hipError_t launch_reduce_splits2(const SplitReduce &a, const SplitReduce &b, hip
     const auto wide = [](const SplitReduce &r) {
         return r.count % 4 == 0 && (((uintptr_t)r.in | (uintptr_t)r.out) & 15u) == 0;
     };
+    const auto blocks256 = [](const SplitReduce &r) { return (unsigned)((r.count / 4 + 255) / 256); };
     const bool two = b.count > 0;
     if (wide(a) && (!two || wide(b))) {
         // lanes per thread group by the number of partial rows: a group adds every (1024/E)-th row,
         // so few rows want few, wide groups (with 64 groups and 16 rows three quarters of the
-        // threads would idle)
+        // threads would idle); where 256 lanes per group still give a workgroup per compute unit, four
+        // groups, each thread with a few loads in flight and two steps of the tree instead of four
+        // (1152 x (320 + 192): 9 and 13 rows 8.4 us; 10 and 15 rows with sixteen groups 15.0)
         const int S = two ? (a.S < b.S ? a.S : b.S) : a.S;
 #define MBK_GO(E)                                                                                 \
     {                                                                                             \
@@ -605,8 +608,10 @@ hipError_t launch_reduce_splits2(const SplitReduce &a, const SplitReduce &b, hip
             MBK_GO(16)
         else if (S >= 32)
             MBK_GO(32)
-        else
+        else if (blocks256(a) + (two ? blocks256(b) : 0u) < 256u)
             MBK_GO(64)
+        else
+            MBK_GO(256)
 #undef MBK_GO
     } else {
         const unsigned ba = (unsigned)((a.count + 31) / 32);

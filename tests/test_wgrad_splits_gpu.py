@@ -1,0 +1,31 @@
+"""Weight gradients of the 1x1 convolutions on the bf16 matrix cores: how tiles and splits of the
+contraction are dealt out, and the forms of the sum over the splits, against the oracle at the
+tolerances of parity_util."""
+import pytest
+
+from mbconv_inputs import BlockShape, make_block_inputs
+from oracle import oracle as orc
+from parity_util import compare_block, run_gpu_block
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    # seven splits of 27 tiles (no multiple of eight); sum with 256 lanes to a group
+    "seven_splits": BlockShape(N=12, Cin=192, H=7, W=7, Cexp=1152, Cse=48, Cout=320, k=3, stride=1),
+    # one split, fewer workgroups than the chip has XCDs
+    "one_split": BlockShape(N=1, Cin=40, H=5, W=5, Cexp=240, Cse=10, Cout=48, k=3, stride=1),
+    # 64-row tiles; many splits, the last one shorter
+    "narrow_tile": BlockShape(N=37, Cin=64, H=12, W=12, Cexp=130, Cse=16, Cout=64, k=3, stride=1, residual=True),
+    # more tiles than compute units
+    "many_tiles": BlockShape(N=2, Cin=768, H=6, W=6, Cexp=4608, Cse=32, Cout=160, k=3, stride=1),
+}
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_block_matches_oracle(name):
+    s = SHAPES[name]
+    t = make_block_inputs(s, seed=23)
+    print(f"[wgrad] {name} {s}", flush=True)
+    res, blk = run_gpu_block(s, t)
+    f, b = orc.mbconv_step(s, t)
+    compare_block(s, t, res, f, b, blk)
