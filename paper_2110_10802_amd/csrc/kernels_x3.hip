@@ -94,19 +94,24 @@ struct X3WgradArgs {
     float *partial;
 };
 
-// what a thread keeps per operand for the whole kernel: rows rr + 64*i (i < NP) of the tile
+// What a thread keeps per operand for the whole kernel: rows rr + 64*i (i < NP) of the tile.  Rows past
+// the last one are read at the last one and computed, never stored.
 template <int PRO, int NP>
 struct X3RowConst {
     float k0[NP], k1[NP], k2[NP];
-    uint32_t rmask[NP];
-    __device__ __forceinline__ void init(const X3Operand &o, int row0, int rr, int M)
+    int row[NP];
+    uint32_t at[NP]; // offset of the row within an image
+    bool live[NP];   // uniform: the 64 rows of this pass are not all past the end
+    __device__ __forceinline__ void init(const X3Operand &o, int row0, int rr, int M, int HW)
     {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            const int r = row0 + rr + 64 * i;
-            rmask[i] = r < M ? 0xffffffffu : 0u;
+            const int r = min(row0 + rr + 64 * i, M - 1);
+            row[i] = r;
+            at[i] = (uint32_t)r * (uint32_t)HW;
+            live[i] = row0 + 64 * i < M;
             k0[i] = k1[i] = k2[i] = 0.f;
-            if (PRO != PRO_NONE && r < M) {
+            if (PRO != PRO_NONE) {
                 k0[i] = o.c0[r];
                 k1[i] = o.c1[r];
                 if (PRO == PRO_BNBWD)
@@ -121,16 +126,16 @@ struct X3RowData {
     float v0[NP][4], v1[NP][PRO == PRO_BNBWD ? 4 : 1];
     float g[NP];
     // n, pix: image and first pixel of the run (it lies inside one plane).  Both rows load, also past
-    // the last row (clamped, masked on the way into LDS): a branch around a load would make the loads
-    // behind it wait.
+    // the last row: a branch around a load would make the loads behind it wait.
     template <bool RAG>
-    __device__ __forceinline__ void load(const X3Operand &o, int row0, int rr, int M, int HW, uint32_t n,
-                                         uint32_t pix)
+    __device__ __forceinline__ void load(const X3Operand &o, const X3RowConst<PRO, NP> &c, int M, uint32_t img,
+                                         uint32_t n, uint32_t pix)
     {
+        const size_t base = (size_t)n * img + pix;
+        const uint32_t gbase = n * (uint32_t)M;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            const int r = min(row0 + rr + 64 * i, M - 1);
-            const size_t idx = ((size_t)n * M + r) * HW + pix;
+            const size_t idx = base + c.at[i];
             if (RAG)
                 x3_ld4u(o.p0, idx, v0[i]);
             else
@@ -142,23 +147,26 @@ struct X3RowData {
                     x3_ld4(o.p1, idx, v1[i]);
             }
             if constexpr (PRO == PRO_BNSWISH_GATE)
-                g[i] = o.gate[(size_t)n * M + r];
+                g[i] = o.gate[gbase + (uint32_t)c.row[i]];
         }
     }
-    // prologue, split, three 8-byte LDS stores per row.  fresh: the run's pixels before this one are
-    // zeros (RAG: the last run of an image, moved back to the plane's last four pixels)
-    template <bool RAG>
+    // prologue, split, three 8-byte LDS stores per row; MASK: pixel j survives under mask[j]
+    template <bool MASK>
     __device__ __forceinline__ void store(const X3RowConst<PRO, NP> &c, uint16_t *planes, int rr, int qg,
-                                          uint32_t qmask, int fresh) const
+                                          const uint32_t (&mask)[4]) const
     {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
+            if (!c.live[i])
+                continue;
             float y[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                y[j] = and_mask(x3_apply<PRO>(v0[i][j], v1[i][PRO == PRO_BNBWD ? j : 0], c.k0[i], c.k1[i],
-                                              PRO == PRO_BNSWISH_GATE ? g[i] : c.k2[i]),
-                                (RAG && j < fresh) ? 0u : qmask & c.rmask[i]);
+            for (int j = 0; j < 4; ++j) {
+                y[j] = x3_apply<PRO>(v0[i][j], v1[i][PRO == PRO_BNBWD ? j : 0], c.k0[i], c.k1[i],
+                                     PRO == PRO_BNSWISH_GATE ? g[i] : c.k2[i]);
+                if (MASK)
+                    y[j] = and_mask(y[j], mask[j]);
+            }
             uint32_t w0[3], w1[3];
             x3_split2(y[0], y[1], w0);
             x3_split2(y[2], y[3], w1);
@@ -206,13 +214,15 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
     const int qg = tid & 7, rr = tid >> 3;
     X3RowConst<PROU, 2> cu;
     X3RowConst<PROV, VB / 64> cv;
-    cu.init(a.U, a0, rr, a.Ma);
-    cv.init(a.V, b0, rr, a.Mb);
+    cu.init(a.U, a0, rr, a.Ma, a.HW);
+    cv.init(a.V, b0, rr, a.Mb, a.HW);
+    const uint32_t imgU = (uint32_t)a.Ma * (uint32_t)a.HW, imgV = (uint32_t)a.Mb * (uint32_t)a.HW;
+    const bool work = a0 + ua < a.Ma && b0 + vb < a.Mb; // uniform: the wavefront's part is not all padding
     X3RowData<PROU, 2> du[2];
     X3RowData<PROV, VB / 64> dv[2];
     uint32_t qmask[2] = {0u, 0u};
     int fresh[2] = {0, 0};
-    // unconditional clamped loads, validity as an AND mask on the way into LDS
+    // unconditional clamped loads; the validity of a pixel is an AND mask on V's way into LDS
     auto load = [&](int s, int chunk) __attribute__((always_inline)) {
         const uint32_t run = (uint32_t)chunk * (BQ / 4) + (uint32_t)qg;
         qmask[s] = run < a.runs ? 0xffffffffu : 0u;
@@ -220,12 +230,16 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
         const uint32_t n = fdiv(rc, a.divRuns);
         const uint32_t want = 4u * (rc - n * a.divRuns.d), pix = RAG ? min(want, (uint32_t)a.HW - 4u) : want;
         fresh[s] = (int)(want - pix);
-        du[s].template load<RAG>(a.U, a0, rr, a.Ma, a.HW, n, pix);
-        dv[s].template load<RAG>(a.V, b0, rr, a.Mb, a.HW, n, pix);
+        du[s].template load<RAG>(a.U, cu, a.Ma, imgU, n, pix);
+        dv[s].template load<RAG>(a.V, cv, a.Mb, imgV, n, pix);
     };
     auto store = [&](int s) __attribute__((always_inline)) {
-        du[s].template store<RAG>(cu, Us, rr, qg, qmask[s], fresh[s]);
-        dv[s].template store<RAG>(cv, Vs, rr, qg, qmask[s], fresh[s]);
+        uint32_t mask[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            mask[j] = (RAG && j < fresh[s]) ? 0u : qmask[s];
+        du[s].template store<false>(cu, Us, rr, qg, mask);
+        dv[s].template store<true>(cv, Vs, rr, qg, mask);
     };
 
     float16v acc[NA];
@@ -244,20 +258,22 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
             // the loads are all issued before the MFMAs start and nothing that uses their data
             // moves up among the MFMAs (the scheduler would otherwise wait for them there)
             __builtin_amdgcn_sched_barrier(0);
+            if (work) {
 #pragma unroll
-            for (int s = 0; s < BQ / 16; ++s) {
-                const int ko = 16 * s + 8 * (lane >> 5);
-                bf16x8 av[NA][3], bv[3];
+                for (int s = 0; s < BQ / 16; ++s) {
+                    const int ko = 16 * s + 8 * (lane >> 5);
+                    bf16x8 av[NA][3], bv[3];
 #pragma unroll
-                for (int pl = 0; pl < 3; ++pl) {
+                    for (int pl = 0; pl < 3; ++pl) {
+#pragma unroll
+                        for (int i = 0; i < NA; ++i)
+                            av[i][pl] = x3_lds8(Us + pl * kPlane + x3_img_at(ua + 32 * i + (lane & 31), ko));
+                        bv[pl] = x3_lds8(Vs + pl * kPlaneV + x3_img_at(vb + (lane & 31), ko));
+                    }
 #pragma unroll
                     for (int i = 0; i < NA; ++i)
-                        av[i][pl] = x3_lds8(Us + pl * kPlane + x3_img_at(ua + 32 * i + (lane & 31), ko));
-                    bv[pl] = x3_lds8(Vs + pl * kPlaneV + x3_img_at(vb + (lane & 31), ko));
+                        acc[i] = x3_mfma6(av[i], bv, acc[i]);
                 }
-#pragma unroll
-                for (int i = 0; i < NA; ++i)
-                    acc[i] = x3_mfma6(av[i], bv, acc[i]); // rows past the end are zeros
             }
             __builtin_amdgcn_sched_barrier(0);
             __syncthreads(); // every wavefront has read the chunk
@@ -333,7 +349,7 @@ bool x3_wgrad_plan(int Ma, int Mb, int N, int HW, int *splits)
     const long long Q = (long long)N * HW;
     // (a side of at most 32 channels belongs to the fused backward kernels of kernels_wave.hip,
     // which size their partial tiles by the plan of that file)
-    if (Q >= (1ll << 31) || HW < 4 || std::min(Ma, Mb) <= 32 || std::max(Ma, Mb) < 64)
+    if (Q >= (1ll << 31) || (long long)std::max(Ma, Mb) * HW >= (1ll << 31) || HW < 4 || std::min(Ma, Mb) <= 32 || std::max(Ma, Mb) < 64)
         return false;
     const int wide = std::max(Ma, Mb), narrow = std::min(Ma, Mb), vb = narrow <= 64 ? 64 : 128;
     const long long tiles = (long long)((wide + 127) / 128) * ((narrow + vb - 1) / vb);
