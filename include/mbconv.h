@@ -187,12 +187,13 @@ typedef enum {
     /* forward */
     MBCONV_STEP_EXPAND_CONV = 1,   /* 1x1 expansion conv + BN1 partial statistics (and, where that conv reads
                                       re-encoded weights, the launch that writes them) */
-    MBCONV_STEP_BN1_FINALIZE = 2,  /* BN1_FINALIZE and BN3_FINALIZE do not occur where the kernel
-                                      that consumes the statistics finalises them itself: DW_FWD
-                                      and BN3_APPLY do for planes of 1024 elements or more (DW_FWD:
-                                      stride 1, W % 4 == 0, recompute policy) */
+    MBCONV_STEP_BN1_FINALIZE = 2,  /* the three FINALIZE steps do not occur where the kernel that consumes
+                                      the statistics finalises them itself: DW_FWD for planes of 1024
+                                      elements or more (stride 1, W % 4 == 0, recompute policy) and where
+                                      a wavefront owns a channel, SE_POOL for planes of at most 1024
+                                      elements, BN3_APPLY always */
     MBCONV_STEP_DW_FWD = 3,        /* BN1 + Swish + depthwise conv + BN2 partial statistics */
-    MBCONV_STEP_BN2_FINALIZE = 4,  /* also re-encodes the 1x1 conv weights for the wide blocks' kernels and,
+    MBCONV_STEP_BN2_FINALIZE = 4,  /* (or SE_POOL in its place) also re-encodes the 1x1 conv weights for the wide blocks' kernels and,
                                       when no_se, fills the gate with ones (in evaluation mode the launch
                                       of the coefficient blocks does both) */
     MBCONV_STEP_SE_POOL = 5,       /* BN2 + Swish + plane means; does not occur when no_se */
@@ -203,7 +204,8 @@ typedef enum {
     /* backward */
     MBCONV_STEP_BN3_BWD_REDUCE = 10,
     MBCONV_STEP_BN3_BWD_FINALIZE = 11, /* does not occur where PROJ_DGRAD is the one-kernel form, which
-                                          finalises BN3's backward itself */
+                                          finalises BN3's backward itself, nor where BN3_BWD_REDUCE does
+                                          (planes of at most 1024 elements, a few planes per thread group) */
     MBCONV_STEP_PROJ_DGRAD = 12,   /* for Cout <= 32 (and H*W a multiple of 4) one kernel computes the
                                       data gradient and the weight gradient's split partial sums */
     MBCONV_STEP_PROJ_WGRAD = 13,   /* with an expansion conv: the split partial sums only, their sum is

@@ -16,6 +16,7 @@
 #include "mbconv_dev.h"
 #include "mbconv_launch.h"
 #include "mbconv_bnfin.h"
+#include "mbconv_x3.h"
 
 #include <algorithm>
 
@@ -64,12 +65,23 @@ struct PlaneId {
     size_t plane;
 };
 
-template <int TPP>
+// CHAN: a workgroup's planes belong to one channel (BLOCK/TPP consecutive images), so that it can
+// finalise that channel's normalisation itself, once for all of them.
+template <int TPP, bool CHAN = false>
 __device__ __forceinline__ PlaneId plane_of_group(int N, int C, FastDiv divC)
 {
     constexpr int BLOCK = TPP > 256 ? TPP : 256;
     constexpr int PPB = BLOCK / TPP;
     PlaneId p;
+    if (CHAN) {
+        const int per = (N + PPB - 1) / PPB, g = threadIdx.x / TPP; // workgroups per channel
+        p.c = blockIdx.x / per;
+        p.n = (blockIdx.x - p.c * per) * PPB + g;
+        p.active = p.n < N;
+        p.n = p.active ? p.n : 0;
+        p.plane = (size_t)p.n * C + p.c;
+        return p;
+    }
     const size_t plane = (size_t)blockIdx.x * PPB + threadIdx.x / TPP;
     p.active = plane < (size_t)N * C;
     p.plane = p.active ? plane : 0;
@@ -212,7 +224,7 @@ static hipError_t dw_fwd_ks(const DwFwdDev &a, hipStream_t st)
 
 // A consumer finalises a normalisation itself where its planes are large enough that the extra
 // reduction per plane (overlapped with the plane's first loads) costs less than a launch.
-bool plane_finalize_pays(int HW) { return HW >= 1024; }
+static bool plane_finalize_pays(int HW) { return HW >= 1024; }
 
 bool dw_fwd_finalizes_bn1(const DwShape &s, bool stores_a1)
 {
@@ -525,7 +537,8 @@ struct PlaneArgs {
     float o0_scale; // multiplies the first output (1/HW turns a plane sum into a mean)
     void *out;    // elementwise output (bn_apply)
     const void *res;
-    BnFin fin;    // bn_apply, fin.psum non-null: `bn` is derived there from the partial sums
+    BnFin fin;    // pool and bn_apply, fin.psum non-null: `bn` is derived there from the partial sums
+    X3PrepArgs prep; // weight images that the workgroups past the planes' write (channel form of the pool)
 };
 
 // Four consecutive elements at once (16 bytes per lane for fp32, 8 for bf16).
@@ -681,19 +694,113 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void plane_reduce_kernel(Pla
     }
 }
 
+// The pool of small planes with BN2's finalise step: a workgroup works on one channel, on the planes of
+// `rounds` x 256/TPP consecutive images.  Its first wavefront finalises (all four would put more
+// instructions into the sum than the pool itself has: 64 x 1152 planes of 7x7 13.7 us, now 10.8; the
+// finalise launch and the pool without it took 5.4 + 6.3); the
+// first planes are requested before.  The workgroups ahead of the planes' write the weight images of
+// convolutions later in the sequence.
 template <typename T, int TPP>
+__global__ __launch_bounds__(256) void pool_chan_kernel(PlaneArgs a, int rounds, int per)
+{
+    constexpr int PPB = 256 / TPP;
+    __shared__ float cf[4];
+    if ((int)blockIdx.x < a.prep.tiles) {
+        x3_prep_tile(a.prep, blockIdx.x);
+        return;
+    }
+    // per: workgroups of a channel.  Neighbouring channels go to one XCD (blockIdx.x mod 8): their results
+    // lie next to each other, and a line written from several L2s costs a partial write each.
+    const int total = a.C * per, i = blockIdx.x - a.prep.tiles;
+    const int b = (i & 7) * ((total + 7) >> 3) + (i >> 3), c = b / per, part = b - c * per;
+    if (b >= total)
+        return;
+    const int lt = threadIdx.x % TPP;
+    BnFinRegs fr;
+    if (threadIdx.x < 64)
+        bn_fin_issue<64>(a.fin, c, threadIdx.x, fr);
+    float sc, sh, mu, rs;
+    const auto coefs = [&]() {
+        if (threadIdx.x < 64) {
+            bn_fin_finish<64>(a.fin, a.C, c, threadIdx.x, part == 0, nullptr, fr, sc, sh, mu, rs);
+            if (threadIdx.x == 0) {
+                cf[0] = sc;
+                cf[1] = sh;
+                cf[2] = mu;
+                cf[3] = rs;
+            }
+        }
+        __syncthreads();
+        sc = cf[0];
+        sh = cf[1];
+        mu = cf[2];
+        rs = cf[3];
+    };
+    int n = part * rounds * PPB + threadIdx.x / TPP;
+    for (int r = 0; r < rounds; ++r, n += PPB) {
+        const size_t plane = (size_t)(n < a.N ? n : 0) * a.C + c, base = plane * a.HW;
+        float acc[3] = {0.f, 0.f, 0.f};
+        if ((a.HW & 3) == 0) { // at most 16 * TPP elements
+            float v[4][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int idx = 4 * (lt + TPP * u);
+                ldvec4<T>((const T *)a.t0, base + (idx < a.HW ? idx : 0), v[u]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (r == 0)
+                coefs();
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (4 * (lt + TPP * u) < a.HW) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        OpPool::eval(v[u][j], 0.f, sc, sh, mu, rs, acc);
+                }
+        } else {
+            for (int idx0 = lt; idx0 - lt < a.HW; idx0 += 4 * TPP) { // (equally often in all threads)
+                float v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int idx = idx0 + TPP * u;
+                    v[u] = ld<T>((const T *)a.t0, base + (idx < a.HW ? idx : 0));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (r == 0 && idx0 == lt)
+                    coefs();
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (idx0 + TPP * u < a.HW)
+                        OpPool::eval(v[u], 0.f, sc, sh, mu, rs, acc);
+            }
+        }
+        group_sum<3, TPP>(acc, nullptr);
+        if (n < a.N && lt == 0) {
+            a.o0[plane] = acc[0] * a.o0_scale;
+            a.o1[plane] = acc[1];
+            a.o2[plane] = acc[2];
+        }
+    }
+}
+
+// CHAN (planes of at most 1024 elements, training): the workgroup's planes belong to one channel, whose
+// BN3 it finalises first; the launch that did it before took 4.7 us in front of one of 5.
+template <typename T, int TPP, bool CHAN>
 __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void bn_apply_kernel(PlaneArgs a)
 {
     constexpr int BLOCK = TPP > 256 ? TPP : 256;
     __shared__ double redd[2 * (BLOCK / 64)];
     const int lt = threadIdx.x % TPP;
-    const PlaneId pl = plane_of_group<TPP>(a.N, a.C, a.divC);
-    if (!pl.active) // (TPP > 64: one plane per workgroup, always active)
+    const PlaneId pl = plane_of_group<TPP, CHAN>(a.N, a.C, a.divC);
+    if (!CHAN && !pl.active) // (TPP > 64: one plane per workgroup, always active)
         return;
+    // the threads that finalise together: the plane's, or with CHAN the workgroup
+    constexpr int FIN = CHAN || TPP < 64 ? 256 : TPP;
+    const bool fin = CHAN || (TPP > 64 && a.fin.psum);
     float sc, sh;
     BnFinRegs fr;
-    if (TPP >= 64 && a.fin.psum) { // (a 16-lane group never finalises: its planes are small)
-        bn_fin_issue<TPP>(a.fin, pl.c, lt, fr);
+    if (fin) {
+        bn_fin_issue<FIN>(a.fin, pl.c, CHAN ? (int)threadIdx.x : lt, fr);
     } else {
         sc = a.bn[pl.c];
         sh = a.bn[a.C + pl.c];
@@ -701,9 +808,11 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void bn_apply_kernel(PlaneAr
     __builtin_amdgcn_sched_barrier(0);
     const auto coefs = [&]() {
         float mu, rs;
-        if constexpr (TPP >= 64) {
-            if (a.fin.psum)
-                bn_fin_finish<TPP>(a.fin, a.C, pl.c, lt, pl.n == 0, redd, fr, sc, sh, mu, rs);
+        if constexpr (CHAN || TPP > 64) {
+            const bool writer =
+                CHAN ? blockIdx.x % ((a.N + BLOCK / TPP - 1) / (BLOCK / TPP)) == 0 : pl.n == 0;
+            if (fin)
+                bn_fin_finish<FIN>(a.fin, a.C, pl.c, CHAN ? (int)threadIdx.x : lt, writer, redd, fr, sc, sh, mu, rs);
         }
     };
     const size_t base = pl.plane * (size_t)a.HW;
@@ -725,6 +834,8 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void bn_apply_kernel(PlaneAr
         load_round(idx0);
         coefs();
         __builtin_amdgcn_sched_barrier(0);
+        if (CHAN && !pl.active)
+            return;
         while (true) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -746,12 +857,84 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void bn_apply_kernel(PlaneAr
         }
     } else {
         coefs();
+        if (CHAN && !pl.active)
+            return;
         for (int idx = lt; idx < a.HW; idx += TPP) {
             float v = fmaf(ld<T>((const T *)a.t0, base + idx), sc, sh);
             if (a.res)
                 v += ld<T>((const T *)a.res, base + idx);
             st<T>((T *)a.out, base + idx, v);
         }
+    }
+}
+
+// BN3's backward reductions and their finalise step in one launch: a workgroup owns a channel, TPP
+// lanes a plane.  The planes' sums are added over the workgroup in fp64, in a fixed order, and one
+// thread turns them into dgamma, dbeta and the coefficients {c0, c1, c2}.  Latency is all it costs:
+// 64 x 320 planes of 7x7 5.9 us, 4.8 + 4.7 as two launches.
+template <typename T, int TPP>
+__global__ __launch_bounds__(1024) void bn_bwd_chan_kernel(PlaneArgs a, BnBwdFin f)
+{
+    constexpr int G = 1024 / TPP; // planes in flight
+    __shared__ double red[2][16];
+    const int c = blockIdx.x, lt = threadIdx.x % TPP;
+    const float gm = f.gamma[c], mu = a.bn[2 * a.C + c], rs = a.bn[3 * a.C + c];
+    double sb = 0.0, sr = 0.0;
+    for (int n = threadIdx.x / TPP; n < a.N; n += G) {
+        const size_t base = ((size_t)n * a.C + c) * a.HW;
+        float acc[2] = {0.f, 0.f};
+        if ((a.HW & 3) == 0) { // at most 16 * TPP elements: one round
+            float v0[4][4], v1[4][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int idx = 4 * (lt + TPP * u), ic = idx < a.HW ? idx : 0;
+                ldvec4<T>((const T *)a.t0, base + ic, v0[u]);
+                ldvec4<T>((const T *)a.t1, base + ic, v1[u]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (4 * (lt + TPP * u) < a.HW) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        OpDot::eval(v0[u][r], v1[u][r], 0.f, 0.f, mu, rs, acc);
+                }
+        } else {
+            for (int idx0 = lt; idx0 < a.HW; idx0 += 4 * TPP) {
+                float v0[4], v1[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int ic = idx0 + TPP * u < a.HW ? idx0 + TPP * u : idx0;
+                    v0[u] = ld<T>((const T *)a.t0, base + ic);
+                    v1[u] = ld<T>((const T *)a.t1, base + ic);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (idx0 + TPP * u < a.HW)
+                        OpDot::eval(v0[u], v1[u], 0.f, 0.f, mu, rs, acc);
+            }
+        }
+        sb += (double)acc[0];
+        sr += (double)acc[1];
+    }
+    sb = wave_sum_d(sb);
+    sr = wave_sum_d(sr);
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = sb;
+        red[1][threadIdx.x >> 6] = sr;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        sb = sr = 0.0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            sb += red[0][w];
+            sr += red[1][w];
+        }
+        f.dbeta[c] = (float)sb;
+        f.dgamma[c] = (float)sr;
+        bn_bwd_coef_vals(a.C, c, f.m, sr, sb, gm, mu, rs, f.coef);
     }
 }
 
@@ -791,8 +974,13 @@ static PlaneArgs plane_args(int N, int C, int HW, const void *t0, const void *t1
     return a;
 }
 
+// Small planes (16 or 64 lanes each): the pool finalises BN2's statistics itself, a channel's planes to
+// a workgroup.  Larger planes have workgroups of their own and would repeat the sum for each of them;
+// there the finalise step is a launch.
+bool plane_channel_form(int HW) { return HW <= 1024; }
+
 hipError_t launch_pool(bool bf16, int N, int C, int HW, const void *d, const float *bn2, float *z,
-                       float *s3, float *s4, hipStream_t st)
+                       float *s3, float *s4, const BnFin *fin, const X3PrepArgs *prep, hipStream_t st)
 {
     PlaneArgs a = plane_args(N, C, HW, d, nullptr, bn2);
     a.o0 = z;
@@ -800,7 +988,53 @@ hipError_t launch_pool(bool bf16, int N, int C, int HW, const void *d, const flo
     a.o2 = s4;
     a.layoutCN = 0;
     a.o0_scale = 1.f / (float)HW;
+    if (fin) {
+        a.fin = *fin;
+        if (prep)
+            a.prep = *prep;
+        // images per workgroup: as many as leave eight workgroups per compute unit, up to four rounds
+        const int ppb = 256 / pick_tpp_plane(HW);
+        int rounds = 1;
+        while (rounds < 4 && (long long)C * ((N + 2 * rounds * ppb - 1) / (2 * rounds * ppb)) >= 2048)
+            rounds *= 2;
+        const int per = (N + rounds * ppb - 1) / (rounds * ppb);
+        const dim3 grid((unsigned)((C * per + 7) / 8 * 8 + a.prep.tiles));
+        if (ppb == 16 && bf16)
+            hipLaunchKernelGGL((pool_chan_kernel<bf16_t, 16>), grid, dim3(256), 0, st, a, rounds, per);
+        else if (ppb == 16)
+            hipLaunchKernelGGL((pool_chan_kernel<float, 16>), grid, dim3(256), 0, st, a, rounds, per);
+        else if (bf16)
+            hipLaunchKernelGGL((pool_chan_kernel<bf16_t, 64>), grid, dim3(256), 0, st, a, rounds, per);
+        else
+            hipLaunchKernelGGL((pool_chan_kernel<float, 64>), grid, dim3(256), 0, st, a, rounds, per);
+        return hipGetLastError();
+    }
     return bf16 ? plane_reduce_launch<bf16_t, OpPool>(a, st) : plane_reduce_launch<float, OpPool>(a, st);
+}
+
+// A workgroup per channel reads 2*N*HW elements: with more than two planes to a thread group it
+// would take longer than the launch that it saves.
+bool bn_bwd_chan_supported(int N, int HW)
+{
+    return HW <= 1024 && N <= 2 * 1024 / pick_tpp_plane(HW);
+}
+
+hipError_t launch_bn_bwd_chan(bool bf16, int N, int C, int HW, const void *dy, const void *raw, const float *bn,
+                              const BnBwdFin &f, hipStream_t st)
+{
+    const PlaneArgs a = plane_args(N, C, HW, dy, raw, bn);
+    if (pick_tpp_plane(HW) == 16) {
+        if (bf16)
+            hipLaunchKernelGGL((bn_bwd_chan_kernel<bf16_t, 16>), dim3((unsigned)C), dim3(1024), 0, st, a, f);
+        else
+            hipLaunchKernelGGL((bn_bwd_chan_kernel<float, 16>), dim3((unsigned)C), dim3(1024), 0, st, a, f);
+    } else {
+        if (bf16)
+            hipLaunchKernelGGL((bn_bwd_chan_kernel<bf16_t, 64>), dim3((unsigned)C), dim3(1024), 0, st, a, f);
+        else
+            hipLaunchKernelGGL((bn_bwd_chan_kernel<float, 64>), dim3((unsigned)C), dim3(1024), 0, st, a, f);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_plane_dot(bool bf16, int N, int C, int HW, const void *dy, const void *raw,
@@ -834,23 +1068,27 @@ hipError_t launch_bn_apply(bool bf16, int N, int C, int HW, const void *p, const
     a.res = res;
     const int tpp = pick_tpp_plane(HW);
     const size_t planes = (size_t)N * C;
-#define MBK_LAUNCH(TPP)                                                                           \
+#define MBK_LAUNCH(TPP, CHAN)                                                                     \
     {                                                                                             \
-        constexpr int BLOCK = TPP > 256 ? TPP : 256;                                              \
-        const unsigned grid = (unsigned)((planes + BLOCK / TPP - 1) / (BLOCK / TPP));             \
+        constexpr int BLOCK = TPP > 256 ? TPP : 256, PPB = BLOCK / TPP;                           \
+        const unsigned grid = (unsigned)(CHAN ? (size_t)C * ((N + PPB - 1) / PPB) : (planes + PPB - 1) / PPB); \
         if (bf16)                                                                                 \
-            hipLaunchKernelGGL((bn_apply_kernel<bf16_t, TPP>), dim3(grid), dim3(BLOCK), 0, st, a);\
+            hipLaunchKernelGGL((bn_apply_kernel<bf16_t, TPP, CHAN>), dim3(grid), dim3(BLOCK), 0, st, a);       \
         else                                                                                      \
-            hipLaunchKernelGGL((bn_apply_kernel<float, TPP>), dim3(grid), dim3(BLOCK), 0, st, a); \
+            hipLaunchKernelGGL((bn_apply_kernel<float, TPP, CHAN>), dim3(grid), dim3(BLOCK), 0, st, a);        \
         return hipGetLastError();                                                                 \
     }
+    if (fin && tpp == 16)
+        MBK_LAUNCH(16, true)
+    if (fin && tpp == 64)
+        MBK_LAUNCH(64, true)
     if (tpp == 16)
-        MBK_LAUNCH(16)
+        MBK_LAUNCH(16, false)
     if (tpp == 64)
-        MBK_LAUNCH(64)
+        MBK_LAUNCH(64, false)
     if (tpp == 256)
-        MBK_LAUNCH(256)
-    MBK_LAUNCH(1024)
+        MBK_LAUNCH(256, false)
+    MBK_LAUNCH(1024, false)
 #undef MBK_LAUNCH
 }
 

@@ -3,16 +3,9 @@
 // second stage of the split reductions.  All of them touch O(N*C) values.
 #include <algorithm>
 #include "mbconv_x3.h"
+#include "mbconv_bnfin.h"
 
 namespace mbk {
-
-__device__ __forceinline__ double wave_sum_d(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-        v += __shfl_xor(v, o, kWave);
-    return v;
-}
 
 // One wavefront per channel.  Partials are fp32 sums over at most a plane or a GEMM tile;
 // they are combined in fp64 so that var = E[x^2]-E[x]^2 loses nothing in this stage.
@@ -166,18 +159,6 @@ hipError_t launch_bn_eval_coef(int C1, const float *gamma1, const float *beta1, 
     return hipGetLastError();
 }
 
-// dx = gamma*rstd*(dy - dbeta/m - xhat*dgamma/m) with xhat = (raw-mean)*rstd, rewritten as
-// c0*dy + c1*raw + c2 so the consumer's prologue is two fused multiply-adds.
-__device__ __forceinline__ void bn_bwd_coef_vals(int C, int c, double m, double dgamma, double dbeta,
-                                                 float gamma, double mean, double rstd, float *coef)
-{
-    const double c0 = (double)gamma * rstd;
-    const double c1 = -c0 * rstd * dgamma / m;
-    const double c2 = -c0 * dbeta / m - c1 * mean;
-    coef[c] = (float)c0;
-    coef[C + c] = (float)c1;
-    coef[2 * C + c] = (float)c2;
-}
 __device__ __forceinline__ void bn_bwd_coef(int C, int c, double m, double dgamma, double dbeta,
                                             float gamma, const float *bn, float *coef)
 {

@@ -359,9 +359,9 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
         dw_in = e;
     }
     // A normalisation's finalise step (partial sums -> scale, shift, mean, rstd, running
-    // statistics) runs inside the kernel that first consumes the statistics where that pays (BN1
-    // in the vectorised depthwise kernel, BN3 in the final elementwise pass, both for large
-    // planes; measured for BN2 in the pooling kernel: no gain); otherwise it is a launch of its own.
+    // statistics) runs inside the kernel that first consumes the statistics where that pays: BN1
+    // in the vectorised depthwise kernel for large planes, BN2 in the pooling kernel for small ones
+    // (measured for large ones: no gain), BN3 in the final elementwise pass; otherwise it is a launch of its own.
     const DwShape ds = {P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p};
     void *a1_store = (P.store && P.expand && !eval) ? at<char>(saved, P.o_a1) : nullptr;
     const double m1 = (double)P.N * P.HW, m2 = (double)P.N * P.HWo;
@@ -370,7 +370,7 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     const BnFin fin3 = make_bn_fin(psum, psq, prm->bn3_gamma, prm->bn3_beta, run ? run->bn3_mean : nullptr,
                                    run ? run->bn3_var : nullptr, bn3, P.NT5, eps, mom, m2);
     const bool fuse1 = !eval && P.expand && dw_fwd_finalizes_bn1(ds, a1_store != nullptr);
-    const bool fuse3 = !eval && plane_finalize_pays(P.HWo);
+    const bool fuse2 = !eval && P.se && plane_channel_form(P.HWo);
     if (P.expand && !eval && !fuse1)
         MBK_STEP(MBCONV_STEP_BN1_FINALIZE, launch_bn_finalize(P.Cexp, P.NT1, m1, psum, psq, prm->bn1_gamma,
                                    prm->bn1_beta, eps, mom, fin1.run_mean, fin1.run_var, bn1, st));
@@ -378,14 +378,16 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     MBK_STEP(MBCONV_STEP_DW_FWD, launch_dw_fwd(bf, ds, dw_in, bn1, prm->w_dw, d, psum2, psq2, a1_store,
                                                fuse1 ? &fin1 : nullptr, st));
     // BN2 + Swish + SE squeeze, SE excite
-    if (!eval)
+    const BnFin fin2 = make_bn_fin(psum2, psq2, prm->bn2_gamma, prm->bn2_beta, run ? run->bn2_mean : nullptr,
+                                   run ? run->bn2_var : nullptr, bn2, P.NPdw, eps, mom, m2);
+    if (!eval && !fuse2)
         MBK_STEP(MBCONV_STEP_BN2_FINALIZE, launch_bn_finalize(P.Cexp, P.NPdw, m2, psum2, psq2, prm->bn2_gamma,
-                                   prm->bn2_beta, eps, mom, run ? run->bn2_mean : nullptr,
-                                   run ? run->bn2_var : nullptr, bn2, st, ones, ones_count,
+                                   prm->bn2_beta, eps, mom, fin2.run_mean, fin2.run_var, bn2, st, ones, ones_count,
                                    prep_first ? nullptr : &prep));
     if (P.se) {
         MBK_STEP(MBCONV_STEP_SE_POOL, launch_pool(bf, P.N, P.Cexp, P.HWo, d, bn2, z, at<float>(saved, P.o_s3),
-                            at<float>(saved, P.o_s4), st));
+                            at<float>(saved, P.o_s4), fuse2 ? &fin2 : nullptr,
+                            prep_first ? nullptr : &prep, st));
         MBK_STEP(MBCONV_STEP_SE_FC, launch_se_fwd(P.N, P.Cexp, P.Cse, z, prm->se_w1, prm->se_b1, prm->se_w2, prm->se_b2, q,
                               g, st));
     }
@@ -416,13 +418,10 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
                                   nullptr, psum, psq, sc_store, splitk, st, wimg(1));
         };
         MBK_STEP(MBCONV_STEP_PROJ_CONV, conv());
-        if (!eval && !fuse3)
-            MBK_STEP(MBCONV_STEP_BN3_FINALIZE, launch_bn_finalize(P.Cout, P.NT5, m2, psum, psq, prm->bn3_gamma,
-                                       prm->bn3_beta, eps, mom, fin3.run_mean, fin3.run_var, bn3, st));
     }
     // BN3 (+ residual), finalising BN3's statistics on the way in training mode
     MBK_STEP(MBCONV_STEP_BN3_APPLY, launch_bn_apply(bf, P.N, P.Cout, P.HWo, p, bn3, P.res ? x : nullptr, out,
-                                                    fuse3 ? &fin3 : nullptr, st));
+                                                    eval ? nullptr : &fin3, st));
     return MBCONV_OK;
 }
 
@@ -468,13 +467,17 @@ mbconv_status backward_impl(const mbconv_desc *desc, const mbconv_params *prm, c
     const double m2 = (double)P.N * P.HWo;
 
     // BN3 backward reductions
-    MBK_STEP(MBCONV_STEP_BN3_BWD_REDUCE, launch_plane_dot(bf, P.N, P.Cout, P.HWo, dout, p, bn3, pa, pb, st));
     // (where one kernel computes both gradients of the projection conv, it also finalises BN3's
     // backward: no launch for that step)
     int psplits = 0;
     const bool proj_fused = projbwd_fused_plan(P.N, P.Cexp, P.Cout, P.HWo, &psplits);
     const BnBwdFin fin3 = {pa, pb, prm->bn3_gamma, bn3, gr->bn3_gamma, gr->bn3_beta, coef3, P.N, m2};
-    if (!proj_fused)
+    const bool chan3 = !proj_fused && bn_bwd_chan_supported(P.N, P.HWo);
+    if (chan3)
+        MBK_STEP(MBCONV_STEP_BN3_BWD_REDUCE, launch_bn_bwd_chan(bf, P.N, P.Cout, P.HWo, dout, p, bn3, fin3, st));
+    else
+        MBK_STEP(MBCONV_STEP_BN3_BWD_REDUCE, launch_plane_dot(bf, P.N, P.Cout, P.HWo, dout, p, bn3, pa, pb, st));
+    if (!proj_fused && !chan3)
         MBK_STEP(MBCONV_STEP_BN3_BWD_FINALIZE, launch_bn_bwd_finalize(P.Cout, P.N, m2, pa, pb, prm->bn3_gamma, bn3,
                                        gr->bn3_gamma, gr->bn3_beta, coef3, st));
     // projection conv: data gradient G = W_p^T dp and weight gradient dW_p = dp * sc^T,

@@ -132,4 +132,17 @@ __device__ __forceinline__ void bn_fin_finish(const BnFin &f, int C, int c, int 
     }
 }
 
+// dx = gamma*rstd*(dy - dbeta/m - xhat*dgamma/m) with xhat = (raw-mean)*rstd, rewritten as
+// c0*dy + c1*raw + c2 so the consumer's prologue is two fused multiply-adds.
+__device__ __forceinline__ void bn_bwd_coef_vals(int C, int c, double m, double dgamma, double dbeta,
+                                                 float gamma, double mean, double rstd, float *coef)
+{
+    const double c0 = (double)gamma * rstd;
+    const double c1 = -c0 * rstd * dgamma / m;
+    const double c2 = -c0 * dbeta / m - c1 * mean;
+    coef[c] = (float)c0;
+    coef[C + c] = (float)c1;
+    coef[2 * C + c] = (float)c2;
+}
+
 } // namespace mbk

@@ -214,14 +214,16 @@ size_t dw_bwd_lds_bytes(const DwShape &s);
 // With `fin` non-null (only when dw_fwd_finalizes_bn1 says so) the kernel derives bn1 from fin's
 // partial sums and writes it to fin->bn_out; psum/psq must not overlap fin's partials.
 bool dw_fwd_finalizes_bn1(const DwShape &s, bool stores_a1);
-bool plane_finalize_pays(int HW); // launch_bn_apply: worth passing `fin` for planes of HW elements
 hipError_t launch_dw_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
                          const void *w_dw, void *d, float *psum, float *psq, void *a1_store,
                          const BnFin *fin, hipStream_t st);
 
 // Per plane of d: z = mean swish(y2), s3 = sum swish'(y2), s4 = sum swish'(y2)*dhat.
+// With `fin` non-null (only when plane_channel_form says so) the kernel derives bn2 from fin's partial
+// sums and writes it to fin->bn_out, and writes the weight images of `prep` (may be null).
+bool plane_channel_form(int HW);
 hipError_t launch_pool(bool bf16, int N, int C, int HW, const void *d, const float *bn2, float *z,
-                       float *s3, float *s4, hipStream_t st);
+                       float *s3, float *s4, const BnFin *fin, const X3PrepArgs *prep, hipStream_t st);
 
 // SE excite: q = W1 z + b1, g = sigmoid(W2 swish(q) + b2).
 hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, const float *w1, const float *b1,
@@ -235,6 +237,12 @@ hipError_t launch_bn_apply(bool bf16, int N, int C, int HW, const void *p, const
 // Per plane: sums of dy and dy*xhat with xhat = (raw-mean)*rstd, laid out [C][N].
 hipError_t launch_plane_dot(bool bf16, int N, int C, int HW, const void *dy, const void *raw,
                             const float *bn, float *psb, float *psr, hipStream_t st);
+
+// launch_plane_dot and launch_bn_bwd_finalize (f.coef, f.dgamma, f.dbeta) in one launch; f's partial sums
+// are not used.
+bool bn_bwd_chan_supported(int N, int HW);
+hipError_t launch_bn_bwd_chan(bool bf16, int N, int C, int HW, const void *dy, const void *raw, const float *bn,
+                              const BnBwdFin &f, hipStream_t st);
 
 // Per plane of (G, d): dg = sum G*a2, A1 = sum G*swish'(y2), A2 = sum G*swish'(y2)*dhat.
 hipError_t launch_gate_sums(bool bf16, int N, int C, int HW, const void *G, const void *d,
