@@ -192,6 +192,17 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
+// A value that all lanes of the wavefront share (its channel's filter and coefficients) goes to a
+// scalar register in the backward kernel: the filter alone would take 25 of the vector registers
+// that decide how many wavefronts a SIMD holds (5x5: 142 registers, three wavefronts; 104, four.  128
+// images of 672 14x14 planes in bf16, with the image ranges of dwr_args: 79 us before, 71 now).  The
+// forward kernel has room for its filter: with the 5x5 one in scalar registers it took 42 us instead
+// of 39, with the 3x3 one 0.5 us less of 15.6.
+__device__ __forceinline__ float uniform(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
 // Lane geometry shared by forward and backward.
 struct DwrLane {
     int c, seg;      // channel and image range of this wavefront
@@ -200,11 +211,15 @@ struct DwrLane {
     bool lane_ok;    // the lane has a run
     int n_begin, n_end, iters;
 };
+// UNIFORM: channel and image range are known to be the same in all lanes (see `uniform`).
+template <bool UNIFORM>
 __device__ __forceinline__ DwrLane dwr_lane(const DwrArgs &a)
 {
     DwrLane L;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int slot = blockIdx.x * 4 + wave;
+    const int lane = threadIdx.x & 63;
+    int slot = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (UNIFORM)
+        slot = __builtin_amdgcn_readfirstlane(slot);
     L.c = (int)fdiv((uint32_t)slot, a.divNseg);
     L.seg = slot - L.c * a.nseg;
     L.wave_ok = L.c < a.C;
@@ -230,7 +245,7 @@ __global__ __launch_bounds__(256) void dwr_fwd_kernel(DwrArgs a)
     const int H = a.H, W = a.W, WP = a.WP;
     const int tileElems = (H + 2 * P) * WP;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const DwrLane L = dwr_lane(a);
+    const DwrLane L = dwr_lane<K == 3>(a);
     // per wavefront: two buffers of PW tiles
     float *mine = lds + wave * (2 * a.PW * tileElems);
     for (int i = lane; i < 2 * a.PW * tileElems / 4; i += 64)
@@ -330,7 +345,7 @@ __global__ __launch_bounds__(256) void dwr_bwd_kernel(DwrArgs a)
     const int H = a.H, W = a.W, WP = a.WP, C = a.C;
     const int tileElems = (H + 2 * P) * WP;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const DwrLane L = dwr_lane(a);
+    const DwrLane L = dwr_lane<true>(a);
     // per wavefront: two buffers of PW dd tiles.  There is no a1 tile: the filter gradient
     // dW[u][v] = sum_p dd[p] * a1[p + (u,v) - P] is summed over q = p + (u,v) - P, which pairs each
     // lane's own a1 values (registers) with the dd window elements the input gradient reads anyway.
@@ -341,16 +356,16 @@ __global__ __launch_bounds__(256) void dwr_bwd_kernel(DwrArgs a)
     float wt[K * K];
 #pragma unroll
     for (int t = 0; t < K * K; ++t)
-        wt[t] = ld<T>((const T *)a.w, (size_t)L.c * K * K + t);
+        wt[t] = uniform(ld<T>((const T *)a.w, (size_t)L.c * K * K + t));
     float scale1 = 1.f, shift1 = 0.f, mean1 = 0.f, rstd1 = 0.f;
     if (EXPAND) {
-        scale1 = a.bn1[L.c];
-        shift1 = a.bn1[C + L.c];
-        mean1 = a.bn1[2 * C + L.c];
-        rstd1 = a.bn1[3 * C + L.c];
+        scale1 = uniform(a.bn1[L.c]);
+        shift1 = uniform(a.bn1[C + L.c]);
+        mean1 = uniform(a.bn1[2 * C + L.c]);
+        rstd1 = uniform(a.bn1[3 * C + L.c]);
     }
-    const float scale2 = a.bn2[L.c], shift2 = a.bn2[C + L.c];
-    const float c0 = a.coef2[L.c], c1 = a.coef2[C + L.c], c2 = a.coef2[2 * C + L.c];
+    const float scale2 = uniform(a.bn2[L.c]), shift2 = uniform(a.bn2[C + L.c]);
+    const float c0 = uniform(a.coef2[L.c]), c1 = uniform(a.coef2[C + L.c]), c2 = uniform(a.coef2[2 * C + L.c]);
     const size_t hw = (size_t)H * W;
     const int off = L.h * W + L.x0;
 
@@ -488,14 +503,22 @@ static DwrArgs dwr_args(const DwShape &s)
     a.PW = 64 / a.runs;
     if (a.PW > s.N)
         a.PW = s.N;
-    // image ranges: enough wavefronts to fill the chip, at least four pipeline steps each
-    int nseg = (4096 + s.C - 1) / s.C;
+    // Image ranges: about 4096 wavefronts (four on each of the 1024 SIMDs), at least four pipeline steps
+    // each.  Of the two nearest numbers the one whose busiest SIMD has less to do, counted in steps, a
+    // wavefront's setup and reductions as one and a half (672 channels: 4704 wavefronts leave every
+    // second SIMD with a fifth one, six ranges fit; 1152 channels of 7x7: four short ranges beat three).
     const int cap = s.N / (4 * a.PW) > 1 ? s.N / (4 * a.PW) : 1;
-    if (nseg > cap)
-        nseg = cap;
-    a.nper = (s.N + nseg - 1) / nseg;
-    a.nper = (a.nper + a.PW - 1) / a.PW * a.PW;
-    a.nseg = (s.N + a.nper - 1) / a.nper;
+    const auto pick = [&](int nseg) {
+        nseg = nseg > cap ? cap : nseg < 1 ? 1 : nseg;
+        a.nper = (s.N + nseg - 1) / nseg;
+        a.nper = (a.nper + a.PW - 1) / a.PW * a.PW;
+        a.nseg = (s.N + a.nper - 1) / a.nper;
+        return ((long long)s.C * a.nseg + 1023) / 1024 * (2 * (a.nper / a.PW) + 3);
+    };
+    const int many = (4096 + s.C - 1) / s.C, few = 4096 / s.C;
+    const long long cost_many = pick(many);
+    if (pick(few) >= cost_many)
+        pick(many);
     a.divRuns = make_div((uint32_t)a.runs);
     a.divW4 = make_div((uint32_t)a.W4);
     a.divNseg = make_div((uint32_t)a.nseg);
