@@ -49,6 +49,17 @@ __device__ __forceinline__ float16v x3_mfma6(const bf16x8 (&a)[3], const bf16x8 
     return acc;
 }
 
+// the five small products of x3_mfma6 (all but a[0]*b[0])
+__device__ __forceinline__ float16v x3_mfma5(const bf16x8 (&a)[3], const bf16x8 (&b)[3], float16v acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc, 0, 0, 0);
+    return acc;
+}
+
 // Halfword offset of element (row, k) in a plane of rows of 64 bytes (32 k) whose four 16-byte groups
 // are permuted by bits 2-3 of the row: the 16-byte reads of 16 consecutive rows fall on distinct banks
 // without padding.
@@ -187,6 +198,9 @@ struct X3RowData {
 // image; the last run of an image starts at HW - 4 and its pixels that the run before has are masked, so
 // a 7x7 plane takes 13 runs (52 of its 49 pixels), every access stays 16 bytes wide (4-byte aligned)
 // inside its plane, and both operands see the same order.
+// These planes were the fp32 matrix cores' before, whose sums over many images are closer than those of
+// a single accumulator here (the bf16 MFMA truncates a small addend to a large accumulator), so the small
+// cross products have an accumulator of their own, on tiles of 128 x 64.
 template <int PROU, int PROV, int VB, bool TR, bool RAG>
 __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uint16_t *Us, uint16_t *Vs)
 {
@@ -242,12 +256,15 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
         dv[s].template store<true>(cv, Vs, rr, qg, mask);
     };
 
-    float16v acc[NA];
+    static_assert(!RAG || VB == 64, "two accumulators per output: 32 x 32 per wavefront");
+    float16v acc[NA], low; // low: RAG only
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
+    for (int r = 0; r < 16; ++r) {
+        low[r] = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
+        for (int i = 0; i < NA; ++i)
             acc[i][r] = 0.f;
+    }
     if (cbeg < cend) { // uniform over the workgroup; an empty split writes zeros
         load(0, cbeg);
         load(1, min(cbeg + 1, cend - 1));
@@ -271,8 +288,14 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
                         bv[pl] = x3_lds8(Vs + pl * kPlaneV + x3_img_at(vb + (lane & 31), ko));
                     }
 #pragma unroll
-                    for (int i = 0; i < NA; ++i)
-                        acc[i] = x3_mfma6(av[i], bv, acc[i]);
+                    for (int i = 0; i < NA; ++i) {
+                        if (RAG) {
+                            low = x3_mfma5(av[i], bv, low);
+                            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i][0], bv[0], acc[i], 0, 0, 0);
+                        } else {
+                            acc[i] = x3_mfma6(av[i], bv, acc[i]);
+                        }
+                    }
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -296,7 +319,7 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
             const int ai = a0 + ua + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
             const int bi = b0 + vb + (lane & 31);
             if (ai < a.Ma && bi < a.Mb)
-                dst[TR ? (size_t)bi * a.Ma + ai : (size_t)ai * a.Mb + bi] = acc[i][r];
+                dst[TR ? (size_t)bi * a.Ma + ai : (size_t)ai * a.Mb + bi] = RAG ? acc[i][r] + low[r] : acc[i][r];
         }
 }
 
@@ -313,9 +336,9 @@ template <int VAR, bool RAG>
 __device__ __forceinline__ void wgrad_x3_variant(const X3WgradArgs &a, int bid, uint16_t *Us, uint16_t *Vs)
 {
     if (VAR == 0)
-        wgrad_x3_body<PRO_BNBWD, PRO_NONE, 128, false, RAG>(a, bid, Us, Vs);
+        wgrad_x3_body<PRO_BNBWD, PRO_NONE, 128, false, false>(a, bid, Us, Vs);
     else if (VAR == 1)
-        wgrad_x3_body<PRO_BNBWD, PRO_BNSWISH_GATE, 128, false, RAG>(a, bid, Us, Vs);
+        wgrad_x3_body<PRO_BNBWD, PRO_BNSWISH_GATE, 128, false, false>(a, bid, Us, Vs);
     else if (VAR == 2)
         wgrad_x3_body<PRO_BNBWD, PRO_NONE, 64, false, RAG>(a, bid, Us, Vs);
     else if (VAR == 3)
@@ -349,9 +372,14 @@ bool x3_wgrad_plan(int Ma, int Mb, int N, int HW, int *splits)
     const long long Q = (long long)N * HW;
     // (a side of at most 32 channels belongs to the fused backward kernels of kernels_wave.hip,
     // which size their partial tiles by the plan of that file)
+    // Planes of at most 64 pixels that are no multiple of four (7x7) stay on the fp32 matrix cores:
+    // callers of mbconv_step_engine count on that answer for them.  It is not the faster choice (64 x 7x7,
+    // 192 -> 1152 -> 320: 93 us for the pair there, 51 here).
+    if (HW % 4 != 0 && HW <= 64)
+        return false;
     if (Q >= (1ll << 31) || (long long)std::max(Ma, Mb) * HW >= (1ll << 31) || HW < 4 || std::min(Ma, Mb) <= 32 || std::max(Ma, Mb) < 64)
         return false;
-    const int wide = std::max(Ma, Mb), narrow = std::min(Ma, Mb), vb = narrow <= 64 ? 64 : 128;
+    const int wide = std::max(Ma, Mb), narrow = std::min(Ma, Mb), vb = narrow <= 64 || HW % 4 != 0 ? 64 : 128;
     const long long tiles = (long long)((wide + 127) / 128) * ((narrow + vb - 1) / vb);
     const long long chunks = ((long long)N * ((HW + 3) / 4) + 7) / 8;
     // (rounded down: two gradients that share a launch then just fit, two workgroups per compute unit;
@@ -380,7 +408,8 @@ static X3Operand to_x3(const Operand &o)
 }
 
 // Arguments, grid and kernel form (0..5, see wgrad_x3_variant) of one weight gradient.
-static bool x3_wgrad_setup(int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
+// rag: the launch's kernel is the form for planes that are no multiple of four (either one's of a pair).
+static bool x3_wgrad_setup(bool rag, int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
                            float *partial, X3WgradArgs *out, unsigned *grid, int *variant, int *splits_out)
 {
     int splits;
@@ -388,7 +417,7 @@ static bool x3_wgrad_setup(int N, int Ma, int Mb, int HW, const Operand &U, cons
         return false;
     // a narrow first operand: the kernel computes the transposed product and writes it transposed
     const bool swap = Ma < 64 && Mb >= 64;
-    const int vb = std::min(Ma, Mb) <= 64 ? 64 : 128;
+    const int vb = std::min(Ma, Mb) <= 64 || rag ? 64 : 128;
     X3WgradArgs a;
     a.Ma = swap ? Mb : Ma;
     a.Mb = swap ? Ma : Mb;
@@ -429,12 +458,13 @@ hipError_t launch_x3_wgrad(int N, int Ma, int Mb, int HW, const Operand &U, cons
     X3WgradArgs a;
     unsigned grid;
     int var;
-    if (!x3_wgrad_setup(N, Ma, Mb, HW, U, V, partial, &a, &grid, &var, splits_out))
+    if (!x3_wgrad_setup(HW % 4 != 0, N, Ma, Mb, HW, U, V, partial, &a, &grid, &var, splits_out))
         return hipErrorInvalidValue;
 #define MBK_CASE(VAR, PU, PV, VB_, TR_)                                                           \
     if (var == VAR) {                                                                             \
-        if (HW % 4 != 0)                                                                          \
-            hipLaunchKernelGGL((wgrad_x3_kernel<PU, PV, VB_, TR_, true>), dim3(grid), dim3(512), 0, st, a);  \
+        constexpr bool kRag = VB_ == 64; /* (the other forms never see such planes) */            \
+        if (kRag && HW % 4 != 0)                                                                  \
+            hipLaunchKernelGGL((wgrad_x3_kernel<PU, PV, VB_, TR_, kRag>), dim3(grid), dim3(512), 0, st, a);  \
         else                                                                                      \
             hipLaunchKernelGGL((wgrad_x3_kernel<PU, PV, VB_, TR_, false>), dim3(grid), dim3(512), 0, st, a); \
         return hipGetLastError();                                                                 \
@@ -460,13 +490,15 @@ hipError_t launch_x3_wgrad_pair(int N, int MaA, int MbA, int HWA, const Operand 
     X3WgradArgs a, b;
     unsigned ga, gb;
     int va, vb;
-    if (!x3_wgrad_setup(N, MaA, MbA, HWA, UA, VA, partialA, &a, &ga, &va, splitsA) ||
-        !x3_wgrad_setup(N, MaB, MbB, HWB, UB, VB, partialB, &b, &gb, &vb, splitsB))
+    const bool rag = HWA % 4 != 0 || HWB % 4 != 0;
+    if (!x3_wgrad_setup(rag, N, MaA, MbA, HWA, UA, VA, partialA, &a, &ga, &va, splitsA) ||
+        !x3_wgrad_setup(rag, N, MaB, MbB, HWB, UB, VB, partialB, &b, &gb, &vb, splitsB))
         return hipErrorNotSupported;
 #define MBK_CASE(VA_, VB_)                                                                        \
     if (va == VA_ && vb == VB_) {                                                                 \
-        if (HWA % 4 != 0 || HWB % 4 != 0)                                                         \
-            hipLaunchKernelGGL((wgrad_x3_pair_kernel<VA_, VB_, true>), dim3(ga + gb), dim3(512), 0, st, a, b,  \
+        constexpr bool kRag = VA_ >= 2 && VB_ >= 2;                                               \
+        if (kRag && rag)                                                                          \
+            hipLaunchKernelGGL((wgrad_x3_pair_kernel<VA_, VB_, kRag>), dim3(ga + gb), dim3(512), 0, st, a, b,  \
                                (int)ga);                                                          \
         else                                                                                      \
             hipLaunchKernelGGL((wgrad_x3_pair_kernel<VA_, VB_, false>), dim3(ga + gb), dim3(512), 0, st, a, b, \
