@@ -214,8 +214,8 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
     // The (split, tile) pairs in order, an eighth of them to each XCD (blockIdx.x mod 8): workgroups
     // that read the same pixels (all tiles of one split) mostly share an XCD's L2, and no XCD has more
     // than one workgroup above the others, whatever the number of splits.  (Whole splits dealt to the
-    // XCDs: ten of them gave two XCDs twice the work; the pair of 64 x 7x7, 192 -> 1152 -> 320: 66.7 us
-    // against 51.5 now.)
+    // XCDs: ten of them gave two XCDs twice the work; 1152 x (320 + 192) over 3136 pixels: 66.7
+    // us, 51.5 this way.)
     const int tiles = a.tilesA * a.tilesB, perXcd = (tiles * a.splits + 7) >> 3;
     const int item = (bid & 7) * perXcd + (bid >> 3);
     const int split = item / tiles, tile = item % tiles;
