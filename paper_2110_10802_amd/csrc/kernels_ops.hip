@@ -256,9 +256,9 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const float *__restr
                 ab.v[j][k] += d.v[j][k];
                 a.v[j][k] = xh;
                 d.v[j][k] = gg;
-                const float gm = a.own(cols, t, j, k) ? gg : 0.f;
-                s1 += gm;
-                s2 = fmaf(gm, xh, s2);
+                // (the sums are selected, not the terms: a masked term could still be 0 * infinity)
+                s1 = a.own(cols, t, j, k) ? s1 + gg : s1;
+                s2 = a.own(cols, t, j, k) ? fmaf(gg, xh, s2) : s2;
             }
         const float m1 = row_reduce<TPR>(s1, red, false) * inv, m2 = row_reduce<TPR>(s2, red, false) * inv;
 #pragma unroll
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(256) void softmax_kernel(const float *__restrict__ 
             for (int j = 0; j < NV; ++j)
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    s = fmaf(d.v[j][k], a.own(cols, t, j, k) ? a.v[j][k] : 0.f, s);
+                    s = a.own(cols, t, j, k) ? fmaf(d.v[j][k], a.v[j][k], s) : s; // (not 0 * dy: dy may be infinite)
             s = row_reduce<TPR>(s, red, false);
 #pragma unroll
             for (int j = 0; j < NV; ++j)

@@ -59,3 +59,46 @@ def test_rows_match_oracle(rows, cols):
     assert rel_err(_host(dx), dxo, abs_floor=scale) <= GRAD
     floor = float(np.sqrt(np.mean(dy.astype(np.float64) ** 2)) * np.sqrt(rows))
     assert rel_err(_host(dg), dgo, abs_floor=floor) <= GRAD and rel_err(_host(db), dbo, abs_floor=floor) <= GRAD
+
+
+@pytest.mark.parametrize("rows,cols", SHAPES)
+def test_infinities_stay_where_the_arithmetic_puts_them(rows, cols):
+    """An infinite gradient in the columns that two threads read must count once, as a number: the other
+    columns of the row are infinite, not NaN, and the other rows untouched."""
+    import torch
+    from paper_2110_10802_amd import dnnops as D
+    rng = np.random.default_rng(cols)
+    y = rng.random((rows, cols)).astype(np.float32) / cols + np.float32(1e-6)
+    dy = rng.standard_normal((rows, cols)).astype(np.float32)
+    dy[1, cols - 2] = np.inf
+    yd, dyd = _dev(y), _dev(dy)
+    dx = torch.empty_like(yd)
+    print(f"[rows/inf] {rows}x{cols}", flush=True)
+    D.softmax_backward(yd, dyd, dx, rows, cols)
+    torch.cuda.synchronize()
+    got = _host(dx)
+    with np.errstate(invalid="ignore"):
+        s = (y.astype(np.float64) * dy).sum(1, keepdims=True)
+        ref = y * (dy - s)  # row 1: -inf, and inf - inf in the column itself
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref).sum() == 1
+    assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.all(got[1][np.isinf(ref[1])] < 0)
+    ok = np.isfinite(ref)
+    assert rel_err(got[ok], ref[ok]) <= GRAD
+
+    # a row whose reciprocal deviation is infinite (a constant row, eps 0): with gamma and dy above zero
+    # both sums of the row are infinite, with x above the mean so are all terms
+    x = (1 + rng.random((rows, cols))).astype(np.float32)
+    gamma = (1 + rng.random(cols)).astype(np.float32)
+    dyp = (1 + rng.random((rows, cols))).astype(np.float32)
+    mean, rstd = np.zeros(rows, np.float32), np.ones(rows, np.float32)
+    rstd[1] = np.inf
+    xd, gd, dyd = _dev(x), _dev(gamma), _dev(dyp)
+    dg, db = torch.empty_like(gd), torch.empty_like(gd)
+    scratch = torch.empty(D.layernorm_backward_scratch_bytes(rows, cols), dtype=torch.uint8, device="cuda:0")
+    D.layernorm_backward(xd, dyd, gd, _dev(mean), _dev(rstd), rows, cols, dx, dg, db, scratch)
+    torch.cuda.synchronize()
+    got = _host(dx)
+    # dx of that row is inf * (dy - m1 - inf * inf): -inf
+    assert np.all(np.isinf(got[1])) and np.all(got[1] < 0)
+    assert np.all(np.isfinite(np.delete(got, 1, 0)))
+    assert np.all(np.isinf(_host(dg))) and np.all(np.isfinite(_host(db)))
