@@ -244,8 +244,8 @@ hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm
                              void *out, int epi, float *psum, float *psq, hipStream_t st);
 // kernels_xk.hip
 bool xk_conv_plan(bool bf16, int N, int M, int K, int HW, int pro, int *chunks);
-hipError_t launch_xk_conv1x1(bool bf16, int N, int M, int K, int HW, const void *wimg, const Operand &B,
-                             void *out, int epi, const void *res, float *psum, float *psq, hipStream_t st);
+hipError_t launch_xk_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w, int sAm, int sAk,
+                             const void *wimg, const Operand &B, void *out, int epi, const void *res, float *psum, float *psq, hipStream_t st);
 #ifndef MBK_X3W
 #define MBK_X3W 1
 #endif
@@ -340,7 +340,7 @@ hipError_t launch_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w,
         if (xk_applies(bf16, N, M, K, HW, sc_store != nullptr, B.pro, epi, &nt)) {
             if (!wimg)
                 return hipErrorInvalidValue;
-            return launch_xk_conv1x1(bf16, N, M, K, HW, wimg, B, out, epi, res, psum, psq, st);
+            return launch_xk_conv1x1(bf16, N, M, K, HW, w, sAm, sAk, wimg, B, out, epi, res, psum, psq, st);
         }
     }
     const int kind = sc_store ? 0 : wave_conv_kind(M, K, HW);
@@ -394,7 +394,7 @@ hipError_t launch_conv1x1_affine(bool bf16, int N, int M, int K, int HW, const v
         // (the image is that of the training-mode role, whose kernel this one shares)
         int nt;
         if (xk_applies(bf16, N, M, K, HW, false, B.pro, EPI_STATS, &nt))
-            return wimg ? launch_xk_conv1x1(bf16, N, M, K, HW, wimg, B, out, EPI_AFFINE, res, sc, sh, st)
+            return wimg ? launch_xk_conv1x1(bf16, N, M, K, HW, w, sAm, sAk, wimg, B, out, EPI_AFFINE, res, sc, sh, st)
                         : hipErrorNotSupported;
     }
     if (wave_conv_kind(M, K, HW) || (sAm != 1 && sAk != 1) || HW % 4 != 0)

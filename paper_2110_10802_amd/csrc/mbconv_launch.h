@@ -53,7 +53,7 @@ size_t conv1x1_splitk_floats(bool bf16, int N, int M, int K, int HW, bool stores
 // the order the kernels read them, see kernels_x3.hip): where
 // conv1x1_uses_weight_image(...) says so, `wimg` must point to the image of this A (M rows, K
 // contraction indices), x3_weight_image_bytes(M, K) bytes, written by launch_x3_prep beforehand;
-// `w` is then not read.
+// `w` is then read only for outputs that the image's planes cannot give (infinite operands).
 bool conv1x1_uses_weight_image(bool bf16, int N, int M, int K, int HW, bool stores_operand,
                                int pro = -1, int epi = -1);
 size_t x3_weight_image_bytes(bool bf16, int M, int K);

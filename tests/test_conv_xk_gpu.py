@@ -69,3 +69,50 @@ def test_eval_matches_oracle(name, policy):
     out = to_numpy(blk.forward_eval(blk.to_device(t["x"])))
     torch.cuda.synchronize()
     assert metric_for(s)(out, orc.mbconv_forward_eval(s, t)) <= TOL[s.dtype]["fwd"]
+
+
+def _small(**kw):
+    return _s(**{**dict(Cin=43, Cexp=258, Cout=43, H=9, W=5, activation="relu6", has_se=False, Cse=1), **kw})
+
+
+INFINITE = {
+    # (shape, tensor, {index: value}): in x with ReLU6 (the clamp makes everything behind it finite, the
+    # residual carries the infinities), the largest finite values (their bf16 rounding is infinite), in weights
+    "x": (_small(), "x", {(0, 3, 2, 2): np.inf, (1, 2, 1, 1): -np.inf}),
+    "x_largest": (_small(), "x", {(1, 5, 4, 4): np.finfo(np.float32).max, (0, 7, 0, 0): -3.4e38}),
+    "w_expand": (_small(), "w_expand", {(7, 3): np.inf}),
+    "w_proj": (_small(), "w_proj", {(7, 3): -np.inf}),
+    # the last channel of a contraction that ends inside a 32-deep step (the step's other rows repeat it)
+    "last_channel": (_s(Cin=72, Cexp=72, Cout=48, has_expand=False, residual=False, has_se=False, Cse=1, H=5, W=7),
+                     "x", {(0, 71, 2, 2): np.inf}),
+    "last_channel_bf16": (_s(N=1, Cin=136, Cexp=136, Cout=48, has_expand=False, residual=False, has_se=False,
+                             Cse=1, dtype="bf16"), "x", {(0, 135, 2, 2): np.inf}),
+}
+
+
+@pytest.mark.parametrize("name", list(INFINITE))
+def test_infinite_operands(name):
+    """Evaluation mode: infinities and NaN where 64-bit arithmetic has them, finite values elsewhere."""
+    import torch
+    from paper_2110_10802_amd.harness import DeviceBlock, to_numpy
+
+    s, what, values = INFINITE[name]
+    t = make_block_inputs(s, seed=20)
+    t["w_dw"] = np.abs(t["w_dw"])  # (no sums of opposite infinities)
+    for i, c in ((1, s.Cexp), (2, s.Cexp), (3, s.Cout)):
+        t[f"bn{i}_mean"], t[f"bn{i}_var"] = np.zeros(c, np.float32), np.ones(c, np.float32)
+    t[what] = t[what].copy()
+    for at, v in values.items():
+        t[what][at] = v
+    print(f"[conv_xk/inf] {name}", flush=True)
+    blk = DeviceBlock(s, t)
+    got = to_numpy(blk.forward_eval(blk.to_device(t["x"]))).astype(np.float64)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        ref = orc.mbconv_forward_eval(s, t)
+    ref = np.where(np.abs(ref) > np.finfo(np.float32).max, np.sign(ref) * np.inf, ref)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.where(np.isinf(got), np.sign(got), 0), np.where(np.isinf(ref), np.sign(ref), 0))
+    ok = np.isfinite(ref) & (np.abs(ref) < 1e30)
+    assert ok.sum() > ref.size // 2
+    assert metric_for(s)(got[ok], ref[ok]) <= TOL[s.dtype]["fwd"]
