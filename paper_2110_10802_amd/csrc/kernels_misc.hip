@@ -311,7 +311,8 @@ __global__ __launch_bounds__(256) void se_fwd_kernel(int C, int Cse, const float
 // The same form of the backward kernel measured no faster, 6.8 and 11.4 against 6.8 and 11, and is not
 // used.)
 // Rows whose length is no multiple of four are read in pieces of four that are clamped to the row's
-// end; the elements a piece shares with the one before it are masked.
+// end; the elements a piece shares with the one before it are masked, in both factors: either may be
+// infinite.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 template <int CI, int JR>
 __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int slice,
@@ -323,6 +324,7 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
                                                            float *g)
 {
     constexpr int RU = JR * CI <= 15 ? JR : 10 / CI > 1 ? 10 / CI : 1; // rows of W1 in flight (128 registers)
+    constexpr int FULL = CI == 5 || CI == 8 ? CI - 2 : CI - 1; // pieces of a row that end before C in every lane
     __shared__ float rs[64];
     const int n = blockIdx.x, sl = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -351,11 +353,12 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
     };
     fetch_w2(c);
     __builtin_amdgcn_sched_barrier(0);
+    const auto own = [&](int i, int e) { return min(4 * (lane + 64 * i), C - 4) + e >= 4 * (lane + 64 * i); };
 #pragma unroll
-    for (int i = 0; i < CI; ++i) // (a piece past the end, or the part of one that another lane has)
+    for (int i = FULL; i < CI; ++i) // (a piece past the end, or the part of one that another lane has)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            zv[i][e] = min(4 * (lane + 64 * i), C - 4) + e >= 4 * (lane + 64 * i) ? zv[i][e] : 0.f;
+            zv[i][e] = own(i, e) ? zv[i][e] : 0.f;
 #pragma unroll
     for (int u = 0; u < JR; ++u) {
         const int j = wave + 16 * u;
@@ -364,7 +367,7 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
         for (int i = 0; i < CI; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                acc = fmaf(wv[u % RU][i][e], zv[i][e], acc);
+                acc = fmaf(i < FULL || own(i, e) ? wv[u % RU][i][e] : 0.f, zv[i][e], acc);
         if (u + RU < JR)
             fetch_w1(u + RU);
         acc = wave_sum(acc);
@@ -385,7 +388,7 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
             const int want = 4 * (part + 4 * v), at = min(want, Cse - 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                acc = fmaf(at + e >= want ? w2v[v][e] : 0.f, rs[at + e], acc);
+                acc = fmaf(at + e >= want ? w2v[v][e] : 0.f, at + e >= want ? rs[at + e] : 0.f, acc);
         }
         fetch_w2(c + 256);
         acc += __shfl_xor(acc, 1, kWave);
