@@ -344,14 +344,11 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
         fetch_w1(u);
     // W2: four threads per channel, thread t%4 takes the pieces t%4, t%4 + 4, ...
     const int part = tid & 3, cend = min(C, (sl + 1) * slice);
-    int c = sl * slice + (tid >> 2);
-    const auto fetch_w2 = [&](int ch) __attribute__((always_inline)) {
+    const int c = sl * slice + (tid >> 2); // (a slice has at most 256 channels)
 #pragma unroll
-        for (int v = 0; v < JR; ++v)
-            w2v[v] = *reinterpret_cast<const f32x4u *>(w2 + (size_t)min(ch, C - 1) * Cse +
-                                                       min(4 * (part + 4 * v), Cse - 4));
-    };
-    fetch_w2(c);
+    for (int v = 0; v < JR; ++v)
+        w2v[v] = *reinterpret_cast<const f32x4u *>(w2 + (size_t)min(c, C - 1) * Cse +
+                                                   min(4 * (part + 4 * v), Cse - 4));
     __builtin_amdgcn_sched_barrier(0);
     const auto own = [&](int i, int e) { return min(4 * (lane + 64 * i), C - 4) + e >= 4 * (lane + 64 * i); };
 #pragma unroll
@@ -381,7 +378,7 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
             __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
-    for (; c < cend; c += 256) {
+    if (c < cend) {
         float acc = 0.f;
 #pragma unroll
         for (int v = 0; v < JR; ++v) {
@@ -390,7 +387,6 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
             for (int e = 0; e < 4; ++e)
                 acc = fmaf(at + e >= want ? w2v[v][e] : 0.f, at + e >= want ? rs[at + e] : 0.f, acc);
         }
-        fetch_w2(c + 256);
         acc += __shfl_xor(acc, 1, kWave);
         acc += __shfl_xor(acc, 2, kWave);
         if (part == 0)
