@@ -74,23 +74,16 @@ struct XkRaw {
     }
     __device__ __forceinline__ float get(int i) const { return v[i]; }
 };
-template <bool PAIR>
-struct XkRaw<bf16_t, PAIR> {
-    uint32_t v[PAIR ? 1 : 2];
-    __device__ __forceinline__ void load(const bf16_t *p, uint32_t o0, uint32_t o1)
+template <>
+struct XkRaw<bf16_t, true> { // (bf16 is served on planes that are multiples of four)
+    uint32_t v;
+    __device__ __forceinline__ void load(const bf16_t *p, uint32_t o0, uint32_t)
     {
-        if (PAIR) {
-            v[0] = *reinterpret_cast<const uint32_t *>(p + o0);
-        } else {
-            v[0] = p[o0].bits;
-            v[PAIR ? 0 : 1] = p[o1].bits;
-        }
+        v = *reinterpret_cast<const uint32_t *>(p + o0);
     }
     __device__ __forceinline__ float get(int i) const
     {
-        if (PAIR)
-            return __uint_as_float(i ? v[0] & 0xffff0000u : v[0] << 16);
-        return __uint_as_float(v[PAIR ? 0 : i] << 16);
+        return __uint_as_float(i ? v & 0xffff0000u : v << 16);
     }
 };
 
@@ -545,15 +538,18 @@ static hipError_t xk_launch(const XkArgs &a, const XkPlan &p, int pro, hipStream
 {
     const bool pair = a.HW % 2 == 0;
     const dim3 grid((unsigned)(8 * a.chunksPerDie * a.slabs));
+// (bf16: the forms that xk_plan lets through)
 #define MBK_CASE(RT_, PAIR_, PRO_)                                                                \
-    if (p.rt == RT_ && pair == PAIR_ && pro == PRO_) {                                            \
-        auto kern = conv_xk_kernel<T, RT_, PAIR_, PRO_>;                                          \
-        const hipError_t e_ = hipFuncSetAttribute(                                                \
-            (const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);          \
-        if (e_ != hipSuccess)                                                                     \
-            return e_;                                                                            \
-        hipLaunchKernelGGL(kern, grid, dim3((unsigned)(64 * p.W)), p.lds, st, a);                 \
-        return hipGetLastError();                                                                 \
+    if constexpr (sizeof(T) == 4 || (PAIR_ && PRO_ != PRO_NONE)) {                                \
+        if (p.rt == RT_ && pair == PAIR_ && pro == PRO_) {                                        \
+            auto kern = conv_xk_kernel<T, RT_, PAIR_, PRO_>;                                      \
+            const hipError_t e_ = hipFuncSetAttribute(                                            \
+                (const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);      \
+            if (e_ != hipSuccess)                                                                 \
+                return e_;                                                                        \
+            hipLaunchKernelGGL(kern, grid, dim3((unsigned)(64 * p.W)), p.lds, st, a);             \
+            return hipGetLastError();                                                             \
+        }                                                                                         \
     }
 #define MBK_RT(RT_)                                                                               \
     MBK_CASE(RT_, true, PRO_BNSWISH_GATE)                                                         \
