@@ -1058,6 +1058,18 @@ hipError_t launch_gate_sums(bool bf16, int N, int C, int HW, const void *G, cons
     return bf16 ? plane_reduce_launch<bf16_t, OpGate>(a, st) : plane_reduce_launch<float, OpGate>(a, st);
 }
 
+// Every workgroup that finalises BN3 reads all of its channel's partial sums (one per 32 pixels of the
+// whole batch behind conv_xk), so the repeated reads grow with the square of the batch, the launch they
+// save does not.  Up to two and a half rounds of eight workgroups per compute unit they are hidden
+// (with / without the step inside, one forward pass of a block with Cout channels: 112, 64 images of
+// 17x17 78.3 / 80.3 us; 40, 128 images of 112x112 987 / 1014), beyond that they are not (112, 512 of
+// 17x17 492 / 474; 64, 1024 of 24x24 437 / 364; 112, 256 of 56x56 1728 / 1514).
+bool bn_apply_finalizes(int N, int C, int HW)
+{
+    const int tpp = pick_tpp_plane(HW), ppb = tpp < 256 ? 256 / tpp : 1;
+    return (long long)C * ((N + ppb - 1) / ppb) <= 5 * 1024;
+}
+
 hipError_t launch_bn_apply(bool bf16, int N, int C, int HW, const void *p, const float *bn3,
                            const void *res, void *out, const BnFin *fin, hipStream_t st)
 {

@@ -361,7 +361,8 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     // A normalisation's finalise step (partial sums -> scale, shift, mean, rstd, running
     // statistics) runs inside the kernel that first consumes the statistics where that pays: BN1
     // in the vectorised depthwise kernel for large planes, BN2 in the pooling kernel for small ones
-    // (measured for large ones: no gain), BN3 in the final elementwise pass; otherwise it is a launch of its own.
+    // (measured for large ones: no gain), BN3 in the final elementwise pass of batches that are not
+    // large; otherwise it is a launch of its own.
     const DwShape ds = {P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p};
     void *a1_store = (P.store && P.expand && !eval) ? at<char>(saved, P.o_a1) : nullptr;
     const double m1 = (double)P.N * P.HW, m2 = (double)P.N * P.HWo;
@@ -370,6 +371,7 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     const BnFin fin3 = make_bn_fin(psum, psq, prm->bn3_gamma, prm->bn3_beta, run ? run->bn3_mean : nullptr,
                                    run ? run->bn3_var : nullptr, bn3, P.NT5, eps, mom, m2);
     const bool fuse1 = !eval && P.expand && dw_fwd_finalizes_bn1(ds, a1_store != nullptr);
+    const bool fuse3 = !eval && bn_apply_finalizes(P.N, P.Cout, P.HWo);
     const bool fuse2 = !eval && P.se && plane_channel_form(P.HWo);
     if (P.expand && !eval && !fuse1)
         MBK_STEP(MBCONV_STEP_BN1_FINALIZE, launch_bn_finalize(P.Cexp, P.NT1, m1, psum, psq, prm->bn1_gamma,
@@ -418,10 +420,13 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
                                   nullptr, psum, psq, sc_store, splitk, st, wimg(1));
         };
         MBK_STEP(MBCONV_STEP_PROJ_CONV, conv());
+        if (!eval && !fuse3)
+            MBK_STEP(MBCONV_STEP_BN3_FINALIZE, launch_bn_finalize(P.Cout, P.NT5, m2, psum, psq, prm->bn3_gamma,
+                                       prm->bn3_beta, eps, mom, fin3.run_mean, fin3.run_var, bn3, st));
     }
     // BN3 (+ residual), finalising BN3's statistics on the way in training mode
     MBK_STEP(MBCONV_STEP_BN3_APPLY, launch_bn_apply(bf, P.N, P.Cout, P.HWo, p, bn3, P.res ? x : nullptr, out,
-                                                    eval ? nullptr : &fin3, st));
+                                                    fuse3 ? &fin3 : nullptr, st));
     return MBCONV_OK;
 }
 

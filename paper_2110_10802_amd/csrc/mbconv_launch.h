@@ -230,7 +230,9 @@ hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, const float *w1,
                          const float *w2, const float *b2, float *q, float *g, hipStream_t st);
 
 // out = p*scale3+shift3 (+ x).
-// With `fin` non-null the kernel derives bn3 from fin's partial sums and writes it to fin->bn_out.
+// With `fin` non-null (only where bn_apply_finalizes says so) the kernel derives bn3 from fin's partial
+// sums and writes it to fin->bn_out.
+bool bn_apply_finalizes(int N, int C, int HW);
 hipError_t launch_bn_apply(bool bf16, int N, int C, int HW, const void *p, const float *bn3,
                            const void *res, void *out, const BnFin *fin, hipStream_t st);
 

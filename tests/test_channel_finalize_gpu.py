@@ -32,6 +32,10 @@ SHAPES = {
     "images_128": _s(N=128, H=4, W=4),
     "images_129": _s(N=129, H=4, W=4),
     "images_33": _s(N=33, H=17, W=17),
+    # channels times images (in groups of sixteen on small planes) where the BN3 step is inside the last
+    # pass for the last time, and where it is a launch
+    "bn3_inside": _s(N=2032, Cin=16, H=2, W=2, Cexp=32, Cse=4, Cout=40, residual=False),
+    "bn3_launch": _s(N=2064, Cin=16, H=2, W=2, Cexp=32, Cse=4, Cout=40, residual=False),
     "no_se": _s(has_se=False, Cse=1, activation="relu6"),
     "bf16": _s(N=19, H=10, W=10, dtype="bf16"),
 }
@@ -45,3 +49,33 @@ def test_block_matches_oracle(name):
     res, blk = run_gpu_block(s, t)
     f, b = orc.mbconv_step(s, t)
     compare_block(s, t, res, f, b, blk)
+
+
+def _occurs(s, step):
+    """Whether a training forward pass has that step: its events are recorded anew."""
+    import torch
+    from paper_2110_10802_amd import binding as B
+    from paper_2110_10802_amd.harness import DeviceBlock
+    t = make_block_inputs(s, seed=30)
+    blk = DeviceBlock(s, t)
+    x = blk.to_device(t["x"])
+    blk.forward(x)
+    big = torch.empty(1 << 27, device="cuda:0")
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record()
+    big.zero_()  # (half a gigabyte: longer than any step below)
+    e1.record()
+    torch.cuda.synchronize()
+    before = e0.elapsed_time(e1)
+    B.mbconv_forward_probed(blk.desc, blk.params, blk.running, x, blk.out, blk.saved, blk.scratch, 0,
+                            B.Probe(B.STEPS[step], e0.cuda_event, e1.cuda_event))
+    torch.cuda.synchronize()
+    return e0.elapsed_time(e1) != before
+
+
+@pytest.mark.parametrize("shape", [dict(H=2, W=2, N=2064), dict(H=6, W=43, N=520), dict(H=40, W=40, N=130)])
+def test_bn3_step_is_a_launch_for_large_batches(shape):
+    """Every workgroup of the last pass would read all partial sums of its channel."""
+    s = _s(**{**dict(Cin=16, Cexp=32, Cse=4, Cout=40, residual=False), **shape})
+    assert _occurs(s, "bn3_finalize")
+    assert not _occurs(s.with_batch(s.N // 2), "bn3_finalize")
