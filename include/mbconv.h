@@ -191,8 +191,8 @@ typedef enum {
                                       the statistics finalises them itself: DW_FWD for planes of 1024
                                       elements or more (stride 1, W % 4 == 0, recompute policy) and where
                                       a wavefront owns a channel, SE_POOL for planes of at most 1024
-                                      elements, BN3_APPLY unless channels
-                                      times images are many thousands */
+                                      elements and BN3_APPLY, both unless channels times images are
+                                      many thousands */
     MBCONV_STEP_DW_FWD = 3,        /* BN1 + Swish + depthwise conv + BN2 partial statistics */
     MBCONV_STEP_BN2_FINALIZE = 4,  /* (or SE_POOL in its place) also re-encodes the 1x1 conv weights for the wide blocks' kernels and,
                                       when no_se, fills the gate with ones (in evaluation mode the launch

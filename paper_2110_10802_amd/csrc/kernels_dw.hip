@@ -975,9 +975,18 @@ static PlaneArgs plane_args(int N, int C, int HW, const void *t0, const void *t1
 }
 
 // Small planes (16 or 64 lanes each): the pool finalises BN2's statistics itself, a channel's planes to
-// a workgroup.  Larger planes have workgroups of their own and would repeat the sum for each of them;
-// there the finalise step is a launch.
-bool plane_channel_form(int HW) { return HW <= 1024; }
+// a workgroup, in at most two rounds of images.  Larger planes have workgroups of their own and would
+// repeat the sum for each of them; there the finalise step is a launch, and so it is where there are
+// more workgroups than a round and a half of eight per compute unit: the workgroups of the following
+// rounds wait for their coefficients again, or with four rounds of images each have too few loads in
+// flight (with / without the step inside, one forward pass: 384 channels, 256 images of 12x12 105.9 /
+// 106.9 us, 512 of 14x14 258.7 / 254.1; 96 channels, 2048 of 17x17 826 / 794).
+static long long pool_chan_groups(int N, int C, int HW, int rounds)
+{
+    const int per = rounds * (256 / pick_tpp_plane(HW));
+    return (long long)C * ((N + per - 1) / per);
+}
+bool plane_channel_form(int N, int C, int HW) { return HW <= 1024 && pool_chan_groups(N, C, HW, 2) <= 3 * 1024; }
 
 hipError_t launch_pool(bool bf16, int N, int C, int HW, const void *d, const float *bn2, float *z,
                        float *s3, float *s4, const BnFin *fin, const X3PrepArgs *prep, hipStream_t st)
@@ -992,11 +1001,9 @@ hipError_t launch_pool(bool bf16, int N, int C, int HW, const void *d, const flo
         a.fin = *fin;
         if (prep)
             a.prep = *prep;
-        // images per workgroup: as many as leave eight workgroups per compute unit, up to four rounds
+        // images per workgroup: two rounds where that leaves eight workgroups per compute unit
         const int ppb = 256 / pick_tpp_plane(HW);
-        int rounds = 1;
-        while (rounds < 4 && (long long)C * ((N + 2 * rounds * ppb - 1) / (2 * rounds * ppb)) >= 2048)
-            rounds *= 2;
+        const int rounds = pool_chan_groups(N, C, HW, 2) >= 2048 ? 2 : 1;
         const int per = (N + rounds * ppb - 1) / (rounds * ppb);
         const dim3 grid((unsigned)((C * per + 7) / 8 * 8 + a.prep.tiles));
         if (ppb == 16 && bf16)

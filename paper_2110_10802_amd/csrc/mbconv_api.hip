@@ -372,7 +372,7 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
                                    run ? run->bn3_var : nullptr, bn3, P.NT5, eps, mom, m2);
     const bool fuse1 = !eval && P.expand && dw_fwd_finalizes_bn1(ds, a1_store != nullptr);
     const bool fuse3 = !eval && bn_apply_finalizes(P.N, P.Cout, P.HWo);
-    const bool fuse2 = !eval && P.se && plane_channel_form(P.HWo);
+    const bool fuse2 = !eval && P.se && plane_channel_form(P.N, P.Cexp, P.HWo);
     if (P.expand && !eval && !fuse1)
         MBK_STEP(MBCONV_STEP_BN1_FINALIZE, launch_bn_finalize(P.Cexp, P.NT1, m1, psum, psq, prm->bn1_gamma,
                                    prm->bn1_beta, eps, mom, fin1.run_mean, fin1.run_var, bn1, st));

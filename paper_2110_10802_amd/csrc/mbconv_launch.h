@@ -221,7 +221,7 @@ hipError_t launch_dw_fwd(bool bf16, const DwShape &s, const void *e, const float
 // Per plane of d: z = mean swish(y2), s3 = sum swish'(y2), s4 = sum swish'(y2)*dhat.
 // With `fin` non-null (only when plane_channel_form says so) the kernel derives bn2 from fin's partial
 // sums and writes it to fin->bn_out, and writes the weight images of `prep` (may be null).
-bool plane_channel_form(int HW);
+bool plane_channel_form(int N, int C, int HW);
 hipError_t launch_pool(bool bf16, int N, int C, int HW, const void *d, const float *bn2, float *z,
                        float *s3, float *s4, const BnFin *fin, const X3PrepArgs *prep, hipStream_t st);
 

@@ -20,8 +20,8 @@ SHAPES = {
     "last_group_of_one_image": _s(),
     "odd_plane": _s(N=33, H=5, W=7),
     "one_element_planes": _s(N=5, H=1, W=1, Cexp=96),
-    # several rounds of images per workgroup, the last one short, planes of four and of three elements
-    "rounds": _s(N=70, Cin=48, H=2, W=2, Cexp=1100, Cout=48),
+    # two rounds of images per workgroup, the last one short, planes of four and of three elements
+    "rounds": _s(N=55, Cin=48, H=2, W=2, Cexp=1100, Cout=48),
     "rounds_odd": _s(N=35, Cin=48, H=1, W=3, Cexp=1100, Cout=48),
     # the largest plane of 16 lanes, the smallest and the largest of a wavefront, the next one
     "plane_256": _s(N=3, H=16, W=16),
@@ -36,6 +36,9 @@ SHAPES = {
     # pass for the last time, and where it is a launch
     "bn3_inside": _s(N=2032, Cin=16, H=2, W=2, Cexp=32, Cse=4, Cout=40, residual=False),
     "bn3_launch": _s(N=2064, Cin=16, H=2, W=2, Cexp=32, Cse=4, Cout=40, residual=False),
+    # the same for BN2 and the pool (images in pairs of groups); weight images written by either
+    "bn2_inside": _s(N=96, Cin=32, H=2, W=2, Cexp=1024, Cse=8, Cout=48, residual=False),
+    "bn2_launch": _s(N=97, Cin=32, H=2, W=2, Cexp=1024, Cse=8, Cout=48, residual=False),
     "no_se": _s(has_se=False, Cse=1, activation="relu6"),
     "bf16": _s(N=19, H=10, W=10, dtype="bf16"),
 }
@@ -79,3 +82,10 @@ def test_bn3_step_is_a_launch_for_large_batches(shape):
     s = _s(**{**dict(Cin=16, Cexp=32, Cse=4, Cout=40, residual=False), **shape})
     assert _occurs(s, "bn3_finalize")
     assert not _occurs(s.with_batch(s.N // 2), "bn3_finalize")
+
+
+@pytest.mark.parametrize("shape", [dict(H=2, W=2, N=97), dict(H=6, W=43, N=25)])
+def test_bn2_step_is_a_launch_for_large_batches(shape):
+    s = _s(**{**dict(Cin=32, Cexp=1024, Cse=4, Cout=16, residual=False), **shape})
+    assert _occurs(s, "bn2_finalize")
+    assert not _occurs(s.with_batch(s.N - 1), "bn2_finalize")
