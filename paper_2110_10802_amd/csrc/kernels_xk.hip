@@ -474,9 +474,8 @@ struct XkPlan {
 };
 
 // Shapes and split.  bf16 storage: the shapes whose convolutions take bf16 operands (as
-// bf_conv_plan), in the roles with fewer rows than contraction indices (measured, batch 128, 14x14:
-// 672 -> 112 channels 25 -> 20 us, its gradient counterpart 30.6 -> 28.3; 112 -> 672 stays with
-// conv_bf, 31 us either way, and so does the expansion conv, whose operand has no prologue).
+// bf_conv_plan), in the roles with fewer rows than contraction indices, up to a size (below); 112 -> 672
+// stays with conv_bf, 31 us either way, and so does the expansion conv, whose operand has no prologue.
 static bool xk_plan(bool bf16, int N, int M, int K, int HW, int pro, XkPlan *p)
 {
     const long long Q = (long long)N * HW;
@@ -515,6 +514,14 @@ static bool xk_plan(bool bf16, int N, int M, int K, int HW, int pro, XkPlan *p)
     p->W = wgs <= 256 ? 8 : wgs <= 512 ? 4 : 2;
     while (p->W > ch)
         p->W /= 2;
+    // bf16: up to a number of 16 x 32 output tiles, beyond which conv_bf's 64-pixel tiles are the better
+    // ones, and not for contractions of one to three steps in the forward role (64 <- 96, 12x12, 512
+    // images, evaluation of a block 46.5 us there, 48.5 here).  conv_bf / here, 14x14: projection conv
+    // 112 <- 672, 128 images (5488 tiles) 25.8 / 22.8, 256 images 39.8 / 43.2; 320 <- 1152, 64 images (8232)
+    // 46.8 / 50.2; data gradient 112 <- 672, 128 images 33.8 / 26.3, 512 images (21952) 107.5 / 113.7,
+    // 20x20, 128 images (11200) 57.5 / 62.7.
+    if (bf16 && (wgs * p->rt > (pro == PRO_BNSWISH_GATE ? 6400 : 10000) || (pro == PRO_BNSWISH_GATE && ch < 4)))
+        return false;
     const int nimg = 31 / HW + 2; // images a chunk can touch
     const size_t coef = pro == PRO_BNBWD ? (size_t)16 * 32 * ch
                         : pro == PRO_BNSWISH_GATE ? (size_t)(2 + nimg) * 4 * 32 * ch

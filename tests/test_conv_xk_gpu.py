@@ -37,6 +37,12 @@ SHAPES = {
     "se_ragged": _s(N=3, Cin=42, Cexp=250, Cse=11, Cout=42, H=5, W=5),
     "many_workgroups": _s(N=40, Cin=40, Cexp=160, Cout=40, H=24, W=24),
     "relu6": _s(N=3, H=7, W=7, activation="relu6", has_se=False, Cse=1),
+    # bf16: the largest forward launch (2133 chunks of three row tiles), the next one and a contraction too
+    # short (both conv_bf)
+    "bf16_6399_tiles": _s(N=79, Cin=16, Cexp=128, Cse=8, Cout=40, H=24, W=36, dtype="bf16", residual=False),
+    "bf16_6432_tiles": _s(N=67, Cin=16, Cexp=128, Cse=8, Cout=40, H=32, W=32, dtype="bf16", residual=False),
+    "bf16_short": _s(N=6, Cin=96, Cexp=96, Cse=8, Cout=40, H=12, W=12, dtype="bf16", residual=False,
+                     has_expand=False),
     "bf16": _s(N=16, Cin=64, Cexp=384, Cse=16, Cout=96, H=10, W=10, dtype="bf16", residual=False),
 }
 
