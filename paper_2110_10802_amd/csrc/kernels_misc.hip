@@ -344,11 +344,14 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
         fetch_w1(u);
     // W2: four threads per channel, thread t%4 takes the pieces t%4, t%4 + 4, ...
     const int part = tid & 3, cend = min(C, (sl + 1) * slice);
-    const int c = sl * slice + (tid >> 2); // (a slice has at most 256 channels)
+    int c = sl * slice + (tid >> 2);
+    const auto fetch_w2 = [&](int ch) __attribute__((always_inline)) {
 #pragma unroll
-    for (int v = 0; v < JR; ++v)
-        w2v[v] = *reinterpret_cast<const f32x4u *>(w2 + (size_t)min(c, C - 1) * Cse +
-                                                   min(4 * (part + 4 * v), Cse - 4));
+        for (int v = 0; v < JR; ++v)
+            w2v[v] = *reinterpret_cast<const f32x4u *>(w2 + (size_t)min(ch, C - 1) * Cse +
+                                                       min(4 * (part + 4 * v), Cse - 4));
+    };
+    fetch_w2(c);
     __builtin_amdgcn_sched_barrier(0);
     const auto own = [&](int i, int e) { return min(4 * (lane + 64 * i), C - 4) + e >= 4 * (lane + 64 * i); };
 #pragma unroll
@@ -378,7 +381,7 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
             __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
-    if (c < cend) {
+    for (; c < cend; c += 256) { // (once, unless the slice is the whole of a wide block)
         float acc = 0.f;
 #pragma unroll
         for (int v = 0; v < JR; ++v) {
@@ -387,6 +390,8 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
             for (int e = 0; e < 4; ++e)
                 acc = fmaf(at + e >= want ? w2v[v][e] : 0.f, at + e >= want ? rs[at + e] : 0.f, acc);
         }
+        if (c + 256 < sl * slice + slice) // (uniform over the workgroup but for the last round)
+            fetch_w2(c + 256);
         acc += __shfl_xor(acc, 1, kWave);
         acc += __shfl_xor(acc, 2, kWave);
         if (part == 0)
@@ -415,9 +420,10 @@ hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, const float *w1,
 {
     // (128 channels and more: 240 -> 10, batch 64, 7.8 -> 4.8 us; 96 -> 4, two images, no faster)
     if (C >= 128 && C <= 2048 && Cse >= 4 && Cse <= 64) {
-        // channel slices per image: at most 256 channels each (a thread then owns one), about 256
-        // workgroups
-        const int G = std::max((C + 255) / 256, std::min(8, std::min(256 / N, (C + 63) / 64)));
+        // channel slices per image: as many as leave one workgroup per compute unit, since every one of
+        // them computes the whole of q (1152 -> 48: 64 images, four slices 9.0 us, five 12.8; 128, two
+        // 10.0, five 17.1; 512, one 20.5, five 49.5)
+        const int G = std::max(1, std::min(8, std::min(256 / N, (C + 63) / 64)));
         const int slice = (C + G - 1) / G, ci = (C + 255) / 256, jr = (Cse + 15) / 16;
 #define MBK_CASE(CI_, JR_)                                                                        \
     if (ci <= CI_ && jr == JR_) {                                                                 \

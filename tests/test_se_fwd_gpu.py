@@ -37,3 +37,20 @@ def test_gate_matches_oracle(C, Cse, what):
         ref = orc.mbconv_forward_eval(s, t)
     assert np.all(np.isfinite(ref))
     assert rel_err(got, ref) <= TOL["f32"]["fwd"]
+
+
+@pytest.mark.parametrize("N,C,Cse", [(33, 300, 8), (86, 514, 12), (129, 1030, 7), (300, 640, 20)])
+def test_slices_of_any_batch(N, C, Cse):
+    """Five, two, one and one slices of an image's channels; more than 256 channels go in rounds."""
+    import torch
+    from paper_2110_10802_amd.harness import DeviceBlock, to_numpy
+
+    s = BlockShape(N=N, Cin=C, H=1, W=1, Cexp=C, Cse=Cse, Cout=16, k=3, stride=1, has_expand=False)
+    t = make_block_inputs(s, seed=N)
+    for i, c in ((2, s.Cexp), (3, s.Cout)):
+        t[f"bn{i}_mean"], t[f"bn{i}_var"] = np.zeros(c, np.float32), np.ones(c, np.float32)
+    print(f"[se] {N} x {C}->{Cse}", flush=True)
+    blk = DeviceBlock(s, t)
+    got = to_numpy(blk.forward_eval(blk.to_device(t["x"])))
+    torch.cuda.synchronize()
+    assert rel_err(got, orc.mbconv_forward_eval(s, t)) <= TOL["f32"]["fwd"]
