@@ -36,6 +36,8 @@ SHAPES = {
     # pass for the last time, and where it is a launch
     "bn3_inside": _s(N=2032, Cin=16, H=2, W=2, Cexp=32, Cse=4, Cout=40, residual=False),
     "bn3_launch": _s(N=2064, Cin=16, H=2, W=2, Cexp=32, Cse=4, Cout=40, residual=False),
+    # more partial sums than the finalise launch adds in one round, no multiple of it
+    "many_partials": _s(N=2064, Cin=16, H=4, W=5, Cexp=32, Cse=4, Cout=40, residual=False),
     # the same for BN2 and the pool (images in pairs of groups); weight images written by either
     "bn2_inside": _s(N=96, Cin=32, H=2, W=2, Cexp=1024, Cse=8, Cout=48, residual=False),
     "bn2_launch": _s(N=97, Cin=32, H=2, W=2, Cexp=1024, Cse=8, Cout=48, residual=False),
