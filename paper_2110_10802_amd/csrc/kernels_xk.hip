@@ -511,7 +511,10 @@ static bool xk_plan(bool bf16, int N, int M, int K, int HW, int pro, XkPlan *p)
     // workgroups) with eight 18.4 us, four 20.6, two 31; 672 -> 112 (392) with four 21, two 33, eight
     // 26; 192 -> 1152 (882) with two 21.7, four 24.
     const long long wgs = (long long)p->chunks * p->slabs;
-    p->W = wgs <= 256 ? 8 : wgs <= 512 ? 4 : 2;
+    // (up to three steps, which two wavefronts share unevenly or hardly at all: one, once there are four
+    // workgroups per compute unit; 64 <- 96, 28x28, 512 images 86 us with two, 68 with one, 32 images 11.7
+    // and 12.9)
+    p->W = wgs <= 256 ? 8 : wgs <= 512 ? 4 : ch <= 3 && wgs > 1024 ? 1 : 2;
     while (p->W > ch)
         p->W /= 2;
     // bf16: up to a number of 16 x 32 output tiles, beyond which conv_bf's 64-pixel tiles are the better

@@ -36,6 +36,8 @@ SHAPES = {
     "stride2_into_7x7": _s(N=3, Cin=48, Cexp=288, Cout=64, H=14, W=14, stride=2, residual=False),
     "se_ragged": _s(N=3, Cin=42, Cexp=250, Cse=11, Cout=42, H=5, W=5),
     "many_workgroups": _s(N=40, Cin=40, Cexp=160, Cout=40, H=24, W=24),
+    # a short contraction on many pixels: one wavefront, all of the steps
+    "one_wavefront": _s(N=57, Cin=40, Cexp=80, Cse=10, Cout=40, H=24, W=25),
     "relu6": _s(N=3, H=7, W=7, activation="relu6", has_se=False, Cse=1),
     # bf16: the largest forward launch (2133 chunks of three row tiles), the next one and a contraction too
     # short (both conv_bf)
