@@ -35,16 +35,16 @@ hipError_t launch_dw2_fwd(bool bf16, const DwShape &s, const void *e, const floa
 hipError_t launch_dw2_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st);
 // kernels_dwr.hip
 bool dwr_supported(const DwShape &s);
-int dwr_num_partials(const DwShape &s);
+int dwr_num_partials(bool bf16, const DwShape &s, bool bwd);
 hipError_t launch_dwr_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
                           const void *w_dw, void *d, float *psum, float *psq, const BnFin *fin,
                           hipStream_t st);
 hipError_t launch_dwr_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st);
 
-int dw_num_partials(const DwShape &s, bool stores_a1)
+int dw_num_partials(bool bf16, const DwShape &s, bool stores_a1, bool bwd)
 {
     if (!stores_a1 && !dw4_supported(s) && dwr_supported(s))
-        return dwr_num_partials(s);
+        return dwr_num_partials(bf16, s, bwd);
     return s.N;
 }
 

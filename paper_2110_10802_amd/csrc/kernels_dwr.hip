@@ -490,7 +490,7 @@ bool dwr_supported(const DwShape &s)
     return s.s == 1 && (s.k == 3 || s.k == 5) && s.Ho == s.H && s.Wo == s.W && s.H * w4 <= 64;
 }
 
-static DwrArgs dwr_args(const DwShape &s)
+static DwrArgs dwr_args(bool bf16, const DwShape &s, bool bwd)
 {
     DwrArgs a = {};
     a.N = s.N;
@@ -503,10 +503,16 @@ static DwrArgs dwr_args(const DwShape &s)
     a.PW = 64 / a.runs;
     if (a.PW > s.N)
         a.PW = s.N;
-    // Image ranges: about 4096 wavefronts (four on each of the 1024 SIMDs), at least four pipeline steps
-    // each.  Of the two nearest numbers the one whose busiest SIMD has less to do, counted in steps, a
-    // wavefront's setup and reductions as one and a half (672 channels: 4704 wavefronts leave every
-    // second SIMD with a fifth one, six ranges fit; 1152 channels of 7x7: four short ranges beat three).
+    // Image ranges: at least 4096 wavefronts (four on each of the 1024 SIMDs), at least four pipeline steps
+    // each.  The 5x5 backward kernel has registers for four wavefronts on a SIMD: a fifth waits for the
+    // first ones to end, so the next lower number is taken if that leaves the busiest SIMD less to do,
+    // counted in steps, a wavefront's setup and reductions as one and a half (bf16, 672 channels of 7x7,
+    // 1024 images: 4704 wavefronts 307 us, 4032 217; fp32, 480 of 14x14, 256: 102 and 91).  The other
+    // kernels hold more, and for bf16 every one of them counts (960 of 7x7, 1024 images: forward 118 us
+    // with 4800 wavefronts, 131 with 3840, 3x3 backward 312 and 349); in fp32, nearer to what memory
+    // delivers, the 3x3 ones gain from fitting as well (480 of 14x14, 128 images 25.1 -> 23.7 and 43.0 ->
+    // 39.0), the 5x5 forward one does not for large tensors (512 images 133 -> 142).  fp32: by five per
+    // cent at least (960 of 7x7, 1024 images, three per cent less to do: 183 -> 196 and 305 -> 332).
     const int cap = s.N / (4 * a.PW) > 1 ? s.N / (4 * a.PW) : 1;
     const auto pick = [&](int nseg) {
         nseg = nseg > cap ? cap : nseg < 1 ? 1 : nseg;
@@ -517,15 +523,18 @@ static DwrArgs dwr_args(const DwShape &s)
     };
     const int many = (4096 + s.C - 1) / s.C, few = 4096 / s.C;
     const long long cost_many = pick(many);
-    if (pick(few) >= cost_many)
-        pick(many);
+    if (s.k == 5 ? bwd : !bf16) {
+        const long long cost_few = pick(few);
+        if (cost_few >= cost_many || (!bf16 && 21 * cost_few >= 20 * cost_many))
+            pick(many);
+    }
     a.divRuns = make_div((uint32_t)a.runs);
     a.divW4 = make_div((uint32_t)a.W4);
     a.divNseg = make_div((uint32_t)a.nseg);
     return a;
 }
 
-int dwr_num_partials(const DwShape &s) { return dwr_args(s).nseg; }
+int dwr_num_partials(bool bf16, const DwShape &s, bool bwd) { return dwr_args(bf16, s, bwd).nseg; }
 
 static size_t dwr_lds(const DwrArgs &a, int k, int tiles)
 {
@@ -563,7 +572,7 @@ hipError_t launch_dwr_fwd(bool bf16, const DwShape &s, const void *e, const floa
                           const void *w_dw, void *d, float *psum, float *psq, const BnFin *fin,
                           hipStream_t st)
 {
-    DwrArgs a = dwr_args(s);
+    DwrArgs a = dwr_args(bf16, s, false);
     if (fin)
         a.fin = *fin;
     a.e = e;
@@ -587,7 +596,7 @@ hipError_t launch_dwr_fwd(bool bf16, const DwShape &s, const void *e, const floa
 
 hipError_t launch_dwr_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st)
 {
-    DwrArgs a = dwr_args(h.s);
+    DwrArgs a = dwr_args(bf16, h.s, true);
     a.e = h.e;
     a.bn1 = h.bn1;
     a.w = h.w_dw;

@@ -39,7 +39,7 @@ struct Plan {
     size_t o_splitk; // partial tiles of a split 1x1 convolution
     size_t scratch_bytes;
     int NT1, NT5; // q-tiles of the expansion / projection conv
-    int NPdw;     // partial results per channel of the depthwise kernels
+    int NPdw, NPdwB; // partial results per channel of the depthwise kernels, forward and backward
 };
 
 mbconv_status check_desc(const mbconv_desc *d)
@@ -128,7 +128,8 @@ Plan make_plan(const mbconv_desc *d)
     P.nP = (size_t)P.N * P.Cout * P.HWo;
     {
         const DwShape ds = {P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p};
-        P.NPdw = dw_num_partials(ds, P.store && P.expand);
+        P.NPdw = dw_num_partials(P.bf16, ds, P.store && P.expand, false);
+        P.NPdwB = dw_num_partials(P.bf16, ds, P.store && P.expand, true);
     }
     P.NT1 = conv1x1_num_partials(P.bf16, P.N, P.Cexp, P.Cin, P.HW, false, PRO_NONE, EPI_STATS);
     P.NT5 = conv1x1_num_partials(P.bf16, P.N, P.Cout, P.Cexp, P.HWo, d->policy == MBCONV_STORE,
@@ -603,11 +604,11 @@ mbconv_status backward_impl(const mbconv_desc *desc, const mbconv_params *prm, c
         if (P.expand) {
             // one launch: filter-gradient partials and BN1's backward finalisation
             MBK_STEP(MBCONV_STEP_DW_WGRAD_REDUCE,
-                     launch_dw_bwd_finalize(a.pdw, P.Cexp, P.NPdw, P.k * P.k, gr->w_dw, (double)P.N * P.HW, pa,
+                     launch_dw_bwd_finalize(a.pdw, P.Cexp, P.NPdwB, P.k * P.k, gr->w_dw, (double)P.N * P.HW, pa,
                                             pb, prm->bn1_gamma, bn1, gr->bn1_gamma, gr->bn1_beta,
                                             at<float>(scratch, P.o_coef1), st));
         } else {
-            MBK_STEP(MBCONV_STEP_DW_WGRAD_REDUCE, launch_reduce_planes(a.pdw, P.Cexp, P.NPdw, P.k * P.k, gr->w_dw, st));
+            MBK_STEP(MBCONV_STEP_DW_WGRAD_REDUCE, launch_reduce_planes(a.pdw, P.Cexp, P.NPdwB, P.k * P.k, gr->w_dw, st));
         }
     }
     if (P.expand) {
