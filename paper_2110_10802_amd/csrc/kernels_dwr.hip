@@ -193,14 +193,16 @@ __device__ __forceinline__ void wave_lds_sync()
 }
 
 // A value that all lanes of the wavefront share (its channel's filter and coefficients) goes to a
-// scalar register in the backward kernel: the filter alone would take 25 of the vector registers
-// that decide how many wavefronts a SIMD holds (5x5: 142 registers, three wavefronts; 104, four.  128
-// images of 672 14x14 planes in bf16, with the image ranges of dwr_args: 79 us before, 71 now).  The
-// forward kernel has room for its filter: with the 5x5 one in scalar registers it took 42 us instead
-// of 39, with the 3x3 one 0.5 us less of 15.6.
+// scalar register where that pays (UNIFORM): in the 5x5 backward kernel, whose filter alone would take 25
+// of the vector registers that decide how many wavefronts a SIMD holds (142 registers, three wavefronts;
+// 104, four.  128 images of 672 14x14 planes in bf16, with the image ranges of dwr_args: 79 us before,
+// 71 now), and in the 3x3 ones in fp32 (480 of 14x14, 1024 images: forward 256 us without, 202 with).  The
+// 5x5 forward kernel took 42 us instead of 39 with it, the 3x3 ones in bf16 174 instead of 171 and 295
+// instead of 285 (480 of 14x14, 1024 images).
+template <bool UNIFORM>
 __device__ __forceinline__ float uniform(float v)
 {
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+    return UNIFORM ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))) : v;
 }
 
 // Lane geometry shared by forward and backward.
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(256) void dwr_fwd_kernel(DwrArgs a)
     const int H = a.H, W = a.W, WP = a.WP;
     const int tileElems = (H + 2 * P) * WP;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const DwrLane L = dwr_lane<K == 3>(a);
+    const DwrLane L = dwr_lane<K == 3 && sizeof(T) == 4>(a);
     // per wavefront: two buffers of PW tiles
     float *mine = lds + wave * (2 * a.PW * tileElems);
     for (int i = lane; i < 2 * a.PW * tileElems / 4; i += 64)
@@ -345,7 +347,8 @@ __global__ __launch_bounds__(256) void dwr_bwd_kernel(DwrArgs a)
     const int H = a.H, W = a.W, WP = a.WP, C = a.C;
     const int tileElems = (H + 2 * P) * WP;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const DwrLane L = dwr_lane<true>(a);
+    constexpr bool U = K == 5 || sizeof(T) == 4;
+    const DwrLane L = dwr_lane<U>(a);
     // per wavefront: two buffers of PW dd tiles.  There is no a1 tile: the filter gradient
     // dW[u][v] = sum_p dd[p] * a1[p + (u,v) - P] is summed over q = p + (u,v) - P, which pairs each
     // lane's own a1 values (registers) with the dd window elements the input gradient reads anyway.
@@ -356,16 +359,16 @@ __global__ __launch_bounds__(256) void dwr_bwd_kernel(DwrArgs a)
     float wt[K * K];
 #pragma unroll
     for (int t = 0; t < K * K; ++t)
-        wt[t] = uniform(ld<T>((const T *)a.w, (size_t)L.c * K * K + t));
+        wt[t] = uniform<U>(ld<T>((const T *)a.w, (size_t)L.c * K * K + t));
     float scale1 = 1.f, shift1 = 0.f, mean1 = 0.f, rstd1 = 0.f;
     if (EXPAND) {
-        scale1 = uniform(a.bn1[L.c]);
-        shift1 = uniform(a.bn1[C + L.c]);
-        mean1 = uniform(a.bn1[2 * C + L.c]);
-        rstd1 = uniform(a.bn1[3 * C + L.c]);
+        scale1 = uniform<U>(a.bn1[L.c]);
+        shift1 = uniform<U>(a.bn1[C + L.c]);
+        mean1 = uniform<U>(a.bn1[2 * C + L.c]);
+        rstd1 = uniform<U>(a.bn1[3 * C + L.c]);
     }
-    const float scale2 = uniform(a.bn2[L.c]), shift2 = uniform(a.bn2[C + L.c]);
-    const float c0 = uniform(a.coef2[L.c]), c1 = uniform(a.coef2[C + L.c]), c2 = uniform(a.coef2[2 * C + L.c]);
+    const float scale2 = uniform<U>(a.bn2[L.c]), shift2 = uniform<U>(a.bn2[C + L.c]);
+    const float c0 = uniform<U>(a.coef2[L.c]), c1 = uniform<U>(a.coef2[C + L.c]), c2 = uniform<U>(a.coef2[2 * C + L.c]);
     const size_t hw = (size_t)H * W;
     const int off = L.h * W + L.x0;
 
