@@ -105,11 +105,16 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 template <int NV, int TPR, bool RAG>
 struct RowRegs {
     float v[NV][4];
-    static __device__ __forceinline__ int start(int cols, int t, int j) { return min(4 * (t + TPR * j), cols - 4); }
+    // (row_nv takes the smallest form that holds the row: the first half of the vectors never reach its end)
+    static __device__ __forceinline__ int start(int cols, int t, int j)
+    {
+        const int c = 4 * (t + TPR * j);
+        return j < NV / 2 ? c : min(c, cols - 4);
+    }
     static __device__ __forceinline__ bool own(int cols, int t, int j, int k)
     {
         const int c = 4 * (t + TPR * j);
-        return c < cols && (!RAG || min(c, cols - 4) + k >= c);
+        return j < NV / 2 || (c < cols && (!RAG || min(c, cols - 4) + k >= c));
     }
     __device__ __forceinline__ void load(const float *row, int cols, int t)
     {
@@ -125,7 +130,7 @@ struct RowRegs {
     {
 #pragma unroll
         for (int j = 0; j < NV; ++j)
-            if (4 * (t + TPR * j) < cols)
+            if (j < NV / 2 || 4 * (t + TPR * j) < cols)
                 *reinterpret_cast<f32x4u *>(row + start(cols, t, j)) = (f32x4u){v[j][0], v[j][1], v[j][2], v[j][3]};
     }
 };
@@ -239,9 +244,15 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const float *__restr
     if (AHEAD && first < rows)
         fetch(first);
     for (int r = first; r < rows; r += step) {
-        if (!AHEAD)
-            fetch(r);
-        RowRegs<NV, TPR, RAG> a = na, d = nd;
+        RowRegs<NV, TPR, RAG> a, d;
+        if (AHEAD) {
+            a = na;
+            d = nd;
+        } else {
+            a.load(x + (size_t)r * cols, cols, t);
+            d.load(dy + (size_t)r * cols, cols, t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         const float mu = mean[r], rs = rstd[r];
         if (AHEAD)
             fetch(min(r + step, rows - 1)); // (past the end the last row again, never used)
@@ -295,13 +306,23 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const float *__restr
                 part[1][grp][c] = ab.v[j][k];
             }
     __syncthreads();
-    for (int i = threadIdx.x; i < 2 * cols; i += 256) {
-        const int w = i >= cols, c = i - w * cols;
+    const auto total = [&](int w, int c) {
         float s = 0.f;
 #pragma unroll
         for (int u = 0; u < G; u += 4)
             s += (part[w][u][c % GC] + part[w][(u + 1) % G][c % GC]) + (part[w][(u + 2) % G][c % GC] + part[w][(u + 3) % G][c % GC]);
-        (w ? pbeta : pgamma)[(size_t)blockIdx.x * cols + c] = s;
+        return s;
+    };
+    if (TPR == 16) { // at most 128 columns
+        if ((int)threadIdx.x < 2 * cols) {
+            const int w = (int)threadIdx.x >= cols, c = threadIdx.x - w * cols;
+            (w ? pbeta : pgamma)[(size_t)blockIdx.x * cols + c] = total(w, c);
+        }
+        return;
+    }
+    for (int c = threadIdx.x; c < cols; c += 256) {
+        pgamma[(size_t)blockIdx.x * cols + c] = total(0, c);
+        pbeta[(size_t)blockIdx.x * cols + c] = total(1, c);
     }
 }
 
