@@ -30,8 +30,7 @@ SHAPES = {
     "slab_8": _s(N=3, Cin=40, Cexp=240, Cout=128, H=14, W=14, residual=False),
     "slab_7": _s(N=70, Cin=56, Cexp=224, Cout=112, H=12, W=16, residual=False),
     "slab_5": _s(N=41, Cin=80, Cexp=320, Cout=320, H=9, W=9, residual=False),
-    # no expansion conv; a stride into an odd plane (the two weight gradients of different planes in one
-    # launch); squeezed channels that are no multiple of four
+    # no expansion conv; a stride from an even into an odd plane; squeezed channels that are no multiple of four
     "noexpand": _s(Cin=72, Cexp=72, Cse=7, Cout=48, has_expand=False, residual=False),
     "stride2_into_7x7": _s(N=3, Cin=48, Cexp=288, Cout=64, H=14, W=14, stride=2, residual=False),
     "se_ragged": _s(N=3, Cin=42, Cexp=250, Cse=11, Cout=42, H=5, W=5),
