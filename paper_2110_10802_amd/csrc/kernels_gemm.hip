@@ -645,7 +645,8 @@ static hipError_t wgrad_dispatch(const WgradArgs &a, int pu, int pv, dim3 grid, 
 // *ra and *rb for the caller to launch.  hipErrorNotSupported (nothing was launched) unless
 // wgrad1x1_pair_supported holds.
 // 1: both are shapes of the split-operand kernel; 2: both go to the 64 x 64-tile kernel of
-// kernels_big.hip with planes that are not a multiple of four pixels (the 7x7 stages); 0: no pair
+// kernels_big.hip with planes that are not a multiple of four pixels (the 7x7 stages); 0: no pair (also a
+// stride from a plane of the first kernel into one of the second, 14x14 -> 7x7)
 static int wgrad1x1_pair_kind(bool bf16, int N, int MaA, int MbA, int HWA, int MaB, int MbB, int HWB)
 {
     if (!MBK_X3PAIR)

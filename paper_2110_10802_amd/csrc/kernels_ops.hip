@@ -98,8 +98,8 @@ __global__ __launch_bounds__(256) void mish_kernel(const float *__restrict__ x, 
 // whose length is no multiple of four start at any 4-byte boundary (the 16-byte accesses of this chip
 // may) and end in a partial vector: it is moved back to the row's last four columns, `own` tells the
 // columns that no other thread covers, and both threads write the same values to the others.  Softmax
-// of 48768 x 381, forward and backward: 63.5 us (5.9 TB/s); with a workgroup per row, the row in LDS and
-// 4-byte accesses 112.6.  4000 x 8192: 112 us against 270.  The 16 lanes: 65536 x 45 10.9 us against 21.6
+// of 48768 x 381, forward and backward: 64.9 us (5.7 TB/s); with a workgroup per row, the row in LDS and
+// 4-byte accesses 108.0.  4000 x 8192: 112 us against 270.  The 16 lanes: 65536 x 45 10.9 us against 21.6
 // with a wavefront per row.  RAG: cols % 4 != 0 (the masks cost 4096 x 1024 five per cent forward).
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 template <int NV, int TPR, bool RAG>

@@ -198,7 +198,7 @@ struct X3RowData {
 // of 128 and of VB rows)
 // RAG: the plane size is no multiple of four.  The contraction runs over runs of four pixels, image by
 // image; the last run of an image starts at HW - 4 and its pixels that the run before has are masked, so
-// a 7x7 plane takes 13 runs (52 of its 49 pixels), every access stays 16 bytes wide (4-byte aligned)
+// a 15x15 plane takes 57 runs (228 for its 225 pixels), every access stays 16 bytes wide (4-byte aligned)
 // inside its plane, and both operands see the same order.
 // These planes were the fp32 matrix cores' before, whose sums over many images are closer than those of
 // a single accumulator here (the bf16 MFMA truncates a small addend to a large accumulator), so the small
@@ -374,9 +374,10 @@ bool x3_wgrad_plan(int Ma, int Mb, int N, int HW, int *splits)
     const long long Q = (long long)N * HW;
     // (a side of at most 32 channels belongs to the fused backward kernels of kernels_wave.hip,
     // which size their partial tiles by the plan of that file)
-    // Planes of at most 64 pixels that are no multiple of four (7x7) stay on the fp32 matrix cores:
-    // callers of mbconv_step_engine count on that answer for them.  It is not the faster choice (64 x 7x7,
-    // 192 -> 1152 -> 320: 93 us for the pair there, 51 here).
+    // Planes of at most 64 pixels that are no multiple of four (7x7) stay on the fp32 matrix cores, the
+    // engine that mbconv_step_engine has answered for them so far.  Neither speed nor accuracy asks for
+    // it (64 x 7x7, 192 -> 1152 -> 320: 93 us for the pair there, 51 here; error against 64 bits 3.9e-7 and
+    // 4.9e-7 there, 2.7e-7 and 3.5e-7 here).
     if (HW % 4 != 0 && HW <= 64)
         return false;
     if (Q >= (1ll << 31) || (long long)std::max(Ma, Mb) * HW >= (1ll << 31) || HW < 4 || std::min(Ma, Mb) <= 32 || std::max(Ma, Mb) < 64)
@@ -411,6 +412,10 @@ static X3Operand to_x3(const Operand &o)
 
 // Arguments, grid and kernel form (0..5, see wgrad_x3_variant) of one weight gradient.
 // rag: the launch's kernel is the form for planes that are no multiple of four (either one's of a pair).
+// The other one's plane then goes through 64-row tiles too, in the splits planned for 128-row ones: up
+// to 512 workgroups, which measured as fast as fewer splits (18x18 -> 9x9, 64 images, 48 -> 288 -> 80:
+// backward 94.5 / 94.0 us) or faster (192 -> 1152 -> 320, 32 images 219 / 230), and faster than two
+// launches (100 and 232) but where both are long (34x34 -> 17x17, 64 images, 112 -> 448 -> 192: 461, 448).
 static bool x3_wgrad_setup(bool rag, int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
                            float *partial, X3WgradArgs *out, unsigned *grid, int *variant, int *splits_out)
 {
@@ -928,7 +933,7 @@ __global__ __launch_bounds__(256, 2) void conv_xw_kernel(X3WArgs a)
         }
     }
     // the lane's eight contraction rows of step s start at row 32s + 8g, clamped to the last
-    // group of eight (K % 8 == 0; the weight image is zero past K, the values read are finite)
+    // group of eight (K % 8 == 0; the slab is zero past K)
     uint32_t vrow[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s)
