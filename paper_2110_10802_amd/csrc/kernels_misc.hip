@@ -324,7 +324,7 @@ __global__ __launch_bounds__(256) void se_fwd_kernel(int C, int Cse, const float
 // (16*CI bytes per lane and row), the thread's part of its channel's row of W2 - is requested before
 // the first one is used.  Every workgroup of an image recomputes the whole of q, which keeps the
 // kernel free of a grid-wide dependency.  (One image: 480 -> 20 channels 4.1 us, 1152 -> 48 6.3; with
-// 256 threads and 16 rows of W1 at a time 6.6 and 11.  Batch 64: 4.2 and 11.4 against 4.7 and 12.3.
+// 256 threads and 16 rows of W1 at a time 6.6 and 11.  Batch 64: 4.7 and 8.1 against 4.7 and 12.3.
 // The same form of the backward kernel measured no faster, 6.8 and 11.4 against 6.8 and 11, and is not
 // used.)
 // Rows whose length is no multiple of four are read in pieces of four that are clamped to the row's
