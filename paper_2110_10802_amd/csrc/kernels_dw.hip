@@ -17,6 +17,7 @@
 #include "mbconv_launch.h"
 #include "mbconv_bnfin.h"
 #include "mbconv_x3.h"
+#include "mbconv_eval.h"
 
 #include <algorithm>
 
@@ -26,19 +27,20 @@ namespace mbk {
 bool dw4_supported(const DwShape &s);
 hipError_t launch_dw4_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
                           const void *w_dw, void *d, float *psum, float *psq, const BnFin *fin,
-                          hipStream_t st);
+                          const DwEval *ev, hipStream_t st);
 hipError_t launch_dw4_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st);
 // kernels_dw2.hip
 bool dw2_supported(const DwShape &s);
 hipError_t launch_dw2_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
-                          const void *w_dw, void *d, float *psum, float *psq, hipStream_t st);
+                          const void *w_dw, void *d, float *psum, float *psq, const DwEval *ev,
+                          hipStream_t st);
 hipError_t launch_dw2_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st);
 // kernels_dwr.hip
 bool dwr_supported(const DwShape &s);
 int dwr_num_partials(bool bf16, const DwShape &s, bool bwd);
 hipError_t launch_dwr_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
                           const void *w_dw, void *d, float *psum, float *psq, const BnFin *fin,
-                          hipStream_t st);
+                          const DwEval *ev, hipStream_t st);
 hipError_t launch_dwr_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st);
 
 int dw_num_partials(bool bf16, const DwShape &s, bool stores_a1, bool bwd)
@@ -103,12 +105,18 @@ struct DwFwdDev {
     void *a1_store;
 };
 
-template <typename T, int K, int S, int TPP>
-__global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw_fwd_kernel(DwFwdDev a)
+template <typename T, int K, int S, int TPP, typename EVT>
+__global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw_fwd_kernel(DwFwdDev a, EVT ev)
 {
     constexpr int P = (K - 1) / 2;
     constexpr int BLOCK = TPP > 256 ? TPP : 256;
     constexpr int PPB = BLOCK / TPP;
+    if constexpr (EVT::kEval) {
+        if ((int)blockIdx.x >= ev.main) {
+            dw_eval_extra(ev, (int)blockIdx.x - ev.main, BLOCK);
+            return;
+        }
+    }
     extern __shared__ float lds[];
     const int H = a.s.H, W = a.s.W, Ho = a.s.Ho, Wo = a.s.Wo, C = a.s.C, N = a.s.N;
     const int Hp = H + 2 * P, Wp = W + 2 * P;
@@ -120,11 +128,19 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw_fwd_kernel(DwFwdDev 
     float w[K * K];
     float scale = 1.f, shift = 0.f;
     const bool bn = a.bn1 != nullptr;
+    BnEvalCoef k2 = {1.f, 0.f, 0.f, 1.f}; // evaluation mode
     if (pl.active) {
 #pragma unroll
         for (int t = 0; t < K * K; ++t)
             w[t] = ld<T>((const T *)a.w, (size_t)pl.c * K * K + t);
-        if (bn) {
+        if constexpr (EVT::kEval) {
+            k2 = bn_eval_coef(bn_eval_issue(ev.bn2, pl.c), ev.eps);
+            if (bn) {
+                const BnEvalCoef k1 = bn_eval_coef(bn_eval_issue(ev.bn1, pl.c), ev.eps);
+                scale = k1.scale;
+                shift = k1.shift;
+            }
+        } else if (bn) {
             scale = a.bn1[pl.c];
             shift = a.bn1[C + pl.c];
         }
@@ -160,14 +176,24 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw_fwd_kernel(DwFwdDev 
                     acc = fmaf(w[u * K + v], t0[u * Wp + v], acc);
             st<T>((T *)a.d, obase + idx, acc);
             const float sv = as_stored<T>(acc);
-            acc2[0] += sv;
-            acc2[1] += sv * sv;
+            if constexpr (EVT::kEval) {
+                if (ev.z)
+                    acc2[0] += actf(fmaf(sv, k2.scale, k2.shift));
+            } else {
+                acc2[0] += sv;
+                acc2[1] += sv * sv;
+            }
         }
     }
     group_sum<2, TPP>(acc2, red);
     if (pl.active && lt == 0) {
-        a.psum[(size_t)pl.c * N + pl.n] = acc2[0];
-        a.psq[(size_t)pl.c * N + pl.n] = acc2[1];
+        if constexpr (EVT::kEval) {
+            if (ev.z)
+                ev.z[pl.plane] = acc2[0] * ev.inv_hw;
+        } else {
+            a.psum[(size_t)pl.c * N + pl.n] = acc2[0];
+            a.psq[(size_t)pl.c * N + pl.n] = acc2[1];
+        }
     }
 }
 
@@ -180,8 +206,8 @@ size_t dw_fwd_lds_bytes(const DwShape &s)
     return sizeof(float) * ((size_t)ppb * (s.H + 2 * p) * (s.W + 2 * p) + (block / 64) * 2);
 }
 
-template <typename T, int K, int S>
-static hipError_t dw_fwd_tpp(const DwFwdDev &a, hipStream_t st)
+template <typename T, int K, int S, typename EVT>
+static hipError_t dw_fwd_tpp(const DwFwdDev &a, hipStream_t st, EVT ev)
 {
     const DwShape &s = a.s;
     const int tpp = pick_tpp(s.H * s.W);
@@ -190,13 +216,14 @@ static hipError_t dw_fwd_tpp(const DwFwdDev &a, hipStream_t st)
 #define MBK_LAUNCH(TPP)                                                                           \
     {                                                                                             \
         constexpr int BLOCK = TPP > 256 ? TPP : 256;                                              \
-        auto kern = dw_fwd_kernel<T, K, S, TPP>;                                                  \
+        auto kern = dw_fwd_kernel<T, K, S, TPP, EVT>;                                             \
         hipError_t e = hipFuncSetAttribute((const void *)kern,                                    \
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
         if (e != hipSuccess)                                                                      \
             return e;                                                                             \
         const unsigned grid = (unsigned)((planes + BLOCK / TPP - 1) / (BLOCK / TPP));             \
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), lds, st, a);                            \
+        const unsigned extra = dw_eval_extra_blocks(ev, grid, BLOCK);                             \
+        hipLaunchKernelGGL(kern, dim3(grid + extra), dim3(BLOCK), lds, st, a, ev);                \
         return hipGetLastError();                                                                 \
     }
     if (tpp == 64)
@@ -207,18 +234,18 @@ static hipError_t dw_fwd_tpp(const DwFwdDev &a, hipStream_t st)
 #undef MBK_LAUNCH
 }
 
-template <typename T>
-static hipError_t dw_fwd_ks(const DwFwdDev &a, hipStream_t st)
+template <typename T, typename EVT>
+static hipError_t dw_fwd_ks(const DwFwdDev &a, hipStream_t st, const EVT &ev)
 {
     const int k = a.s.k, s = a.s.s;
     if (k == 3 && s == 1)
-        return dw_fwd_tpp<T, 3, 1>(a, st);
+        return dw_fwd_tpp<T, 3, 1>(a, st, ev);
     if (k == 3 && s == 2)
-        return dw_fwd_tpp<T, 3, 2>(a, st);
+        return dw_fwd_tpp<T, 3, 2>(a, st, ev);
     if (k == 5 && s == 1)
-        return dw_fwd_tpp<T, 5, 1>(a, st);
+        return dw_fwd_tpp<T, 5, 1>(a, st, ev);
     if (k == 5 && s == 2)
-        return dw_fwd_tpp<T, 5, 2>(a, st);
+        return dw_fwd_tpp<T, 5, 2>(a, st, ev);
     return hipErrorInvalidValue;
 }
 
@@ -237,16 +264,16 @@ bool dw_fwd_finalizes_bn1(const DwShape &s, bool stores_a1)
 
 hipError_t launch_dw_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
                          const void *w_dw, void *d, float *psum, float *psq, void *a1_store,
-                         const BnFin *fin, hipStream_t st)
+                         const BnFin *fin, const DwEval *ev, hipStream_t st)
 {
     if (fin && !dw_fwd_finalizes_bn1(s, a1_store != nullptr))
         return hipErrorInvalidValue;
     if (!a1_store && dw4_supported(s))
-        return launch_dw4_fwd(bf16, s, e, bn1, w_dw, d, psum, psq, fin, st);
+        return launch_dw4_fwd(bf16, s, e, bn1, w_dw, d, psum, psq, fin, ev, st);
     if (!a1_store && dwr_supported(s))
-        return launch_dwr_fwd(bf16, s, e, bn1, w_dw, d, psum, psq, fin, st);
+        return launch_dwr_fwd(bf16, s, e, bn1, w_dw, d, psum, psq, fin, ev, st);
     if (!a1_store && dw2_supported(s))
-        return launch_dw2_fwd(bf16, s, e, bn1, w_dw, d, psum, psq, st);
+        return launch_dw2_fwd(bf16, s, e, bn1, w_dw, d, psum, psq, ev, st);
     DwFwdDev a;
     a.s = s;
     a.divC = make_div((uint32_t)s.C);
@@ -259,7 +286,9 @@ hipError_t launch_dw_fwd(bool bf16, const DwShape &s, const void *e, const float
     a.psum = psum;
     a.psq = psq;
     a.a1_store = a1_store;
-    return bf16 ? dw_fwd_ks<bf16_t>(a, st) : dw_fwd_ks<float>(a, st);
+    if (ev)
+        return bf16 ? dw_fwd_ks<bf16_t>(a, st, *ev) : dw_fwd_ks<float>(a, st, *ev);
+    return bf16 ? dw_fwd_ks<bf16_t>(a, st, DwTrain()) : dw_fwd_ks<float>(a, st, DwTrain());
 }
 
 // ---- backward ---------------------------------------------------------------------------------
@@ -706,7 +735,7 @@ __global__ __launch_bounds__(256) void pool_chan_kernel(PlaneArgs a, int rounds,
     constexpr int PPB = 256 / TPP;
     __shared__ float cf[4];
     if ((int)blockIdx.x < a.prep.tiles) {
-        x3_prep_tile(a.prep, blockIdx.x);
+        x3_prep_tile(a.prep, blockIdx.x, threadIdx.x);
         return;
     }
     // per: workgroups of a channel.  Neighbouring channels go to one XCD (blockIdx.x mod 8): their results

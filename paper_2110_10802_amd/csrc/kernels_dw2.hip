@@ -15,6 +15,7 @@
 // Partial sums per (channel, image); no atomics.
 #include "mbconv_dev.h"
 #include "mbconv_launch.h"
+#include "mbconv_eval.h"
 
 namespace mbk {
 
@@ -195,12 +196,18 @@ __device__ __forceinline__ void d2_window(const float *tile, int row, int WP, in
 }
 
 // ---- forward ---------------------------------------------------------------------------------
-template <typename T, int K, int TPP, bool EXPAND, int GVO, int GVI>
-__global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw2_fwd_kernel(Dw2Args a)
+template <typename T, int K, int TPP, bool EXPAND, int GVO, int GVI, typename EVT>
+__global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw2_fwd_kernel(Dw2Args a, EVT ev)
 {
     constexpr int P = (K - 1) / 2, NGI = 4;
     constexpr int BLOCK = TPP > 256 ? TPP : 256;
     constexpr int PPB = BLOCK / TPP;
+    if constexpr (EVT::kEval) {
+        if ((int)blockIdx.x >= ev.main) {
+            dw_eval_extra(ev, (int)blockIdx.x - ev.main, BLOCK);
+            return;
+        }
+    }
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int H = a.H, W = a.W, WP = a.WP;
     const int tileElems = (H + 2 * P) * WP;
@@ -212,9 +219,15 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw2_fwd_kernel(Dw2Args 
     const bool active = d2_plane<TPP>(a, plane, n, c);
 
     float wt[K * K];
+    BnEvalCoef k1 = {1.f, 0.f, 0.f, 1.f}, k2 = k1; // evaluation mode
     if (active) {
         float scale = 1.f, shift = 0.f;
-        if (EXPAND) {
+        BnEvalRegs er1, er2;
+        if constexpr (EVT::kEval) {
+            if (EXPAND)
+                er1 = bn_eval_issue(ev.bn1, c);
+            er2 = bn_eval_issue(ev.bn2, c);
+        } else if (EXPAND) {
             scale = a.bn1[c];
             shift = a.bn1[a.C + c];
         }
@@ -223,15 +236,22 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw2_fwd_kernel(Dw2Args 
             wt[t] = ld<T>((const T *)a.w, (size_t)c * K * K + t);
         d2_zero_border<TPP>(tile, H, P, P, 4 * a.W4, WP, lt);
         const size_t base = plane * (size_t)H * W;
-        float ev[NGI][4]; // all loads first, then the arithmetic (one memory round trip)
+        float raw[NGI][4]; // all loads first, then the arithmetic (one memory round trip)
 #pragma unroll
         for (int i = 0; i < NGI; ++i) {
             const int gidx = lt + TPP * i < a.inRuns ? lt + TPP * i : 0;
             const int h = (int)fdiv((uint32_t)gidx, a.divW4);
             const int x0 = 4 * (gidx - h * a.W4);
-            d2_in_load<T, GVI>((const T *)a.e, base + (size_t)h * W + x0, x0, W, ev[i]);
+            d2_in_load<T, GVI>((const T *)a.e, base + (size_t)h * W + x0, x0, W, raw[i]);
         }
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (EVT::kEval) {
+            if (EXPAND)
+                k1 = bn_eval_coef(er1, ev.eps);
+            k2 = bn_eval_coef(er2, ev.eps);
+            scale = k1.scale;
+            shift = k1.shift;
+        }
 #pragma unroll
         for (int i = 0; i < NGI; ++i) {
             const int gidx = lt + TPP * i;
@@ -243,7 +263,7 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw2_fwd_kernel(Dw2Args 
                 for (int r = 0; r < 4; ++r) {
                     // straight-line code for all four elements (a branch per element would run
                     // the four exp/rcp chains one after the other); whole runs need no mask
-                    const float t = EXPAND ? actf(fmaf(ev[i][r], scale, shift)) : ev[i][r];
+                    const float t = EXPAND ? actf(fmaf(raw[i][r], scale, shift)) : raw[i][r];
                     v[r] = GVI == 4 ? t : and_mask(t, x0 + r < W ? 0xffffffffu : 0u);
                 }
                 *reinterpret_cast<float4v *>(tile + (h + P) * WP + 4 + x0) =
@@ -272,15 +292,25 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw2_fwd_kernel(Dw2Args 
         for (int r = 0; r < 4; ++r) {
             if (GVO == 4 || j0 + r < a.Wo) {
                 const float sv = as_stored<T>(o[r]);
-                acc2[0] += sv;
-                acc2[1] = fmaf(sv, sv, acc2[1]);
+                if constexpr (EVT::kEval) {
+                    if (ev.z)
+                        acc2[0] += actf(fmaf(sv, k2.scale, k2.shift));
+                } else {
+                    acc2[0] += sv;
+                    acc2[1] = fmaf(sv, sv, acc2[1]);
+                }
             }
         }
     }
     group_sum<2, TPP>(acc2, red);
     if (active && lt == 0) {
-        a.psum[(size_t)c * a.N + n] = acc2[0];
-        a.psq[(size_t)c * a.N + n] = acc2[1];
+        if constexpr (EVT::kEval) {
+            if (ev.z)
+                ev.z[plane] = acc2[0] * ev.inv_hw;
+        } else {
+            a.psum[(size_t)c * a.N + n] = acc2[0];
+            a.psq[(size_t)c * a.N + n] = acc2[1];
+        }
     }
 }
 
@@ -527,8 +557,8 @@ static size_t dw2_lds(const Dw2Args &a, int k, int tpp, bool bwd)
     return sizeof(float) * (ppb * per + (size_t)(block / 64) * nv);
 }
 
-template <typename KERN>
-static hipError_t dw2_launch(KERN kern, const Dw2Args &a, int tpp, size_t lds, hipStream_t st)
+template <typename KERN, typename... EV>
+static hipError_t dw2_launch(KERN kern, const Dw2Args &a, int tpp, size_t lds, hipStream_t st, EV... ev)
 {
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
@@ -536,37 +566,56 @@ static hipError_t dw2_launch(KERN kern, const Dw2Args &a, int tpp, size_t lds, h
         return e;
     const int block = tpp > 256 ? tpp : 256, ppb = block / tpp;
     const size_t planes = (size_t)a.N * a.C;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((planes + ppb - 1) / ppb)), dim3(block), lds, st, a);
+    const unsigned grid = (unsigned)((planes + ppb - 1) / ppb);
+    const unsigned extra = (0u + ... + dw_eval_extra_blocks(ev, grid, block));
+    hipLaunchKernelGGL(kern, dim3(grid + extra), dim3(block), lds, st, a, ev...);
     return hipGetLastError();
 }
 
-#define MBK_DW2_TPP(KERNEL, T, K, EXP, GVO)                                                       \
+#define MBK_DW2_TPP(KERNEL, EXP, GVO, ...)                                                        \
     {                                                                                             \
         if (s.W % 4 != 0) /* ragged rows: only the small planes of the late stages */             \
-            return tpp == 16   ? dw2_launch(KERNEL<T, K, 16, EXP, 1, 2>, a, tpp, lds, st)         \
-                   : tpp == 64 ? dw2_launch(KERNEL<T, K, 64, EXP, 1, 2>, a, tpp, lds, st)         \
-                               : dw2_launch(KERNEL<T, K, 256, EXP, 1, 2>, a, tpp, lds, st);       \
+            return tpp == 16   ? dw2_launch(KERNEL(16, EXP, 1, 2), a, tpp, lds, st __VA_ARGS__)   \
+                   : tpp == 64 ? dw2_launch(KERNEL(64, EXP, 1, 2), a, tpp, lds, st __VA_ARGS__)   \
+                               : dw2_launch(KERNEL(256, EXP, 1, 2), a, tpp, lds, st __VA_ARGS__); \
         if (tpp == 16)                                                                            \
-            return dw2_launch(KERNEL<T, K, 16, EXP, GVO, 4>, a, tpp, lds, st);                    \
+            return dw2_launch(KERNEL(16, EXP, GVO, 4), a, tpp, lds, st __VA_ARGS__);              \
         if (tpp == 64)                                                                            \
-            return dw2_launch(KERNEL<T, K, 64, EXP, GVO, 4>, a, tpp, lds, st);                    \
+            return dw2_launch(KERNEL(64, EXP, GVO, 4), a, tpp, lds, st __VA_ARGS__);              \
         if (tpp == 256)                                                                           \
-            return dw2_launch(KERNEL<T, K, 256, EXP, GVO, 4>, a, tpp, lds, st);                   \
-        return dw2_launch(KERNEL<T, K, 1024, EXP, GVO, 4>, a, tpp, lds, st);                      \
+            return dw2_launch(KERNEL(256, EXP, GVO, 4), a, tpp, lds, st __VA_ARGS__);             \
+        return dw2_launch(KERNEL(1024, EXP, GVO, 4), a, tpp, lds, st __VA_ARGS__);                \
     }
-#define MBK_DW2_GO(KERNEL, T, K)                                                                  \
-    {                                                                                             \
-        if (ex && gvo == 4)                                                                       \
-            MBK_DW2_TPP(KERNEL, T, K, true, 4)                                                    \
-        if (ex)                                                                                   \
-            MBK_DW2_TPP(KERNEL, T, K, true, 1)                                                    \
-        if (gvo == 4)                                                                             \
-            MBK_DW2_TPP(KERNEL, T, K, false, 4)                                                   \
-        MBK_DW2_TPP(KERNEL, T, K, false, 1)                                                       \
-    }
+#define MBK_DW2_GO(KERNEL, ...)                                                                   \
+    const bool ex = a.bn1 != nullptr, whole = s.Wo % 4 == 0;                                      \
+    if (ex && whole)                                                                              \
+        MBK_DW2_TPP(KERNEL, true, 4, __VA_ARGS__)                                                 \
+    if (ex)                                                                                       \
+        MBK_DW2_TPP(KERNEL, true, 1, __VA_ARGS__)                                                 \
+    if (whole)                                                                                    \
+        MBK_DW2_TPP(KERNEL, false, 4, __VA_ARGS__)                                                \
+    MBK_DW2_TPP(KERNEL, false, 1, __VA_ARGS__)
+
+template <typename T, int K, typename EVT>
+static hipError_t dw2_fwd_go(const Dw2Args &a, const DwShape &s, int tpp, size_t lds, hipStream_t st, const EVT &ev)
+{
+#define MBK_KERNEL(TPP, EXP, GVO, GVI) dw2_fwd_kernel<T, K, TPP, EXP, GVO, GVI, EVT>
+    MBK_DW2_GO(MBK_KERNEL, , ev)
+#undef MBK_KERNEL
+}
+template <typename T, int K>
+static hipError_t dw2_bwd_go(const Dw2Args &a, const DwShape &s, int tpp, size_t lds, hipStream_t st)
+{
+#define MBK_KERNEL(TPP, EXP, GVO, GVI) dw2_bwd_kernel<T, K, TPP, EXP, GVO, GVI>
+    MBK_DW2_GO(MBK_KERNEL)
+#undef MBK_KERNEL
+}
+#undef MBK_DW2_GO
+#undef MBK_DW2_TPP
 
 hipError_t launch_dw2_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
-                          const void *w_dw, void *d, float *psum, float *psq, hipStream_t st)
+                          const void *w_dw, void *d, float *psum, float *psq, const DwEval *ev,
+                          hipStream_t st)
 {
     Dw2Args a = dw2_args(s);
     a.e = e;
@@ -579,16 +628,17 @@ hipError_t launch_dw2_fwd(bool bf16, const DwShape &s, const void *e, const floa
     if (!dw2_shape(s, &tpp))
         return hipErrorInvalidValue;
     const size_t lds = dw2_lds(a, s.k, tpp, false);
-    const bool ex = bn1 != nullptr;
-    const int gvo = s.Wo % 4 == 0 ? 4 : 1;
+#define MBK_GO(T, K)                                                                              \
+    return ev ? dw2_fwd_go<T, K>(a, s, tpp, lds, st, *ev) : dw2_fwd_go<T, K>(a, s, tpp, lds, st, DwTrain());
     if (bf16) {
         if (s.k == 3)
-            MBK_DW2_GO(dw2_fwd_kernel, bf16_t, 3)
-        MBK_DW2_GO(dw2_fwd_kernel, bf16_t, 5)
+            MBK_GO(bf16_t, 3)
+        MBK_GO(bf16_t, 5)
     }
     if (s.k == 3)
-        MBK_DW2_GO(dw2_fwd_kernel, float, 3)
-    MBK_DW2_GO(dw2_fwd_kernel, float, 5)
+        MBK_GO(float, 3)
+    MBK_GO(float, 5)
+#undef MBK_GO
 }
 
 hipError_t launch_dw2_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st)
@@ -612,18 +662,9 @@ hipError_t launch_dw2_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st)
     if (!dw2_shape(s, &tpp) || h.res)
         return hipErrorInvalidValue;
     const size_t lds = dw2_lds(a, s.k, tpp, true);
-    const bool ex = h.bn1 != nullptr;
-    const int gvo = s.Wo % 4 == 0 ? 4 : 1;
-    if (bf16) {
-        if (s.k == 3)
-            MBK_DW2_GO(dw2_bwd_kernel, bf16_t, 3)
-        MBK_DW2_GO(dw2_bwd_kernel, bf16_t, 5)
-    }
-    if (s.k == 3)
-        MBK_DW2_GO(dw2_bwd_kernel, float, 3)
-    MBK_DW2_GO(dw2_bwd_kernel, float, 5)
+    if (bf16)
+        return s.k == 3 ? dw2_bwd_go<bf16_t, 3>(a, s, tpp, lds, st) : dw2_bwd_go<bf16_t, 5>(a, s, tpp, lds, st);
+    return s.k == 3 ? dw2_bwd_go<float, 3>(a, s, tpp, lds, st) : dw2_bwd_go<float, 5>(a, s, tpp, lds, st);
 }
-#undef MBK_DW2_GO
-#undef MBK_DW2_TPP
 
 } // namespace mbk

@@ -15,6 +15,7 @@
 #include "mbconv_dev.h"
 #include "mbconv_launch.h"
 #include "mbconv_bnfin.h"
+#include "mbconv_eval.h"
 
 namespace mbk {
 
@@ -136,12 +137,19 @@ __device__ __forceinline__ void read_window_row(const float *tile, int row, int 
 
 // ---- forward ---------------------------------------------------------------------------------
 
-template <typename T, int K, int TPP, int NG, bool EXPAND>
-__global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw4_fwd_kernel(Dw4Args a)
+// EVT: DwTrain or DwEval
+template <typename T, int K, int TPP, int NG, bool EXPAND, typename EVT>
+__global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw4_fwd_kernel(Dw4Args a, EVT ev)
 {
     constexpr int P = (K - 1) / 2;
     constexpr int BLOCK = TPP > 256 ? TPP : 256;
     constexpr int PPB = BLOCK / TPP;
+    if constexpr (EVT::kEval) {
+        if ((int)blockIdx.x >= ev.main) {
+            dw_eval_extra(ev, (int)blockIdx.x - ev.main, BLOCK);
+            return;
+        }
+    }
     extern __shared__ float lds[];
     const int H = a.H, W = a.W, WP = a.WP;
     const int tileElems = (H + 2 * P) * WP;
@@ -154,13 +162,19 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw4_fwd_kernel(Dw4Args 
     const bool active = plane_of<TPP>(a, plane, n, c);
 
     float wt[K * K];
+    BnEvalCoef k1 = {1.f, 0.f, 0.f, 1.f}, k2 = k1; // evaluation mode
     if (active) { // (TPP > 64: one plane per workgroup, always active)
         // BN1's coefficients are requested first (or the partial sums they are finalised from),
         // then the plane: loads return in order, so the finalisation runs while the plane's data
         // is still on its way
         float scale = 1.f, shift = 0.f;
         BnFinRegs fr;
-        if (EXPAND) {
+        BnEvalRegs er1, er2;
+        if constexpr (EVT::kEval) {
+            if (EXPAND)
+                er1 = bn_eval_issue(ev.bn1, c);
+            er2 = bn_eval_issue(ev.bn2, c);
+        } else if (EXPAND) {
             if (a.fin.psum) {
                 bn_fin_issue<TPP>(a.fin, c, lt, fr);
             } else {
@@ -176,14 +190,20 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw4_fwd_kernel(Dw4Args 
         const size_t base = plane * (size_t)H * W;
         // all runs of the thread are loaded before any is transformed (one memory round trip,
         // not one per run; the fence keeps the scheduler from re-pairing load and use)
-        float ev[NG][4];
+        float raw[NG][4];
 #pragma unroll
         for (int i = 0; i < NG; ++i) {
             const int gidx = lt + TPP * i;
-            gload4<T>((const T *)a.e, base + 4 * (size_t)(gidx < a.groups ? gidx : 0), ev[i]);
+            gload4<T>((const T *)a.e, base + 4 * (size_t)(gidx < a.groups ? gidx : 0), raw[i]);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (EXPAND && a.fin.psum) {
+        if constexpr (EVT::kEval) {
+            if (EXPAND)
+                k1 = bn_eval_coef(er1, ev.eps);
+            k2 = bn_eval_coef(er2, ev.eps);
+            scale = k1.scale;
+            shift = k1.shift;
+        } else if (EXPAND && a.fin.psum) {
             float mu, rs;
             bn_fin_finish<TPP>(a.fin, a.C, c, lt, n == 0, redd, fr, scale, shift, mu, rs);
         }
@@ -197,7 +217,7 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw4_fwd_kernel(Dw4Args 
                 float v[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    v[r] = ev[i][r];
+                    v[r] = raw[i][r];
                 if (EXPAND) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
@@ -233,16 +253,26 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw4_fwd_kernel(Dw4Args 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float sv = as_stored<T>(o[r]);
-                    acc2[0] += sv;
-                    acc2[1] = fmaf(sv, sv, acc2[1]);
+                    if constexpr (EVT::kEval) {
+                        if (ev.z)
+                            acc2[0] += actf(fmaf(sv, k2.scale, k2.shift));
+                    } else {
+                        acc2[0] += sv;
+                        acc2[1] = fmaf(sv, sv, acc2[1]);
+                    }
                 }
             }
         }
     }
     group_sum<2, TPP>(acc2, red);
     if (active && lt == 0) {
-        a.psum[(size_t)c * a.N + n] = acc2[0];
-        a.psq[(size_t)c * a.N + n] = acc2[1];
+        if constexpr (EVT::kEval) {
+            if (ev.z)
+                ev.z[plane] = acc2[0] * ev.inv_hw;
+        } else {
+            a.psum[(size_t)c * a.N + n] = acc2[0];
+            a.psq[(size_t)c * a.N + n] = acc2[1];
+        }
     }
 }
 
@@ -250,10 +280,16 @@ __global__ __launch_bounds__(TPP > 256 ? TPP : 256) void dw4_fwd_kernel(Dw4Args 
 // BN1 constants (or their finalisation from the partial sums), and the tile's zero border are set
 // up once, and the next plane's loads are issued before the current plane is convolved, so they
 // travel under the arithmetic.
-template <typename T, int K, int NG, bool EXPAND>
-__global__ __launch_bounds__(256) void dw4_fwd_multi_kernel(Dw4Args a)
+template <typename T, int K, int NG, bool EXPAND, typename EVT>
+__global__ __launch_bounds__(256) void dw4_fwd_multi_kernel(Dw4Args a, EVT ev)
 {
     constexpr int P = (K - 1) / 2, TPP = 256;
+    if constexpr (EVT::kEval) {
+        if ((int)blockIdx.x >= ev.main) {
+            dw_eval_extra(ev, (int)blockIdx.x - ev.main, TPP);
+            return;
+        }
+    }
     extern __shared__ float lds[];
     const int H = a.H, W = a.W, WP = a.WP;
     const int tileElems = (H + 2 * P) * WP;
@@ -268,7 +304,13 @@ __global__ __launch_bounds__(256) void dw4_fwd_multi_kernel(Dw4Args a)
     float wt[K * K];
     float scale = 1.f, shift = 0.f;
     BnFinRegs fr;
-    if (EXPAND) {
+    BnEvalRegs er1, er2;
+    BnEvalCoef k1 = {1.f, 0.f, 0.f, 1.f}, k2 = k1;
+    if constexpr (EVT::kEval) {
+        if (EXPAND)
+            er1 = bn_eval_issue(ev.bn1, c);
+        er2 = bn_eval_issue(ev.bn2, c);
+    } else if (EXPAND) {
         if (a.fin.psum) {
             bn_fin_issue<TPP>(a.fin, c, lt, fr);
         } else {
@@ -281,18 +323,24 @@ __global__ __launch_bounds__(256) void dw4_fwd_multi_kernel(Dw4Args a)
         wt[t] = ld<T>((const T *)a.w, (size_t)c * K * K + t);
     __builtin_amdgcn_sched_barrier(0);
     zero_border<P, TPP>(tile, H, W, WP, lt);
-    float ev[NG][4];
+    float raw[NG][4];
     const auto fetch = [&](int n) {
         const size_t base = ((size_t)n * a.C + c) * HW;
 #pragma unroll
         for (int i = 0; i < NG; ++i) {
             const int gidx = lt + TPP * i;
-            gload4<T>((const T *)a.e, base + 4 * (size_t)(gidx < a.groups ? gidx : 0), ev[i]);
+            gload4<T>((const T *)a.e, base + 4 * (size_t)(gidx < a.groups ? gidx : 0), raw[i]);
         }
     };
     fetch(n0);
     __builtin_amdgcn_sched_barrier(0);
-    if (EXPAND && a.fin.psum) {
+    if constexpr (EVT::kEval) {
+        if (EXPAND)
+            k1 = bn_eval_coef(er1, ev.eps);
+        k2 = bn_eval_coef(er2, ev.eps);
+        scale = k1.scale;
+        shift = k1.shift;
+    } else if (EXPAND && a.fin.psum) {
         float mu, rs;
         bn_fin_finish<TPP>(a.fin, a.C, c, lt, n0 == 0, redd, fr, scale, shift, mu, rs);
     }
@@ -307,7 +355,7 @@ __global__ __launch_bounds__(256) void dw4_fwd_multi_kernel(Dw4Args a)
                 float v[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    v[r] = EXPAND ? actf(fmaf(ev[i][r], scale, shift)) : ev[i][r];
+                    v[r] = EXPAND ? actf(fmaf(raw[i][r], scale, shift)) : raw[i][r];
                 float4v t4 = {v[0], v[1], v[2], v[3]};
                 *reinterpret_cast<float4v *>(tile + (h + P) * WP + 4 + w) = t4;
             }
@@ -338,16 +386,26 @@ __global__ __launch_bounds__(256) void dw4_fwd_multi_kernel(Dw4Args a)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float sv = as_stored<T>(o[r]);
-                    acc2[0] += sv;
-                    acc2[1] = fmaf(sv, sv, acc2[1]);
+                    if constexpr (EVT::kEval) {
+                        if (ev.z)
+                            acc2[0] += actf(fmaf(sv, k2.scale, k2.shift));
+                    } else {
+                        acc2[0] += sv;
+                        acc2[1] = fmaf(sv, sv, acc2[1]);
+                    }
                 }
             }
         }
         // (two barriers inside: every read of this plane's tile precedes the next plane's stores)
         group_sum<2, TPP>(acc2, red);
         if (lt == 0) {
-            a.psum[(size_t)c * a.N + n] = acc2[0];
-            a.psq[(size_t)c * a.N + n] = acc2[1];
+            if constexpr (EVT::kEval) {
+                if (ev.z)
+                    ev.z[(size_t)n * a.C + c] = acc2[0] * ev.inv_hw;
+            } else {
+                a.psum[(size_t)c * a.N + n] = acc2[0];
+                a.psq[(size_t)c * a.N + n] = acc2[1];
+            }
         }
     }
 }
@@ -565,9 +623,9 @@ static Dw4Args dw4_args(const DwShape &s)
     return a;
 }
 
-template <typename KERN>
+template <typename KERN, typename... EV>
 static hipError_t dw4_launch(KERN kern, const Dw4Args &a, int block, int ppb, size_t lds,
-                             hipStream_t st)
+                             hipStream_t st, EV... ev)
 {
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
@@ -575,33 +633,57 @@ static hipError_t dw4_launch(KERN kern, const Dw4Args &a, int block, int ppb, si
         return e;
     const size_t planes = (size_t)a.N * a.C;
     const unsigned grid = (unsigned)((planes + ppb - 1) / ppb);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), lds, st, a);
+    const unsigned extra = (0u + ... + dw_eval_extra_blocks(ev, grid, block));
+    hipLaunchKernelGGL(kern, dim3(grid + extra), dim3(block), lds, st, a, ev...);
     return hipGetLastError();
 }
 
-#define MBK_DW4_SHAPES(KERNEL, T, K, EXP)                                                         \
+#define MBK_DW4_SHAPES(KERNEL, ...)                                                               \
     if (tpp == 64 && ng == 1)                                                                     \
-        return dw4_launch(KERNEL<T, K, 64, 1, EXP>, a, 256, 4, lds, st);                          \
+        return dw4_launch(KERNEL(64, 1), a, 256, 4, lds, st __VA_ARGS__);                         \
     if (tpp == 64 && ng == 4)                                                                     \
-        return dw4_launch(KERNEL<T, K, 64, 4, EXP>, a, 256, 4, lds, st);                          \
+        return dw4_launch(KERNEL(64, 4), a, 256, 4, lds, st __VA_ARGS__);                         \
     if (tpp == 256)                                                                               \
-        return dw4_launch(KERNEL<T, K, 256, 4, EXP>, a, 256, 1, lds, st);                         \
-    return dw4_launch(KERNEL<T, K, 1024, 4, EXP>, a, 1024, 1, lds, st);
+        return dw4_launch(KERNEL(256, 4), a, 256, 1, lds, st __VA_ARGS__);                        \
+    return dw4_launch(KERNEL(1024, 4), a, 1024, 1, lds, st __VA_ARGS__);
 
-template <typename T, int K, bool EXP>
-static hipError_t dw4_fwd_go(const Dw4Args &a, int tpp, int ng, size_t lds, hipStream_t st)
+template <typename T, int K, bool EXP, typename EVT>
+static hipError_t dw4_fwd_go(const Dw4Args &a, int tpp, int ng, size_t lds, hipStream_t st, const EVT &ev)
 {
-    MBK_DW4_SHAPES(dw4_fwd_kernel, T, K, EXP)
+#define MBK_KERNEL(TPP, NG) dw4_fwd_kernel<T, K, TPP, NG, EXP, EVT>
+    MBK_DW4_SHAPES(MBK_KERNEL, , ev)
+#undef MBK_KERNEL
 }
 template <typename T, int K, bool EXP>
 static hipError_t dw4_bwd_go(const Dw4Args &a, int tpp, int ng, size_t lds, hipStream_t st)
 {
-    MBK_DW4_SHAPES(dw4_bwd_kernel, T, K, EXP)
+#define MBK_KERNEL(TPP, NG) dw4_bwd_kernel<T, K, TPP, NG, EXP>
+    MBK_DW4_SHAPES(MBK_KERNEL)
+#undef MBK_KERNEL
+}
+
+template <typename T, int K, bool EXP, typename EVT>
+static hipError_t dw4_fwd_form(Dw4Args &a, int tpp, int ng, size_t lds, hipStream_t st, EVT ev)
+{
+    // 56x56-class planes (a workgroup of 256 threads per plane): two images of a channel per
+    // workgroup where that still leaves eight workgroups per CU (config 1: 26.4 us against 29.5
+    // for the step; four images 26.6, eight 29.5)
+    a.PL = (tpp == 256 && ng == 4 && (long long)a.C * ((a.N + 1) / 2) >= 2048) ? 2 : 1;
+    if (a.PL == 1)
+        return dw4_fwd_go<T, K, EXP>(a, tpp, ng, lds, st, ev);
+    const unsigned grid = (unsigned)(a.C * ((a.N + a.PL - 1) / a.PL));
+    auto kern = dw4_fwd_multi_kernel<T, K, 4, EXP, EVT>;
+    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess)
+        return e;
+    const unsigned extra = dw_eval_extra_blocks(ev, grid, 256);
+    hipLaunchKernelGGL(kern, dim3(grid + extra), dim3(256), lds, st, a, ev);
+    return hipGetLastError();
 }
 
 hipError_t launch_dw4_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
                           const void *w_dw, void *d, float *psum, float *psq, const BnFin *fin,
-                          hipStream_t st)
+                          const DwEval *ev, hipStream_t st)
 {
     Dw4Args a = dw4_args(s);
     if (fin)
@@ -616,41 +698,15 @@ hipError_t launch_dw4_fwd(bool bf16, const DwShape &s, const void *e, const floa
     dw4_shape(a.groups, &tpp, &ng);
     const size_t lds = dw4_lds(s, 1, 2);
     const bool ex = bn1 != nullptr;
-    // 56x56-class planes (a workgroup of 256 threads per plane): two images of a channel per
-    // workgroup where that still leaves eight workgroups per CU (config 1: 26.4 us against 29.5
-    // for the step; four images 26.6, eight 29.5)
-    a.PL = (tpp == 256 && ng == 4 && (long long)a.C * ((a.N + 1) / 2) >= 2048) ? 2 : 1;
-    if (a.PL > 1) {
-        const unsigned grid = (unsigned)(a.C * ((a.N + a.PL - 1) / a.PL));
-#define MBK_MULTI(T, K, EXP)                                                                      \
-    {                                                                                             \
-        auto kern = dw4_fwd_multi_kernel<T, K, 4, EXP>;                                           \
-        hipError_t e_ = hipFuncSetAttribute((const void *)kern,                                   \
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
-        if (e_ != hipSuccess)                                                                     \
-            return e_;                                                                            \
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, a);                              \
-        return hipGetLastError();                                                                 \
-    }
-#define MBK_MULTI_K(T, EXP)                                                                       \
-    {                                                                                             \
-        if (s.k == 3)                                                                             \
-            MBK_MULTI(T, 3, EXP)                                                                  \
-        MBK_MULTI(T, 5, EXP)                                                                      \
-    }
-        if (bf16) {
-            if (ex)
-                MBK_MULTI_K(bf16_t, true)
-            MBK_MULTI_K(bf16_t, false)
-        }
-        if (ex)
-            MBK_MULTI_K(float, true)
-        MBK_MULTI_K(float, false)
-#undef MBK_MULTI_K
-#undef MBK_MULTI
-    }
+#define MBK_EV(T, K, EXP)                                                                         \
+    return ev ? dw4_fwd_form<T, K, EXP>(a, tpp, ng, lds, st, *ev)                                 \
+              : dw4_fwd_form<T, K, EXP>(a, tpp, ng, lds, st, DwTrain());
 #define MBK_GO(T, K)                                                                              \
-    return ex ? dw4_fwd_go<T, K, true>(a, tpp, ng, lds, st) : dw4_fwd_go<T, K, false>(a, tpp, ng, lds, st);
+    {                                                                                             \
+        if (ex)                                                                                   \
+            MBK_EV(T, K, true)                                                                    \
+        MBK_EV(T, K, false)                                                                       \
+    }
     if (bf16) {
         if (s.k == 3)
             MBK_GO(bf16_t, 3)
@@ -660,6 +716,7 @@ hipError_t launch_dw4_fwd(bool bf16, const DwShape &s, const void *e, const floa
         MBK_GO(float, 3)
     MBK_GO(float, 5)
 #undef MBK_GO
+#undef MBK_EV
 }
 
 hipError_t launch_dw4_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st)

@@ -17,6 +17,7 @@
 #include "mbconv_dev.h"
 #include "mbconv_launch.h"
 #include "mbconv_bnfin.h"
+#include "mbconv_eval.h"
 
 namespace mbk {
 
@@ -239,10 +240,16 @@ __device__ __forceinline__ DwrLane dwr_lane(const DwrArgs &a)
 }
 
 // ---- forward: d = depthwise(swish(bn1(e))), partial sums of d and d^2 per (channel, range) ----
-template <typename T, int K, int GV, bool EXPAND>
-__global__ __launch_bounds__(256) void dwr_fwd_kernel(DwrArgs a)
+template <typename T, int K, int GV, bool EXPAND, typename EVT>
+__global__ __launch_bounds__(256) void dwr_fwd_kernel(DwrArgs a, EVT ev)
 {
-    constexpr int P = (K - 1) / 2;
+    constexpr int P = (K - 1) / 2, BLOCK = 256;
+    if constexpr (EVT::kEval) {
+        if ((int)blockIdx.x >= ev.main) {
+            dw_eval_extra(ev, (int)blockIdx.x - ev.main, BLOCK);
+            return;
+        }
+    }
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int H = a.H, W = a.W, WP = a.WP;
     const int tileElems = (H + 2 * P) * WP;
@@ -262,8 +269,13 @@ __global__ __launch_bounds__(256) void dwr_fwd_kernel(DwrArgs a)
     // wavefront, not once per plane; the wavefront of the channel's first range stores the block.
     float scale = 1.f, shift = 0.f;
     BnFinRegs fr;
-    const bool fuse = EXPAND && a.fin.psum != nullptr;
-    if (EXPAND) {
+    BnEvalRegs er1, er2;
+    const bool fuse = EXPAND && !EVT::kEval && a.fin.psum != nullptr;
+    if constexpr (EVT::kEval) {
+        if (EXPAND)
+            er1 = bn_eval_issue(ev.bn1, L.c);
+        er2 = bn_eval_issue(ev.bn2, L.c);
+    } else if (EXPAND) {
         if (fuse) {
             bn_fin_issue<64>(a.fin, L.c, lane, fr);
         } else {
@@ -286,6 +298,14 @@ __global__ __launch_bounds__(256) void dwr_fwd_kernel(DwrArgs a)
         float mu, rs;
         bn_fin_finish<64>(a.fin, a.C, L.c, lane, L.wave_ok && L.seg == 0, nullptr, fr, scale, shift, mu, rs);
     }
+    BnEvalCoef k1 = {1.f, 0.f, 0.f, 1.f}, k2 = k1; // evaluation mode
+    if constexpr (EVT::kEval) {
+        if (EXPAND)
+            k1 = bn_eval_coef(er1, ev.eps);
+        k2 = bn_eval_coef(er2, ev.eps);
+        scale = k1.scale;
+        shift = k1.shift;
+    }
     float acc0 = 0.f, acc1 = 0.f;
     wave_lds_sync();
     for (int it = 0; it < L.iters; ++it) {
@@ -306,6 +326,8 @@ __global__ __launch_bounds__(256) void dwr_fwd_kernel(DwrArgs a)
         if (it + 1 < L.iters)
             cur_ok = prefetch(it + 1);
         wave_lds_sync();
+        if constexpr (EVT::kEval)
+            acc0 = 0.f; // sums per plane
         if (ok) {
             float o[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -323,12 +345,29 @@ __global__ __launch_bounds__(256) void dwr_fwd_kernel(DwrArgs a)
             for (int r = 0; r < 4; ++r) {
                 if (L.x0 + r < W) {
                     const float sv = as_stored<T>(o[r]);
-                    acc0 += sv;
-                    acc1 = fmaf(sv, sv, acc1);
+                    if constexpr (EVT::kEval) {
+                        if (ev.z)
+                            acc0 += actf(fmaf(sv, k2.scale, k2.shift));
+                    } else {
+                        acc0 += sv;
+                        acc1 = fmaf(sv, sv, acc1);
+                    }
+                }
+            }
+        }
+        if constexpr (EVT::kEval) {
+            if (ev.z) { // (the planes side by side, one after the other)
+                const int first = L.n_begin + it * a.PW;
+                for (int p = 0; p < a.PW && first + p < L.n_end; ++p) {
+                    const float sum = wave_sum(L.pw == p ? acc0 : 0.f);
+                    if (L.wave_ok && lane == 0)
+                        ev.z[(size_t)(first + p) * a.C + L.c] = sum * ev.inv_hw;
                 }
             }
         }
     }
+    if constexpr (EVT::kEval)
+        return;
     acc0 = wave_sum(acc0);
     acc1 = wave_sum(acc1);
     if (L.wave_ok && lane == 0) {
@@ -545,8 +584,8 @@ static size_t dwr_lds(const DwrArgs &a, int k, int tiles)
     return sizeof(float) * 4 * (size_t)(2 * tiles * a.PW) * (a.H + 2 * p) * a.WP;
 }
 
-template <typename KERN>
-static hipError_t dwr_launch(KERN kern, const DwrArgs &a, size_t lds, hipStream_t st)
+template <typename KERN, typename... EV>
+static hipError_t dwr_launch(KERN kern, const DwrArgs &a, size_t lds, hipStream_t st, EV... ev)
 {
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute((const void *)kern,
@@ -555,25 +594,42 @@ static hipError_t dwr_launch(KERN kern, const DwrArgs &a, size_t lds, hipStream_
             return e;
     }
     const long long slots = (long long)a.C * a.nseg;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((slots + 3) / 4)), dim3(256), lds, st, a);
+    const unsigned grid = (unsigned)((slots + 3) / 4);
+    const unsigned extra = (0u + ... + dw_eval_extra_blocks(ev, grid, 256));
+    hipLaunchKernelGGL(kern, dim3(grid + extra), dim3(256), lds, st, a, ev...);
     return hipGetLastError();
 }
 
-#define MBK_DWR_GO(KERNEL, T, K)                                                                  \
-    {                                                                                             \
-        if (gv == 4)                                                                              \
-            return ex ? dwr_launch(KERNEL<T, K, 4, true>, a, lds, st)                             \
-                      : dwr_launch(KERNEL<T, K, 4, false>, a, lds, st);                           \
-        if (gv == 2)                                                                              \
-            return ex ? dwr_launch(KERNEL<T, K, 2, true>, a, lds, st)                             \
-                      : dwr_launch(KERNEL<T, K, 2, false>, a, lds, st);                           \
-        return ex ? dwr_launch(KERNEL<T, K, 1, true>, a, lds, st)                                 \
-                  : dwr_launch(KERNEL<T, K, 1, false>, a, lds, st);                               \
-    }
+#define MBK_DWR_GO(KERNEL, ...)                                                                   \
+    const bool ex = a.bn1 != nullptr;                                                             \
+    if (a.W % 4 == 0)                                                                             \
+        return ex ? dwr_launch(KERNEL(4, true), a, lds, st __VA_ARGS__)                           \
+                  : dwr_launch(KERNEL(4, false), a, lds, st __VA_ARGS__);                         \
+    if (a.W % 2 == 0)                                                                             \
+        return ex ? dwr_launch(KERNEL(2, true), a, lds, st __VA_ARGS__)                           \
+                  : dwr_launch(KERNEL(2, false), a, lds, st __VA_ARGS__);                         \
+    return ex ? dwr_launch(KERNEL(1, true), a, lds, st __VA_ARGS__)                               \
+              : dwr_launch(KERNEL(1, false), a, lds, st __VA_ARGS__);
+
+template <typename T, int K, typename EVT>
+static hipError_t dwr_fwd_go(const DwrArgs &a, size_t lds, hipStream_t st, const EVT &ev)
+{
+#define MBK_KERNEL(GV, EXP) dwr_fwd_kernel<T, K, GV, EXP, EVT>
+    MBK_DWR_GO(MBK_KERNEL, , ev)
+#undef MBK_KERNEL
+}
+template <typename T, int K>
+static hipError_t dwr_bwd_go(const DwrArgs &a, size_t lds, hipStream_t st)
+{
+#define MBK_KERNEL(GV, EXP) dwr_bwd_kernel<T, K, GV, EXP>
+    MBK_DWR_GO(MBK_KERNEL)
+#undef MBK_KERNEL
+}
+#undef MBK_DWR_GO
 
 hipError_t launch_dwr_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
                           const void *w_dw, void *d, float *psum, float *psq, const BnFin *fin,
-                          hipStream_t st)
+                          const DwEval *ev, hipStream_t st)
 {
     DwrArgs a = dwr_args(bf16, s, false);
     if (fin)
@@ -585,16 +641,17 @@ hipError_t launch_dwr_fwd(bool bf16, const DwShape &s, const void *e, const floa
     a.psum = psum;
     a.psq = psq;
     const size_t lds = dwr_lds(a, s.k, 1);
-    const bool ex = bn1 != nullptr;
-    const int gv = s.W % 4 == 0 ? 4 : (s.W % 2 == 0 ? 2 : 1);
+#define MBK_GO(T, K)                                                                              \
+    return ev ? dwr_fwd_go<T, K>(a, lds, st, *ev) : dwr_fwd_go<T, K>(a, lds, st, DwTrain());
     if (bf16) {
         if (s.k == 3)
-            MBK_DWR_GO(dwr_fwd_kernel, bf16_t, 3)
-        MBK_DWR_GO(dwr_fwd_kernel, bf16_t, 5)
+            MBK_GO(bf16_t, 3)
+        MBK_GO(bf16_t, 5)
     }
     if (s.k == 3)
-        MBK_DWR_GO(dwr_fwd_kernel, float, 3)
-    MBK_DWR_GO(dwr_fwd_kernel, float, 5)
+        MBK_GO(float, 3)
+    MBK_GO(float, 5)
+#undef MBK_GO
 }
 
 hipError_t launch_dwr_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st)
@@ -616,17 +673,9 @@ hipError_t launch_dwr_bwd(bool bf16, const DwBwdArgs &h, hipStream_t st)
     a.psr = h.psr;
     const DwShape &s = h.s;
     const size_t lds = dwr_lds(a, s.k, 1);
-    const bool ex = h.bn1 != nullptr;
-    const int gv = s.W % 4 == 0 ? 4 : (s.W % 2 == 0 ? 2 : 1);
-    if (bf16) {
-        if (s.k == 3)
-            MBK_DWR_GO(dwr_bwd_kernel, bf16_t, 3)
-        MBK_DWR_GO(dwr_bwd_kernel, bf16_t, 5)
-    }
-    if (s.k == 3)
-        MBK_DWR_GO(dwr_bwd_kernel, float, 3)
-    MBK_DWR_GO(dwr_bwd_kernel, float, 5)
+    if (bf16)
+        return s.k == 3 ? dwr_bwd_go<bf16_t, 3>(a, lds, st) : dwr_bwd_go<bf16_t, 5>(a, lds, st);
+    return s.k == 3 ? dwr_bwd_go<float, 3>(a, lds, st) : dwr_bwd_go<float, 5>(a, lds, st);
 }
-#undef MBK_DWR_GO
 
 } // namespace mbk

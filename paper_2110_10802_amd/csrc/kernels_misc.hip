@@ -23,7 +23,7 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double 
                                                           size_t ones_count, X3PrepArgs prep)
 {
     if (PREP && (int)blockIdx.x >= (C + 3) / 4) {
-        x3_prep_tile(prep, blockIdx.x - (C + 3) / 4);
+        x3_prep_tile(prep, blockIdx.x - (C + 3) / 4, threadIdx.x);
         return;
     }
     // a block without squeeze-and-excitation has its gate buffer set to one here, by the launch
@@ -108,71 +108,6 @@ hipError_t launch_bn_finalize(int C, int NP, double m, const float *psum, const 
     else
         hipLaunchKernelGGL(bn_finalize_kernel<false>, dim3(own), dim3(256), 0, st, C, NP, m, psum, psq, gamma, beta,
                            eps, momentum, run_mean, run_var, bn, ones, ones ? ones_count : 0, X3PrepArgs());
-    return hipGetLastError();
-}
-
-// Evaluation mode: the same {scale, shift, mean, rstd} blocks from the stored running
-// statistics, for up to three normalisations in one launch (a batch-norm layer with fixed
-// statistics is an affine map per channel; section "Background and Related Work", paragraph
-// "Training vs. inference compilation": BN behaves differently in inference).
-struct BnEvalOne {
-    int C;
-    const float *gamma, *beta, *run_mean, *run_var;
-    float *bn;
-};
-struct BnEvalArgs {
-    BnEvalOne b[3];
-    float eps;
-    int blocks;       // workgroups of the coefficients; those past them write the weight images
-    float *ones;      // gate of a block without squeeze-and-excitation, set to one
-    size_t ones_count;
-    X3PrepArgs prep;
-};
-__global__ __launch_bounds__(256) void bn_eval_coef_kernel(BnEvalArgs a)
-{
-    if ((int)blockIdx.x >= a.blocks) {
-        x3_prep_tile(a.prep, blockIdx.x - a.blocks);
-        return;
-    }
-    for (size_t j = (size_t)blockIdx.x * 256 + threadIdx.x; j < a.ones_count; j += (size_t)a.blocks * 256)
-        a.ones[j] = 1.0f;
-    int i = blockIdx.x * 256 + threadIdx.x;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const BnEvalOne &b = a.b[k];
-        if (i >= 0 && i < b.C) {
-            const double mean = (double)b.run_mean[i];
-            const double rstd = 1.0 / sqrt((double)b.run_var[i] + (double)a.eps);
-            const double scale = (double)b.gamma[i] * rstd;
-            b.bn[i] = (float)scale;
-            b.bn[b.C + i] = (float)((double)b.beta[i] - mean * scale);
-            b.bn[2 * b.C + i] = (float)mean;
-            b.bn[3 * b.C + i] = (float)rstd;
-        }
-        i -= b.C;
-    }
-}
-
-hipError_t launch_bn_eval_coef(int C1, const float *gamma1, const float *beta1, const float *rm1,
-                               const float *rv1, float *bn1, int C2, const float *gamma2,
-                               const float *beta2, const float *rm2, const float *rv2, float *bn2,
-                               int C3, const float *gamma3, const float *beta3, const float *rm3,
-                               const float *rv3, float *bn3, float eps, hipStream_t st, float *ones,
-                               size_t ones_count, const X3PrepArgs *prep)
-{
-    BnEvalArgs a = {};
-    a.b[0] = {C1, gamma1, beta1, rm1, rv1, bn1};
-    a.b[1] = {C2, gamma2, beta2, rm2, rv2, bn2};
-    a.b[2] = {C3, gamma3, beta3, rm3, rv3, bn3};
-    a.eps = eps;
-    a.ones = ones;
-    a.ones_count = ones ? ones_count : 0;
-    if (prep)
-        a.prep = *prep;
-    // (the coefficients need a thread each; the ones, where there are any, eight to a thread)
-    const size_t want = std::max((size_t)(C1 + C2 + C3), (a.ones_count + 7) / 8);
-    a.blocks = (int)std::max<size_t>((C1 + C2 + C3 + 255) / 256, std::min<size_t>((want + 255) / 256, 1024));
-    hipLaunchKernelGGL(bn_eval_coef_kernel, dim3((unsigned)(a.blocks + a.prep.tiles)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

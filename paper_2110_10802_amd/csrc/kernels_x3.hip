@@ -73,7 +73,7 @@ __device__ __forceinline__ int x3_img_at(int row, int k)
 // one for bf16), cut into tiles of 64 rows x 32 k in the lane order of v_mfma_f32_16x16x32_bf16:
 // tile (mt, ch) is [row tile of 16][plane][lane][8 k] with lane = row % 16 + 16 * (k / 8), so that a
 // wavefront reads an operand as 64 consecutive 16-byte pieces.  Rows and k past the end are zeros.
-__global__ __launch_bounds__(256) void x3_prep_kernel(X3PrepArgs a) { x3_prep_tile(a, blockIdx.x); }
+__global__ __launch_bounds__(256) void x3_prep_kernel(X3PrepArgs a) { x3_prep_tile(a, blockIdx.x, threadIdx.x); }
 
 size_t x3_weight_image_bytes(bool bf16, int M, int K)
 {

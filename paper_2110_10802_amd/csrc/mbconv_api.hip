@@ -263,9 +263,8 @@ mbconv_status check_params(const mbconv_desc *d, const mbconv_params *p)
 
 
 // Training mode (eval == false): batch statistics, running statistics updated when run != NULL.
-// Evaluation mode: run is read only and supplies the statistics of all three normalisations;
-// their coefficient blocks come from one launch ahead of everything else, attributed to the
-// first BN-finalise step the block has, and the other finalise steps launch nothing.
+// Evaluation mode: run is read only and supplies the statistics of all three normalisations; the
+// depthwise kernel turns them into coefficients, so that the BN-finalise steps and the pool launch nothing.
 mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mbconv_bn_state *run,
                            bool eval, const void *x, void *out, void *saved, void *scratch,
                            void *hip_stream, const mbconv_probe *probe)
@@ -307,9 +306,9 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     const float eps = desc->bn_eps, mom = desc->bn_momentum;
 
     // Weight images of the convolutions that want them (the two data-gradient images only in
-    // training mode).  They are written by a launch that precedes their first reader anyway: the BN
-    // coefficients' in evaluation mode, BN2's finalise step in training mode, unless the expansion
-    // conv itself reads one.
+    // training mode).  They are written by a launch that precedes their first reader anyway: the depthwise
+    // kernel's in evaluation mode, BN2's finalise step in training mode, unless the expansion conv itself
+    // reads one.
     const auto wimg = [&](int i) -> const void * {
         return P.o_wimg[i] == kAbsent ? nullptr : at<char>(saved, P.o_wimg[i]);
     };
@@ -327,21 +326,28 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
             add(3, prm->w_expand, P.Cin, P.Cexp, 1, P.Cin);
         }
     }
-    const bool prep_first = !eval && P.o_wimg[0] != kAbsent;
+    const bool prep_first = P.o_wimg[0] != kAbsent;
     float *z = at<float>(saved, P.o_z), *g = at<float>(saved, P.o_g), *q = at<float>(saved, P.o_q);
     // no squeeze-and-excitation stage: the gate every later prologue multiplies by is one, written by
     // the same launches
     float *ones = P.se ? nullptr : g;
     const size_t ones_count = (size_t)P.N * P.Cexp;
-    const auto eval_coefs = [&]() {
-        return launch_bn_eval_coef(P.expand ? P.Cexp : 0, prm->bn1_gamma, prm->bn1_beta, run->bn1_mean,
-                                   run->bn1_var, bn1, P.Cexp, prm->bn2_gamma, prm->bn2_beta,
-                                   run->bn2_mean, run->bn2_var, bn2, P.Cout, prm->bn3_gamma,
-                                   prm->bn3_beta, run->bn3_mean, run->bn3_var, bn3, eps, st, ones, ones_count,
-                                   &prep);
-    };
-    if (eval)
-        MBK_STEP(P.expand ? MBCONV_STEP_BN1_FINALIZE : MBCONV_STEP_BN2_FINALIZE, eval_coefs());
+    // Evaluation mode: the depthwise launch brings the coefficients, the pool and the weight images.
+    DwEval ev = {};
+    if (eval) {
+        if (P.expand)
+            ev.bn1 = {P.Cexp, prm->bn1_gamma, prm->bn1_beta, run->bn1_mean, run->bn1_var, bn1};
+        ev.bn2 = {P.Cexp, prm->bn2_gamma, prm->bn2_beta, run->bn2_mean, run->bn2_var, bn2};
+        ev.bn3 = {P.Cout, prm->bn3_gamma, prm->bn3_beta, run->bn3_mean, run->bn3_var, bn3};
+        ev.eps = eps;
+        ev.z = P.se ? z : nullptr;
+        ev.inv_hw = 1.f / (float)P.HWo;
+        ev.ones = ones;
+        ev.ones_count = ones ? ones_count : 0;
+        if (!prep_first)
+            ev.prep = prep;
+        MBK_STEP(P.expand ? MBCONV_STEP_BN1_FINALIZE : MBCONV_STEP_BN2_FINALIZE, hipSuccess); // (no launch)
+    }
     // expansion conv + BN1 statistics
     const void *dw_in = x;
     if (P.expand) {
@@ -379,7 +385,7 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
                                    prm->bn1_beta, eps, mom, fin1.run_mean, fin1.run_var, bn1, st));
     // BN1 + Swish + depthwise + BN2 statistics
     MBK_STEP(MBCONV_STEP_DW_FWD, launch_dw_fwd(bf, ds, dw_in, bn1, prm->w_dw, d, psum2, psq2, a1_store,
-                                               fuse1 ? &fin1 : nullptr, st));
+                                               fuse1 ? &fin1 : nullptr, eval ? &ev : nullptr, st));
     // BN2 + Swish + SE squeeze, SE excite
     const BnFin fin2 = make_bn_fin(psum2, psq2, prm->bn2_gamma, prm->bn2_beta, run ? run->bn2_mean : nullptr,
                                    run ? run->bn2_var : nullptr, bn2, P.NPdw, eps, mom, m2);
@@ -388,9 +394,13 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
                                    prm->bn2_beta, eps, mom, fin2.run_mean, fin2.run_var, bn2, st, ones, ones_count,
                                    prep_first ? nullptr : &prep));
     if (P.se) {
-        MBK_STEP(MBCONV_STEP_SE_POOL, launch_pool(bf, P.N, P.Cexp, P.HWo, d, bn2, z, at<float>(saved, P.o_s3),
-                            at<float>(saved, P.o_s4), fuse2 ? &fin2 : nullptr,
-                            prep_first ? nullptr : &prep, st));
+        const auto pool = [&]() {
+            return eval ? hipSuccess
+                        : launch_pool(bf, P.N, P.Cexp, P.HWo, d, bn2, z, at<float>(saved, P.o_s3),
+                                      at<float>(saved, P.o_s4), fuse2 ? &fin2 : nullptr,
+                                      prep_first ? nullptr : &prep, st);
+        };
+        MBK_STEP(MBCONV_STEP_SE_POOL, pool());
         MBK_STEP(MBCONV_STEP_SE_FC, launch_se_fwd(P.N, P.Cexp, P.Cse, z, prm->se_w1, prm->se_b1, prm->se_w2, prm->se_b2, q,
                               g, st));
     }

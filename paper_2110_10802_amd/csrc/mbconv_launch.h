@@ -59,7 +59,7 @@ bool conv1x1_uses_weight_image(bool bf16, int N, int M, int K, int HW, bool stor
 size_t x3_weight_image_bytes(bool bf16, int M, int K);
 // Up to four images: set i is of A(m,k) = w[m*sm + k*sk], M x K (w in the activation dtype).  They are
 // written by a launch of their own, or by extra workgroups of a launch that precedes their first
-// reader anyway (launch_bn_finalize, launch_bn_eval_coef).
+// reader anyway (launch_bn_finalize, launch_pool, launch_dw_fwd in evaluation mode).
 struct X3PrepSet {
     const void *w;
     int M, K, sm, sk;
@@ -175,14 +175,32 @@ hipError_t launch_bn_finalize(int C, int NP, double m, const float *psum, const 
                               float *ones = nullptr, size_t ones_count = 0,
                               const X3PrepArgs *prep = nullptr);
 
-// Evaluation mode: the same blocks from running statistics, three normalisations per launch
-// (C1 = 0 skips the first); ones and prep as above.
-hipError_t launch_bn_eval_coef(int C1, const float *gamma1, const float *beta1, const float *rm1,
-                               const float *rv1, float *bn1, int C2, const float *gamma2,
-                               const float *beta2, const float *rm2, const float *rv2, float *bn2,
-                               int C3, const float *gamma3, const float *beta3, const float *rm3,
-                               const float *rv3, float *bn3, float eps, hipStream_t st, float *ones,
-                               size_t ones_count, const X3PrepArgs *prep);
+// Evaluation mode: a normalisation with its running statistics.
+struct BnEval {
+    int C; // 0: the block has none
+    const float *gamma, *beta, *run_mean, *run_var;
+    float *bn; // {scale, shift, mean, rstd}[C], for consumers that read the block
+};
+// What the depthwise launch of an evaluation-mode forward does besides the convolution: the kernel takes
+// BN1's and BN2's coefficients from the running statistics and, where z is non-null, writes the SE stage's
+// squeeze (the mean of each plane after BN2 and activation), and workgroups past the convolution's write
+// what later kernels read: the blocks of BN2 and BN3, the gate of ones of a block without SE, and weight
+// images.  The launches these would be (coefficients, pool) are a few microseconds each, which is what a
+// forward of one image consists of.
+struct DwEval {
+    static constexpr bool kEval = true;
+    BnEval bn1, bn2, bn3;
+    float eps;
+    float *z;
+    float inv_hw;
+    float *ones;
+    size_t ones_count;
+    X3PrepArgs prep;
+    int main, coef; // workgroups of the convolution and of the coefficients (the launcher's)
+};
+struct DwTrain { // training mode: no such work
+    static constexpr bool kEval = false;
+};
 
 // Block without a squeeze-and-excitation stage (gate = 1, dz = 0): BN2's backward from the
 // plane sums A1 = sum G*act'(y2), A2 = sum G*act'(y2)*dhat, both [N][C]:
@@ -214,10 +232,11 @@ size_t dw_bwd_lds_bytes(const DwShape &s);
 // partial sums of d and d^2 laid out [C][N].  a1_store (optional) receives swish(bn1(e)).
 // With `fin` non-null (only when dw_fwd_finalizes_bn1 says so) the kernel derives bn1 from fin's
 // partial sums and writes it to fin->bn_out; psum/psq must not overlap fin's partials.
+// With `ev` non-null (evaluation mode) there are no partial sums, and of bn1 only whether it is null counts.
 bool dw_fwd_finalizes_bn1(const DwShape &s, bool stores_a1);
 hipError_t launch_dw_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
                          const void *w_dw, void *d, float *psum, float *psq, void *a1_store,
-                         const BnFin *fin, hipStream_t st);
+                         const BnFin *fin, const DwEval *ev, hipStream_t st);
 
 // Per plane of d: z = mean swish(y2), s3 = sum swish'(y2), s4 = sum swish'(y2)*dhat.
 // With `fin` non-null (only when plane_channel_form says so) the kernel derives bn2 from fin's partial

@@ -68,9 +68,9 @@ __device__ __forceinline__ void x3_split8(const float (&v)[8], uint32_t (&p)[4][
     }
 }
 
-// One tile (64 rows x 32 k) of a weight image, by a workgroup of 256 threads: thread -> (row tid/4,
-// eight k at 8*(tid%4)).  The layout: kernels_x3.hip.
-__device__ __forceinline__ void x3_prep_tile(const X3PrepArgs &a, int tile)
+// One tile (64 rows x 32 k) of a weight image, by 256 threads: thread -> (row tid/4, eight k at
+// 8*(tid%4)).  The layout: kernels_x3.hip.
+__device__ __forceinline__ void x3_prep_tile(const X3PrepArgs &a, int tile, int tid)
 {
     int si = 0;
 #pragma unroll
@@ -79,7 +79,7 @@ __device__ __forceinline__ void x3_prep_tile(const X3PrepArgs &a, int tile)
             si = i;
     const X3PrepSet S = a.s[si];
     const int local = tile - S.firstTile, mt = local / S.CH, ch = local % S.CH;
-    const int tid = threadIdx.x, r = tid >> 2, g = tid & 3;
+    const int r = tid >> 2, g = tid & 3;
     const int m = mt * 64 + r, k0 = ch * 32 + 8 * g;
     float v[8];
 #pragma unroll
