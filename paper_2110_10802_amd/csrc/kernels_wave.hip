@@ -1224,8 +1224,7 @@ hipError_t launch_projbwd_fused(bool bf16, int N, int Cw, int Cn, int HW, const 
     // wide sides of up to three tiles (96 channels): a wavefront per pixel chunk.  (Measured with
     // five and six tiles, 144 and 192 channels: the accumulator tiles of all of them plus the
     // prefetch registers no longer fit two wavefronts per SIMD without spilling, and the
-    // workgroup-per-chunk kernel is faster there.  The expansion conv's fused backward in this form
-    // measured no faster than bwd1x1_lt on 16 -> 96 channels, 164 against 169 us, and was dropped.)
+    // workgroup-per-chunk kernel is faster there.)
     const int ntw = (Cw + 31) / 32;
     if (fin && ntw <= 3) {
         const size_t wv_lds = sizeof(float) * (4 * 2 * 32 * kLtPitch + 96 + 2 * 32 * ntw + (size_t)ntw * 16 * 64);
@@ -1282,23 +1281,18 @@ hipError_t launch_projbwd_fused(bool bf16, int N, int Cw, int Cn, int HW, const 
 #undef MBK_CASE
 }
 
-// kernels_x3.hip
-bool bwd1x1_x3_supported(int Cw, int Cn, int HW);
-hipError_t launch_bwd1x1_x3(int N, int Cw, int Cn, int HW, const Operand &de, const void *xin,
-                            const void *w, void *dx, const void *res, float *partial, int splits,
-                            hipStream_t st);
-
-#ifndef MBK_X3B
-#define MBK_X3B 1
-#endif
+// kernels_bwd1x1.hip
+bool bwd1x1_re_supported(int N, int Cw, int Cn, int HW);
+hipError_t launch_bwd1x1_re(int N, int Cw, int Cn, int HW, const Operand &de, const void *xin, const void *w, void *dx,
+                            const void *res, float *partial, int splits, int *used, hipStream_t st);
 // which matrix-core form serves the fused backward of this shape: 1 = fp32 MFMA (bwd1x1_lt),
-// 3 = three bf16 planes (bwd1x1_x3); 0: the shape is not fused
+// 3 = three bf16 planes (bwd1x1_re); 0: the shape is not fused
 int bwd1x1_fused_engine(bool bf16, int N, int Cw, int Cn, int HW)
 {
     int splits;
     if (!bwd1x1_fused_plan(N, Cw, Cn, HW, &splits))
         return 0;
-    return (!bf16 && MBK_X3B && bwd1x1_x3_supported(Cw, Cn, HW)) ? 3 : 1; // (bf16 storage: fp32 MFMA)
+    return !bf16 && bwd1x1_re_supported(N, Cw, Cn, HW) ? 3 : 1; // (bf16 storage: fp32 MFMA)
 }
 
 bool bwd1x1_fused_plan(int N, int Cw, int Cn, int HW, int *splits)
@@ -1317,12 +1311,9 @@ hipError_t launch_bwd1x1_fused(bool bf16, int N, int Cw, int Cn, int HW, const O
     int splits;
     if (!bwd1x1_fused_plan(N, Cw, Cn, HW, &splits) || de.pro != PRO_BNBWD)
         return hipErrorInvalidValue;
-    // fp32, at most 16 -> 96 channels: the wave-per-chunk kernel on the bf16 matrix cores
-    // (same partial-tile layout and count)
-    if (bwd1x1_fused_engine(bf16, N, Cw, Cn, HW) == 3) {
-        *splits_out = splits;
-        return launch_bwd1x1_x3(N, Cw, Cn, HW, de, xin, w, dx, res, partial, splits, st);
-    }
+    // fp32: the kernel that computes e again (same partial-tile layout)
+    if (!bf16 && bwd1x1_re_supported(N, Cw, Cn, HW))
+        return launch_bwd1x1_re(N, Cw, Cn, HW, de, xin, w, dx, res, partial, splits, splits_out, st);
     Bwd1x1Args b = {};
     WgradClArgs &a = b.g;
     a.N = N;
