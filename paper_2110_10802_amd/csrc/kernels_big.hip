@@ -1,12 +1,10 @@
-// 1x1 convolutions and their weight gradients for the wide blocks (tens to a thousand
-// channels on both sides), where the contraction is long enough to be bound by the matrix
+// 1x1 convolutions for the wide blocks (tens to a thousand channels on both sides), where the contraction is long enough to be bound by the matrix
 // cores rather than by HBM.
 //
 // The batch is flattened: the GEMM column index is q = n*HW + pixel over all images, so small
 // planes (14x14, 7x7) fill whole tiles.  A workgroup of four waves owns a (64*WT) x (64*WT) output
 // tile, every wave a (32*WT) x (32*WT) block of v_mfma_f32_32x32x2_f32 accumulators; the
-// contraction is consumed 16 (convolution) or 32 (weight gradient) at a time through two LDS
-// buffers: the global loads of chunk i+1 are issued before the MFMAs of chunk i and land in LDS
+// contraction is consumed 16 at a time through two LDS buffers: the global loads of chunk i+1 are issued before the MFMAs of chunk i and land in LDS
 // after them, so one barrier per chunk suffices.  The activation operand goes through its
 // elementwise prologue on the way into LDS (Swish(BN(.))*gate, or the BN-backward expression),
 // so these intermediates never exist in HBM (sections "Local Data Movement Reduction" and
@@ -654,304 +652,6 @@ hipError_t launch_big_conv1x1(bool bf16, int N, int M, int K, int HW, const void
                                         psq, qtiles, st)
                 : splitk_finish<float>(splitk_ws, splits, M, a.Q, HW, out, res, user_epi, psum, psq,
                                        qtiles, st);
-}
-
-// ---- weight gradient -------------------------------------------------------------------
-// dW[a,b] = sum_q op(U)[a,q] * op(V)[b,q]: both operands are pixel-contiguous in memory and
-// the matrix cores want the channel index across lanes, so both tiles are transposed on their
-// way into LDS ([q][channel], pitch = 2 mod 8 keeps the scalar stores 2-way at worst).  The
-// contraction is split over blockIdx.z; each split writes its own partial tile and a
-// fixed-order second stage adds them (no atomics: the map-fission step of section "Guided
-// Optimization Case Study: EfficientNet").
-
-struct BigWgradArgs {
-    int Ma, Mb, HW;
-    uint32_t Q;
-    int chunksPerSplit; // chunks of 32 pixels
-    FastDiv divHW;
-    BigOperand U, V;
-    float *partial;
-};
-
-// (bx, by, bz: tile of U rows, tile of V rows, split; Us, Vs: the LDS buffers)
-template <typename T, int PROU, int PROV, int WA, int WB, int VEC>
-__device__ __forceinline__ void wgrad_big_body(const BigWgradArgs &a, int bx, int by, int bz,
-                                               float (*Us)[32][64 * WA + 2], float (*Vs)[32][64 * WB + 2])
-{
-    constexpr int BA = 64 * WA, BB = 64 * WB, BQ = 32;
-    constexpr int QCOLS = BQ / VEC;     // runs per operand row
-    constexpr int RROWS = 256 / QCOLS;  // rows staged per pass
-    constexpr int NRU = BA / RROWS, NRV = BB / RROWS; // runs per thread of U and of V
-    // two LDS buffers, except for the 128x128 tile, where two would exceed 64 KiB
-    constexpr int NBUF = (WA == 2 && WB == 2) ? 1 : 2;
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wa = wave >> 1, wb = wave & 1;
-    const int a0 = bx * BA, b0 = by * BB;
-    const int numChunks = (int)((a.Q + BQ - 1) / BQ);
-    const int cbeg = bz * a.chunksPerSplit;
-    const int cend = min(cbeg + a.chunksPerSplit, numChunks);
-
-    const int qcol = tid % QCOLS, rrow = tid / QCOLS;
-    Staged<PROU, VEC> ru[NRU];
-    Staged<PROV, VEC> rv[NRV];
-    // per-row coefficients do not depend on the chunk (rows past the end keep zeros, which
-    // make apply() return 0 for zero data)
-#pragma unroll
-    for (int i = 0; i < NRU; ++i) {
-        const int ra = a0 + rrow + RROWS * i;
-        ru[i].zero();
-        if (PROU != PRO_NONE && ra < a.Ma) {
-            ru[i].k0 = a.U.c0[ra];
-            ru[i].k1 = a.U.c1[ra];
-            if (PROU == PRO_BNBWD)
-                ru[i].k2 = a.U.c2[ra];
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < NRV; ++i) {
-        const int rb = b0 + rrow + RROWS * i;
-        rv[i].zero();
-        if (PROV != PRO_NONE && rb < a.Mb) {
-            rv[i].k0 = a.V.c0[rb];
-            rv[i].k1 = a.V.c1[rb];
-            if (PROV == PRO_BNBWD)
-                rv[i].k2 = a.V.c2[rb];
-        }
-    }
-    // Unconditional loads with clamped indices (see conv_big_kernel): rows past the end read
-    // the last row, a run past the end reads pixel 0; both are zeroed by an AND mask on their
-    // way into LDS, so there is no branch between a load and its use.
-    uint32_t umask[NRU], vmask[NRV], qmask = 0u;
-#pragma unroll
-    for (int i = 0; i < NRU; ++i)
-        umask[i] = a0 + rrow + RROWS * i < a.Ma ? 0xffffffffu : 0u;
-#pragma unroll
-    for (int i = 0; i < NRV; ++i)
-        vmask[i] = b0 + rrow + RROWS * i < a.Mb ? 0xffffffffu : 0u;
-    auto load = [&](int chunk) __attribute__((always_inline)) {
-        const uint32_t q = (uint32_t)chunk * BQ + (uint32_t)qcol * VEC;
-        const bool valid = q < a.Q;
-        qmask = valid ? 0xffffffffu : 0u;
-        const uint32_t qc = valid ? q : 0u;
-        const uint32_t n = fdiv(qc, a.divHW);
-        const uint32_t pix = qc - n * (uint32_t)a.HW;
-#pragma unroll
-        for (int i = 0; i < NRU; ++i) {
-            const int ra = min(a0 + rrow + RROWS * i, a.Ma - 1);
-            ru[i].template load<T>(a.U, ((size_t)n * a.Ma + ra) * a.HW + pix);
-            if (PROU == PRO_BNSWISH_GATE)
-                ru[i].k2 = a.U.gate[(size_t)n * a.Ma + ra];
-        }
-#pragma unroll
-        for (int i = 0; i < NRV; ++i) {
-            const int rb = min(b0 + rrow + RROWS * i, a.Mb - 1);
-            rv[i].template load<T>(a.V, ((size_t)n * a.Mb + rb) * a.HW + pix);
-            if (PROV == PRO_BNSWISH_GATE)
-                rv[i].k2 = a.V.gate[(size_t)n * a.Mb + rb];
-        }
-    };
-    auto store = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < NRU; ++i) {
-#pragma unroll
-            for (int j = 0; j < VEC; ++j)
-                Us[buf][qcol * VEC + j][rrow + RROWS * i] = and_mask(ru[i].apply(j), qmask & umask[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < NRV; ++i) {
-#pragma unroll
-            for (int j = 0; j < VEC; ++j)
-                Vs[buf][qcol * VEC + j][rrow + RROWS * i] = and_mask(rv[i].apply(j), qmask & vmask[i]);
-        }
-    };
-
-    float16v acc[WA][WB];
-#pragma unroll
-    for (int i = 0; i < WA; ++i)
-#pragma unroll
-        for (int j = 0; j < WB; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                acc[i][j][r] = 0.f;
-
-    if (cbeg < cend) { // uniform over the workgroup; an empty split writes zeros
-        load(cbeg);
-        store(0);
-        __syncthreads();
-        for (int c = cbeg; c < cend; ++c) {
-            const int buf = NBUF == 2 ? (c - cbeg) & 1 : 0;
-            load(min(c + 1, cend - 1)); // the repeated last chunk is stored but never consumed
-#pragma unroll
-            for (int kk = 0; kk < BQ; kk += 2) {
-                float av[WA], bv[WB];
-#pragma unroll
-                for (int i = 0; i < WA; ++i)
-                    av[i] = Us[buf][kk + (lane >> 5)][wa * 32 * WA + 32 * i + (lane & 31)];
-#pragma unroll
-                for (int j = 0; j < WB; ++j)
-                    bv[j] = Vs[buf][kk + (lane >> 5)][wb * 32 * WB + 32 * j + (lane & 31)];
-#pragma unroll
-                for (int i = 0; i < WA; ++i)
-#pragma unroll
-                    for (int j = 0; j < WB; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
-            }
-            if (NBUF == 1)
-                __syncthreads();
-            store(NBUF == 2 ? buf ^ 1 : 0);
-            __syncthreads();
-        }
-    }
-    float *dst = a.partial + (size_t)bz * a.Ma * a.Mb;
-#pragma unroll
-    for (int i = 0; i < WA; ++i)
-#pragma unroll
-        for (int j = 0; j < WB; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int ai = a0 + wa * 32 * WA + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                const int bi = b0 + wb * 32 * WB + 32 * j + (lane & 31);
-                if (ai < a.Ma && bi < a.Mb)
-                    dst[(size_t)ai * a.Mb + bi] = acc[i][j][r];
-            }
-}
-
-template <typename T, int PROU, int PROV, int WA, int WB, int VEC>
-__global__ __launch_bounds__(256) void wgrad_big_kernel(BigWgradArgs a)
-{
-    constexpr int NBUF = (WA == 2 && WB == 2) ? 1 : 2;
-    __shared__ __attribute__((aligned(16))) float Us[NBUF][32][64 * WA + 2];
-    __shared__ __attribute__((aligned(16))) float Vs[NBUF][32][64 * WB + 2];
-    wgrad_big_body<T, PROU, PROV, WA, WB, VEC>(a, (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, Us, Vs);
-}
-
-// Two weight gradients of one block in one launch (64 x 64 tiles, no run vectorisation: the 7x7
-// stages): the launches are a few hundred workgroups each and bound by the latency of their own
-// load-stage-multiply chain, so together they fill the wavefront slots either leaves empty.
-// The first gridA workgroups work on `a` (projection conv: dp x gated activation), the others on
-// `b` (expansion conv: de x block input); tiles and splits are decoded from the linear index.
-template <typename T>
-__global__ __launch_bounds__(256) void wgrad_big_pair_kernel(BigWgradArgs a, BigWgradArgs b, int gridA)
-{
-    __shared__ __attribute__((aligned(16))) float Us[2][32][66];
-    __shared__ __attribute__((aligned(16))) float Vs[2][32][66];
-    if ((int)blockIdx.x < gridA) { // uniform over the workgroup
-        const int i = (int)blockIdx.x, ta = (a.Ma + 63) / 64, tb = (a.Mb + 63) / 64;
-        wgrad_big_body<T, PRO_BNBWD, PRO_BNSWISH_GATE, 1, 1, 1>(a, i % ta, (i / ta) % tb, i / (ta * tb), Us, Vs);
-    } else {
-        const int i = (int)blockIdx.x - gridA, ta = (b.Ma + 63) / 64, tb = (b.Mb + 63) / 64;
-        wgrad_big_body<T, PRO_BNBWD, PRO_NONE, 1, 1, 1>(b, i % ta, (i / ta) % tb, i / (ta * tb), Us, Vs);
-    }
-}
-
-// `wt` packs the tile factors as 4*WA + WB.
-bool big_wgrad_plan(int Ma, int Mb, int N, int HW, int *wt, int *splits)
-{
-    const long long Q = (long long)N * HW;
-    if (Q >= (1ll << 31))
-        return false;
-    // measured: 64x64 tiles with many contraction splits beat larger tiles on every shape of
-    // the late EfficientNet stages (workgroups in flight hide the staging latency)
-    const int wa = 1, wb = 1;
-    *wt = 4 * wa + wb;
-    const long long tiles = (long long)((Ma + 63) / 64) * ((Mb + 63) / 64);
-    const long long chunks = (Q + 31) / 32;
-    long long s = (640 + tiles - 1) / tiles;
-    const long long smax = (chunks + 3) / 4; // at least four chunks per split
-    if (s > smax)
-        s = smax;
-    if (s < 1)
-        s = 1;
-    const long long per = (chunks + s - 1) / s;
-    *splits = (int)((chunks + per - 1) / per);
-    return true;
-}
-
-template <typename T, int WA, int WB, int VEC>
-static hipError_t big_wgrad_dispatch(const BigWgradArgs &a, int pu, int pv, dim3 grid, hipStream_t st)
-{
-#define MBK_CASE(PU, PV)                                                                          \
-    if (pu == PU && pv == PV) {                                                                   \
-        hipLaunchKernelGGL((wgrad_big_kernel<T, PU, PV, WA, WB, VEC>), grid, dim3(256), 0, st, a); \
-        return hipGetLastError();                                                                 \
-    }
-    MBK_CASE(PRO_BNBWD, PRO_NONE)
-    MBK_CASE(PRO_BNBWD, PRO_BNSWISH_GATE)
-#undef MBK_CASE
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_big_wgrad(bool bf16, int N, int Ma, int Mb, int HW, const Operand &U,
-                            const Operand &V, float *partial, int *splits_out, hipStream_t st)
-{
-    int wt, splits;
-    if (!big_wgrad_plan(Ma, Mb, N, HW, &wt, &splits))
-        return hipErrorInvalidValue;
-    const int wa = wt >> 2, wb = wt & 3;
-    BigWgradArgs a;
-    a.Ma = Ma;
-    a.Mb = Mb;
-    a.HW = HW;
-    a.Q = (uint32_t)((long long)N * HW);
-    const int chunks = (int)((a.Q + 31u) / 32u);
-    a.chunksPerSplit = (chunks + splits - 1) / splits;
-    a.divHW = make_div((uint32_t)HW);
-    a.U = to_big(U);
-    a.V = to_big(V);
-    a.partial = partial;
-    *splits_out = splits;
-    dim3 grid((unsigned)((Ma + 64 * wa - 1) / (64 * wa)), (unsigned)((Mb + 64 * wb - 1) / (64 * wb)),
-              (unsigned)splits);
-    const bool v4 = HW % 4 == 0;
-#define MBK_GO(TT)                                                                                \
-    (!v4 ? big_wgrad_dispatch<TT, 1, 1, 1>(a, U.pro, V.pro, grid, st)                             \
-         : big_wgrad_dispatch<TT, 1, 1, 4>(a, U.pro, V.pro, grid, st))
-    if (wa != 1 || wb != 1)
-        return hipErrorInvalidValue;
-    return bf16 ? MBK_GO(bf16_t) : MBK_GO(float);
-#undef MBK_GO
-}
-
-// The pair of launch_big_wgrad calls (A: U = BN-backward operand, V = gated activation; B: U =
-// BN-backward operand, V = plain) in one launch; hipErrorNotSupported (nothing launched) for
-// other operand kinds, tile shapes or plane sizes that are a multiple of four.
-hipError_t launch_big_wgrad_pair(bool bf16, int N, int MaA, int MbA, int HWA, const Operand &UA,
-                                 const Operand &VA, float *partialA, int *splitsA, int MaB, int MbB,
-                                 int HWB, const Operand &UB, const Operand &VB, float *partialB,
-                                 int *splitsB, hipStream_t st)
-{
-    int wta, wtb, sa, sb;
-    if (!big_wgrad_plan(MaA, MbA, N, HWA, &wta, &sa) || !big_wgrad_plan(MaB, MbB, N, HWB, &wtb, &sb))
-        return hipErrorNotSupported;
-    if (wta != 5 || wtb != 5 || HWA % 4 == 0 || HWB % 4 == 0 || UA.pro != PRO_BNBWD ||
-        VA.pro != PRO_BNSWISH_GATE || UB.pro != PRO_BNBWD || VB.pro != PRO_NONE)
-        return hipErrorNotSupported;
-    const auto fill = [N](BigWgradArgs &a, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
-                          float *partial, int splits) {
-        a.Ma = Ma;
-        a.Mb = Mb;
-        a.HW = HW;
-        a.Q = (uint32_t)((long long)N * HW);
-        const int chunks = (int)((a.Q + 31u) / 32u);
-        a.chunksPerSplit = (chunks + splits - 1) / splits;
-        a.divHW = make_div((uint32_t)HW);
-        a.U = to_big(U);
-        a.V = to_big(V);
-        a.partial = partial;
-        return ((Ma + 63) / 64) * ((Mb + 63) / 64) * splits;
-    };
-    BigWgradArgs a, b;
-    const int ga = fill(a, MaA, MbA, HWA, UA, VA, partialA, sa);
-    const int gb = fill(b, MaB, MbB, HWB, UB, VB, partialB, sb);
-    *splitsA = sa;
-    *splitsB = sb;
-    if (bf16)
-        hipLaunchKernelGGL(wgrad_big_pair_kernel<bf16_t>, dim3((unsigned)(ga + gb)), dim3(256), 0, st, a, b, ga);
-    else
-        hipLaunchKernelGGL(wgrad_big_pair_kernel<float>, dim3((unsigned)(ga + gb)), dim3(256), 0, st, a, b, ga);
-    return hipGetLastError();
 }
 
 } // namespace mbk

@@ -209,9 +209,13 @@ size_t big_conv_splitk_floats(int N, int M, int K, int HW);
 hipError_t launch_big_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w, int sAm,
                               int sAk, const Operand &B, void *out, int epi, const void *res,
                               float *psum, float *psq, float *splitk_ws, hipStream_t st);
-bool big_wgrad_plan(int Ma, int Mb, int N, int HW, int *wt, int *splits);
-hipError_t launch_big_wgrad(bool bf16, int N, int Ma, int Mb, int HW, const Operand &U,
-                            const Operand &V, float *partial, int *splits_out, hipStream_t st);
+// kernels_wgr.hip
+bool wgr_plan(bool bf16, int Ma, int Mb, int N, int HW, int *splits);
+hipError_t launch_wgr(bool bf16, int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V, float *partial,
+                      int *splits_out, hipStream_t st);
+hipError_t launch_wgr_pair(bool bf16, int N, int MaA, int MbA, int HWA, const Operand &UA, const Operand &VA,
+                           float *partialA, int *splitsA, int MaB, int MbB, int HWB, const Operand &UB,
+                           const Operand &VB, float *partialB, int *splitsB, hipStream_t st);
 
 // kernels_bf.hip
 bool bf_conv_plan(int N, int M, int K, int HW, int *qtiles, int *splits);
@@ -234,11 +238,6 @@ hipError_t launch_x3_wgrad_pair(int N, int MaA, int MbA, int HWA, const Operand 
 #ifndef MBK_X3PAIR
 #define MBK_X3PAIR 1
 #endif
-// kernels_big.hip
-hipError_t launch_big_wgrad_pair(bool bf16, int N, int MaA, int MbA, int HWA, const Operand &UA,
-                                 const Operand &VA, float *partialA, int *splitsA, int MaB, int MbB,
-                                 int HWB, const Operand &UB, const Operand &VB, float *partialB,
-                                 int *splitsB, hipStream_t st);
 bool xw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt);
 hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm, int sAk, const Operand &B,
                              void *out, int epi, float *psum, float *psq, hipStream_t st);
@@ -499,8 +498,7 @@ int wgrad_splits(bool bf16, int Ma, int Mb, int N, int HW)
         return splits;
     if (bf16 && bf_wgrad_plan(Ma, Mb, N, HW, &splits))
         return splits;
-    int wt;
-    if (big_wgrad_plan(Ma, Mb, N, HW, &wt, &splits))
+    if (wgr_plan(bf16, Ma, Mb, N, HW, &splits))
         return splits;
     const long long Q = (long long)N * HW;
     const long long chunk = wgrad_chunk(Ma, Mb, Q);
@@ -644,24 +642,23 @@ static hipError_t wgrad_dispatch(const WgradArgs &a, int pu, int pv, dim3 grid, 
 // where both are shapes of the split-operand kernel; the sums over their splits are described in
 // *ra and *rb for the caller to launch.  hipErrorNotSupported (nothing was launched) unless
 // wgrad1x1_pair_supported holds.
-// 1: both are shapes of the split-operand kernel; 2: both go to the 64 x 64-tile kernel of
-// kernels_big.hip with planes that are not a multiple of four pixels (the 7x7 stages); 0: no pair (also a
-// stride from a plane of the first kernel into one of the second, 14x14 -> 7x7)
+// 1: both are shapes of the split-operand kernel; 2: both go to the kernel of kernels_wgr.hip (the 7x7
+// stages); 0: no pair (also a stride from a plane of the first kernel into one of the second, 14x14 -> 7x7)
 static int wgrad1x1_pair_kind(bool bf16, int N, int MaA, int MbA, int HWA, int MaB, int MbB, int HWB)
 {
     if (!MBK_X3PAIR)
         return 0;
-    int s, wt;
+    int s;
     bool swap;
     const bool xa = MBK_X3W && !bf16 && x3_wgrad_plan(MaA, MbA, N, HWA, &s);
     const bool xb = MBK_X3W && !bf16 && x3_wgrad_plan(MaB, MbB, N, HWB, &s);
     if (xa && xb)
         return 1;
-    const auto big = [&](bool x3, int Ma, int Mb, int HW) {
-        return !x3 && HW % 4 != 0 && !wgrad_cl_plan(Ma, Mb, N, HW, &swap, &s) &&
-               !(bf16 && bf_wgrad_plan(Ma, Mb, N, HW, &s)) && big_wgrad_plan(Ma, Mb, N, HW, &wt, &s) && wt == 5;
+    const auto rest = [&](bool x3, int Ma, int Mb, int HW) {
+        return !x3 && !wgrad_cl_plan(Ma, Mb, N, HW, &swap, &s) && !(bf16 && bf_wgrad_plan(Ma, Mb, N, HW, &s)) &&
+               wgr_plan(bf16, Ma, Mb, N, HW, &s);
     };
-    return big(xa, MaA, MbA, HWA) && big(xb, MaB, MbB, HWB) ? 2 : 0;
+    return rest(xa, MaA, MbA, HWA) && rest(xb, MaB, MbB, HWB) ? 2 : 0;
 }
 bool wgrad1x1_pair_supported(bool bf16, int N, int MaA, int MbA, int HWA, int MaB, int MbB, int HWB)
 {
@@ -688,13 +685,8 @@ hipError_t launch_wgrad1x1_pair(bool bf16, int N, int MaA, int MbA, int HWA, con
                 e = launch_x3_wgrad(N, MaB, MbB, HWB, UB, VB, partialB, &sb, st);
         }
     } else {
-        e = launch_big_wgrad_pair(bf16, N, MaA, MbA, HWA, UA, VA, partialA, &sa, MaB, MbB, HWB, UB, VB,
-                                  partialB, &sb, st);
-        if (e == hipErrorNotSupported) {
-            e = launch_big_wgrad(bf16, N, MaA, MbA, HWA, UA, VA, partialA, &sa, st);
-            if (e == hipSuccess)
-                e = launch_big_wgrad(bf16, N, MaB, MbB, HWB, UB, VB, partialB, &sb, st);
-        }
+        e = launch_wgr_pair(bf16, N, MaA, MbA, HWA, UA, VA, partialA, &sa, MaB, MbB, HWB, UB, VB, partialB, &sb,
+                            st);
     }
     if (e != hipSuccess)
         return e;
@@ -737,9 +729,8 @@ hipError_t launch_wgrad1x1(bool bf16, int N, int Ma, int Mb, int HW, const Opera
                 return e;
             return finish(splits);
         }
-        int wt;
-        if (big_wgrad_plan(Ma, Mb, N, HW, &wt, &splits)) {
-            hipError_t e = launch_big_wgrad(bf16, N, Ma, Mb, HW, U, V, partial, &splits, st);
+        if (wgr_plan(bf16, Ma, Mb, N, HW, &splits)) {
+            hipError_t e = launch_wgr(bf16, N, Ma, Mb, HW, U, V, partial, &splits, st);
             if (e != hipSuccess)
                 return e;
             return finish(splits);
