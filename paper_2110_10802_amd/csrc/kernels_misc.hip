@@ -351,22 +351,6 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
     }
 }
 
-// channel slices per image so that a wide block launches a few hundred workgroups
-static int se_slices(int N, int C)
-{
-    int G = (512 + N - 1) / N;
-    const int maxG = (C + 63) / 64;
-    if (G > maxG)
-        G = maxG;
-    if (G > 8)
-        G = 8;
-    return G < 1 ? 1 : G;
-}
-static bool se_wide(int C, int Cse)
-{
-    return C >= 256 && C <= 2048 && C % 4 == 0 && Cse % 4 == 0 && Cse <= 64;
-}
-
 hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, const float *w1, const float *b1,
                          const float *w2, const float *b2, float *q, float *g, hipStream_t st)
 {
@@ -510,188 +494,152 @@ __global__ __launch_bounds__(256) void se_bwd_batch_kernel(SeBwdArgs a)
     }
 }
 
-// Wide-block variants of the two SE backward kernels (Cse % 4 == 0, Cse <= 64).
-// Per (image, channel slice): dt for every channel, dq by a [C x Cse] sweep of W2 with float4
-// loads (a thread owns four consecutive j of every RP-th row; row groups are combined in LDS in
-// a fixed order), then dzs for the slice.
-__global__ __launch_bounds__(256) void se_bwd_image_wide_kernel(SeBwdArgs a, int slice)
+// The two steps for 4 to 64 squeezed channels.  Both are a chain of memory round trips and nothing else, so
+// every load of a kernel (of a round, for large batches and channel counts) is requested before the first
+// is used, no product is computed twice, and what does not depend on each other has workgroups of its own.
+//
+// Step 1: a workgroup per image and sixteen squeezed channels.  dt = dg*g*(1-g) for all channels (the first
+// slice stores it), dq = (W2^T dt)*swish'(q): four threads read 64 bytes of a row of W2, 64 rows at a
+// time.  (1152 channels, 48 squeezed, 64 images, step 1 and 2: 11.8 + 8.1 us with the whole of W2 in every one of
+// eight slices of channels and the dzs of a slice behind it; now 5.0 + 5.1, little above an
+// empty launch.  672, 28, 128 images: 7.5 + 13.1 then, 4.8 + 5.7 now.)
+__global__ __launch_bounds__(256) void se_bwd_dq_kernel(SeBwdArgs a)
 {
-    extern __shared__ float lds[];
-    const int C = a.C, Cse = a.Cse;
-    float *dts = lds, *dqs = lds + C, *red = dqs + Cse; // red: [RP][Cse]
-    const int n = blockIdx.x, part = blockIdx.y, tid = threadIdx.x;
-    for (int c = tid; c < C; c += 256) {
-        const float gv = a.g[(size_t)n * C + c];
-        const float v = a.dg[(size_t)n * C + c] * gv * (1.f - gv);
-        dts[c] = v;
-        if (part == 0)
-            a.dt[(size_t)n * C + c] = v;
-    }
-    __syncthreads();
-    const int JQ = Cse >> 2, RP = 256 / JQ;
-    const int jq = tid % JQ, r0 = tid / JQ;
-    if (r0 < RP) {
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int cb = r0; cb < C; cb += 16 * RP) { // 16 independent loads per round
-            float4 w[16];
+    constexpr int U = 12; // rows in flight
+    __shared__ float red[4][16];
+    const int C = a.C, Cse = a.Cse, n = blockIdx.x, j0 = 16 * blockIdx.y;
+    const int tid = threadIdx.x, part = tid & 3, row = tid >> 2;
+    // (a piece that would end past the row is moved back; what it shares with the piece before it counts there)
+    const int want = j0 + 4 * part, at = min(want, Cse - 4);
+    const float *dg = a.dg + (size_t)n * C, *gt = a.g + (size_t)n * C;
+    const float qv = a.q[(size_t)n * Cse + min(j0 + (tid & 15), Cse - 1)];
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int c0 = row; c0 < C; c0 += 64 * U) {
+        f32x4u w[U];
+        float dv[U], gv[U];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int c = cb + u * RP;
-                w[u] = c < C ? *reinterpret_cast<const float4 *>(a.w2 + (size_t)c * Cse + 4 * jq)
-                             : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+        for (int u = 0; u < U; ++u) {
+            const int c = min(c0 + 64 * u, C - 1);
+            dv[u] = dg[c];
+            gv[u] = gt[c];
+            w[u] = *reinterpret_cast<const f32x4u *>(a.w2 + (size_t)c * Cse + at);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int c = cb + u * RP;
-                const float d = c < C ? dts[c] : 0.f;
-                acc.x = fmaf(w[u].x, d, acc.x);
-                acc.y = fmaf(w[u].y, d, acc.y);
-                acc.z = fmaf(w[u].z, d, acc.z);
-                acc.w = fmaf(w[u].w, d, acc.w);
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + 64 * u;
+            if (c < C) {
+                const float dt = dv[u] * gv[u] * (1.f - gv[u]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc[e] = fmaf(w[u][e], dt, acc[e]);
+                if (j0 == 0 && part == 0)
+                    a.dt[(size_t)n * C + c] = dt;
             }
         }
-        *reinterpret_cast<float4 *>(red + (size_t)r0 * Cse + 4 * jq) = acc;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1)
+            acc[e] += __shfl_xor(acc[e], o, kWave);
+        // element e of the piece is squeezed channel at + e
+        const int j = at + e - j0;
+        if ((tid & 63) < 4 && at + e >= want && j < 16)
+            red[tid >> 6][j] = acc[e];
     }
     __syncthreads();
-    if (tid < Cse) {
-        float s = 0.f;
-        for (int r = 0; r < RP; ++r)
-            s += red[(size_t)r * Cse + tid];
+    if (tid < 16 && j0 + tid < Cse) {
         float val, grad;
-        swish_both(a.q[(size_t)n * Cse + tid], val, grad);
-        const float v = s * grad;
-        dqs[tid] = v;
-        if (part == 0)
-            a.dq[(size_t)n * Cse + tid] = v;
-    }
-    __syncthreads();
-    const float inv = 1.f / (float)a.HW;
-    const int cend = min(C, (part + 1) * slice);
-    for (int c = part * slice + tid; c < cend; c += 256) {
-        float acc = 0.f;
-        for (int j0 = 0; j0 < Cse; j0 += 16) { // sixteen unconditional loads per round
-            float w[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                w[u] = a.w1[(size_t)min(j0 + u, Cse - 1) * C + c];
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                acc = fmaf(j0 + u < Cse ? w[u] : 0.f, dqs[min(j0 + u, Cse - 1)], acc);
-        }
-        a.dzs[(size_t)n * C + c] = acc * inv;
+        swish_both(qv, val, grad);
+        a.dq[(size_t)n * Cse + j0 + tid] = ((red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid])) * grad;
     }
 }
 
-// Sums over the batch for a tile of 16 channels: thread (c, jq) owns dW2[c][4jq..4jq+3] and
-// dW1[4jq..4jq+3][c]; the batch is walked 32 images at a time through LDS, always in the same
-// order, and the j-contiguous operands are read as one 16-byte LDS access per image.  The
-// per-channel sums (db2, BN2's dbeta/dgamma/coef) are split over the 16 jq groups and combined
-// in a fixed order.  The three kinds of sums are independent chains of memory round trips and
-// there are far fewer channel tiles than compute units, so each kind has workgroups of its own
-// (blockIdx.y: 0 the weight gradients, 1 the per-channel sums, 2 db1 in one workgroup) and the
-// launch lasts as long as the longest chain, not their sum.
-__global__ __launch_bounds__(256) void se_bwd_batch_wide_kernel(SeBwdArgs a)
+// Step 2.  The first `chan` workgroups own sixteen channels: dzs = (W1^T dq)/HW for every image, and the batch
+// sums of the channel: db2 = sum dt, BN2's dbeta = sum g*A1 + dzs*s3, dgamma = sum g*A2 + dzs*s4 and coefficients.
+// The next `fc` have a tile of sixteen channels by sixteen squeezed ones per wavefront, of both weight
+// gradients: dW2[c][j] = sum_n dt[n][c]*swish(q[n][j]), dW1[j][c] = sum_n dq[n][j]*z[n][c], fp32 MFMA on four
+// images at a time, operands straight from memory.  The last adds db1[j] = sum_n dq[n][j].
+__global__ __launch_bounds__(256) void se_bwd_sums_kernel(SeBwdArgs a, int chan, int fc)
 {
-    constexpr int TC = 16, TN = 32, JQ = 16; // Cse <= 4*JQ
-    __shared__ float dtL[TN][TC], zL[TN][TC];
-    __shared__ __attribute__((aligned(16))) float rL[TN][4 * JQ], dqL[TN][4 * JQ];
-    __shared__ float sbL[JQ][TC];
-    __shared__ double dbL[JQ][TC], dgL[JQ][TC];
+    constexpr int TN = 64; // images a round
+    __shared__ __attribute__((aligned(16))) float dqL[TN][64], w1L[64][16];
+    __shared__ float sbL[16][16];
+    __shared__ double dbL[16][16], dgL[16][16];
     const int C = a.C, Cse = a.Cse, N = a.N;
-    const int tid = threadIdx.x, cl = tid & 15, jq = tid >> 4;
-    const int c0 = blockIdx.x * TC, c = c0 + cl;
-    const int role = blockIdx.y;
-    if (role == 0) {
-        float acc2[4] = {0.f, 0.f, 0.f, 0.f}, acc1[4] = {0.f, 0.f, 0.f, 0.f};
-        // A round's loads (all in flight together, clamped addresses and masks instead of branches)
-        // are issued one round ahead: they travel while the previous round is multiplied.
-        float t0[2], t1[2], t2[8], t3[8];
-        const auto fetch = [&](int n0) {
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < chan) {
+        const int cl = tid & 15, nl = tid >> 4, c = 16 * blockIdx.x + cl, cc = min(c, C - 1);
+        const int J4 = (Cse + 3) / 4;
+        const float inv = 1.f / (float)a.HW;
+        float wv[4];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int i = tid + 256 * u, nn = i >> 4, cc = i & 15;
-                const bool ok = n0 + nn < N && c0 + cc < C;
-                const size_t at = ok ? (size_t)(n0 + nn) * C + c0 + cc : 0;
-                t0[u] = and_mask(a.dt[at], ok ? 0xffffffffu : 0u);
-                t1[u] = and_mask(a.z[at], ok ? 0xffffffffu : 0u);
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = tid + 256 * u, nn = i >> 6, j = i & 63;
-                const bool ok = n0 + nn < N && j < Cse;
-                const size_t at = ok ? (size_t)(n0 + nn) * Cse + j : 0;
-                t2[u] = and_mask(a.q[at], ok ? 0xffffffffu : 0u);
-                t3[u] = and_mask(a.dq[at], ok ? 0xffffffffu : 0u);
-            }
-        };
-        fetch(0);
+        for (int u = 0; u < 4; ++u) // W1's column, squeezed channel nl + 16u
+            wv[u] = and_mask(a.w1[(size_t)min(nl + 16 * u, Cse - 1) * C + cc], nl + 16 * u < Cse ? 0xffffffffu : 0u);
+        const float gm = a.gamma2[cc], mean = a.bn2[2 * C + cc], rstd = a.bn2[3 * C + cc];
+        float sb = 0.f;
+        double dbeta = 0.0, dgamma = 0.0;
         for (int n0 = 0; n0 < N; n0 += TN) {
-            __syncthreads();
+            // the round's dq, [image][squeezed channel], and the channel's own values of four images a thread
+            float dv[TN * 64 / 256], dt[4], g[4], A1[4], A2[4], s3[4], s4[4];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int i = tid + 256 * u;
-                dtL[i >> 4][i & 15] = t0[u];
-                zL[i >> 4][i & 15] = t1[u];
+            for (int u = 0; u < TN * 64 / 256; ++u) {
+                const int nn = (tid >> 6) + 4 * u, j = tid & 63;
+                dv[u] = a.dq[(size_t)min(n0 + nn, N - 1) * Cse + min(j, Cse - 1)];
             }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = tid + 256 * u;
-                rL[i >> 6][i & 63] = (i & 63) < Cse ? swishf(t2[u]) : 0.f;
-                dqL[i >> 6][i & 63] = t3[u];
-            }
-            if (n0 + TN < N)
-                fetch(n0 + TN);
-            __syncthreads();
-#pragma unroll 8
-            for (int nn = 0; nn < TN; ++nn) {
-                const float dtv = dtL[nn][cl], zv = zL[nn][cl];
-                const float4 r4 = *reinterpret_cast<const float4 *>(&rL[nn][4 * jq]);
-                const float4 q4 = *reinterpret_cast<const float4 *>(&dqL[nn][4 * jq]);
-                acc2[0] = fmaf(dtv, r4.x, acc2[0]);
-                acc2[1] = fmaf(dtv, r4.y, acc2[1]);
-                acc2[2] = fmaf(dtv, r4.z, acc2[2]);
-                acc2[3] = fmaf(dtv, r4.w, acc2[3]);
-                acc1[0] = fmaf(q4.x, zv, acc1[0]);
-                acc1[1] = fmaf(q4.y, zv, acc1[1]);
-                acc1[2] = fmaf(q4.z, zv, acc1[2]);
-                acc1[3] = fmaf(q4.w, zv, acc1[3]);
-            }
-        }
-        if (c < C) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int j = 4 * jq + u;
-                if (j < Cse) {
-                    a.dw2[(size_t)c * Cse + j] = acc2[u];
-                    a.dw1[(size_t)j * C + c] = acc1[u];
+                const size_t o = (size_t)min(n0 + nl + 16 * u, N - 1) * C + cc;
+                dt[u] = a.dt[o];
+                g[u] = a.g[o];
+                A1[u] = a.A1[o];
+                A2[u] = a.A2[o];
+                s3[u] = a.s3[o];
+                s4[u] = a.s4[o];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < TN * 64 / 256; ++u)
+                dqL[(tid >> 6) + 4 * u][tid & 63] = dv[u];
+            if (n0 == 0) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    w1L[nl + 16 * u][cl] = wv[u];
+            }
+            __syncthreads();
+            float dz[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int j4 = 0; j4 < J4; ++j4) { // (past the last squeezed channel the weights are zero)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float4 d4 = *reinterpret_cast<const float4 *>(&dqL[nl + 16 * u][4 * j4]);
+                    dz[u] = fmaf(w1L[4 * j4][cl], d4.x, dz[u]);
+                    dz[u] = fmaf(w1L[4 * j4 + 1][cl], d4.y, dz[u]);
+                    dz[u] = fmaf(w1L[4 * j4 + 2][cl], d4.z, dz[u]);
+                    dz[u] = fmaf(w1L[4 * j4 + 3][cl], d4.w, dz[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int n = n0 + nl + 16 * u;
+                if (n < N && c < C) {
+                    const float d = dz[u] * inv;
+                    a.dzs[(size_t)n * C + c] = d;
+                    sb += dt[u];
+                    dbeta += (double)g[u] * A1[u] + (double)d * s3[u];
+                    dgamma += (double)g[u] * A2[u] + (double)d * s4[u];
                 }
             }
         }
-    } else if (role == 1) {
-        // per-channel sums: the 16 thread groups take every 16th image, then group 0 adds the
-        // partial sums in order
-        float sb = 0.f;
-        double dbeta = 0.0, dgamma = 0.0;
-        if (c < C) {
-#pragma unroll 8
-            for (int n = jq; n < N; n += JQ) {
-                const size_t o = (size_t)n * C + c;
-                const float dtv = a.dt[o], gv = a.g[o], a1 = a.A1[o], a2 = a.A2[o];
-                const float dz = a.dzs[o], s3 = a.s3[o], s4 = a.s4[o];
-                sb += dtv;
-                dbeta += (double)gv * a1 + (double)dz * s3;
-                dgamma += (double)gv * a2 + (double)dz * s4;
-            }
-        }
-        sbL[jq][cl] = sb;
-        dbL[jq][cl] = dbeta;
-        dgL[jq][cl] = dgamma;
+        sbL[nl][cl] = sb;
+        dbL[nl][cl] = dbeta;
+        dgL[nl][cl] = dgamma;
         __syncthreads();
-        if (jq == 0 && c < C) {
+        if (nl == 0 && c < C) {
             sb = 0.f;
             dbeta = dgamma = 0.0;
-            for (int u = 0; u < JQ; ++u) {
+            for (int u = 0; u < 16; ++u) {
                 sb += sbL[u][cl];
                 dbeta += dbL[u][cl];
                 dgamma += dgL[u][cl];
@@ -699,38 +647,71 @@ __global__ __launch_bounds__(256) void se_bwd_batch_wide_kernel(SeBwdArgs a)
             a.db2[c] = sb;
             a.dbeta2[c] = (float)dbeta;
             a.dgamma2[c] = (float)dgamma;
-            bn_bwd_coef(C, c, (double)N * a.HW, dgamma, dbeta, a.gamma2[c], a.bn2, a.coef2);
+            bn_bwd_coef_vals(C, c, (double)N * a.HW, dgamma, dbeta, gm, mean, rstd, a.coef2);
         }
-    } else if (blockIdx.x == 0) {
-        // db1[j] = sum_n dq[n][j]: four thread groups take every fourth image (sixteen loads in
-        // flight each: a plain loop would pay one memory round trip per image), combined in a
-        // fixed order
-        __shared__ float db1L[4][64];
-        const int j = tid & 63, part = tid >> 6;
-        float s = 0.f;
-        if (j < Cse) {
-#pragma unroll 16
-            for (int n = part; n < N; n += 4)
-                s += a.dq[(size_t)n * Cse + j];
-        }
-        db1L[part][j] = s;
-        __syncthreads();
-        if (tid < Cse)
-            a.db1[tid] = (db1L[0][tid] + db1L[1][tid]) + (db1L[2][tid] + db1L[3][tid]);
+        return;
     }
+    if ((int)blockIdx.x < chan + fc) {
+        const int lane = tid & 63, r = lane & 15, g = lane >> 4, JT = (Cse + 15) / 16;
+        const int tile = 4 * ((int)blockIdx.x - chan) + __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int c0 = 16 * (tile / JT), j0 = 16 * (tile % JT);
+        if (c0 >= C)
+            return;
+        const int c = min(c0 + r, C - 1), j = min(j0 + r, Cse - 1);
+        f32x4 acc2 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc2;
+        for (int n0 = 0; n0 < N; n0 += 32) {
+            float dt[8], z[8], q[8], dq[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const size_t n = (size_t)min(n0 + 4 * u + g, N - 1);
+                dt[u] = a.dt[n * C + c];
+                z[u] = a.z[n * C + c];
+                q[u] = a.q[n * Cse + j];
+                dq[u] = a.dq[n * Cse + j];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool ok = n0 + 4 * u + g < N;
+                acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? dt[u] : 0.f, ok ? swishf(q[u]) : 0.f, acc2, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? dq[u] : 0.f, ok ? z[u] : 0.f, acc1, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (c0 + 4 * g + v < C && j0 + r < Cse)
+                a.dw2[(size_t)(c0 + 4 * g + v) * Cse + j0 + r] = acc2[v];
+            if (j0 + 4 * g + v < Cse && c0 + r < C)
+                a.dw1[(size_t)(j0 + 4 * g + v) * C + c0 + r] = acc1[v];
+        }
+        return;
+    }
+    // db1: four thread groups take every fourth image (sixteen loads in flight each), combined in a fixed order
+    const int j = tid & 63, part = tid >> 6;
+    float s = 0.f;
+    if (j < Cse) {
+#pragma unroll 16
+        for (int n = part; n < N; n += 4)
+            s += a.dq[(size_t)n * Cse + j];
+    }
+    dqL[part][j] = s;
+    __syncthreads();
+    if (tid < Cse)
+        a.db1[tid] = (dqL[0][tid] + dqL[1][tid]) + (dqL[2][tid] + dqL[3][tid]);
 }
 
 hipError_t launch_se_bwd(const SeBwdArgs &a, hipStream_t st)
 {
-    if (se_wide(a.C, a.Cse)) {
-        const int G = se_slices(a.N, a.C), slice = (a.C + G - 1) / G;
-        const int RP = 256 / (a.Cse / 4);
-        const size_t lds = sizeof(float) * ((size_t)a.C + a.Cse + (size_t)RP * a.Cse);
-        hipLaunchKernelGGL(se_bwd_image_wide_kernel, dim3(a.N, G), dim3(256), lds, st, a, slice);
-        hipError_t e = hipGetLastError();
+    // (few channels of few images: the plain kernels' shorter chain; backward of a block, plain / here, 96
+    // channels, 2 images 38.0 / 39.1 us, 32 images 44.7 / 45.0; 144, 8 images 37.7 / 38.0, 32 images 158 / 157; 240, 2
+    // images 46.5 / 45.8)
+    if (a.Cse >= 4 && a.Cse <= 64 && (a.C >= 160 || (long long)a.N * a.C >= 4096)) {
+        hipLaunchKernelGGL(se_bwd_dq_kernel, dim3(a.N, (a.Cse + 15) / 16), dim3(256), 0, st, a);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
-        hipLaunchKernelGGL(se_bwd_batch_wide_kernel, dim3((a.C + 15) / 16, 3), dim3(256), 0, st, a);
+        const int chan = (a.C + 15) / 16, fc = (chan * ((a.Cse + 15) / 16) + 3) / 4;
+        hipLaunchKernelGGL(se_bwd_sums_kernel, dim3(chan + fc + 1), dim3(256), 0, st, a, chan, fc);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(se_bwd_image_kernel, dim3(a.N), dim3(256), sizeof(float) * (a.C + a.Cse), st,

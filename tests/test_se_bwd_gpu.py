@@ -1,0 +1,21 @@
+"""Squeeze-and-excitation backward: rows of W2 read in overlapping pieces, tiles of sixteen channels and squeezed
+channels that are not full, batches of less than, exactly and more than a round of 64 images, and the plain
+kernels of few channels, against the oracle at the tolerances of parity_util."""
+import pytest
+
+from mbconv_inputs import BlockShape, make_block_inputs
+from oracle import oracle as orc
+from parity_util import compare_block, run_gpu_block
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,C,Cse", [(2, 160, 4), (64, 70, 5), (65, 170, 17), (3, 787, 33), (130, 161, 6),
+                                     (2, 1154, 63), (9, 200, 64), (7, 60, 4), (6, 300, 3), (4, 40, 70)])
+def test_gradients_match_oracle(N, C, Cse):
+    s = BlockShape(N=N, Cin=C, H=4, W=4, Cexp=C, Cse=Cse, Cout=16, k=3, stride=1, has_expand=False)
+    t = make_block_inputs(s, seed=C + Cse)
+    print(f"[se bwd] {s}", flush=True)
+    res, blk = run_gpu_block(s, t)
+    f, b = orc.mbconv_step(s, t)
+    compare_block(s, t, res, f, b, blk)
