@@ -1,5 +1,5 @@
-// bf16 storage on the bf16 matrix cores: 1x1 convolutions and weight gradients for the wide
-// blocks when activations and conv weights are stored as bf16 (benchmark config 3).
+// bf16 storage on the bf16 matrix cores: 1x1 convolutions of the wide blocks when activations and conv
+// weights are stored as bf16 (benchmark config 3).
 //
 // Same decomposition as kernels_big.hip (flattened batch, 64-pixel output tiles per workgroup of
 // four wavefronts, two LDS buffers fed from a two-slot register ring, fixed-order split
@@ -496,282 +496,6 @@ hipError_t launch_bf_conv1x1(int N, int M, int K, int HW, const void *w, int sAm
     MBK_CASE(EPI_NONE)
     MBK_CASE(EPI_STATS)
     MBK_CASE(EPI_RES)
-#undef MBK_CASE
-    return hipErrorInvalidValue;
-}
-
-// ---- weight gradient -------------------------------------------------------------------------
-// dW[a,b] = sum_q op(U)[a,q] * op(V)[b,q]: both operands are pixel-contiguous, which is exactly
-// the [row][k] layout the instruction wants, so the tiles go into LDS untransposed (8-byte runs
-// of four pixels per thread).  64 pixels per chunk; the contraction is split over blockIdx.z.
-struct BfWgradArgs {
-    int Ma, Mb, HW;
-    uint32_t Q;
-    int chunksPerSplit; // chunks of 64 pixels
-    int tilesA, tilesB, splits;
-    FastDiv divHW;
-    BfOperand U, V;
-    float *partial;
-};
-
-// A workgroup owns 64*WA rows of U by 64*WB rows of V; each wavefront 32*WA by 32*WB.  A tile
-// that spans all rows of the narrow operand stages the wide one (and evaluates its prologue)
-// only once in the whole grid.
-template <int PROU, int PROV, int WA, int WB>
-__global__ __launch_bounds__(256) void wgrad_bf_kernel(BfWgradArgs a)
-{
-    constexpr int BA = 64 * WA, BB = 64 * WB, BQ = 64, PQ = BQ + 8;
-    constexpr int NU = 4 * WA, NV = 4 * WB; // 16 rows per pass
-    __shared__ __attribute__((aligned(16))) uint16_t Us[2][BA][PQ];
-    __shared__ __attribute__((aligned(16))) uint16_t Vs[2][BB][PQ];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wa = wave >> 1, wb = wave & 1;
-    // workgroups that read the same pixels (all tiles of one split) run on the same XCD
-    // (blockIdx.x mod 8), so the operand that several tiles share comes out of that XCD's L2
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int tiles = a.tilesA * a.tilesB;
-    const int split = (slot / tiles) * 8 + xcd, tile = slot % tiles;
-    if (split >= a.splits)
-        return;
-    const int a0 = (tile % a.tilesA) * BA, b0 = (tile / a.tilesA) * BB;
-    const int numChunks = (int)((a.Q + BQ - 1) / BQ);
-    const int cbeg = split * a.chunksPerSplit;
-    const int cend = min(cbeg + a.chunksPerSplit, numChunks);
-
-    const int qg = tid & 15, rrow = tid >> 4;
-    float uk[NU][3], vk[NV][3];
-    uint32_t umask[NU], vmask[NV];
-#pragma unroll
-    for (int i = 0; i < NU; ++i) {
-        const int ra = a0 + rrow + 16 * i;
-        umask[i] = ra < a.Ma ? 0xffffffffu : 0u;
-        uk[i][0] = uk[i][1] = uk[i][2] = 0.f;
-        if (PROU != PRO_NONE && ra < a.Ma) {
-            uk[i][0] = a.U.c0[ra];
-            uk[i][1] = a.U.c1[ra];
-            if (PROU == PRO_BNBWD)
-                uk[i][2] = a.U.c2[ra];
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int rb = b0 + rrow + 16 * i;
-        vmask[i] = rb < a.Mb ? 0xffffffffu : 0u;
-        vk[i][0] = vk[i][1] = vk[i][2] = 0.f;
-        if (PROV != PRO_NONE && rb < a.Mb) {
-            vk[i][0] = a.V.c0[rb];
-            vk[i][1] = a.V.c1[rb];
-            if (PROV == PRO_BNBWD)
-                vk[i][2] = a.V.c2[rb];
-        }
-    }
-    // Ring of two register slots (see conv_bf_kernel): unconditional clamped loads, validity as
-    // an AND mask on the way into LDS.
-    uint2 u0[2][NU], u1[2][NU], v0[2][NV], v1[2][NV];
-    float ug[2][NU], vg[2][NV];
-    uint32_t qmask[2];
-    auto load = [&](int slot, int chunk) __attribute__((always_inline)) {
-        const uint32_t q = (uint32_t)chunk * BQ + 4u * qg;
-        const bool valid = q < a.Q;
-        qmask[slot] = valid ? 0xffffffffu : 0u;
-        const uint32_t qc = valid ? q : 0u;
-        const uint32_t n = fdiv(qc, a.divHW);
-        const uint32_t pix = qc - n * (uint32_t)a.HW;
-#pragma unroll
-        for (int i = 0; i < NU; ++i) {
-            const int ra = min(a0 + rrow + 16 * i, a.Ma - 1);
-            const size_t iu = ((size_t)n * a.Ma + ra) * a.HW + pix;
-            u0[slot][i] = *reinterpret_cast<const uint2 *>(a.U.p0 + iu);
-            if (PROU == PRO_BNBWD)
-                u1[slot][i] = *reinterpret_cast<const uint2 *>(a.U.p1 + iu);
-            if (PROU == PRO_BNSWISH_GATE)
-                ug[slot][i] = a.U.gate[(size_t)n * a.Ma + ra];
-        }
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int rb = min(b0 + rrow + 16 * i, a.Mb - 1);
-            const size_t iv = ((size_t)n * a.Mb + rb) * a.HW + pix;
-            v0[slot][i] = *reinterpret_cast<const uint2 *>(a.V.p0 + iv);
-            if (PROV == PRO_BNBWD)
-                v1[slot][i] = *reinterpret_cast<const uint2 *>(a.V.p1 + iv);
-            if (PROV == PRO_BNSWISH_GATE)
-                vg[slot][i] = a.V.gate[(size_t)n * a.Mb + rb];
-        }
-    };
-    auto store = [&](int slot, int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < NU; ++i) {
-            const int row = rrow + 16 * i;
-            const uint32_t mk = qmask[slot] & umask[i];
-            if (PROU == PRO_NONE) {
-                *reinterpret_cast<uint2 *>(&Us[buf][row][4 * qg]) = make_uint2(u0[slot][i].x & mk, u0[slot][i].y & mk);
-            } else {
-                float x0[4], x1[4] = {0.f, 0.f, 0.f, 0.f}, y[4];
-                bf_unpack4(u0[slot][i], x0);
-                if (PROU == PRO_BNBWD)
-                    bf_unpack4(u1[slot][i], x1);
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    y[r] = and_mask(bf_apply<PROU>(x0[r], x1[r], uk[i][0], uk[i][1],
-                                                   PROU == PRO_BNSWISH_GATE ? ug[slot][i] : uk[i][2]), mk);
-                *reinterpret_cast<uint2 *>(&Us[buf][row][4 * qg]) =
-                    make_uint2(bf_pack2(y[0], y[1]), bf_pack2(y[2], y[3]));
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int row = rrow + 16 * i;
-            const uint32_t mk = qmask[slot] & vmask[i];
-            if (PROV == PRO_NONE) {
-                *reinterpret_cast<uint2 *>(&Vs[buf][row][4 * qg]) = make_uint2(v0[slot][i].x & mk, v0[slot][i].y & mk);
-            } else {
-                float x0[4], x1[4] = {0.f, 0.f, 0.f, 0.f}, y[4];
-                bf_unpack4(v0[slot][i], x0);
-                if (PROV == PRO_BNBWD)
-                    bf_unpack4(v1[slot][i], x1);
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    y[r] = and_mask(bf_apply<PROV>(x0[r], x1[r], vk[i][0], vk[i][1],
-                                                   PROV == PRO_BNSWISH_GATE ? vg[slot][i] : vk[i][2]), mk);
-                *reinterpret_cast<uint2 *>(&Vs[buf][row][4 * qg]) =
-                    make_uint2(bf_pack2(y[0], y[1]), bf_pack2(y[2], y[3]));
-            }
-        }
-    };
-
-    float16v acc[WA][WB];
-#pragma unroll
-    for (int i = 0; i < WA; ++i)
-#pragma unroll
-        for (int j = 0; j < WB; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                acc[i][j][r] = 0.f;
-    if (cbeg < cend) { // uniform over the workgroup; an empty split writes zeros
-        load(0, cbeg);
-        load(1, min(cbeg + 1, cend - 1));
-        store(0, 0);
-        __syncthreads();
-        auto step = [&](int u, int cc) __attribute__((always_inline)) {
-            const int buf = (cc - cbeg) & 1;
-            load(u, min(cc + 2, cend - 1)); // slot u is free: its chunk went to LDS last iteration
-#pragma unroll
-            for (int s = 0; s < BQ / 16; ++s) {
-                bf16x8 av[WA], bv[WB];
-#pragma unroll
-                for (int i = 0; i < WA; ++i)
-                    av[i] = bf_lds8(&Us[buf][wa * 32 * WA + 32 * i + (lane & 31)][16 * s + 8 * (lane >> 5)]);
-#pragma unroll
-                for (int j = 0; j < WB; ++j)
-                    bv[j] = bf_lds8(&Vs[buf][wb * 32 * WB + 32 * j + (lane & 31)][16 * s + 8 * (lane >> 5)]);
-#pragma unroll
-                for (int i = 0; i < WA; ++i)
-#pragma unroll
-                    for (int j = 0; j < WB; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
-            }
-            store(u ^ 1, buf ^ 1); // the repeated last chunk is stored but never consumed
-            __syncthreads();
-        };
-        const int turns = (cend - cbeg) / 2;
-        int cc = cbeg;
-        for (int g = 0; g < turns; ++g) {
-            step(0, cc);
-            step(1, cc + 1);
-            cc += 2;
-        }
-        if ((cend - cbeg) & 1)
-            step(0, cc);
-    }
-    float *dst = a.partial + (size_t)split * a.Ma * a.Mb;
-#pragma unroll
-    for (int i = 0; i < WA; ++i)
-#pragma unroll
-        for (int j = 0; j < WB; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int ai = a0 + wa * 32 * WA + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                const int bi = b0 + wb * 32 * WB + 32 * j + (lane & 31);
-                if (ai < a.Ma && bi < a.Mb)
-                    dst[(size_t)ai * a.Mb + bi] = acc[i][j][r];
-            }
-}
-
-// Tile shape.  A narrow second operand (65-128 rows: the block input of the expansion weight
-// gradient) is covered by one 128-row tile, so the wide first operand is staged once in the whole
-// grid (measured 45 against 54 us on 672 x 112 channels, batch 128, 14x14); the mirrored shape
-// (narrow first operand) measured slower than 64 x 64 and is not used.
-static void bf_wgrad_tile(int Ma, int Mb, int *wa, int *wb)
-{
-    (void)Ma;
-    *wa = 1;
-    *wb = (Mb > 64 && Mb <= 128) ? 2 : 1;
-}
-
-bool bf_wgrad_plan(int Ma, int Mb, int N, int HW, int *splits)
-{
-    const long long Q = (long long)N * HW;
-    if (HW % 4 != 0 || Q >= (1ll << 31))
-        return false;
-    int wa, wb;
-    bf_wgrad_tile(Ma, Mb, &wa, &wb);
-    const long long tiles = (long long)((Ma + 64 * wa - 1) / (64 * wa)) * ((Mb + 64 * wb - 1) / (64 * wb));
-    const long long chunks = (Q + 63) / 64;
-    long long s = (640 + tiles - 1) / tiles;
-    const long long smax = (chunks + 3) / 4; // at least four chunks per split
-    if (s > smax)
-        s = smax;
-    if (s < 1)
-        s = 1;
-    const long long per = (chunks + s - 1) / s;
-    *splits = (int)((chunks + per - 1) / per);
-    return true;
-}
-
-hipError_t launch_bf_wgrad(int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
-                           float *partial, int *splits_out, hipStream_t st)
-{
-    int splits;
-    if (!bf_wgrad_plan(Ma, Mb, N, HW, &splits))
-        return hipErrorInvalidValue;
-    BfWgradArgs a;
-    a.Ma = Ma;
-    a.Mb = Mb;
-    a.HW = HW;
-    a.Q = (uint32_t)((long long)N * HW);
-    const int chunks = (int)((a.Q + 63u) / 64u);
-    a.chunksPerSplit = (chunks + splits - 1) / splits;
-    a.divHW = make_div((uint32_t)HW);
-    a.U.p0 = (const bf16_t *)U.p0;
-    a.U.p1 = (const bf16_t *)U.p1;
-    a.U.c0 = U.c0;
-    a.U.c1 = U.c1;
-    a.U.c2 = U.c2;
-    a.U.gate = U.gate;
-    a.V.p0 = (const bf16_t *)V.p0;
-    a.V.p1 = (const bf16_t *)V.p1;
-    a.V.c0 = V.c0;
-    a.V.c1 = V.c1;
-    a.V.c2 = V.c2;
-    a.V.gate = V.gate;
-    a.partial = partial;
-    *splits_out = splits;
-    int wa, wb;
-    bf_wgrad_tile(Ma, Mb, &wa, &wb);
-    a.tilesA = (Ma + 64 * wa - 1) / (64 * wa);
-    a.tilesB = (Mb + 64 * wb - 1) / (64 * wb);
-    a.splits = splits;
-    dim3 grid((unsigned)(((splits + 7) / 8) * 8 * a.tilesA * a.tilesB));
-#define MBK_CASE(PU, PV, A, B)                                                                    \
-    if (U.pro == PU && V.pro == PV && wa == A && wb == B) {                                       \
-        hipLaunchKernelGGL((wgrad_bf_kernel<PU, PV, A, B>), grid, dim3(256), 0, st, a);           \
-        return hipGetLastError();                                                                 \
-    }
-#define MBK_TILES(PU, PV) MBK_CASE(PU, PV, 1, 1) MBK_CASE(PU, PV, 1, 2)
-    MBK_TILES(PRO_BNBWD, PRO_NONE)
-    MBK_TILES(PRO_BNBWD, PRO_BNSWISH_GATE)
-#undef MBK_TILES
 #undef MBK_CASE
     return hipErrorInvalidValue;
 }

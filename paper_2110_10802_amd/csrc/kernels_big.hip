@@ -1,11 +1,11 @@
-// 1x1 convolutions for the wide blocks (tens to a thousand channels on both sides), where the contraction is long enough to be bound by the matrix
-// cores rather than by HBM.
+// 1x1 convolutions for the wide blocks (tens to a thousand channels on both sides), where the
+// contraction is long enough to be bound by the matrix cores rather than by HBM.
 //
 // The batch is flattened: the GEMM column index is q = n*HW + pixel over all images, so small
 // planes (14x14, 7x7) fill whole tiles.  A workgroup of four waves owns a (64*WT) x (64*WT) output
 // tile, every wave a (32*WT) x (32*WT) block of v_mfma_f32_32x32x2_f32 accumulators; the
-// contraction is consumed 16 at a time through two LDS buffers: the global loads of chunk i+1 are issued before the MFMAs of chunk i and land in LDS
-// after them, so one barrier per chunk suffices.  The activation operand goes through its
+// contraction is consumed 16 at a time through two LDS buffers: the global loads of chunk i+1 are
+// issued before the MFMAs of chunk i and land in LDS after them, so one barrier per chunk suffices.  The activation operand goes through its
 // elementwise prologue on the way into LDS (Swish(BN(.))*gate, or the BN-backward expression),
 // so these intermediates never exist in HBM (sections "Local Data Movement Reduction" and
 // "Backpropagation and Data Movement").  Workgroups that share an activation tile are placed on

@@ -223,15 +223,12 @@ size_t bf_conv_splitk_floats(int N, int M, int K, int HW);
 hipError_t launch_bf_conv1x1(int N, int M, int K, int HW, const void *w, int sAm, int sAk,
                              const Operand &B, void *out, int epi, const void *res, float *psum,
                              float *psq, float *splitk_ws, hipStream_t st);
-bool bf_wgrad_plan(int Ma, int Mb, int N, int HW, int *splits);
-hipError_t launch_bf_wgrad(int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
-                           float *partial, int *splits_out, hipStream_t st);
 
 // kernels_x3.hip
-bool x3_wgrad_plan(int Ma, int Mb, int N, int HW, int *splits);
-hipError_t launch_x3_wgrad(int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
+bool x3_wgrad_plan(bool bf16, int Ma, int Mb, int N, int HW, int *splits);
+hipError_t launch_x3_wgrad(bool bf16, int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
                            float *partial, int *splits_out, hipStream_t st);
-hipError_t launch_x3_wgrad_pair(int N, int MaA, int MbA, int HWA, const Operand &UA, const Operand &VA,
+hipError_t launch_x3_wgrad_pair(bool bf16, int N, int MaA, int MbA, int HWA, const Operand &UA, const Operand &VA,
                                 float *partialA, int *splitsA, int MaB, int MbB, int HWB,
                                 const Operand &UB, const Operand &VB, float *partialB, int *splitsB,
                                 hipStream_t st);
@@ -245,9 +242,6 @@ hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm
 bool xk_conv_plan(bool bf16, int N, int M, int K, int HW, int pro, int *chunks);
 hipError_t launch_xk_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w, int sAm, int sAk,
                              const void *wimg, const Operand &B, void *out, int epi, const void *res, float *psum, float *psq, hipStream_t st);
-#ifndef MBK_X3W
-#define MBK_X3W 1
-#endif
 
 // short contraction, many rows, a role the kernel has: weights resident in LDS (conv_xw)
 static bool xw_applies(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi,
@@ -288,12 +282,10 @@ int wgrad1x1_engine(bool bf16, int Ma, int Mb, int N, int HW)
 {
     bool swap;
     int splits;
-    if (MBK_X3W && !bf16 && x3_wgrad_plan(Ma, Mb, N, HW, &splits))
-        return 3;
+    if (x3_wgrad_plan(bf16, Ma, Mb, N, HW, &splits))
+        return bf16 ? 2 : 3;
     if (wgrad_cl_plan(Ma, Mb, N, HW, &swap, &splits))
         return 1;
-    if (bf16 && bf_wgrad_plan(Ma, Mb, N, HW, &splits))
-        return 2;
     return 1;
 }
 
@@ -492,11 +484,9 @@ int wgrad_splits(bool bf16, int Ma, int Mb, int N, int HW)
 {
     bool swap;
     int splits;
-    if (MBK_X3W && !bf16 && x3_wgrad_plan(Ma, Mb, N, HW, &splits))
+    if (x3_wgrad_plan(bf16, Ma, Mb, N, HW, &splits))
         return splits;
     if (wgrad_cl_plan(Ma, Mb, N, HW, &swap, &splits))
-        return splits;
-    if (bf16 && bf_wgrad_plan(Ma, Mb, N, HW, &splits))
         return splits;
     if (wgr_plan(bf16, Ma, Mb, N, HW, &splits))
         return splits;
@@ -650,13 +640,12 @@ static int wgrad1x1_pair_kind(bool bf16, int N, int MaA, int MbA, int HWA, int M
         return 0;
     int s;
     bool swap;
-    const bool xa = MBK_X3W && !bf16 && x3_wgrad_plan(MaA, MbA, N, HWA, &s);
-    const bool xb = MBK_X3W && !bf16 && x3_wgrad_plan(MaB, MbB, N, HWB, &s);
+    const bool xa = x3_wgrad_plan(bf16, MaA, MbA, N, HWA, &s);
+    const bool xb = x3_wgrad_plan(bf16, MaB, MbB, N, HWB, &s);
     if (xa && xb)
         return 1;
     const auto rest = [&](bool x3, int Ma, int Mb, int HW) {
-        return !x3 && !wgrad_cl_plan(Ma, Mb, N, HW, &swap, &s) && !(bf16 && bf_wgrad_plan(Ma, Mb, N, HW, &s)) &&
-               wgr_plan(bf16, Ma, Mb, N, HW, &s);
+        return !x3 && !wgrad_cl_plan(Ma, Mb, N, HW, &swap, &s) && wgr_plan(bf16, Ma, Mb, N, HW, &s);
     };
     return rest(xa, MaA, MbA, HWA) && rest(xb, MaB, MbB, HWB) ? 2 : 0;
 }
@@ -675,14 +664,14 @@ hipError_t launch_wgrad1x1_pair(bool bf16, int N, int MaA, int MbA, int HWA, con
     int sa = 0, sb = 0;
     hipError_t e;
     if (kind == 1) {
-        e = launch_x3_wgrad_pair(N, MaA, MbA, HWA, UA, VA, partialA, &sa, MaB, MbB, HWB, UB, VB, partialB, &sb,
+        e = launch_x3_wgrad_pair(bf16, N, MaA, MbA, HWA, UA, VA, partialA, &sa, MaB, MbB, HWB, UB, VB, partialB, &sb,
                                  st);
         if (e == hipErrorNotSupported) {
             // a pair of kernel forms the launch does not have (e.g. a stored activation on the
             // projection side): one after the other
-            e = launch_x3_wgrad(N, MaA, MbA, HWA, UA, VA, partialA, &sa, st);
+            e = launch_x3_wgrad(bf16, N, MaA, MbA, HWA, UA, VA, partialA, &sa, st);
             if (e == hipSuccess)
-                e = launch_x3_wgrad(N, MaB, MbB, HWB, UB, VB, partialB, &sb, st);
+                e = launch_x3_wgrad(bf16, N, MaB, MbB, HWB, UB, VB, partialB, &sb, st);
         }
     } else {
         e = launch_wgr_pair(bf16, N, MaA, MbA, HWA, UA, VA, partialA, &sa, MaB, MbB, HWB, UB, VB, partialB, &sb,
@@ -711,20 +700,14 @@ hipError_t launch_wgrad1x1(bool bf16, int N, int Ma, int Mb, int HW, const Opera
     {
         bool swap;
         int splits;
-        if (MBK_X3W && !bf16 && x3_wgrad_plan(Ma, Mb, N, HW, &splits)) {
-            hipError_t e = launch_x3_wgrad(N, Ma, Mb, HW, U, V, partial, &splits, st);
+        if (x3_wgrad_plan(bf16, Ma, Mb, N, HW, &splits)) {
+            hipError_t e = launch_x3_wgrad(bf16, N, Ma, Mb, HW, U, V, partial, &splits, st);
             if (e != hipSuccess)
                 return e;
             return finish(splits);
         }
         if (wgrad_cl_plan(Ma, Mb, N, HW, &swap, &splits)) {
             hipError_t e = launch_wgrad_cl(bf16, N, Ma, Mb, HW, U, V, partial, &splits, st);
-            if (e != hipSuccess)
-                return e;
-            return finish(splits);
-        }
-        if (bf16 && bf_wgrad_plan(Ma, Mb, N, HW, &splits)) {
-            hipError_t e = launch_bf_wgrad(N, Ma, Mb, HW, U, V, partial, &splits, st);
             if (e != hipSuccess)
                 return e;
             return finish(splits);

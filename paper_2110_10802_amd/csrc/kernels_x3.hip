@@ -95,14 +95,57 @@ hipError_t launch_x3_prep(const X3PrepArgs &a, hipStream_t st)
 // through its prologue, once in the whole grid.  Chunks are loaded two iterations ahead into a
 // ring of two register slots, so HBM stays busy while a chunk is split and multiplied.  The
 // splits' partial tiles are added by a fixed-order second stage.
+//
+// bf16 storage (T = bf16_t): the same kernel with one plane per operand, rounded once after the fp32
+// prologue, and one MFMA per product block (the accumulation is fp32 either way).  128 images of 14x14,
+// 112 -> 672 -> 112: 75 us in two launches of 64-row tiles, 43 for the pair here; chunks of 64 pixels
+// 70, their registers spill.
+struct X3WgradOperand {
+    const void *p0, *p1;
+    const float *c0, *c1, *c2, *gate;
+};
 struct X3WgradArgs {
     int Ma, Mb, HW;
     uint32_t runs;      // runs of four pixels: (HW + 3)/4 per image
     int chunksPerSplit; // chunks of eight runs
     int tilesA, tilesB, splits;
     FastDiv divRuns; // by the runs of an image
-    X3Operand U, V;
+    X3WgradOperand U, V;
     float *partial;
+};
+
+constexpr int kWgRuns = 8; // runs of a chunk
+template <typename T>
+constexpr int kWgPlanes = sizeof(T) == 4 ? 3 : 1;
+// a run of four pixels as it comes from memory
+template <typename T>
+struct X3Run;
+template <>
+struct X3Run<float> {
+    float v[4];
+    template <bool RAG>
+    __device__ __forceinline__ void load(const void *p, size_t i)
+    {
+        if (RAG)
+            x3_ld4u((const float *)p, i, v);
+        else
+            x3_ld4((const float *)p, i, v);
+    }
+    __device__ __forceinline__ float get(int j) const { return v[j]; }
+};
+template <>
+struct X3Run<bf16_t> {
+    uint2 v;
+    template <bool RAG>
+    __device__ __forceinline__ void load(const void *p, size_t i)
+    {
+        v = *reinterpret_cast<const uint2 *>((const bf16_t *)p + i);
+    }
+    __device__ __forceinline__ float get(int j) const
+    {
+        const uint32_t w = j < 2 ? v.x : v.y;
+        return __uint_as_float(j & 1 ? w & 0xffff0000u : w << 16);
+    }
 };
 
 // What a thread keeps per operand for the whole kernel: rows rr + 64*i (i < NP) of the tile.  Rows past
@@ -114,8 +157,8 @@ struct X3RowConst {
     float k0[NP], k1[NP], k2[NP];
     int row[NP];
     uint32_t at[NP]; // offset of the row within an image
-    bool live[NP];   // uniform: the wavefront's eight rows of this pass are not all past the end
-    __device__ __forceinline__ void init(const X3Operand &o, int row0, int rr, int wave, int M, int HW)
+    bool live[NP];   // uniform: the wavefront's rows of this pass are not all past the end
+    __device__ __forceinline__ void init(const X3WgradOperand &o, int row0, int rr, int wave, int M, int HW)
     {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
@@ -134,14 +177,14 @@ struct X3RowConst {
     }
 };
 // one ring slot of an operand: the raw pixel runs (four pixels at 4*qg) of the thread's rows
-template <int PRO, int NP>
+template <typename T, int PRO, int NP>
 struct X3RowData {
-    float v0[NP][4], v1[NP][PRO == PRO_BNBWD ? 4 : 1];
+    X3Run<T> v0[NP], v1[PRO == PRO_BNBWD ? NP : 1];
     float g[NP];
     // n, pix: image and first pixel of the run (it lies inside one plane).  Both rows load, also past
     // the last row: a branch around a load would make the loads behind it wait.
     template <bool RAG>
-    __device__ __forceinline__ void load(const X3Operand &o, const X3RowConst<PRO, NP> &c, int M, uint32_t img,
+    __device__ __forceinline__ void load(const X3WgradOperand &o, const X3RowConst<PRO, NP> &c, int M, uint32_t img,
                                          uint32_t n, uint32_t pix)
     {
         const size_t base = (size_t)n * img + pix;
@@ -149,21 +192,14 @@ struct X3RowData {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const size_t idx = base + c.at[i];
-            if (RAG)
-                x3_ld4u(o.p0, idx, v0[i]);
-            else
-                x3_ld4(o.p0, idx, v0[i]);
-            if constexpr (PRO == PRO_BNBWD) {
-                if (RAG)
-                    x3_ld4u(o.p1, idx, v1[i]);
-                else
-                    x3_ld4(o.p1, idx, v1[i]);
-            }
+            v0[i].template load<RAG>(o.p0, idx);
+            if constexpr (PRO == PRO_BNBWD)
+                v1[i].template load<RAG>(o.p1, idx);
             if constexpr (PRO == PRO_BNSWISH_GATE)
                 g[i] = o.gate[gbase + (uint32_t)c.row[i]];
         }
     }
-    // prologue, split, three 8-byte LDS stores per row; MASK: pixel j survives under mask[j]
+    // prologue, split, an 8-byte LDS store per row and plane; MASK: pixel j survives under mask[j]
     template <bool MASK>
     __device__ __forceinline__ void store(const X3RowConst<PRO, NP> &c, uint16_t *planes, int rr, int qg,
                                           const uint32_t (&mask)[4]) const
@@ -175,18 +211,22 @@ struct X3RowData {
             float y[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                y[j] = x3_apply<PRO>(v0[i][j], v1[i][PRO == PRO_BNBWD ? j : 0], c.k0[i], c.k1[i],
-                                     PRO == PRO_BNSWISH_GATE ? g[i] : c.k2[i]);
+                y[j] = x3_apply<PRO>(v0[i].get(j), PRO == PRO_BNBWD ? v1[PRO == PRO_BNBWD ? i : 0].get(j) : 0.f, c.k0[i],
+                                     c.k1[i], PRO == PRO_BNSWISH_GATE ? g[i] : c.k2[i]);
                 if (MASK)
                     y[j] = and_mask(y[j], mask[j]);
             }
-            uint32_t w0[3], w1[3];
-            x3_split2(y[0], y[1], w0);
-            x3_split2(y[2], y[3], w1);
+            uint16_t *at = planes + x3_img_at(rr + 64 * i, 4 * qg);
+            if constexpr (kWgPlanes<T> == 1) {
+                *reinterpret_cast<uint2 *>(at) = make_uint2(bf16_pack2(y[0], y[1]), bf16_pack2(y[2], y[3]));
+            } else {
+                uint32_t w0[3], w1[3];
+                x3_split2(y[0], y[1], w0);
+                x3_split2(y[2], y[3], w1);
 #pragma unroll
-            for (int pl = 0; pl < 3; ++pl)
-                *reinterpret_cast<uint2 *>(planes + pl * (NP * 64 * 32) + x3_img_at(rr + 64 * i, 4 * qg)) =
-                    make_uint2(w0[pl], w1[pl]);
+                for (int pl = 0; pl < 3; ++pl)
+                    *reinterpret_cast<uint2 *>(at + pl * (NP * 64 * 32)) = make_uint2(w0[pl], w1[pl]);
+            }
         }
     }
 };
@@ -203,10 +243,11 @@ struct X3RowData {
 // These planes were the fp32 matrix cores' before, whose sums over many images are closer than those of
 // a single accumulator here (the bf16 MFMA truncates a small addend to a large accumulator), so the small
 // cross products have an accumulator of their own, on tiles of 128 x 64.
-template <int PROU, int PROV, int VB, bool TR, bool RAG>
+template <typename T, int PROU, int PROV, int VB, bool TR, bool RAG>
 __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uint16_t *Us, uint16_t *Vs)
 {
-    constexpr int BQ = 32, kPlane = 128 * 32, kPlaneV = VB * 32; // planes in the layout of x3_img_at
+    constexpr int QG = kWgRuns, NPL = kWgPlanes<T>, BQ = 4 * QG, NPU = 2, NPV = VB / 64;
+    constexpr int kPlane = 128 * 32, kPlaneV = VB * 32; // planes in the layout of x3_img_at
     constexpr int NA = VB == 128 ? 2 : 1;                        // 32-row blocks of U per wavefront
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -224,23 +265,23 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
     if (split >= a.splits)
         return;
     const int a0 = (tile % a.tilesA) * 128, b0 = (tile / a.tilesA) * VB;
-    const int numChunks = (int)((a.runs + BQ / 4 - 1) / (BQ / 4));
+    const int numChunks = (int)((a.runs + QG - 1) / QG);
     const int cbeg = split * a.chunksPerSplit;
     const int cend = min(cbeg + a.chunksPerSplit, numChunks);
-    const int qg = tid & 7, rr = tid >> 3;
-    X3RowConst<PROU, 2> cu;
-    X3RowConst<PROV, VB / 64> cv;
+    const int qg = tid % QG, rr = tid / QG;
+    X3RowConst<PROU, NPU> cu;
+    X3RowConst<PROV, NPV> cv;
     cu.init(a.U, a0, rr, wave, a.Ma, a.HW);
     cv.init(a.V, b0, rr, wave, a.Mb, a.HW);
     const uint32_t imgU = (uint32_t)a.Ma * (uint32_t)a.HW, imgV = (uint32_t)a.Mb * (uint32_t)a.HW;
     const bool work = a0 + ua < a.Ma && b0 + vb < a.Mb; // uniform: the wavefront's part is not all padding
-    X3RowData<PROU, 2> du[2];
-    X3RowData<PROV, VB / 64> dv[2];
+    X3RowData<T, PROU, NPU> du[2];
+    X3RowData<T, PROV, NPV> dv[2];
     uint32_t qmask[2] = {0u, 0u};
     int fresh[2] = {0, 0};
     // unconditional clamped loads; the validity of a pixel is an AND mask on V's way into LDS
     auto load = [&](int s, int chunk) __attribute__((always_inline)) {
-        const uint32_t run = (uint32_t)chunk * (BQ / 4) + (uint32_t)qg;
+        const uint32_t run = (uint32_t)chunk * QG + (uint32_t)qg;
         qmask[s] = run < a.runs ? 0xffffffffu : 0u;
         const uint32_t rc = qmask[s] ? run : 0u;
         const uint32_t n = fdiv(rc, a.divRuns);
@@ -281,9 +322,9 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
 #pragma unroll
                 for (int s = 0; s < BQ / 16; ++s) {
                     const int ko = 16 * s + 8 * (lane >> 5);
-                    bf16x8 av[NA][3], bv[3];
+                    bf16x8 av[NA][NPL], bv[NPL];
 #pragma unroll
-                    for (int pl = 0; pl < 3; ++pl) {
+                    for (int pl = 0; pl < NPL; ++pl) {
 #pragma unroll
                         for (int i = 0; i < NA; ++i)
                             av[i][pl] = x3_lds8(Us + pl * kPlane + x3_img_at(ua + 32 * i + (lane & 31), ko));
@@ -291,7 +332,9 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
                     }
 #pragma unroll
                     for (int i = 0; i < NA; ++i) {
-                        if (RAG) {
+                        if constexpr (NPL == 1) {
+                            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i][0], bv[0], acc[i], 0, 0, 0);
+                        } else if constexpr (RAG) {
                             low = x3_mfma5(av[i], bv, low);
                             acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i][0], bv[0], acc[i], 0, 0, 0);
                         } else {
@@ -325,51 +368,51 @@ __device__ __forceinline__ void wgrad_x3_body(const X3WgradArgs &a, int bid, uin
         }
 }
 
-template <int PROU, int PROV, int VB, bool TR, bool RAG>
+template <typename T, int PROU, int PROV, int VB, bool TR, bool RAG>
 __global__ __launch_bounds__(512) void wgrad_x3_kernel(X3WgradArgs a)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t Us[3 * 128 * 32];
-    __shared__ __attribute__((aligned(16))) uint16_t Vs[3 * VB * 32];
-    wgrad_x3_body<PROU, PROV, VB, TR, RAG>(a, (int)blockIdx.x, Us, Vs);
+    __shared__ __attribute__((aligned(16))) uint16_t Us[kWgPlanes<T> * 128 * 32];
+    __shared__ __attribute__((aligned(16))) uint16_t Vs[kWgPlanes<T> * VB * 32];
+    wgrad_x3_body<T, PROU, PROV, VB, TR, RAG>(a, (int)blockIdx.x, Us, Vs);
 }
 
 // The six forms of the kernel above, by number (x3_wgrad_variant).
-template <int VAR, bool RAG>
+template <typename T, int VAR, bool RAG>
 __device__ __forceinline__ void wgrad_x3_variant(const X3WgradArgs &a, int bid, uint16_t *Us, uint16_t *Vs)
 {
     if (VAR == 0)
-        wgrad_x3_body<PRO_BNBWD, PRO_NONE, 128, false, false>(a, bid, Us, Vs);
+        wgrad_x3_body<T, PRO_BNBWD, PRO_NONE, 128, false, false>(a, bid, Us, Vs);
     else if (VAR == 1)
-        wgrad_x3_body<PRO_BNBWD, PRO_BNSWISH_GATE, 128, false, false>(a, bid, Us, Vs);
+        wgrad_x3_body<T, PRO_BNBWD, PRO_BNSWISH_GATE, 128, false, false>(a, bid, Us, Vs);
     else if (VAR == 2)
-        wgrad_x3_body<PRO_BNBWD, PRO_NONE, 64, false, RAG>(a, bid, Us, Vs);
+        wgrad_x3_body<T, PRO_BNBWD, PRO_NONE, 64, false, RAG>(a, bid, Us, Vs);
     else if (VAR == 3)
-        wgrad_x3_body<PRO_BNBWD, PRO_BNSWISH_GATE, 64, false, RAG>(a, bid, Us, Vs);
+        wgrad_x3_body<T, PRO_BNBWD, PRO_BNSWISH_GATE, 64, false, RAG>(a, bid, Us, Vs);
     else if (VAR == 4)
-        wgrad_x3_body<PRO_NONE, PRO_BNBWD, 64, true, RAG>(a, bid, Us, Vs);
+        wgrad_x3_body<T, PRO_NONE, PRO_BNBWD, 64, true, RAG>(a, bid, Us, Vs);
     else
-        wgrad_x3_body<PRO_BNSWISH_GATE, PRO_BNBWD, 64, true, RAG>(a, bid, Us, Vs);
+        wgrad_x3_body<T, PRO_BNSWISH_GATE, PRO_BNBWD, 64, true, RAG>(a, bid, Us, Vs);
 }
 
 // Two weight gradients in one launch (a block's projection and expansion conv: independent of
 // each other, each about one workgroup per compute unit and bound by the latency of its own
 // load-stage-multiply chain): the first gridA workgroups work on `a`, the others on `b`, and
 // with at most 128 registers two workgroups, one of each, share a compute unit.
-template <int VARA, int VARB, bool RAG>
+template <typename T, int VARA, int VARB, bool RAG>
 __global__ __launch_bounds__(512, 4) void wgrad_x3_pair_kernel(X3WgradArgs a, X3WgradArgs b, int gridA)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t Us[3 * 128 * 32];
-    __shared__ __attribute__((aligned(16))) uint16_t Vs[3 * 128 * 32];
+    __shared__ __attribute__((aligned(16))) uint16_t Us[kWgPlanes<T> * 128 * 32];
+    __shared__ __attribute__((aligned(16))) uint16_t Vs[kWgPlanes<T> * 128 * 32];
     if ((int)blockIdx.x < gridA) // uniform over the workgroup
-        wgrad_x3_variant<VARA, RAG>(a, (int)blockIdx.x, Us, Vs);
+        wgrad_x3_variant<T, VARA, RAG>(a, (int)blockIdx.x, Us, Vs);
     else
-        wgrad_x3_variant<VARB, RAG>(b, (int)blockIdx.x - gridA, Us, Vs);
+        wgrad_x3_variant<T, VARB, RAG>(b, (int)blockIdx.x - gridA, Us, Vs);
 }
 
 // Tile and splits.  The wider operand gets 128-row tiles; the other one 128-row tiles, or one
 // 64-row tile when it has at most 64 rows (and more than 32).  Splits of the contraction: at most one workgroup (eight
 // wavefronts) per compute unit, at least two chunks each.
-bool x3_wgrad_plan(int Ma, int Mb, int N, int HW, int *splits)
+bool x3_wgrad_plan(bool bf16, int Ma, int Mb, int N, int HW, int *splits)
 {
     const long long Q = (long long)N * HW;
     // (a side of at most 32 channels belongs to the fused backward kernels of kernels_wave.hip,
@@ -380,11 +423,15 @@ bool x3_wgrad_plan(int Ma, int Mb, int N, int HW, int *splits)
     // 4.9e-7 there, 2.7e-7 and 3.5e-7 here).
     if (HW % 4 != 0 && HW <= 64)
         return false;
-    if (Q >= (1ll << 31) || (long long)std::max(Ma, Mb) * HW >= (1ll << 31) || HW < 4 || std::min(Ma, Mb) <= 32 || std::max(Ma, Mb) < 64)
+    // bf16: operands are rounded here; up to 64 x 256 rows, and on planes that are no multiple of four, the fp32
+    // kernels (wgrad_lt, wgrad_rd) take them as they are
+    if (bf16 && (HW % 4 != 0 || (std::min(Ma, Mb) <= 64 && std::max(Ma, Mb) <= 256)))
+        return false;
+    if (Q >= (1ll << 31) || (long long)std::max(Ma, Mb) * HW >= (1ll << 31) || HW < 4 || (!bf16 && std::min(Ma, Mb) <= 32) || std::max(Ma, Mb) < 64)
         return false;
     const int wide = std::max(Ma, Mb), narrow = std::min(Ma, Mb), vb = narrow <= 64 || HW % 4 != 0 ? 64 : 128;
     const long long tiles = (long long)((wide + 127) / 128) * ((narrow + vb - 1) / vb);
-    const long long chunks = ((long long)N * ((HW + 3) / 4) + 7) / 8;
+    const long long chunks = ((long long)N * ((HW + 3) / 4) + kWgRuns - 1) / kWgRuns;
     // (rounded down: two gradients that share a launch then just fit, two workgroups per compute unit;
     // 512 workgroups of one gradient measured slower: twice the partial tiles)
     long long s = 256 / tiles;
@@ -410,17 +457,19 @@ static X3Operand to_x3(const Operand &o)
     return d;
 }
 
+static X3WgradOperand to_wgrad(const Operand &o) { return {o.p0, o.p1, o.c0, o.c1, o.c2, o.gate}; }
+
 // Arguments, grid and kernel form (0..5, see wgrad_x3_variant) of one weight gradient.
 // rag: the launch's kernel is the form for planes that are no multiple of four (either one's of a pair).
 // The other one's plane then goes through 64-row tiles too, in the splits planned for 128-row ones: up
 // to 512 workgroups, which measured as fast as fewer splits (18x18 -> 9x9, 64 images, 48 -> 288 -> 80:
 // backward 94.5 / 94.0 us) or faster (192 -> 1152 -> 320, 32 images 219 / 230), and faster than two
 // launches (100 and 232) but where both are long (34x34 -> 17x17, 64 images, 112 -> 448 -> 192: 461, 448).
-static bool x3_wgrad_setup(bool rag, int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
+static bool x3_wgrad_setup(bool bf16, bool rag, int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
                            float *partial, X3WgradArgs *out, unsigned *grid, int *variant, int *splits_out)
 {
     int splits;
-    if (!x3_wgrad_plan(Ma, Mb, N, HW, &splits))
+    if (!x3_wgrad_plan(bf16, Ma, Mb, N, HW, &splits))
         return false;
     // a narrow first operand: the kernel computes the transposed product and writes it transposed
     const bool swap = Ma < 64 && Mb >= 64;
@@ -431,11 +480,11 @@ static bool x3_wgrad_setup(bool rag, int N, int Ma, int Mb, int HW, const Operan
     a.HW = HW;
     const int perImage = (HW + 3) / 4;
     a.runs = (uint32_t)((long long)N * perImage);
-    const int chunks = (int)((a.runs + 7u) / 8u);
+    const int chunks = (int)((a.runs + kWgRuns - 1u) / kWgRuns);
     a.chunksPerSplit = (chunks + splits - 1) / splits;
     a.divRuns = make_div((uint32_t)perImage);
-    a.U = to_x3(swap ? V : U);
-    a.V = to_x3(swap ? U : V);
+    a.U = to_wgrad(swap ? V : U);
+    a.V = to_wgrad(swap ? U : V);
     a.partial = partial;
     *splits_out = splits;
     a.tilesA = (a.Ma + 127) / 128;
@@ -459,21 +508,23 @@ static bool x3_wgrad_setup(bool rag, int N, int Ma, int Mb, int HW, const Operan
     return true;
 }
 
-hipError_t launch_x3_wgrad(int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
+hipError_t launch_x3_wgrad(bool bf16, int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
                            float *partial, int *splits_out, hipStream_t st)
 {
     X3WgradArgs a;
     unsigned grid;
     int var;
-    if (!x3_wgrad_setup(HW % 4 != 0, N, Ma, Mb, HW, U, V, partial, &a, &grid, &var, splits_out))
+    if (!x3_wgrad_setup(bf16, HW % 4 != 0, N, Ma, Mb, HW, U, V, partial, &a, &grid, &var, splits_out))
         return hipErrorInvalidValue;
 #define MBK_CASE(VAR, PU, PV, VB_, TR_)                                                           \
     if (var == VAR) {                                                                             \
         constexpr bool kRag = VB_ == 64; /* (the other forms never see such planes) */            \
-        if (kRag && HW % 4 != 0)                                                                  \
-            hipLaunchKernelGGL((wgrad_x3_kernel<PU, PV, VB_, TR_, kRag>), dim3(grid), dim3(512), 0, st, a);  \
+        if (bf16)                                                                                 \
+            hipLaunchKernelGGL((wgrad_x3_kernel<bf16_t, PU, PV, VB_, TR_, false>), dim3(grid), dim3(512), 0, st, a); \
+        else if (kRag && HW % 4 != 0)                                                             \
+            hipLaunchKernelGGL((wgrad_x3_kernel<float, PU, PV, VB_, TR_, kRag>), dim3(grid), dim3(512), 0, st, a);   \
         else                                                                                      \
-            hipLaunchKernelGGL((wgrad_x3_kernel<PU, PV, VB_, TR_, false>), dim3(grid), dim3(512), 0, st, a); \
+            hipLaunchKernelGGL((wgrad_x3_kernel<float, PU, PV, VB_, TR_, false>), dim3(grid), dim3(512), 0, st, a);  \
         return hipGetLastError();                                                                 \
     }
     MBK_CASE(0, PRO_BNBWD, PRO_NONE, 128, false)
@@ -489,7 +540,7 @@ hipError_t launch_x3_wgrad(int N, int Ma, int Mb, int HW, const Operand &U, cons
 // The projection conv's weight gradient (A: dp x sc) and the expansion conv's (B: de x x) in one
 // launch.  Returns hipErrorNotSupported, nothing launched, when one of them is not a shape of
 // this file or their forms are not a pair the launch has.
-hipError_t launch_x3_wgrad_pair(int N, int MaA, int MbA, int HWA, const Operand &UA, const Operand &VA,
+hipError_t launch_x3_wgrad_pair(bool bf16, int N, int MaA, int MbA, int HWA, const Operand &UA, const Operand &VA,
                                 float *partialA, int *splitsA, int MaB, int MbB, int HWB,
                                 const Operand &UB, const Operand &VB, float *partialB, int *splitsB,
                                 hipStream_t st)
@@ -498,18 +549,19 @@ hipError_t launch_x3_wgrad_pair(int N, int MaA, int MbA, int HWA, const Operand 
     unsigned ga, gb;
     int va, vb;
     const bool rag = HWA % 4 != 0 || HWB % 4 != 0;
-    if (!x3_wgrad_setup(rag, N, MaA, MbA, HWA, UA, VA, partialA, &a, &ga, &va, splitsA) ||
-        !x3_wgrad_setup(rag, N, MaB, MbB, HWB, UB, VB, partialB, &b, &gb, &vb, splitsB))
+    if (!x3_wgrad_setup(bf16, rag, N, MaA, MbA, HWA, UA, VA, partialA, &a, &ga, &va, splitsA) ||
+        !x3_wgrad_setup(bf16, rag, N, MaB, MbB, HWB, UB, VB, partialB, &b, &gb, &vb, splitsB))
         return hipErrorNotSupported;
 #define MBK_CASE(VA_, VB_)                                                                        \
     if (va == VA_ && vb == VB_) {                                                                 \
         constexpr bool kRag = VA_ >= 2 && VB_ >= 2;                                               \
-        if (kRag && rag)                                                                          \
-            hipLaunchKernelGGL((wgrad_x3_pair_kernel<VA_, VB_, kRag>), dim3(ga + gb), dim3(512), 0, st, a, b,  \
-                               (int)ga);                                                          \
+        const dim3 grid(ga + gb);                                                                 \
+        if (bf16)                                                                                 \
+            hipLaunchKernelGGL((wgrad_x3_pair_kernel<bf16_t, VA_, VB_, false>), grid, dim3(512), 0, st, a, b, (int)ga); \
+        else if (kRag && rag)                                                                     \
+            hipLaunchKernelGGL((wgrad_x3_pair_kernel<float, VA_, VB_, kRag>), grid, dim3(512), 0, st, a, b, (int)ga);   \
         else                                                                                      \
-            hipLaunchKernelGGL((wgrad_x3_pair_kernel<VA_, VB_, false>), dim3(ga + gb), dim3(512), 0, st, a, b, \
-                               (int)ga);                                                          \
+            hipLaunchKernelGGL((wgrad_x3_pair_kernel<float, VA_, VB_, false>), grid, dim3(512), 0, st, a, b, (int)ga);  \
         return hipGetLastError();                                                                 \
     }
     // projection side: dp (BN backward) with the gated activation, 128- or 64-row tile, or
