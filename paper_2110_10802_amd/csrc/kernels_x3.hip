@@ -601,8 +601,8 @@ hipError_t launch_x3_wgrad_pair(bool bf16, int N, int MaA, int MbA, int HWA, con
 //     registers, eight bytes per lane, sixteen lanes to a 128-byte line;
 //   - BN statistics of the output (EPI_STATS) are kept per lane over the wavefront's chunks and
 //     reduced once at the end: lanes of a row, then the four wavefronts in order through LDS.
-// Workgroup b: die = b % 8, then slab and chunk set, so that the workgroups of all slabs that
-// read the same pixel chunks run on the same die and share its L2.
+// The workgroups of all slabs that read the same pixel chunks run on the same die (most of them) and share
+// its L2.
 struct X3WArgs {
     int M, K, HW;
     uint32_t Q;
@@ -614,7 +614,7 @@ struct X3WArgs {
     float *out;
     float *psum, *psq; // EPI_STATS: [M][NT]
     int NT;            // chunk sets (= statistics partials per row)
-    int slabs;
+    int slabs, perDie;
 };
 
 template <int KS, bool PAIR, int PRO, int EPI>
@@ -629,8 +629,14 @@ __global__ __launch_bounds__(256, 2) void conv_xw_kernel(X3WArgs a)
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g = lane >> 4;
     const int M = a.M, K = a.K, HW = a.HW;
-    const int die = blockIdx.x & 7, bi = blockIdx.x >> 3;
-    const int slab = bi % a.slabs, cs = (bi / a.slabs) * 8 + die;
+    // die = workgroup mod 8: all slabs of a chunk set on one, sets in turn; of the sets left over an eighth of the
+    // (set, slab) pairs each
+    const int die = blockIdx.x & 7, bi = blockIdx.x >> 3, whole = (a.NT >> 3) * a.slabs;
+    const int rest = die * (a.perDie - whole) + bi - whole;
+    const int slab = (bi < whole ? bi : rest) % a.slabs;
+    const int cs = bi < whole ? (bi / a.slabs) * 8 + die : (a.NT & ~7) + rest / a.slabs;
+    if (cs >= a.NT) // uniform over the workgroup
+        return;
 
     // the slab's weights: thread -> (row r16, k group) pieces of eight k, of every 32-deep step one;
     // requested here, split into planes and parked in LDS below, after the first chunk's values have
@@ -841,7 +847,7 @@ __global__ __launch_bounds__(256, 2) void conv_xw_kernel(X3WArgs a)
 
 // Shapes and roles served: contraction of at most 192 (96 with the two-tensor prologue), a
 // multiple of 8; at least one 64-row slab of output; fp32.  `nt`: chunk sets = statistics
-// partials per row (a multiple of 8: one per die and round).
+// partials per row.
 bool xw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt)
 {
     const long long Q = (long long)N * HW;
@@ -853,16 +859,15 @@ bool xw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt)
         return false;
     const int slabs = (M + 63) / 64;
     const long long chunks = (Q + 31) / 32;
-    // about two workgroups per CU in all, a multiple of 8 (one per die); of the counts that
-    // need the same number of rounds over the chunk groups (four chunks, one per wavefront),
-    // the smallest
-    long long sets = (512 + slabs - 1) / slabs;
-    sets = (sets + 7) / 8 * 8;
+    // about two workgroups per CU in all; of the counts that need the same number of rounds over the chunk
+    // groups (four chunks, one per wavefront), a small one, and never more than there are groups (192 -> 1152
+    // on 64 planes of 7x7 was 32 sets for 25 groups, 576 workgroups, an eighth of them in a second round: 28.3
+    // us, 22.1 with 25).  Rounded up to a multiple of 8: the smallest leaves too few wavefronts in flight
+    // (80 -> 480, 32 planes of 28x28: step 287 us with 56 sets, 292 with 49).
     const long long groups = (chunks + 3) / 4;
-    if (sets > groups)
-        sets = (groups + 7) / 8 * 8;
+    long long sets = ((512 + slabs - 1) / slabs + 7) / 8 * 8;
     const long long rounds = (groups + sets - 1) / sets;
-    sets = ((groups + rounds - 1) / rounds + 7) / 8 * 8;
+    sets = std::min(groups, ((groups + rounds - 1) / rounds + 7) / 8 * 8);
     *nt = (int)sets;
     return true;
 }
@@ -889,9 +894,10 @@ hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm
     a.psq = psq;
     a.NT = nt;
     a.slabs = (M + 63) / 64;
+    a.perDie = (nt >> 3) * a.slabs + ((nt & 7) * a.slabs + 7) / 8;
     const int ks = (K + 31) / 32;
     const bool pair = HW % 2 == 0;
-    const dim3 grid((unsigned)(a.slabs * nt));
+    const dim3 grid((unsigned)(8 * a.perDie));
     const size_t lds = (size_t)ks * 12288 + (B.pro == PRO_BNBWD ? std::max((size_t)ks * 512, (size_t)2048) : 2048);
 #define MBK_CASE(KS_, PAIR_, PRO_, EPI_)                                                          \
     if (ks == KS_ && pair == PAIR_ && B.pro == PRO_ && epi == EPI_) {                             \
