@@ -495,80 +495,73 @@ int wgrad_splits(bool bf16, int Ma, int Mb, int N, int HW)
     return (int)((Q + chunk - 1) / chunk);
 }
 
-// Second stage of a split reduction: out[i] = sum_k in[k*count+i].  A workgroup owns E*V
-// consecutive outputs (V = 4 when count is a multiple of four: 16-byte loads); its G = 1024/E
-// thread groups each add every G-th partial in ascending order (four independent running sums
-// per thread to keep loads in flight), then the groups are combined by a fixed-shape tree in
-// LDS.  No atomics, bitwise repeatable.
-template <int V, int E>
-__device__ __forceinline__ void reduce_splits_body(const float *__restrict__ in, int S, size_t count,
-                                                   float *__restrict__ out, unsigned block)
+// Second stage of a split reduction: out[i] = sum_k in[k*count+i].  A workgroup owns E*V consecutive outputs
+// (V = 4 when count is a multiple of four: 16-byte loads); each of its G = T/E groups of E lanes adds every
+// G-th partial in ascending order, four loads in flight (clamped to the last row: a load behind a branch would
+// wait for the one before) into four running sums, and sums and groups are combined pairwise.  No atomics, bitwise
+// repeatable.
+//
+// The partials were written by other dies a moment ago and a lane has only a few rows to add, so what bounds this is
+// how many loads are requested before the first has to arrive, and how soon workgroups make room for the
+// next: groups of 256 threads with one barrier.  (Workgroups of 1024 threads, a tree of barriers in LDS, the
+// rows past the fourth one by one: two of 672 x 112 with 42 rows 17.4 us, 12.5 this way; 1152 x (320 + 192) with 8
+// and 13 rows 13.5, 11.6; two of 480 x 80 with 64 rows 12.6, 9.9; two of 144 x 24 with 448 rows 8.2, 7.7.)
+template <int V, int E, int T>
+__device__ __forceinline__ void reduce_splits_body(const SplitReduce &r, unsigned block)
 {
-    constexpr int G = 1024 / E; // thread groups of E lanes; the workgroup owns E*V outputs
-    __shared__ float part[G][E * V + 1];
+    constexpr int G = T / E, B = 4, WAVES = T / 64;
+    static_assert(E < 64 && T % 64 == 0, "a wavefront holds several groups");
+    typedef float vec __attribute__((ext_vector_type(V)));
+    __shared__ vec part[WAVES][E];
     const int e = threadIdx.x % E, grp = threadIdx.x / E;
     const size_t i = ((size_t)block * E + e) * V;
-    float s[4][V];
+    const float *p = r.in + (i < r.count ? i : 0);
+    vec run[B];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < B; ++u)
+        run[u] = 0.f;
+    for (int k0 = 0; k0 < r.S; k0 += B * G) {
+        vec t[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            t[u] = *reinterpret_cast<const vec *>(p + (size_t)min(k0 + u * G + grp, r.S - 1) * r.count);
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (k0 + u * G + grp < r.S)
+                run[u] += t[u];
+    }
+    vec s = (run[0] + run[1]) + (run[2] + run[3]);
+#pragma unroll
+    for (int w = E; w < 64; w *= 2)
 #pragma unroll
         for (int v = 0; v < V; ++v)
-            s[u][v] = 0.f;
-    auto add = [&](int u, int k) __attribute__((always_inline)) {
-        const float *p = in + (size_t)k * count + i;
-        if (V == 4) {
-            const float4 t = *reinterpret_cast<const float4 *>(p);
-            s[u][0] += t.x;
-            s[u][V > 1 ? 1 : 0] += t.y;
-            s[u][V > 2 ? 2 : 0] += t.z;
-            s[u][V > 3 ? 3 : 0] += t.w;
-        } else {
-            s[u][0] += p[0];
-        }
-    };
-    if (i < count) {
-        int k = grp;
-        for (; k + 3 * G < S; k += 4 * G) {
-            add(0, k);
-            add(1, k + G);
-            add(2, k + 2 * G);
-            add(3, k + 3 * G);
-        }
-        for (; k < S; k += G)
-            add(0, k);
-    }
-#pragma unroll
-    for (int v = 0; v < V; ++v)
-        part[grp][e * V + v] = (s[0][v] + s[1][v]) + (s[2][v] + s[3][v]);
+            s[v] += __shfl_xor(s[v], w, 64);
+    if ((threadIdx.x & 63) < E)
+        part[threadIdx.x / 64][e] = s;
     __syncthreads();
-    for (int half = G / 2; half > 0; half >>= 1) {
-        if (grp < half) {
+    if (threadIdx.x < E && i < r.count) {
+        vec sum[WAVES];
 #pragma unroll
-            for (int v = 0; v < V; ++v)
-                part[grp][e * V + v] += part[grp + half][e * V + v];
-        }
-        __syncthreads();
-    }
-    if (grp == 0 && i < count) {
+        for (int w = 0; w < WAVES; ++w)
+            sum[w] = part[w][e];
 #pragma unroll
-        for (int v = 0; v < V; ++v)
-            out[i + v] = part[0][e * V + v];
+        for (int half = WAVES / 2; half > 0; half /= 2)
+#pragma unroll
+            for (int w = 0; w < half; ++w)
+                sum[w] += sum[w + half];
+        *reinterpret_cast<vec *>(r.out + i) = sum[0];
     }
 }
 
 // Up to two independent reductions in one launch (the workgroups of the second follow those of
 // the first): two launches cost a launch latency more than the reductions themselves take.
-// 16 lanes x 4 outputs per thread group with 16-byte loads (64 groups share the partial rows: a
-// 144x24 gradient with 448 splits then runs on 108 workgroups, measured 0.8 us faster than 32
-// lanes x 32 groups on 54), 32 lanes x 1 otherwise.
-template <int V, int E>
-__global__ __launch_bounds__(1024) void reduce_splits_kernel(SplitReduce a, SplitReduce b,
-                                                             unsigned blocks_a)
+template <int V, int E, int T>
+__global__ __launch_bounds__(T) void reduce_splits_kernel(SplitReduce a, SplitReduce b, unsigned blocks_a)
 {
     if (blockIdx.x < blocks_a)
-        reduce_splits_body<V, E>(a.in, a.S, a.count, a.out, blockIdx.x);
+        reduce_splits_body<V, E, T>(a, blockIdx.x);
     else
-        reduce_splits_body<V, E>(b.in, b.S, b.count, b.out, blockIdx.x - blocks_a);
+        reduce_splits_body<V, E, T>(b, blockIdx.x - blocks_a);
 }
 
 hipError_t launch_reduce_splits2(const SplitReduce &a, const SplitReduce &b, hipStream_t st)
@@ -576,36 +569,24 @@ hipError_t launch_reduce_splits2(const SplitReduce &a, const SplitReduce &b, hip
     const auto wide = [](const SplitReduce &r) {
         return r.count % 4 == 0 && (((uintptr_t)r.in | (uintptr_t)r.out) & 15u) == 0;
     };
-    const auto blocks256 = [](const SplitReduce &r) { return (unsigned)((r.count / 4 + 255) / 256); };
     const bool two = b.count > 0;
-    if (wide(a) && (!two || wide(b))) {
-        // lanes per thread group by the number of partial rows: a group adds every (1024/E)-th row,
-        // so few rows want few, wide groups (with 64 groups and 16 rows three quarters of the
-        // threads would idle); where 256 lanes per group still give a workgroup per compute unit, four
-        // groups, each thread with a few loads in flight and two steps of the tree instead of four
-        // (1152 x (320 + 192): 9 and 13 rows 8.4 us; 10 and 15 rows with sixteen groups 15.0)
-        const int S = two ? (a.S < b.S ? a.S : b.S) : a.S;
-#define MBK_GO(E)                                                                                 \
+    const int S = two ? std::min(a.S, b.S) : a.S;
+#define MBK_GO(V, E, T)                                                                           \
     {                                                                                             \
-        const unsigned ba = (unsigned)((a.count / 4 + (E)-1) / (E));                              \
-        const unsigned bb = two ? (unsigned)((b.count / 4 + (E)-1) / (E)) : 0u;                   \
-        hipLaunchKernelGGL((reduce_splits_kernel<4, E>), dim3(ba + bb), dim3(1024), 0, st, a, b,  \
-                           ba);                                                                   \
+        const unsigned ba = (unsigned)((a.count / (V) + (E)-1) / (E));                            \
+        const unsigned bb = two ? (unsigned)((b.count / (V) + (E)-1) / (E)) : 0u;                 \
+        hipLaunchKernelGGL((reduce_splits_kernel<V, E, T>), dim3(ba + bb), dim3(T), 0, st, a, b, ba); \
     }
-        if (S >= 128)
-            MBK_GO(16)
-        else if (S >= 32)
-            MBK_GO(32)
-        else if (blocks256(a) + (two ? blocks256(b) : 0u) < 256u)
-            MBK_GO(64)
-        else
-            MBK_GO(256)
+    // many rows are those of small gradients: more groups, narrower ones, so that more workgroups share the
+    // rows (two of 240 x 40 with 128 rows 6.4 us as here, 6.7 the other way; two of 144 x 24 with 448 rows 7.7, 11.7;
+    // two of 480 x 80 with 64 rows 9.9 either way; 672 x (192 + 112) with 25 and 42 rows 13.3, 12.3)
+    if (!wide(a) || (two && !wide(b)))
+        MBK_GO(1, 32, 1024)
+    else if (S >= 96)
+        MBK_GO(4, 16, 512)
+    else
+        MBK_GO(4, 32, 256)
 #undef MBK_GO
-    } else {
-        const unsigned ba = (unsigned)((a.count + 31) / 32);
-        const unsigned bb = two ? (unsigned)((b.count + 31) / 32) : 0u;
-        hipLaunchKernelGGL((reduce_splits_kernel<1, 32>), dim3(ba + bb), dim3(1024), 0, st, a, b, ba);
-    }
     return hipGetLastError();
 }
 
