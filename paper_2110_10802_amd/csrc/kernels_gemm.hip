@@ -238,23 +238,32 @@ hipError_t launch_x3_wgrad_pair(bool bf16, int N, int MaA, int MbA, int HWA, con
 bool xw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt);
 hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm, int sAk, const Operand &B,
                              void *out, int epi, float *psum, float *psq, hipStream_t st);
+bool xs_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt);
+hipError_t launch_xs_conv1x1(int N, int M, int K, int HW, const void *w, int sAm, int sAk, const Operand &B, void *out,
+                             int epi, float *psum, float *psq, hipStream_t st);
 // kernels_xk.hip
 bool xk_conv_plan(bool bf16, int N, int M, int K, int HW, int pro, int *chunks);
 hipError_t launch_xk_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w, int sAm, int sAk,
                              const void *wimg, const Operand &B, void *out, int epi, const void *res, float *psum, float *psq, hipStream_t st);
 
+// short contraction, few pixels, the expansion conv: a workgroup per tile (conv_xs)
+static bool xs_applies(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi, int *nt)
+{
+    return !bf16 && !stores_operand && xs_conv_plan(N, M, K, HW, pro, epi, nt);
+}
 // short contraction, many rows, a role the kernel has: weights resident in LDS (conv_xw)
 static bool xw_applies(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi,
                        int *nt)
 {
     return !bf16 && !stores_operand && pro >= 0 && epi >= 0 && !wave_conv_kind(M, K, HW) &&
-           xw_conv_plan(N, M, K, HW, pro, epi, nt);
+           !xs_conv_plan(N, M, K, HW, pro, epi, nt) && xw_conv_plan(N, M, K, HW, pro, epi, nt);
 }
 // the other wide shapes: the contraction split over a workgroup's wavefronts (conv_xk)
 static bool xk_applies(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi,
                        int *nt)
 {
     return !stores_operand && pro >= 0 && epi >= 0 && !wave_conv_kind(M, K, HW) &&
+           !xs_applies(bf16, N, M, K, HW, stores_operand, pro, epi, nt) &&
            !xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, nt) &&
            xk_conv_plan(bf16, N, M, K, HW, pro, nt);
 }
@@ -293,9 +302,11 @@ int conv1x1_num_partials(bool bf16, int N, int M, int K, int HW, bool stores_ope
                          int epi)
 {
     const int kind = stores_operand ? 0 : wave_conv_kind(M, K, HW);
+    int wt, qtiles, splits;
+    if (xs_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
+        return qtiles;
     if (kind)
         return wave_conv_num_partials(kind, N, M, HW);
-    int wt, qtiles, splits;
     if (xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
         xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
         return qtiles;
@@ -309,7 +320,7 @@ int conv1x1_num_partials(bool bf16, int N, int M, int K, int HW, bool stores_ope
 size_t conv1x1_splitk_floats(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi)
 {
     int qtiles, splits;
-    if (stores_operand || wave_conv_kind(M, K, HW) ||
+    if (stores_operand || wave_conv_kind(M, K, HW) || xs_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
         xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
         xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
         return 0;
@@ -325,6 +336,8 @@ hipError_t launch_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w,
 {
     {
         int nt;
+        if (xs_applies(bf16, N, M, K, HW, sc_store != nullptr, B.pro, epi, &nt))
+            return launch_xs_conv1x1(N, M, K, HW, w, sAm, sAk, B, out, epi, psum, psq, st);
         if (xw_applies(bf16, N, M, K, HW, sc_store != nullptr, B.pro, epi, &nt)) {
             return launch_xw_conv1x1(N, M, K, HW, w, sAm, sAk, B, out, epi, psum, psq, st);
         }

@@ -935,4 +935,180 @@ hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm
     return hipErrorInvalidValue;
 }
 
+// ---- 1x1 convolution with a short contraction and few pixels: a workgroup per tile ----
+// The expansion conv of a request or a small batch has a few chunks of 32 pixels, and conv_xw, which keeps 64 rows
+// of weights in LDS for many chunks, then spends a chain of latencies on a handful of workgroups: load the slab, split it,
+// barrier, then every step of the contraction in turn on one wavefront (192 -> 1152 channels on one 7x7 plane: 24
+// workgroups, half of whose wavefronts have no chunk, 11.7 us); so does conv_pe, up to 40 input channels, with a
+// workgroup for all rows of 64 pixels (40 -> 240 on one 28x28 plane: 13 workgroups, 12.0 us).  Here a workgroup owns 16 rows by 32 pixels and has a
+// wavefront for each step of 32 of the contraction: everything is requested at once, and the steps are added in order
+// through LDS.  On fp32 MFMA: sixteen instructions of a wavefront take as long as splitting its operands would.
+// Evaluation of the blocks named, 33.3 -> 25.6 and 24.9 -> 17.5 us.
+struct X3SArgs {
+    int M, K, HW;
+    uint32_t Q;
+    FastDiv divHW, divTiles;
+    const float *w, *x; // [M][K], [n][K][HW]
+    float *out;
+    float *psum, *psq;  // [M][chunks]
+    int tiles, chunks;
+};
+
+template <int KS, bool PAIR>
+__global__ __launch_bounds__(64 * KS) void conv_xs_kernel(X3SArgs a)
+{
+    __shared__ f32x4 part[KS][2][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int s = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int M = a.M, K = a.K, HW = a.HW;
+    const int chunk = (int)fdiv(blockIdx.x, a.divTiles), m0 = 16 * ((int)blockIdx.x - chunk * a.tiles);
+    // A: row m0 + r, contraction 32s + 8g .. +7 (past the end clamped; K % 8 == 0).  Instruction t takes k = 8g + t of
+    // every g, the contraction's order being free.
+    const int k0 = min(32 * s + 8 * g, K - 8);
+    const uint32_t kok = 32 * s + 8 * g < K ? 0xffffffffu : 0u;
+    float av[8], d0[8], d1[8];
+    {
+        const float *wr = a.w + (size_t)min(m0 + r, M - 1) * K + k0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(wr + 4 * h);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                av[4 * h + e] = v[e];
+        }
+    }
+    // pixel tile pt: pixel 2r + pt of the chunk (pairs: one image, HW being even) or r + 16 pt
+    uint32_t bo[2], oo[2], okm[2];
+#pragma unroll
+    for (int pt = 0; pt < 2; ++pt) {
+        const uint32_t q = (uint32_t)chunk * 32u + (PAIR ? 2u * (uint32_t)r : 16u * pt + (uint32_t)r);
+        okm[pt] = q < a.Q ? 0xffffffffu : 0u;
+        const uint32_t qs = q < a.Q ? q : 0u;
+        const uint32_t n = fdiv(qs, a.divHW), pix = qs - n * (uint32_t)HW;
+        bo[pt] = (n * (uint32_t)K + (uint32_t)k0) * (uint32_t)HW + pix;
+        oo[pt] = n * (uint32_t)M * (uint32_t)HW + pix;
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const float *pb = a.x + (size_t)t * HW; // uniform
+        if (PAIR) {
+            const f32x2 v = *reinterpret_cast<const f32x2 *>(pb + bo[0]);
+            d0[t] = v[0];
+            d1[t] = v[1];
+        } else {
+            d0[t] = pb[bo[0]];
+            d1[t] = pb[bo[1]];
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // (past the contraction both operands are zero: what was loaded there may be infinite)
+    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const float w = and_mask(av[t], kok);
+        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(w, and_mask(d0[t], okm[0] & kok), acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(w, and_mask(d1[t], okm[1] & kok), acc1, 0, 0, 0);
+    }
+    if (KS > 1) {
+        part[s][0][lane] = acc0;
+        part[s][1][lane] = acc1;
+        __syncthreads();
+        if (s != 0) // uniform over the wavefront
+            return;
+#pragma unroll
+        for (int j = 1; j < KS; ++j) {
+            acc0 += part[j][0][lane];
+            acc1 += part[j][1][lane];
+        }
+    }
+    // rows m0 + 4g + v, the lane's two pixels
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int m = m0 + 4 * g + v;
+        const float x0 = acc0[v], x1 = acc1[v];
+        if (m < M) {
+            float *po = a.out + (size_t)m * HW;
+            if (PAIR) {
+                if (okm[0])
+                    *reinterpret_cast<f32x2 *>(po + oo[0]) = (f32x2){x0, x1};
+            } else {
+                if (okm[0])
+                    po[oo[0]] = x0;
+                if (okm[1])
+                    po[oo[1]] = x1;
+            }
+        }
+        // statistics of the output (pixels past the end were masked to zero on the way in)
+        const float t1 = row16_sum(x0 + x1), t2 = row16_sum(fmaf(x0, x0, x1 * x1));
+        if (r == 0 && m < M) {
+            a.psum[(size_t)m * a.chunks + chunk] = t1;
+            a.psq[(size_t)m * a.chunks + chunk] = t2;
+        }
+    }
+}
+
+// `nt`: chunks = statistics partials per row.
+bool xs_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt)
+{
+    const long long Q = (long long)N * HW, chunks = (Q + 31) / 32;
+    // (the expansion conv's role, and shapes whose rows are whole 32-byte pieces)
+    if (K % 8 != 0 || K < 8 || K > 192 || pro != PRO_NONE || epi != EPI_STATS)
+        return false;
+    if (Q * M >= (1ll << 30) || Q * K >= (1ll << 30)) // 32-bit byte offsets in the kernel
+        return false;
+    // Up to one and a half times what is resident at once; beyond, the rows that every workgroup reads again cost
+    // more than the latencies (training step, the other kernels / here, us: 24 -> 144 on 56x56, 12 images
+    // 142.1 / 139.2, 16 160.8 / 163.3; 80 -> 480 on 14x14, 2 images 82.5 / 78.9, 16 106.2 / 105.5, 32 126.9 / 127.6; 192 ->
+    // 1152 on 7x7, 2 images 110.3 / 101.7, 16 140.8 / 136.9, 32 164.1 / 164.6).  33 to 40 input channels are the
+    // most conv_pe takes, at the fewest wavefronts, and it is later that it wins (40 -> 240 on 28x28, one image 86.9 / 79.9,
+    // 32 181.8 / 175.5, 64 267.3 / 264.5).
+    const long long waves = chunks * ((M + 15) / 16) * ((K + 31) / 32);
+    if (waves > (K > 32 && K <= 40 ? 48 * 1024 : 12 * 1024))
+        return false;
+    *nt = (int)chunks;
+    return true;
+}
+
+hipError_t launch_xs_conv1x1(int N, int M, int K, int HW, const void *w, int sAm, int sAk, const Operand &B, void *out,
+                             int epi, float *psum, float *psq, hipStream_t st)
+{
+    int nt;
+    if (!xs_conv_plan(N, M, K, HW, B.pro, epi, &nt) || sAm != K || sAk != 1)
+        return hipErrorInvalidValue;
+    X3SArgs a;
+    a.M = M;
+    a.K = K;
+    a.HW = HW;
+    a.Q = (uint32_t)((long long)N * HW);
+    a.divHW = make_div((uint32_t)HW);
+    a.w = (const float *)w;
+    a.x = (const float *)B.p0;
+    a.out = (float *)out;
+    a.psum = psum;
+    a.psq = psq;
+    a.tiles = (M + 15) / 16;
+    a.chunks = nt;
+    a.divTiles = make_div((uint32_t)a.tiles);
+    const int ks = (K + 31) / 32;
+    const bool pair = HW % 2 == 0;
+    const dim3 grid((unsigned)(a.tiles * nt));
+#define MBK_KS(KS_)                                                                               \
+    if (ks == KS_) {                                                                              \
+        if (pair)                                                                                 \
+            hipLaunchKernelGGL((conv_xs_kernel<KS_, true>), grid, dim3(64 * KS_), 0, st, a);      \
+        else                                                                                      \
+            hipLaunchKernelGGL((conv_xs_kernel<KS_, false>), grid, dim3(64 * KS_), 0, st, a);     \
+        return hipGetLastError();                                                                 \
+    }
+    MBK_KS(1)
+    MBK_KS(2)
+    MBK_KS(3)
+    MBK_KS(4)
+    MBK_KS(5)
+    MBK_KS(6)
+#undef MBK_KS
+    return hipErrorInvalidValue;
+}
+
 } // namespace mbk
