@@ -940,9 +940,9 @@ hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm
 // of weights in LDS for many chunks, then spends a chain of latencies on a handful of workgroups: load the slab, split it,
 // barrier, then every step of the contraction in turn on one wavefront (192 -> 1152 channels on one 7x7 plane: 24
 // workgroups, half of whose wavefronts have no chunk, 11.7 us); so does conv_pe, up to 40 input channels, with a
-// workgroup for all rows of 64 pixels (40 -> 240 on one 28x28 plane: 13 workgroups, 12.0 us).  Here a workgroup owns 16 rows by 32 pixels and has a
-// wavefront for each step of 32 of the contraction: everything is requested at once, and the steps are added in order
-// through LDS.  On fp32 MFMA: sixteen instructions of a wavefront take as long as splitting its operands would.
+// workgroup for all rows of 64 pixels (40 -> 240 on one 28x28 plane: 13 workgroups, 12.0 us).  Here a workgroup
+// owns 16 rows by 32 pixels and has a wavefront for each step of 32 of the contraction: everything is requested at
+// once, and the steps are added in order through LDS.  On fp32 MFMA: sixteen instructions of a wavefront take as long as splitting its operands would.
 // Evaluation of the blocks named, 33.3 -> 25.6 and 24.9 -> 17.5 us.
 struct X3SArgs {
     int M, K, HW;
