@@ -16,6 +16,7 @@
 // 64 bytes to an instruction, no LDS: 92 us, the rows of odd planes are not aligned and the cache then takes
 // an access per lane.)
 #include <algorithm>
+#include "mbconv_wgr_plan.h"
 #include "mbconv_x3.h"
 
 namespace mbk {
@@ -262,8 +263,7 @@ hipError_t launch_wgr(bool bf16, int N, int Ma, int Mb, int HW, const Operand &U
 }
 
 // Two of them in one launch (A: the projection conv's, B: the expansion conv's), which leave each other's
-// workgroups room: of the numbers of splits with which all are resident at once, the pair whose slower side
-// ends first, counted in chunks times a chunk's cycles.
+// workgroups room (mbconv_wgr_plan.h).
 hipError_t launch_wgr_pair(bool bf16, int N, int MaA, int MbA, int HWA, const Operand &UA, const Operand &VA,
                            float *partialA, int *splitsA, int MaB, int MbB, int HWB, const Operand &UB,
                            const Operand &VB, float *partialB, int *splitsB, hipStream_t st)
@@ -272,27 +272,11 @@ hipError_t launch_wgr_pair(bool bf16, int N, int MaA, int MbA, int HWA, const Op
     if (!wgr_plan(bf16, MaA, MbA, N, HWA, &sa) || !wgr_plan(bf16, MaB, MbB, N, HWB, &sb) || UA.pro != PRO_BNBWD ||
         UB.pro != PRO_BNBWD || VA.pro == PRO_BNBWD || VB.pro != PRO_NONE)
         return hipErrorNotSupported;
-    const int ta = wgr_tiles(MaA, MbA), tb = wgr_tiles(MaB, MbB);
-    const int ca = wgr_chunks(N, HWA), cb = wgr_chunks(N, HWB);
-    const int costA = VA.pro == PRO_NONE ? 12 : 16, costB = 12;
-    long long best = 0;
-    int bestA = 1, bestB = 1;
-    for (int i = 1; i <= sa; ++i)
-        for (int j = 1; j <= sb; ++j) {
-            const long long wgs = (long long)i * ta + (long long)j * tb;
-            if (wgs > kWgrResident && i + j > 2)
-                continue;
-            const long long cost = (long long)std::max((ca + i - 1) / i * costA, (cb + j - 1) / j * costB) * 4096 + wgs;
-            if (!best || cost < best) {
-                best = cost;
-                bestA = i;
-                bestB = j;
-            }
-        }
-    *splitsA = bestA;
-    *splitsB = bestB;
-    return wgr_go(bf16, VA.pro != PRO_NONE, wgr_args(N, MaA, MbA, HWA, UA, VA, partialA, bestA),
-                  wgr_args(N, MaB, MbB, HWB, UB, VB, partialB, bestB), st);
+    const WgrSide a = {wgr_tiles(MaA, MbA), wgr_chunks(N, HWA), VA.pro == PRO_NONE ? 12 : 16, sa};
+    const WgrSide b = {wgr_tiles(MaB, MbB), wgr_chunks(N, HWB), 12, sb};
+    wgr_pair_splits(a, b, kWgrResident, splitsA, splitsB);
+    return wgr_go(bf16, VA.pro != PRO_NONE, wgr_args(N, MaA, MbA, HWA, UA, VA, partialA, *splitsA),
+                  wgr_args(N, MaB, MbB, HWB, UB, VB, partialB, *splitsB), st);
 }
 
 } // namespace mbk
