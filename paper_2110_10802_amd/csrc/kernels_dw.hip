@@ -262,6 +262,46 @@ bool dw_fwd_finalizes_bn1(const DwShape &s, bool stores_a1)
     return dwr_supported(s); // a wavefront per channel and image range: once per wavefront
 }
 
+__global__ __launch_bounds__(256) void dw_eval_coef_kernel(DwEval ev) { dw_eval_extra(ev, (int)blockIdx.x, 256); }
+
+hipError_t launch_dw_eval_coef(DwEval &ev, hipStream_t st)
+{
+    const unsigned blocks = dw_eval_blocks(ev, 256);
+    hipLaunchKernelGGL(dw_eval_coef_kernel, dim3(blocks), dim3(256), 0, st, ev);
+    return hipGetLastError();
+}
+
+// A launch saved is some 4.5 us; the coefficients and the squeeze are about 130 cycles of every wavefront, 0.06 to 0.1 us
+// per thousand of them, where instruction issue is the bound.  Evaluation of a block, with the launches / folded, us:
+//  - nothing saved (a launch precedes the expansion conv anyway, no pool): 62 -> 186 -> 93 on 9x9, stride 2, 48 images
+//    23.4 / 24.7, 77 -> 462 -> 77 on 6x6, 30 images 25.3 / 25.9;
+//  - dw_fwd, a thread group to a plane, one launch saved: 48 -> 288 -> 48 on 25x25, 28 images (32 k wavefronts) 49.7 /
+//    48.7, 111 121 / 126; 40 -> 240 -> 88 on 29x29, stride 2, 17 images (16 k) 33.8 / 32.5, 33 (32 k) 43.6 / 46.1; 61 -> 366
+//    -> 76 on 17x17, stride 2, with SE, 8 images (12 k) 32.5 / 31.2, 64 (94 k) 74.1 / 78.8;
+//  - the pool saved as well, which reads the output once more: with stride 1 folded is as fast or faster at any size
+//    (25x25, 222 images 286 / 287; 57x57, 444 images 1484 / 1359); with stride 2 the output is a quarter (17x17, 672
+//    channels, 24 images, 65 k, 66.1 / 64.5, 48, 129 k, 91.7 / 93.0, 95 158 / 167);
+//  - 5x5 on fp32 planes of 1024 threads: 64 registers and more, which is one workgroup to a compute unit, not two, with
+//    stride 2: 24 -> 144 -> 40 on 72x72, stride 2, 4 images (9 k) 36.6 / 30.8, 16 59.5 / 69.0, 64 162 / 201; stride 1, 16
+//    images (37 k) 90.8 / 84.9, 64 311 / 326, without SE 16 images 74.8 / 80.3; 42 -> 252 -> 40, a launch ahead, stride 2,
+//    one image (4 k) 28.1 / 26.2, 3 39.2 / 40.4.
+// dw4, dw2 and dwr otherwise, where a wavefront has more pixels: folded is as fast or faster at every size measured.
+bool dw_eval_folds(bool bf16, const DwShape &s, bool se, bool coef_ahead)
+{
+    const int saved = (se ? 1 : 0) + (coef_ahead ? 0 : 1);
+    if (!saved)
+        return false;
+    const bool runs = dw4_supported(s) || dw2_supported(s); // (of four pixels)
+    if (!runs && dwr_supported(s))
+        return true;
+    const int items = runs ? s.H * ((s.W + 3) / 4) : s.H * s.W; // and threads to a plane, as the launchers choose them
+    const int threads = items <= 256 ? 64 : items <= (runs ? 1024 : 4096) ? 256 : 1024;
+    const long long waves = (long long)s.N * s.C * (threads / 64);
+    if (!bf16 && s.k == 5 && threads == 1024)
+        return waves <= (se && s.s == 1 ? 48 : coef_ahead ? 4 : 16) * 1024;
+    return runs || (se && s.s == 1) || waves <= (saved == 2 ? 96 : 28) * 1024;
+}
+
 hipError_t launch_dw_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
                          const void *w_dw, void *d, float *psum, float *psq, void *a1_store,
                          const BnFin *fin, const DwEval *ev, hipStream_t st)

@@ -263,8 +263,9 @@ mbconv_status check_params(const mbconv_desc *d, const mbconv_params *p)
 
 
 // Training mode (eval == false): batch statistics, running statistics updated when run != NULL.
-// Evaluation mode: run is read only and supplies the statistics of all three normalisations; the
-// depthwise kernel turns them into coefficients, so that the BN-finalise steps and the pool launch nothing.
+// Evaluation mode: run is read only and supplies the statistics of all three normalisations.  Where it pays the
+// depthwise kernel turns them into coefficients and sums the planes for the squeeze, and the BN-finalise steps and the pool
+// launch nothing; elsewhere the first BN-finalise step the block has writes all coefficients.
 mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mbconv_bn_state *run,
                            bool eval, const void *x, void *out, void *saved, void *scratch,
                            void *hip_stream, const mbconv_probe *probe)
@@ -332,7 +333,10 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     // the same launches
     float *ones = P.se ? nullptr : g;
     const size_t ones_count = (size_t)P.N * P.Cexp;
-    // Evaluation mode: the depthwise launch brings the coefficients, the pool and the weight images.
+    // Evaluation mode: the depthwise launch brings the coefficients, the pool and the weight images, or a launch ahead of
+    // everything else the coefficients and the images (dw_eval_folds).
+    const DwShape ds = {P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p};
+    const bool fold = eval && dw_eval_folds(bf, ds, P.se, prep_first);
     DwEval ev = {};
     if (eval) {
         if (P.expand)
@@ -344,9 +348,10 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
         ev.inv_hw = 1.f / (float)P.HWo;
         ev.ones = ones;
         ev.ones_count = ones ? ones_count : 0;
-        if (!prep_first)
+        if (!prep_first || !fold)
             ev.prep = prep;
-        MBK_STEP(P.expand ? MBCONV_STEP_BN1_FINALIZE : MBCONV_STEP_BN2_FINALIZE, hipSuccess); // (no launch)
+        MBK_STEP(P.expand ? MBCONV_STEP_BN1_FINALIZE : MBCONV_STEP_BN2_FINALIZE,
+                 fold ? hipSuccess : launch_dw_eval_coef(ev, st));
     }
     // expansion conv + BN1 statistics
     const void *dw_in = x;
@@ -356,7 +361,7 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
         B.p0 = x;
         B.pro = PRO_NONE;
         const auto conv = [&]() -> hipError_t {
-            const hipError_t pe = prep_first ? launch_x3_prep(prep, st) : hipSuccess;
+            const hipError_t pe = prep_first && (!eval || fold) ? launch_x3_prep(prep, st) : hipSuccess;
             if (pe != hipSuccess)
                 return pe;
             return launch_conv1x1(bf, P.N, P.Cexp, P.Cin, P.HW, prm->w_expand, P.Cin, 1, B, e, EPI_STATS,
@@ -370,7 +375,6 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     // in the vectorised depthwise kernel for large planes, BN2 in the pooling kernel for small ones
     // (measured for large ones: no gain), BN3 in the final elementwise pass of batches that are not
     // large; otherwise it is a launch of its own.
-    const DwShape ds = {P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p};
     void *a1_store = (P.store && P.expand && !eval) ? at<char>(saved, P.o_a1) : nullptr;
     const double m1 = (double)P.N * P.HW, m2 = (double)P.N * P.HWo;
     const BnFin fin1 = make_bn_fin(psum, psq, prm->bn1_gamma, prm->bn1_beta, run ? run->bn1_mean : nullptr,
@@ -385,7 +389,7 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
                                    prm->bn1_beta, eps, mom, fin1.run_mean, fin1.run_var, bn1, st));
     // BN1 + Swish + depthwise + BN2 statistics
     MBK_STEP(MBCONV_STEP_DW_FWD, launch_dw_fwd(bf, ds, dw_in, bn1, prm->w_dw, d, psum2, psq2, a1_store,
-                                               fuse1 ? &fin1 : nullptr, eval ? &ev : nullptr, st));
+                                               fuse1 ? &fin1 : nullptr, fold ? &ev : nullptr, st));
     // BN2 + Swish + SE squeeze, SE excite
     const BnFin fin2 = make_bn_fin(psum2, psq2, prm->bn2_gamma, prm->bn2_beta, run ? run->bn2_mean : nullptr,
                                    run ? run->bn2_var : nullptr, bn2, P.NPdw, eps, mom, m2);
@@ -395,7 +399,7 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
                                    prep_first ? nullptr : &prep));
     if (P.se) {
         const auto pool = [&]() {
-            return eval ? hipSuccess
+            return fold ? hipSuccess
                         : launch_pool(bf, P.N, P.Cexp, P.HWo, d, bn2, z, at<float>(saved, P.o_s3),
                                       at<float>(saved, P.o_s4), fuse2 ? &fin2 : nullptr,
                                       prep_first ? nullptr : &prep, st);

@@ -42,28 +42,40 @@ __device__ __forceinline__ void dw_eval_extra(const DwEval &ev, int block, int t
     const int step = ev.coef * threads;
     for (size_t j = (size_t)block * threads + tid; j < ev.ones_count; j += step)
         ev.ones[j] = 1.0f;
-    for (int i = block * threads + tid; i < ev.bn2.C + ev.bn3.C; i += step) {
-        const bool second = i < ev.bn2.C;
-        const BnEval b = second ? ev.bn2 : ev.bn3;
-        const int c = second ? i : i - ev.bn2.C;
+    const auto one = [&](const BnEval &b, int c) __attribute__((always_inline)) {
         const BnEvalCoef k = bn_eval_coef(bn_eval_issue(b, c), ev.eps);
         b.bn[c] = k.scale;
         b.bn[b.C + c] = k.shift;
         b.bn[2 * b.C + c] = k.mean;
         b.bn[3 * b.C + c] = k.rstd;
+    };
+    const int C1 = ev.bn1.C, C2 = C1 + ev.bn2.C, C3 = C2 + ev.bn3.C;
+    for (int i = block * threads + tid; i < C3; i += step) {
+        if (i < C1)
+            one(ev.bn1, i);
+        else if (i < C2)
+            one(ev.bn2, i - C1);
+        else
+            one(ev.bn3, i - C2);
     }
+}
+
+// Workgroups of `threads` threads that dw_eval_extra takes
+inline unsigned dw_eval_blocks(DwEval &ev, int threads)
+{
+    // (the coefficients need a thread each; the ones, where there are any, eight to a thread)
+    const size_t want = std::max((size_t)(ev.bn1.C + ev.bn2.C + ev.bn3.C), (ev.ones_count + 7) / 8);
+    ev.coef = (int)std::min<size_t>((want + threads - 1) / threads, 1024);
+    const int per = threads / 256;
+    return (unsigned)(ev.coef + (ev.prep.tiles + per - 1) / per);
 }
 
 // Workgroups to append to a grid of `main` ones of `threads` threads.
 inline unsigned dw_eval_extra_blocks(DwTrain &, unsigned, int) { return 0; }
 inline unsigned dw_eval_extra_blocks(DwEval &ev, unsigned main, int threads)
 {
-    // (the coefficients need a thread each; the ones, where there are any, eight to a thread)
-    const size_t want = std::max((size_t)(ev.bn2.C + ev.bn3.C), (ev.ones_count + 7) / 8);
     ev.main = (int)main;
-    ev.coef = (int)std::min<size_t>((want + threads - 1) / threads, 1024);
-    const int per = threads / 256;
-    return (unsigned)(ev.coef + (ev.prep.tiles + per - 1) / per);
+    return dw_eval_blocks(ev, threads);
 }
 
 } // namespace mbk

@@ -184,8 +184,8 @@ struct BnEval {
 // What the depthwise launch of an evaluation-mode forward does besides the convolution: the kernel takes
 // BN1's and BN2's coefficients from the running statistics and, where z is non-null, writes the SE stage's
 // squeeze (the mean of each plane after BN2 and activation), and workgroups past the convolution's write
-// what later kernels read: the blocks of BN2 and BN3, the gate of ones of a block without SE, and weight
-// images.  The launches these would be (coefficients, pool) are a few microseconds each, which is what a
+// what later kernels read: the blocks of BN2 and BN3 (and BN1's), the gate of ones of a block without SE, and
+// weight images.  The launches these would be (coefficients, pool) are a few microseconds each, which is what a
 // forward of one image consists of.
 struct DwEval {
     static constexpr bool kEval = true;
@@ -234,6 +234,11 @@ size_t dw_bwd_lds_bytes(const DwShape &s);
 // partial sums and writes it to fin->bn_out; psum/psq must not overlap fin's partials.
 // With `ev` non-null (evaluation mode) there are no partial sums, and of bn1 only whether it is null counts.
 bool dw_fwd_finalizes_bn1(const DwShape &s, bool stores_a1);
+// dw_eval_folds: whether evaluation mode should use `ev`.  Elsewhere launch_dw_eval_coef writes what the extra
+// workgroups would, ahead of everything else (`coef_ahead`: a launch is due there anyway, for an image that the
+// expansion conv reads), and the depthwise launch is that of training mode, its partial sums unread.
+bool dw_eval_folds(bool bf16, const DwShape &s, bool se, bool coef_ahead);
+hipError_t launch_dw_eval_coef(DwEval &ev, hipStream_t st);
 hipError_t launch_dw_fwd(bool bf16, const DwShape &s, const void *e, const float *bn1,
                          const void *w_dw, void *d, float *psum, float *psq, void *a1_store,
                          const BnFin *fin, const DwEval *ev, hipStream_t st);

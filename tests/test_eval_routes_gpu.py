@@ -52,3 +52,38 @@ def test_matches_oracle(name, variant):
     got = to_numpy(blk.forward_eval(blk.to_device(t["x"])))
     torch.cuda.synchronize()
     assert metric_for(s)(got, orc.mbconv_forward_eval(s, t)) <= TOL[s.dtype]["fwd"]
+
+
+def check(s, seed):
+    import torch
+    from paper_2110_10802_amd.harness import DeviceBlock, to_numpy
+
+    t = make_block_inputs(s, seed=seed)
+    rng = np.random.default_rng(7)
+    for i, c in ((1, s.Cexp), (2, s.Cexp), (3, s.Cout)):
+        t[f"bn{i}_mean"] = (0.3 * rng.standard_normal(c)).astype(np.float32)
+        t[f"bn{i}_var"] = rng.uniform(0.5, 2.0, c).astype(np.float32)
+    print(f"[eval] {s}", flush=True)
+    blk = DeviceBlock(s, t)
+    got = to_numpy(blk.forward_eval(blk.to_device(t["x"])))
+    torch.cuda.synchronize()
+    assert metric_for(s)(got, orc.mbconv_forward_eval(s, t)) <= TOL[s.dtype]["fwd"]
+
+
+# The other side of the rule: coefficients by a launch of their own, the squeeze by the pool
+AHEAD = {
+    "image_no_se": (13, 61, 366, 76, 10, 5, 2, False),       # a launch for the expansion conv precedes it anyway
+    "image_se": (13, 61, 366, 76, 10, 5, 2, True),           # (folded all the same: the pool is saved)
+    "9x9_no_se": (41, 16, 1024, 24, 9, 3, 2, False),         # 41984 wavefronts
+    "17x17_se_stride_2": (25, 16, 1000, 24, 17, 3, 2, True), # 100000 wavefronts
+    "68x68_5x5": (5, 8, 208, 24, 68, 5, 1, False),           # 1024 threads, 16640 wavefronts: dw4, and dw2
+    "68x68_5x5_stride_2": (5, 8, 208, 24, 68, 5, 2, False),
+    "67x67_5x5_no_expand": (5, None, 208, 24, 67, 5, 1, False),
+}
+
+
+@pytest.mark.parametrize("name", list(AHEAD))
+def test_coefficients_ahead(name):
+    N, Cin, Cexp, Cout, H, k, stride, se = AHEAD[name]
+    check(BlockShape(N=N, Cin=Cin or Cexp, H=H, W=H, Cexp=Cexp, Cse=6, Cout=Cout, k=k, stride=stride,
+                     has_expand=Cin is not None, residual=False, has_se=se), len(name))

@@ -1,0 +1,37 @@
+"""Rules of dispatch (host code of the library, no GPU): which calls a path takes, on either side of its lines."""
+import ctypes as C
+
+import pytest
+
+from paper_2110_10802_amd import binding as B
+
+
+class DwShape(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("N", "C", "H", "W", "Ho", "Wo", "k", "s", "p")]
+
+
+@pytest.mark.parametrize("N,channels,H,k,s,bf16,se,coef_ahead,folds", [
+    (1, 366, 10, 5, 2, False, False, True, False),     # nothing saved
+    (1, 366, 10, 5, 2, False, True, True, True),       # the pool is
+    (1, 48, 7, 3, 1, True, False, False, True),        # the coefficients' launch is
+    (28, 288, 25, 3, 1, False, False, False, False),   # a thread group to a plane: 32256 wavefronts, and fewer
+    (24, 288, 25, 3, 1, False, False, False, True),
+    (222, 288, 25, 3, 1, False, True, False, True),    # stride 1 with the pool: any size
+    (48, 672, 17, 5, 2, False, True, False, False),    # stride 2 with the pool: 129024, 64512, and 93696 with one launch saved
+    (24, 672, 17, 5, 2, False, True, False, True),
+    (64, 366, 17, 5, 2, False, True, True, False),
+    (16, 144, 72, 5, 2, False, True, False, False),    # 1024 threads, 5x5, fp32: 36864, 2304; bf16
+    (1, 144, 72, 5, 2, False, True, False, True),
+    (16, 144, 72, 5, 2, True, True, False, True),
+    (16, 144, 72, 5, 1, False, True, False, True),
+    (64, 144, 72, 5, 1, False, True, False, False),
+    (3, 252, 72, 5, 2, False, True, True, False),
+    (192, 144, 56, 5, 2, False, False, False, True),   # more pixels to a wavefront: any size
+    (192, 1152, 7, 5, 1, False, False, False, True),
+])
+def test_evaluation_folds_launches_into_the_depthwise_kernel(N, channels, H, k, s, bf16, se, coef_ahead, folds):
+    rule = getattr(B.load(), "_ZN3mbk13dw_eval_foldsEbRKNS_7DwShapeEbb")
+    rule.restype, rule.argtypes = C.c_bool, [C.c_bool, C.POINTER(DwShape), C.c_bool, C.c_bool]
+    p = (k - 1) // 2
+    out = (H + 2 * p - k) // s + 1
+    assert rule(bf16, C.byref(DwShape(N, channels, H, H, out, out, k, s, p)), se, coef_ahead) == folds
