@@ -577,25 +577,28 @@ __global__ __launch_bounds__(T) void reduce_splits_kernel(SplitReduce a, SplitRe
         reduce_splits_body<V, E, T>(b, blockIdx.x - blocks_a);
 }
 
+// Many rows are those of small gradients: more groups, narrower ones, so that more workgroups share the rows.  The
+// reduction with more of them decides: the other one loses little by it, and that one waits for its longest lane
+// (144 x 24 twice with 448 rows 8.1 us as here, 12.9 the other way; 240 x 40 with 128 and 240 x 80 with 42 rows 5.7, 6.6; 72 x 24
+// with 499 and 72 x 22 with 32 rows 5.0, 11.1; 480 x 80 twice with 64 rows 10.0 either way; 672 x (192 + 112) with 25 and 42
+// rows 13.7, 12.7).
+bool reduce_splits_many_rows(int Sa, int Sb) { return std::max(Sa, Sb) >= 96; }
+
 hipError_t launch_reduce_splits2(const SplitReduce &a, const SplitReduce &b, hipStream_t st)
 {
     const auto wide = [](const SplitReduce &r) {
         return r.count % 4 == 0 && (((uintptr_t)r.in | (uintptr_t)r.out) & 15u) == 0;
     };
     const bool two = b.count > 0;
-    const int S = two ? std::min(a.S, b.S) : a.S;
 #define MBK_GO(V, E, T)                                                                           \
     {                                                                                             \
         const unsigned ba = (unsigned)((a.count / (V) + (E)-1) / (E));                            \
         const unsigned bb = two ? (unsigned)((b.count / (V) + (E)-1) / (E)) : 0u;                 \
         hipLaunchKernelGGL((reduce_splits_kernel<V, E, T>), dim3(ba + bb), dim3(T), 0, st, a, b, ba); \
     }
-    // many rows are those of small gradients: more groups, narrower ones, so that more workgroups share the
-    // rows (two of 240 x 40 with 128 rows 6.4 us as here, 6.7 the other way; two of 144 x 24 with 448 rows 7.7, 11.7;
-    // two of 480 x 80 with 64 rows 9.9 either way; 672 x (192 + 112) with 25 and 42 rows 13.3, 12.3)
     if (!wide(a) || (two && !wide(b)))
         MBK_GO(1, 32, 1024)
-    else if (S >= 96)
+    else if (reduce_splits_many_rows(a.S, two ? b.S : 0))
         MBK_GO(4, 16, 512)
     else
         MBK_GO(4, 32, 256)

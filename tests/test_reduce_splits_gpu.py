@@ -5,7 +5,10 @@ terms that are each rounded a few times, so it is held to 2^-24 times the sum of
 import pytest
 import torch
 
+from mbconv_inputs import BlockShape, make_block_inputs
+from oracle import oracle as orc
 from paper_2110_10802_amd import dnnops as D
+from parity_util import compare_block, run_gpu_block
 
 pytestmark = pytest.mark.gpu
 
@@ -28,3 +31,13 @@ def test_weight_gradients(rows, cols):
     for got, terms in ((dg, dy.double() * xh), (db, dy.double())):
         bound = 16 * 2.0 ** -24 * terms.abs().sum(0) + 1e-30
         assert bool(((got.cpu().double() - terms.sum(0)).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("N,Cin,Cexp,Cout,H,stride", [(5, 8, 48, 8, 54, 2), (6, 24, 72, 22, 36, 2), (3, 13, 70, 9, 31, 1)])
+def test_two_gradients_of_unequal_rows(N, Cin, Cexp, Cout, H, stride):
+    s = BlockShape(N=N, Cin=Cin, H=H, W=H, Cexp=Cexp, Cse=4, Cout=Cout, k=3, stride=stride)
+    t = make_block_inputs(s, seed=N)
+    print(f"[reduce_splits] {s}", flush=True)
+    res, blk = run_gpu_block(s, t)
+    f, b = orc.mbconv_step(s, t)
+    compare_block(s, t, res, f, b, blk)

@@ -35,3 +35,11 @@ def test_evaluation_folds_launches_into_the_depthwise_kernel(N, channels, H, k, 
     p = (k - 1) // 2
     out = (H + 2 * p - k) // s + 1
     assert rule(bf16, C.byref(DwShape(N, channels, H, H, out, out, k, s, p)), se, coef_ahead) == folds
+
+
+@pytest.mark.parametrize("rows,many", [((448, 448), True), ((499, 32), True), ((20, 456), True), ((128, 0), True),
+                                       ((64, 64), False), ((8, 13), False), ((42, 0), False)])
+def test_sum_of_partial_gradients_goes_by_the_longer_one(rows, many):
+    rule = getattr(B.load(), "_ZN3mbk23reduce_splits_many_rowsEii")
+    rule.restype, rule.argtypes = C.c_bool, [C.c_int, C.c_int]
+    assert rule(*rows) == many
