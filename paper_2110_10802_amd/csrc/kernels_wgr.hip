@@ -193,12 +193,13 @@ constexpr int kWgrResident = 4 * 256 - 16;
 static int wgr_tiles(int Ma, int Mb) { return ((Ma + 63) / 64) * ((Mb + 63) / 64); }
 static int wgr_chunks(int N, int HW) { return (int)(((long long)N * HW + 31) / 32); }
 
-// As many splits as are resident at once, of at least four chunks.
+// As many splits as are resident at once, of four chunks or more (the last one fewer: 117 -> 171 channels on 29 planes of
+// 3x3, nine chunks, training step 75.0 us with two splits, 71.5 with three).
 bool wgr_plan(bool bf16, int Ma, int Mb, int N, int HW, int *splits)
 {
     if ((long long)N * std::max(Ma, Mb) * HW * (bf16 ? 2 : 4) >= (1ll << 32)) // 32-bit byte offsets in the kernel
         return false;
-    const int most = std::max(1, wgr_chunks(N, HW) / 4);
+    const int most = (wgr_chunks(N, HW) + 3) / 4;
     *splits = std::max(1, std::min(std::min(640, kWgrResident) / wgr_tiles(Ma, Mb), most));
     return true;
 }

@@ -43,3 +43,11 @@ def test_sum_of_partial_gradients_goes_by_the_longer_one(rows, many):
     rule = getattr(B.load(), "_ZN3mbk23reduce_splits_many_rowsEii")
     rule.restype, rule.argtypes = C.c_bool, [C.c_int, C.c_int]
     assert rule(*rows) == many
+
+
+@pytest.mark.parametrize("N,Ma,Mb,HW,splits", [(29, 171, 117, 9, 3), (1, 64, 64, 1, 1), (5, 64, 64, 49, 2), (64, 1152, 192, 49, 11)])
+def test_weight_gradient_splits_have_four_chunks(N, Ma, Mb, HW, splits):
+    plan = getattr(B.load(), "_ZN3mbk8wgr_planEbiiiiPi")
+    plan.restype, plan.argtypes = C.c_bool, [C.c_bool] + 4 * [C.c_int] + [C.POINTER(C.c_int)]
+    got = C.c_int(0)
+    assert plan(False, Ma, Mb, N, HW, C.byref(got)) and got.value == splits
