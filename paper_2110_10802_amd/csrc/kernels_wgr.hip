@@ -81,13 +81,17 @@ __device__ __forceinline__ void wgr_body(const WgrArgs &a, int item, float (*Us)
     // items: the wider side's tiles outermost, then the other's, then the splits, so that what shares the
     // wider operand's rows shares a die
     const int split = item % a.splits, t = item / a.splits;
+    const int cbeg = split * a.perSplit, cend = min(cbeg + a.perSplit, a.chunks);
     const bool wideA = a.tilesA >= a.tilesB;
     const int minor = wideA ? a.tilesB : a.tilesA;
     const int ta = wideA ? t / minor : t % minor, tb = wideA ? t % minor : t / minor;
     const int Ma = a.Ma, Mb = a.Mb;
     const uint32_t HW = (uint32_t)a.HW;
-    const char *u0 = (const char *)a.U.p0, *u1 = (const char *)a.U.p1, *v0 = (const char *)a.V.p0;
-    const char *gates = (const char *)a.V.gate;
+    // byte offsets are 32 bits, from the split's first image on: its images lie within 4 GiB (wgr_least)
+    const uint32_t q0 = (uint32_t)min(cbeg, a.chunks - 1) * 32u, n0 = fdiv(q0, a.divHW);
+    const size_t fromU = (size_t)n0 * Ma * HW * sizeof(T), fromV = (size_t)n0 * Mb * HW * sizeof(T);
+    const char *u0 = (const char *)a.U.p0 + fromU, *u1 = (const char *)a.U.p1 + fromU, *v0 = (const char *)a.V.p0 + fromV;
+    const char *gates = (const char *)a.V.gate + (size_t)n0 * Mb * 4u;
     const int qcol = tid % QC, rrow = tid / QC;
 
     // rows rrow + RR*i of the tiles (past the end the last one: never stored), byte offsets within an image
@@ -112,9 +116,9 @@ __device__ __forceinline__ void wgr_body(const WgrArgs &a, int item, float (*Us)
     float gate[NR];
     uint32_t okm = 0; // the run is inside the batch
     const auto fetch = [&](int chunk) __attribute__((always_inline)) {
-        const uint32_t q = (uint32_t)chunk * 32u + (uint32_t)(qcol * VEC), qc = q < a.Q ? q : 0u;
+        const uint32_t q = (uint32_t)chunk * 32u + (uint32_t)(qcol * VEC), qc = q < a.Q ? q : q0;
         okm = q < a.Q ? 0xffffffffu : 0u;
-        const uint32_t n = fdiv(qc, a.divHW), pix = qc - n * HW;
+        const uint32_t image = fdiv(qc, a.divHW), pix = qc - image * HW, n = image - n0;
         const uint32_t bu = (n * (uint32_t)Ma * HW + pix) * (uint32_t)sizeof(T);
         const uint32_t bv = (n * (uint32_t)Mb * HW + pix) * (uint32_t)sizeof(T), bg = n * (uint32_t)Mb * 4u;
 #pragma unroll
@@ -142,7 +146,6 @@ __device__ __forceinline__ void wgr_body(const WgrArgs &a, int item, float (*Us)
 #pragma unroll
     for (int k = 0; k < 16; ++k)
         acc[k] = 0.f;
-    const int cbeg = split * a.perSplit, cend = min(cbeg + a.perSplit, a.chunks);
     const int ua = (lane >> 5) * kWgrPitch + 32 * wa + (lane & 31), va = (lane >> 5) * kWgrPitch + 32 * wb + (lane & 31);
     if (cbeg < cend) { // uniform over the workgroup; an empty split writes zeros
         fetch(cbeg);
@@ -193,15 +196,22 @@ constexpr int kWgrResident = 4 * 256 - 16;
 static int wgr_tiles(int Ma, int Mb) { return ((Ma + 63) / 64) * ((Mb + 63) / 64); }
 static int wgr_chunks(int N, int HW) { return (int)(((long long)N * HW + 31) / 32); }
 
+// The fewest splits whose images each lie within 4 GiB, the span of the kernel's byte offsets; 0: not even a chunk's do.
+static int wgr_least(bool bf16, int Ma, int Mb, int N, int HW)
+{
+    const long long image = (long long)std::max(Ma, Mb) * std::max(HW * (bf16 ? 2 : 4), 4); // (its gates: 4 bytes a row)
+    const long long images = ((1ll << 32) - 1) / image;
+    const long long chunks = images > 2 ? (images - 2) * HW / 32 : 0; // 32*chunks pixels touch that many images at most
+    return chunks ? (int)((wgr_chunks(N, HW) + chunks - 1) / chunks) : 0;
+}
+
 // As many splits as are resident at once, of four chunks or more (the last one fewer: 117 -> 171 channels on 29 planes of
 // 3x3, nine chunks, training step 75.0 us with two splits, 71.5 with three).
 bool wgr_plan(bool bf16, int Ma, int Mb, int N, int HW, int *splits)
 {
-    if ((long long)N * std::max(Ma, Mb) * HW * (bf16 ? 2 : 4) >= (1ll << 32)) // 32-bit byte offsets in the kernel
-        return false;
-    const int most = (wgr_chunks(N, HW) + 3) / 4;
-    *splits = std::max(1, std::min(std::min(640, kWgrResident) / wgr_tiles(Ma, Mb), most));
-    return true;
+    const int most = (wgr_chunks(N, HW) + 3) / 4, least = wgr_least(bf16, Ma, Mb, N, HW);
+    *splits = std::max(least, std::min(std::min(640, kWgrResident) / wgr_tiles(Ma, Mb), most));
+    return least > 0;
 }
 
 static WgrArgs wgr_args(int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V, float *partial, int splits)
@@ -276,6 +286,8 @@ hipError_t launch_wgr_pair(bool bf16, int N, int MaA, int MbA, int HWA, const Op
     const WgrSide a = {wgr_tiles(MaA, MbA), wgr_chunks(N, HWA), VA.pro == PRO_NONE ? 12 : 16, sa};
     const WgrSide b = {wgr_tiles(MaB, MbB), wgr_chunks(N, HWB), 12, sb};
     wgr_pair_splits(a, b, kWgrResident, splitsA, splitsB);
+    *splitsA = std::max(*splitsA, wgr_least(bf16, MaA, MbA, N, HWA));
+    *splitsB = std::max(*splitsB, wgr_least(bf16, MaB, MbB, N, HWB));
     return wgr_go(bf16, VA.pro != PRO_NONE, wgr_args(N, MaA, MbA, HWA, UA, VA, partialA, *splitsA),
                   wgr_args(N, MaB, MbB, HWB, UB, VB, partialB, *splitsB), st);
 }

@@ -51,3 +51,16 @@ def test_weight_gradient_splits_have_four_chunks(N, Ma, Mb, HW, splits):
     plan.restype, plan.argtypes = C.c_bool, [C.c_bool] + 4 * [C.c_int] + [C.POINTER(C.c_int)]
     got = C.c_int(0)
     assert plan(False, Ma, Mb, N, HW, C.byref(got)) and got.value == splits
+
+
+@pytest.mark.parametrize("bf16,N,Ma,Mb,HW,least", [
+    (False, 3500, 96, 7, 3249, 2),           # 4.4 GB in all
+    (False, 1, 60000, 8, 16384, 0),          # 4 GB an image: the general kernel's
+    (True, 1 << 20, 1100, 8, 1, 2),          # one pixel a plane: the gates are the larger
+])
+def test_weight_gradients_of_4_gib_and_more(bf16, N, Ma, Mb, HW, least):
+    plan = getattr(B.load(), "_ZN3mbk8wgr_planEbiiiiPi")
+    plan.restype, plan.argtypes = C.c_bool, [C.c_bool] + 4 * [C.c_int] + [C.POINTER(C.c_int)]
+    got = C.c_int(0)
+    assert plan(bf16, Ma, Mb, N, HW, C.byref(got)) == (least > 0)
+    assert got.value >= least
