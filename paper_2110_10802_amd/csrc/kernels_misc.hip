@@ -602,7 +602,7 @@ __global__ __launch_bounds__(256) void se_bwd_sums_kernel(SeBwdArgs a, int chan,
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < TN * 64 / 256; ++u)
-                dqL[(tid >> 6) + 4 * u][tid & 63] = dv[u];
+                dqL[(tid >> 6) + 4 * u][tid & 63] = and_mask(dv[u], (tid & 63) < Cse ? 0xffffffffu : 0u);
             if (n0 == 0) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
@@ -610,7 +610,7 @@ __global__ __launch_bounds__(256) void se_bwd_sums_kernel(SeBwdArgs a, int chan,
             }
             __syncthreads();
             float dz[4] = {0.f, 0.f, 0.f, 0.f};
-            for (int j4 = 0; j4 < J4; ++j4) { // (past the last squeezed channel the weights are zero)
+            for (int j4 = 0; j4 < J4; ++j4) { // (past the last squeezed channel both factors are zero: dq may be infinite)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const float4 d4 = *reinterpret_cast<const float4 *>(&dqL[nl + 16 * u][4 * j4]);

@@ -19,3 +19,22 @@ def test_gradients_match_oracle(N, C, Cse):
     res, blk = run_gpu_block(s, t)
     f, b = orc.mbconv_step(s, t)
     compare_block(s, t, res, f, b, blk)
+
+
+def test_infinite_squeezed_gradient_stays_infinite():
+    # One squeezed channel of five has an infinite gradient; it reaches one channel through a weight that is not zero, and
+    # that channel's sums are infinite then, not NaN: what fills up the fours of the squeezed channels is left out.
+    import numpy as np
+    C = 176
+    s = BlockShape(N=1, Cin=C, H=4, W=4, Cexp=C, Cse=5, Cout=16, k=3, stride=1, has_expand=False)
+    t = make_block_inputs(s, seed=1)
+    t["se_w1"][4] = 0.0
+    t["se_w1"][4, 7] = 1.0
+    t["se_b1"][4] = 0.0
+    t["bn2_gamma"][7] = t["bn2_beta"][7] = 0.0  # z[7] = 0, so q[4] = 0: no effect on the gate, swish'(0) = 1/2
+    t["se_w2"][:, 4] = 0.0
+    t["se_w2"][11, 4] = 3e38  # one infinite term: none of the other sign to cancel it
+    t["dout"] *= 100.0
+    print(f"[se bwd] {s}", flush=True)
+    res, blk = run_gpu_block(s, t)
+    assert np.isinf(res["grads"]["bn2_beta"][7])
