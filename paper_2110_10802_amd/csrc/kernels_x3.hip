@@ -1048,6 +1048,8 @@ __global__ __launch_bounds__(64 * KS) void conv_xs_kernel(X3SArgs a)
     }
 }
 
+int wave_conv_kind(int M, int K, int HW); // kernels_pv16.hip
+
 // `nt`: chunks = statistics partials per row.
 bool xs_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt)
 {
@@ -1057,14 +1059,25 @@ bool xs_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt)
         return false;
     if (Q * M >= (1ll << 30) || Q * K >= (1ll << 30)) // 32-bit byte offsets in the kernel
         return false;
-    // Up to one and a half times what is resident at once; beyond, the rows that every workgroup reads again cost
-    // more than the latencies (training step, the other kernels / here, us: 24 -> 144 on 56x56, 12 images
-    // 142.1 / 139.2, 16 160.8 / 163.3; 80 -> 480 on 14x14, 2 images 82.5 / 78.9, 16 106.2 / 105.5, 32 126.9 / 127.6; 192 ->
-    // 1152 on 7x7, 2 images 110.3 / 101.7, 16 140.8 / 136.9, 32 164.1 / 164.6).  33 to 40 input channels are the
-    // most conv_pe takes, at the fewest wavefronts, and it is later that it wins (40 -> 240 on 28x28, one image 86.9 / 79.9,
-    // 32 181.8 / 175.5, 64 267.3 / 264.5).
-    const long long waves = chunks * ((M + 15) / 16) * ((K + 31) / 32);
-    if (waves > (K > 32 && K <= 40 ? 48 * 1024 : 12 * 1024))
+    bool ok;
+    // Where the other kernel is conv_pe (kernels_pv16.hip: planes of a multiple of four pixels, up to 40 input and 384 output
+    // channels), whose workgroups take all rows of 64 pixels and are the later to finish the more rows there are, and
+    // leave BN1 fewer partial sums: up to eight chunks a row, 1280 in all.  (Forward, conv_pe / here, us, at a half, once and
+    // one and a half times that: 24 -> 144 on 28x28 1.12, 1.05, 0.96 times as fast, 40 -> 120 on 56x56 1.07, 1.06, 0.98;
+    // 40 -> 240 on 14x14 at 532, 1065 and 2131 chunks 1.23, 1.12, 1.00; 16 -> 192 on 56x56 at 784 and 1568 1.02, 0.97; 40 -> 384
+    // on 28x28 at 759, 1543 and 3062 1.06, 1.03, 0.86; 8 -> 48 on 56x56, 2646 chunks 48.2 / 48.7.)
+    if (wave_conv_kind(M, K, HW))
+        ok = chunks <= std::min(8 * M, 1280);
+    // Elsewhere up to one and a half times what is resident at once; beyond, the rows that every workgroup reads again cost
+    // more than the latencies (80 -> 480 on 14x14 and 15x15 at 8, 16 and 32 thousand wavefronts 1.02 to 1.04, 1.00, 0.9;
+    // 24 -> 144 on 57x57 1.04, 1.02, 1.00).  conv_xw catches up sooner where it has few rows to stage and reads
+    // the pixels once: 64 -> 64 on 14x14, 251, 502 and 998 chunks 1.07, 1.01, 0.92; 32 -> 96 on 27x27, 660 and 1344 1.05, 0.97.
+    else {
+        int sets;
+        const long long waves = chunks * ((M + 15) / 16) * ((K + 31) / 32);
+        ok = waves <= 12 * 1024 && (chunks <= 512 || !xw_conv_plan(N, M, K, HW, pro, epi, &sets));
+    }
+    if (!ok)
         return false;
     *nt = (int)chunks;
     return true;

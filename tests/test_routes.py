@@ -64,3 +64,24 @@ def test_weight_gradients_of_4_gib_and_more(bf16, N, Ma, Mb, HW, least):
     got = C.c_int(0)
     assert plan(bf16, Ma, Mb, N, HW, C.byref(got)) == (least > 0)
     assert got.value >= least
+
+
+@pytest.mark.parametrize("N,M,K,H,chunks", [
+    (32, 240, 40, 28, 784), (64, 240, 40, 28, None),     # beside conv_pe: eight chunks a row, 1280 at most
+    (2, 48, 8, 56, 196), (41, 48, 8, 56, None),
+    (11, 144, 24, 56, 1078), (12, 144, 24, 56, None),
+    (30, 384, 40, 28, 735), (64, 384, 40, 28, None),
+    (17, 240, 40, 27, 388), (18, 240, 40, 27, None),     # odd plane: 12288 wavefronts; so for outputs above conv_pe's
+    (11, 400, 40, 28, None), (9, 400, 40, 28, 221),
+    (18, 576, 96, 14, 111), (19, 576, 96, 14, None),
+    (83, 64, 64, 14, 509), (85, 64, 64, 14, None),       # few rows: conv_xw from 512 chunks on
+    (8, 12, 8, 57, 813), (100, 12, 8, 57, 10154),        # (conv_big: no such line)
+    (1, 240, 41, 7, None), (1, 1536, 256, 7, None),      # channel counts that it does not take
+])
+def test_expansion_conv_of_small_launches(N, M, K, H, chunks):
+    plan = getattr(B.load(), "_ZN3mbk12xs_conv_planEiiiiiiPi")
+    plan.restype, plan.argtypes = C.c_bool, 6 * [C.c_int] + [C.POINTER(C.c_int)]
+    got = C.c_int(0)
+    assert plan(N, M, K, H * H, 0, 1, C.byref(got)) == (chunks is not None)
+    if chunks is not None:
+        assert got.value == chunks
