@@ -6,20 +6,24 @@
 // block, and what bounds a kernel that reads both is memory: 16 -> 96 channels on 803 k pixels are 719 MB,
 // 160 us in this form, 170 with a workgroup per chunk.  But e = W x, and x is here for the weight gradient
 // anyway, so a chunk's e costs matrix-core time only (section "Guided Optimization Case Study:
-// EfficientNet": recompute instead of load): 411 MB, 110 us.
+// EfficientNet": recompute instead of load): 411 MB, 105 us.
 //   - A wavefront owns chunks of 32 pixels (chunk = W*workgroup + wavefront, stride W*grid); nothing crosses
 //     wavefronts inside the loop, so there is no barrier in it.
 //   - Lane (r, g) = (lane % 16, lane / 16) holds pixels 2r and 2r+1, eight bytes per load, sixteen lanes to a
-//     128-byte line.  Of x it loads channels 8g .. 8g+7: their planes (mbconv_x3.h), packed along the
-//     channels, are the B operand of e: one accumulator tile per 16 wide channels that starts at c2;
-//     A = c1*W in planes, in LDS, built once by the workgroup.
+//     128-byte line.  Of x it loads channels 4g .. 4g+3, which are the B operand of e on fp32 MFMA; A = W, in LDS.
+//     e has to be as good as the fp32 value that the forward pass stored: an error that all pixels share, of a rounded
+//     weight or of an accumulator that truncates, meets a mean of x in the weight gradient and does not average out.
+//     (On bf16 MFMA, in three planes, from c2 up: relative error of dW against 64 bits, channels of mean 5, 16 -> 96,
+//     300 k pixels, 1.3e-5; with the stored e 2.4e-6; as here 6.0e-7.)
 //   - The result has the lane's two pixels of channels 4g .. 4g+3, and that is how dy1 is loaded, so
-//     de = c0*dy1 + (c1*e + c2) is one fma per element.
+//     de = c0*dy1 + (c1*e + c2) is two fma per element.
 //   - Data gradient: these registers, split, are its B operand (the contraction's order is free: W^T lies in
-//     LDS to match).
+//     LDS to match); a step's product is complete before it is added (dx 1.3e-7 with one accumulator, now 6.2e-8).
 //   - Weight gradient: a contraction over pixels, so de and x go through LDS once, [channel][pixel], the
-//     lane's two pixels of a channel as one 32-bit store per plane.
-//   - dy1 is requested three steps of 32 channels ahead, across the end of a chunk.
+//     lane's two pixels of a channel as one 32-bit store per plane; large and small products in accumulators of their own
+//     (5.1e-7 together, 1.1e-7 now, for centred channels).
+//   - dy1 is requested three steps of 32 channels ahead (two from 97 channels on, one from 129: registers), across
+//     the end of a chunk.
 // The wavefronts' weight-gradient tiles are added in wavefront order at the end, the workgroups' by
 // reduce_splits: fixed order, no atomics.
 // With 17 to 32 narrow channels the accumulators of two tiles leave no registers to run ahead: 24 -> 144 on
@@ -77,9 +81,9 @@ template <int NT>
 struct ReLds {
     static constexpr int KS = (NT + 1) / 2;       // steps of 32 wide channels
     static constexpr int kWave = 3 * 32 * kReHalf * 2;
-    static constexpr int kExp = NT * 3 * 1024;    // c1*W
-    static constexpr int kBack = KS * 3 * 1024;   // W^T
-    static constexpr int kCoef = 2 * 32 * KS * 4; // c0, c2
+    static constexpr int kExp = NT * 1024;        // W
+    static constexpr int kBack = KS * 3 * 1024;   // W^T in planes
+    static constexpr int kCoef = 3 * 32 * KS * 4; // c0, c1, c2
     static constexpr int kTile = 16 * NT * 16 * 4; // a weight-gradient tile
     static constexpr size_t bytes(int W)
     {
@@ -93,15 +97,15 @@ template <int NT>
 __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
 {
     typedef ReLds<NT> L;
-    constexpr int KS = L::KS, DEPTH = KS < 3 ? KS : 3;
+    constexpr int KS = L::KS, DEPTH = NT > 8 ? 1 : NT > 6 ? 2 : KS < 3 ? KS : 3;
     extern __shared__ __attribute__((aligned(16))) char ldsb[];
     const int tid = threadIdx.x, lane = tid & 63, W = a.W;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g = lane >> 4;
     const int Cn = a.Cn, Cw = a.Cw, HW = a.HW;
-    uint16_t *const We = reinterpret_cast<uint16_t *>(ldsb);
+    f32x4 *const We = reinterpret_cast<f32x4 *>(ldsb);
     uint16_t *const Wt = reinterpret_cast<uint16_t *>(ldsb + L::kExp);
-    float *const C0 = reinterpret_cast<float *>(ldsb + L::kExp + L::kBack), *const C2 = C0 + 32 * KS;
+    float *const C0 = reinterpret_cast<float *>(ldsb + L::kExp + L::kBack), *const C1 = C0 + 32 * KS, *const C2 = C1 + 32 * KS;
     uint16_t *const Lh = reinterpret_cast<uint16_t *>(ldsb + L::kExp + L::kBack + L::kCoef + wv * L::kWave);
 
     // ---- loads: 32-bit element offsets (the host checks the tensors' sizes), uniform bases ----
@@ -115,7 +119,7 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
         vb = n * vimg + pix;
         ub = n * uimg + pix;
     };
-    f32x2 vy[KS][8], xv[8];
+    f32x2 vy[KS][8], xv[4];
     const uint32_t rows4 = (uint32_t)(4 * g) * (uint32_t)HW;
     // rows 16t + 4g .. +3 of tile t; the last tiles' rows are clamped to the last group of four
     // (Cw % 4 == 0; what lies past the end meets zero coefficients)
@@ -133,11 +137,11 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
                 vy[s][4 * t + i] = *reinterpret_cast<const f32x2 *>(p + (size_t)i * HW + o);
         }
     };
-    // channels 8g .. 8g+7 of x, those past the last read it (their weights are zero)
+    // channels 4g .. 4g+3 of x, those past the last read it (their weights are zero)
     const auto fetch_x = [&](uint32_t ub) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            xv[j] = *reinterpret_cast<const f32x2 *>(a.x + (ub + __umul24((uint32_t)min(8 * g + j, Cn - 1), (uint32_t)HW)));
+        for (int j = 0; j < 4; ++j)
+            xv[j] = *reinterpret_cast<const f32x2 *>(a.x + (ub + __umul24((uint32_t)min(4 * g + j, Cn - 1), (uint32_t)HW)));
     };
     const int cStep = W * (int)gridDim.x;
     int ch = W * (int)blockIdx.x + wv;
@@ -154,23 +158,21 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
     // used: a loop of load and store pays a memory round trip per entry) ----
     const int nthr = 64 * W;
     {
-        constexpr int B = 3; // entries of eight values: [tile][lane], then [step][lane]
+        constexpr int B = 3; // entries: [tile][lane] of four weights, then [step][lane] of eight
         for (int e0 = tid; e0 < (NT + KS) * 64; e0 += B * nthr) {
-            float v[B][8], scale[B], k0 = 0.f, k2 = 0.f;
+            float v[B][8];
             const int cf = min(e0, Cw - 1);
-            k0 = a.c0[cf];
-            k2 = a.c2[cf];
+            const float k0 = a.c0[cf], k1 = a.c1[cf], k2 = a.c2[cf];
 #pragma unroll
             for (int u = 0; u < B; ++u) {
                 const int e = e0 + u * nthr, b = e >> 6, er = e & 15, eg = (e >> 4) & 3;
-                // c1*W: row = wide channel 16b + r, contraction = narrow channel 8g + t
+                // W: row = wide channel 16b + r, contraction = narrow channel 4g + t
                 // W^T: row = narrow channel, contraction = wide channels 4g + t and 16 + 4g + t - 4
-                const bool fwd = b < NT;
+                const bool fwd = b < NT; // uniform over the wavefront
                 const int row = fwd ? 16 * b + er : 32 * (b - NT) + 4 * eg;
-                scale[u] = fwd ? a.c1[min(row, Cw - 1)] : 1.f;
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
-                    const int c = fwd ? row : row + (t < 4 ? t : 12 + t), k = fwd ? 8 * eg + t : er;
+                    const int c = fwd ? row : row + (t < 4 ? t : 12 + t), k = fwd ? 4 * eg + t : er;
                     v[u][t] = and_mask(a.w[min(c, Cw - 1) * Cn + min(k, Cn - 1)], c < Cw && k < Cn ? 0xffffffffu : 0u);
                 }
             }
@@ -178,20 +180,22 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
             if (e0 < 32 * KS) {
                 const uint32_t m = e0 < Cw ? 0xffffffffu : 0u;
                 C0[e0] = and_mask(k0, m);
+                C1[e0] = and_mask(k1, m);
                 C2[e0] = and_mask(k2, m);
             }
 #pragma unroll
             for (int u = 0; u < B; ++u) {
-                const int e = e0 + u * nthr;
+                const int e = e0 + u * nthr, b = e >> 6;
                 if (e >= (NT + KS) * 64)
                     break;
-#pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    v[u][t] *= scale[u];
+                if (b < NT) {
+                    We[e] = (f32x4){v[u][0], v[u][1], v[u][2], v[u][3]};
+                    continue;
+                }
                 uint32_t p[4][3];
                 bf16x8 o[3];
                 x3_split8(v[u], p, o);
-                uint16_t *dst = We + (size_t)(e >> 6) * 3 * 512 + (e & 63) * 8;
+                uint16_t *dst = Wt + (size_t)(b - NT) * 3 * 512 + (e & 63) * 8;
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl)
                     *reinterpret_cast<bf16x8 *>(dst + pl * 512) = o[pl];
@@ -200,10 +204,11 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
     }
     __syncthreads();
 
-    f32x4 acc[NT];
+    // (the small products in accumulators of their own: the MFMA truncates a small addend to a large accumulator)
+    f32x4 acc[NT], low[NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i)
-        acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        acc[i] = low[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
     for (; ch < a.numChunks; ch += cStep) {
         // the next chunk (the last one re-reads itself: loads stay unconditional)
@@ -213,31 +218,18 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
 
         // x: B operand of e (column = pixel, contraction = channel), and through LDS of the weight gradient
         // (column = narrow channel, contraction = pixel)
-        bf16x8 bxe[2][3];
+        f32x2 xc[4];
         bf16x8 bx[3];
-        {
-            uint32_t w[8][3];
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                x3_split2(xv[j][0], xv[j][1], w[j]);
-            fetch_x(nub);
+        for (int j = 0; j < 4; ++j) {
+            xc[j] = xv[j];
+            uint32_t w[3];
+            x3_split2(xv[j][0], xv[j][1], w);
 #pragma unroll
-            for (int pl = 0; pl < 3; ++pl) {
-                u32x4 lo, hi;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    lo[t] = re_lo(w[2 * t][pl], w[2 * t + 1][pl]);
-                    hi[t] = re_hi(w[2 * t][pl], w[2 * t + 1][pl]);
-                }
-                bxe[0][pl] = __builtin_bit_cast(bf16x8, lo);
-                bxe[1][pl] = __builtin_bit_cast(bf16x8, hi);
-                if (g < 2) { // (sixteen rows)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        *reinterpret_cast<uint32_t *>(Lh + (pl * 32 + 8 * g + j) * kReHalf + 2 * r) = w[j][pl];
-                }
-            }
+            for (int pl = 0; pl < 3; ++pl)
+                *reinterpret_cast<uint32_t *>(Lh + (pl * 32 + 4 * g + j) * kReHalf + 2 * r) = w[pl];
         }
+        fetch_x(nub);
         re_lds_fence();
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl)
@@ -259,18 +251,20 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
                         d[0][4 * t + i] = d[1][4 * t + i] = 0.f;
                     continue;
                 }
-                bf16x8 av[3];
-#pragma unroll
-                for (int pl = 0; pl < 3; ++pl)
-                    av[pl] = *reinterpret_cast<const bf16x8 *>(We + (size_t)(tile * 3 + pl) * 512 + lane * 8);
-                const f32x4 k2 = *reinterpret_cast<const f32x4 *>(C2 + 16 * tile + 4 * g);
+                const f32x4 aw = We[64 * tile + lane];
                 const f32x4 k0 = *reinterpret_cast<const f32x4 *>(C0 + 16 * tile + 4 * g);
-                f32x4 e0 = k2, e1 = k2;
-                re_mma(av, bxe[0], bxe[1], e0, e1);
+                const f32x4 k1 = *reinterpret_cast<const f32x4 *>(C1 + 16 * tile + 4 * g);
+                const f32x4 k2 = *reinterpret_cast<const f32x4 *>(C2 + 16 * tile + 4 * g);
+                f32x4 e0 = {0.f, 0.f, 0.f, 0.f}, e1 = e0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { // contraction 4g + j of every g
+                    e0 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[j], xc[j][0], e0, 0, 0, 0);
+                    e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[j], xc[j][1], e1, 0, 0, 0);
+                }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    d[0][4 * t + i] = and_mask(fmaf(k0[i], vy[s][4 * t + i][0], e0[i]), okm);
-                    d[1][4 * t + i] = and_mask(fmaf(k0[i], vy[s][4 * t + i][1], e1[i]), okm);
+                    d[0][4 * t + i] = and_mask(fmaf(k0[i], vy[s][4 * t + i][0], fmaf(k1[i], e0[i], k2[i])), okm);
+                    d[1][4 * t + i] = and_mask(fmaf(k0[i], vy[s][4 * t + i][1], fmaf(k1[i], e1[i], k2[i])), okm);
                 }
             }
             if (s + DEPTH < KS)
@@ -308,7 +302,10 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
                     b1[pl] = __builtin_bit_cast(bf16x8, hi);
                     aw[pl] = *reinterpret_cast<const bf16x8 *>(Wt + (size_t)(s * 3 + pl) * 512 + lane * 8);
                 }
-                re_mma(aw, b0, b1, accd0, accd1);
+                f32x4 t0 = {0.f, 0.f, 0.f, 0.f}, t1 = t0;
+                re_mma(aw, b0, b1, t0, t1);
+                accd0 += t0;
+                accd1 += t1;
             }
             re_lds_fence();
 #pragma unroll
@@ -320,7 +317,14 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl)
                     av[pl] = *reinterpret_cast<const bf16x8 *>(Lh + (pl * 32 + 16 * t + r) * kReHalf + 8 * g);
-                acc[tile] = x3_mfma6_16(av, bx, acc[tile]);
+#define MBK_MMA(i, j) low[tile] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bx[j], low[tile], 0, 0, 0);
+                MBK_MMA(2, 0)
+                MBK_MMA(0, 2)
+                MBK_MMA(1, 1)
+                MBK_MMA(1, 0)
+                MBK_MMA(0, 1)
+#undef MBK_MMA
+                acc[tile] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[0], bx[0], acc[tile], 0, 0, 0);
             }
             re_lds_fence(); // these reads before the next step's stores
             __builtin_amdgcn_sched_barrier(0); // (left alone, the scheduler has all steps' operands in flight and spills)
@@ -339,6 +343,9 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
         okm = nokm;
     }
 
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+        acc[i] += low[i];
     // ---- the wavefronts' weight-gradient tiles, in wavefront order: [wide][narrow] ----
     constexpr int TILE = L::kTile / 4;
     float *const Lt = reinterpret_cast<float *>(ldsb);
@@ -381,13 +388,15 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
     }
 }
 
-// The shapes of this file: pixel pairs, groups of four wide channels, and enough chunks that the tables pay
-// (backward of a block, bwd1x1_lt / here: 16 -> 96 channels, 196 chunks 42.9 / 46.4 us, 784 chunks 56.2 / 55.1,
-// 3136 111.0 / 102.2, 25088 391.9 / 325.2; 12 -> 48, 8192 146.8 / 120.5; 9 -> 36, 4608 91.0 / 79.6).
+// The shapes of this file: pixel pairs, groups of four wide channels, and enough chunks that the tables pay (both
+// steps of the gradients, bwd1x1_lt / here, us: 16 -> 32 channels, 16 chunks 14.4 / 13.7, 392 16.1 / 14.3, 4214 36.9 / 21.9; 16 ->
+// 64, 196 chunks 15.4 / 16.2, 392 17.0 / 16.3; 16 -> 96, 392 chunks 18.0 / 18.4, 544 20.6 / 18.6, 12544 102 / 64; 16 -> 144, 544
+// 22.3 / 22.4, 4214 51.8 / 42.7; 16 -> 192, 4214 70.7 / 60.2).
 bool bwd1x1_re_supported(int N, int Cw, int Cn, int HW)
 {
-    return Cn <= 16 && Cn < Cw && Cw <= 192 && Cw % 4 == 0 && HW % 2 == 0 && (long long)N * HW >= 512 * 32 &&
-           (long long)N * Cw * HW < (1ll << 30); // 32-bit byte offsets in the kernel
+    const long long Q = (long long)N * HW, chunks = (Q + 31) / 32;
+    return Cn <= 16 && Cn < Cw && Cw <= 192 && Cw % 4 == 0 && HW % 2 == 0 && chunks >= (Cw <= 32 ? 1 : Cw <= 64 ? 256 : 512) &&
+           Q * Cw < (1ll << 30); // 32-bit byte offsets in the kernel
 }
 
 // At most `splits` workgroups; partial: [*used][Cw][Cn].
