@@ -32,6 +32,7 @@
 // bf16 (aligned shapes): the weights as they are, the activations rounded to bf16 once after their
 // fp32 prologue, one MFMA, fp32 accumulation, as in kernels_bf.hip.
 #include <algorithm>
+#include <type_traits>
 #include "mbconv_x3.h"
 
 namespace mbk {
@@ -223,58 +224,65 @@ __global__ __launch_bounds__(512, 2) void conv_xk_kernel(XkArgs a)
     float *Gt = ldsf + 2 * KP;
     // (all loads of a thread's share requested before the first is used: a loop of load and store pays a
     // memory round trip per iteration, 1152 -> 320 channels on 7x7 27.7 us, now 26.2; 672 -> 112 on 14x14 20.7,
-    // now 20.1)
-    constexpr int CU = 5;
+    // now 20.1.  Where a thread has one entry at most, none is requested for the others: 300 -> 56 channels on two 12x12
+    // planes, the block's evaluation 17.1 us with five, 16.8 with one)
     const int nthr = 64 * W;
-    if (PRO == PRO_BNBWD) {
-        for (int kb = tid; kb < KP; kb += CU * nthr) {
-            float v0[CU], v1[CU], v2[CU];
+    const auto coefficients = [&](auto cu) __attribute__((always_inline)) {
+        constexpr int CU = decltype(cu)::value;
+        if constexpr (PRO == PRO_BNBWD) {
+            for (int kb = tid; kb < KP; kb += CU * nthr) {
+                float v0[CU], v1[CU], v2[CU];
 #pragma unroll
-            for (int u = 0; u < CU; ++u) {
-                const int kk = min(kb + u * nthr, K - 1);
-                v0[u] = a.c0[kk];
-                v1[u] = a.c1[kk];
-                v2[u] = a.c2[kk];
-            }
-            __builtin_amdgcn_sched_barrier(0);
+                for (int u = 0; u < CU; ++u) {
+                    const int kk = min(kb + u * nthr, K - 1);
+                    v0[u] = a.c0[kk];
+                    v1[u] = a.c1[kk];
+                    v2[u] = a.c2[kk];
+                }
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < CU; ++u) {
-                const int k = kb + u * nthr;
-                const uint32_t m = k < K ? 0xffffffffu : 0u;
-                if (k < KP)
-                    Cb[k] = (f32x4){and_mask(v0[u], m), and_mask(v1[u], m), and_mask(v2[u], m), 0.f};
-            }
-        }
-    } else if (PRO == PRO_BNSWISH_GATE) {
-        const uint32_t nl = fdiv(min(q0 + 31u, a.Q - 1u), a.divHW) - n0;
-        const float *gt0 = a.gate + (size_t)n0 * K, *gt1 = a.gate + (size_t)(n0 + min(nl, 1u)) * K;
-        for (int kb = tid; kb < KP; kb += CU * nthr) {
-            float v0[CU], v1[CU], g0[CU], g1[CU];
-#pragma unroll
-            for (int u = 0; u < CU; ++u) {
-                const int kk = min(kb + u * nthr, K - 1);
-                v0[u] = a.c0[kk];
-                v1[u] = a.c1[kk];
-                g0[u] = gt0[kk];
-                g1[u] = gt1[kk];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < CU; ++u) {
-                const int k = kb + u * nthr;
-                const uint32_t m = k < K ? 0xffffffffu : 0u;
-                if (k < KP) {
-                    Cs[k] = (f32x2){and_mask(v0[u], m), and_mask(v1[u], m)};
-                    Gt[k] = and_mask(g0[u], m);
-                    if (nl)
-                        Gt[KP + k] = and_mask(g1[u], m);
+                for (int u = 0; u < CU; ++u) {
+                    const int k = kb + u * nthr;
+                    const uint32_t m = k < K ? 0xffffffffu : 0u;
+                    if (k < KP)
+                        Cb[k] = (f32x4){and_mask(v0[u], m), and_mask(v1[u], m), and_mask(v2[u], m), 0.f};
                 }
             }
+        } else if constexpr (PRO == PRO_BNSWISH_GATE) {
+            const uint32_t nl = fdiv(min(q0 + 31u, a.Q - 1u), a.divHW) - n0;
+            const float *gt0 = a.gate + (size_t)n0 * K, *gt1 = a.gate + (size_t)(n0 + min(nl, 1u)) * K;
+            for (int kb = tid; kb < KP; kb += CU * nthr) {
+                float v0[CU], v1[CU], g0[CU], g1[CU];
+#pragma unroll
+                for (int u = 0; u < CU; ++u) {
+                    const int kk = min(kb + u * nthr, K - 1);
+                    v0[u] = a.c0[kk];
+                    v1[u] = a.c1[kk];
+                    g0[u] = gt0[kk];
+                    g1[u] = gt1[kk];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < CU; ++u) {
+                    const int k = kb + u * nthr;
+                    const uint32_t m = k < K ? 0xffffffffu : 0u;
+                    if (k < KP) {
+                        Cs[k] = (f32x2){and_mask(v0[u], m), and_mask(v1[u], m)};
+                        Gt[k] = and_mask(g0[u], m);
+                        if (nl)
+                            Gt[KP + k] = and_mask(g1[u], m);
+                    }
+                }
+            }
+            for (uint32_t i = 2; i <= nl; ++i) // (planes of less than 31 pixels)
+                for (int k = tid; k < KP; k += nthr)
+                    Gt[i * KP + k] = and_mask(a.gate[(size_t)(n0 + i) * K + min(k, K - 1)], k < K ? 0xffffffffu : 0u);
         }
-        for (uint32_t i = 2; i <= nl; ++i) // (planes of less than 31 pixels)
-            for (int k = tid; k < KP; k += nthr)
-                Gt[i * KP + k] = and_mask(a.gate[(size_t)(n0 + i) * K + min(k, K - 1)], k < K ? 0xffffffffu : 0u);
-    }
+    };
+    if (KP <= nthr) // uniform
+        coefficients(std::integral_constant<int, 1>());
+    else
+        coefficients(std::integral_constant<int, 5>());
     if (PRO != PRO_NONE)
         __syncthreads();
 
