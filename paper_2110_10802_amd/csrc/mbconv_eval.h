@@ -34,7 +34,8 @@ __device__ __forceinline__ void dw_eval_extra(const DwEval &ev, int block, int t
 {
     const int tid = threadIdx.x;
     if (block >= ev.coef) {
-        const int tile = (block - ev.coef) * (threads / 256) + tid / 256;
+        // (uniform over the wavefront, which the compiler has to be told: the set's description then comes by scalar loads)
+        const int tile = (block - ev.coef) * (threads / 256) + __builtin_amdgcn_readfirstlane(tid / 256);
         if (tile < ev.prep.tiles)
             x3_prep_tile(ev.prep, tile, tid & 255);
         return;
