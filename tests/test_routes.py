@@ -17,8 +17,8 @@ class DwShape(C.Structure):
     (28, 288, 25, 3, 1, False, False, False, False),   # a thread group to a plane: 32256 wavefronts, and fewer
     (24, 288, 25, 3, 1, False, False, False, True),
     (222, 288, 25, 3, 1, False, True, False, True),    # stride 1 with the pool: any size
-    (48, 672, 17, 5, 2, False, True, False, False),    # stride 2 with the pool: 129024, 64512, and 93696 with one launch saved
-    (24, 672, 17, 5, 2, False, True, False, True),
+    (24, 672, 17, 5, 2, False, True, False, False),    # stride 2 with the pool: 64512, 48384, and 93696 with one launch saved
+    (18, 672, 17, 5, 2, False, True, False, True),
     (64, 366, 17, 5, 2, False, True, True, False),
     (16, 144, 72, 5, 2, False, True, False, False),    # 1024 threads, 5x5, fp32: 36864, 2304; bf16
     (1, 144, 72, 5, 2, False, True, False, True),
