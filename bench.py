@@ -71,6 +71,12 @@ def _fused(s):
     return fused_proj, fused_exp
 
 
+def _recomputes_e(s) -> bool:
+    """The fused backward of the expansion conv computes the conv's output again instead of reading it."""
+    from paper_2110_10802_amd import binding as B
+    return _fused(s)[1] and B.ENGINES[B.mbconv_step_engine(B.make_desc(s), B.STEPS["expand_dgrad"])] == "mfma_bf16x3"
+
+
 def step_bytes(s) -> dict:
     """Bytes each step must move by the fusion plan (each tensor it consumes or produces
     crosses HBM once), for the steps with an activation-sized operand."""
@@ -87,7 +93,7 @@ def step_bytes(s) -> dict:
         "proj_dgrad": 2 * P + 2 * D if fused_proj else 2 * P + D,
         "proj_wgrad": 2 * P + D, "gate_sums": 2 * D,
         "dw_bwd": (2 * D + 2 * E) if s.has_expand else (2 * D + 2 * X + res),
-        "expand_dgrad": 2 * E + 2 * X + res if fused_exp else 2 * E + X + res,
+        "expand_dgrad": (E if _recomputes_e(s) else 2 * E) + 2 * X + res if fused_exp else 2 * E + X + res,
         "expand_wgrad": 2 * E + X,
     }
     if fused_proj:
@@ -107,7 +113,8 @@ def algorithmic_bytes(s, step: str):
 
 
 def step_flops(s) -> dict:
-    """Multiply-add flops of the 1x1-convolution steps (2 per multiply-add)."""
+    """Multiply-add flops of the 1x1-convolution steps (2 per multiply-add); what a kernel computes a second time
+    (_recomputes_e) is not counted."""
     fe = 2 * s.N * s.H * s.W * s.Cin * s.Cexp
     fp = 2 * s.N * s.Ho * s.Wo * s.Cexp * s.Cout
     fused_proj, fused_exp = _fused(s)

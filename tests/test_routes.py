@@ -85,3 +85,15 @@ def test_expansion_conv_of_small_launches(N, M, K, H, chunks):
     assert plan(N, M, K, H * H, 0, 1, C.byref(got)) == (chunks is not None)
     if chunks is not None:
         assert got.value == chunks
+
+
+def test_benchmark_counts_the_bytes_of_the_kernel_that_runs():
+    import bench
+    from mbconv_inputs import b0_chain
+    blocks = b0_chain()
+    s = blocks[1]  # 16 -> 96, no residual: the expansion conv's output is computed again, not read
+    px = s.N * s.H * s.W * 4
+    assert bench.step_bytes(s)["expand_dgrad"] == px * (s.Cexp + 2 * s.Cin)
+    s = blocks[2]  # 24 -> 144 with a residual: read
+    px = s.N * s.H * s.W * 4
+    assert bench.step_bytes(s)["expand_dgrad"] == px * (2 * s.Cexp + 3 * s.Cin)
