@@ -232,9 +232,6 @@ hipError_t launch_x3_wgrad_pair(bool bf16, int N, int MaA, int MbA, int HWA, con
                                 float *partialA, int *splitsA, int MaB, int MbB, int HWB,
                                 const Operand &UB, const Operand &VB, float *partialB, int *splitsB,
                                 hipStream_t st);
-#ifndef MBK_X3PAIR
-#define MBK_X3PAIR 1
-#endif
 bool xw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt);
 hipError_t launch_xw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm, int sAk, const Operand &B,
                              void *out, int epi, float *psum, float *psq, hipStream_t st);
@@ -289,13 +286,8 @@ int conv1x1_engine(bool bf16, int N, int M, int K, int HW, bool stores_operand, 
 }
 int wgrad1x1_engine(bool bf16, int Ma, int Mb, int N, int HW)
 {
-    bool swap;
     int splits;
-    if (x3_wgrad_plan(bf16, Ma, Mb, N, HW, &splits))
-        return bf16 ? 2 : 3;
-    if (wgrad_cl_plan(Ma, Mb, N, HW, &swap, &splits))
-        return 1;
-    return 1;
+    return !x3_wgrad_plan(bf16, Ma, Mb, N, HW, &splits) ? 1 : bf16 ? 2 : 3;
 }
 
 int conv1x1_num_partials(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro,
@@ -415,6 +407,7 @@ hipError_t launch_conv1x1_affine(bool bf16, int N, int M, int K, int HW, const v
 }
 
 // ---- weight gradient ------------------------------------------------------------------------
+// (the general kernel: images of a gibibyte and more, beyond the offsets of kernels_wgr.hip)
 // dW[a,b] = sum_q U[a,q]*V[b,q]: the contraction runs over all N*HW pixels, so it is
 // split across workgroups; every workgroup writes its own partial tile and a second
 // kernel adds the partials in a fixed order (no atomics: the paper's map-fission step,
@@ -633,8 +626,6 @@ static hipError_t wgrad_dispatch(const WgradArgs &a, int pu, int pv, dim3 grid, 
 // stages); 0: no pair (also a stride from a plane of the first kernel into one of the second, 14x14 -> 7x7)
 static int wgrad1x1_pair_kind(bool bf16, int N, int MaA, int MbA, int HWA, int MaB, int MbB, int HWB)
 {
-    if (!MBK_X3PAIR)
-        return 0;
     int s;
     bool swap;
     const bool xa = x3_wgrad_plan(bf16, MaA, MbA, N, HWA, &s);

@@ -700,12 +700,17 @@ __global__ __launch_bounds__(256) void se_bwd_sums_kernel(SeBwdArgs a, int chan,
         a.db1[tid] = (dqL[0][tid] + dqL[1][tid]) + (dqL[2][tid] + dqL[3][tid]);
 }
 
+// Few channels of few images: the plain kernels' shorter chain; backward of a block, plain / here, 96
+// channels, 2 images 38.0 / 39.1 us, 32 images 44.7 / 45.0; 144, 8 images 37.7 / 38.0, 32 images 158 / 157; 240, 2
+// images 46.5 / 45.8; the step alone, 16 channels, 2048 images 56.6 / 60.3, 32 channels 63.0 / 61.6.
+bool se_bwd_tiled(int N, int C, int Cse)
+{
+    return Cse >= 4 && Cse <= 64 && (C >= 160 || (C >= 32 && (long long)N * C >= 4096));
+}
+
 hipError_t launch_se_bwd(const SeBwdArgs &a, hipStream_t st)
 {
-    // (few channels of few images: the plain kernels' shorter chain; backward of a block, plain / here, 96
-    // channels, 2 images 38.0 / 39.1 us, 32 images 44.7 / 45.0; 144, 8 images 37.7 / 38.0, 32 images 158 / 157; 240, 2
-    // images 46.5 / 45.8; the step alone, 16 channels, 2048 images 56.6 / 60.3, 32 channels 63.0 / 61.6)
-    if (a.Cse >= 4 && a.Cse <= 64 && (a.C >= 160 || (a.C >= 32 && (long long)a.N * a.C >= 4096))) {
+    if (se_bwd_tiled(a.N, a.C, a.Cse)) {
         hipLaunchKernelGGL(se_bwd_dq_kernel, dim3(a.N, (a.Cse + 15) / 16), dim3(256), 0, st, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)

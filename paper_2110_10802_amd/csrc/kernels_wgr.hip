@@ -1,5 +1,5 @@
-// Weight gradient of a 1x1 convolution on fp32 MFMA: the planes and channel counts that the split-operand and
-// bf16 kernels do not take (kernels_x3.hip, kernels_bf.hip), 7x7 above all.
+// Weight gradient of a 1x1 convolution on fp32 MFMA: the planes and channel counts that the bf16 matrix cores'
+// kernel (kernels_x3.hip) and the one for few channels on even planes (kernels_wave.hip) do not take, 7x7 above all.
 //
 //   dW[a][b] = sum_{n,q} op(U)[n][a][q] * op(V)[n][b][q]
 //

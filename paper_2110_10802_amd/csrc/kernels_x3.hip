@@ -419,7 +419,7 @@ bool x3_wgrad_plan(bool bf16, int Ma, int Mb, int N, int HW, int *splits)
     // which size their partial tiles by the plan of that file)
     // Planes of at most 64 pixels that are no multiple of four (7x7) stay on the fp32 matrix cores, the
     // engine that mbconv_step_engine has answered for them so far.  Neither speed nor accuracy asks for
-    // it (64 x 7x7, 192 -> 1152 -> 320: 93 us for the pair there, 51 here; error against 64 bits 3.9e-7 and
+    // it (64 x 7x7, 192 -> 1152 -> 320: 66 us for the pair there, 51 here; error against 64 bits 3.9e-7 and
     // 4.9e-7 there, 2.7e-7 and 3.5e-7 here).
     if (HW % 4 != 0 && HW <= 64)
         return false;

@@ -6,6 +6,7 @@ import pytest
 from mbconv_inputs import BlockShape, make_block_inputs
 from oracle import oracle as orc
 from parity_util import compare_block, run_gpu_block
+from route_util import xs_chunks
 
 pytestmark = pytest.mark.gpu
 
@@ -22,6 +23,7 @@ pytestmark = pytest.mark.gpu
 def test_matches_oracle(N, Cin, Cexp, H):
     s = BlockShape(N=N, Cin=Cin, H=H, W=H, Cexp=Cexp, Cse=8, Cout=24, k=3, stride=1, has_expand=True, residual=False,
                    dtype="f32")
+    assert (xs_chunks(s) is not None) == (N != 19)
     t = make_block_inputs(s, seed=Cin)
     print(f"[conv_xs] {s}", flush=True)
     res, blk = run_gpu_block(s, t)

@@ -3,7 +3,7 @@ import ctypes as C
 
 import pytest
 
-from paper_2110_10802_amd import binding as B
+from route_util import BOOL, INT, plan, rule
 
 
 class DwShape(C.Structure):
@@ -30,27 +30,21 @@ class DwShape(C.Structure):
     (192, 1152, 7, 5, 1, False, False, False, True),
 ])
 def test_evaluation_folds_launches_into_the_depthwise_kernel(N, channels, H, k, s, bf16, se, coef_ahead, folds):
-    rule = getattr(B.load(), "_ZN3mbk13dw_eval_foldsEbRKNS_7DwShapeEbb")
-    rule.restype, rule.argtypes = C.c_bool, [C.c_bool, C.POINTER(DwShape), C.c_bool, C.c_bool]
+    fold = rule("_ZN3mbk13dw_eval_foldsEbRKNS_7DwShapeEbb", BOOL, BOOL, C.POINTER(DwShape), BOOL, BOOL)
     p = (k - 1) // 2
     out = (H + 2 * p - k) // s + 1
-    assert rule(bf16, C.byref(DwShape(N, channels, H, H, out, out, k, s, p)), se, coef_ahead) == folds
+    assert fold(bf16, C.byref(DwShape(N, channels, H, H, out, out, k, s, p)), se, coef_ahead) == folds
 
 
 @pytest.mark.parametrize("rows,many", [((448, 448), True), ((499, 32), True), ((20, 456), True), ((128, 0), True),
                                        ((64, 64), False), ((8, 13), False), ((42, 0), False)])
 def test_sum_of_partial_gradients_goes_by_the_longer_one(rows, many):
-    rule = getattr(B.load(), "_ZN3mbk23reduce_splits_many_rowsEii")
-    rule.restype, rule.argtypes = C.c_bool, [C.c_int, C.c_int]
-    assert rule(*rows) == many
+    assert rule("_ZN3mbk23reduce_splits_many_rowsEii", BOOL, INT, INT)(*rows) == many
 
 
 @pytest.mark.parametrize("N,Ma,Mb,HW,splits", [(29, 171, 117, 9, 3), (1, 64, 64, 1, 1), (5, 64, 64, 49, 2), (64, 1152, 192, 49, 11)])
 def test_weight_gradient_splits_have_four_chunks(N, Ma, Mb, HW, splits):
-    plan = getattr(B.load(), "_ZN3mbk8wgr_planEbiiiiPi")
-    plan.restype, plan.argtypes = C.c_bool, [C.c_bool] + 4 * [C.c_int] + [C.POINTER(C.c_int)]
-    got = C.c_int(0)
-    assert plan(False, Ma, Mb, N, HW, C.byref(got)) and got.value == splits
+    assert plan("_ZN3mbk8wgr_planEbiiiiPi", BOOL, *4 * [INT])(False, Ma, Mb, N, HW) == splits
 
 
 @pytest.mark.parametrize("bf16,N,Ma,Mb,HW,least", [
@@ -59,11 +53,8 @@ def test_weight_gradient_splits_have_four_chunks(N, Ma, Mb, HW, splits):
     (True, 1 << 20, 1100, 8, 1, 2),          # one pixel a plane: the gates are the larger
 ])
 def test_weight_gradients_of_4_gib_and_more(bf16, N, Ma, Mb, HW, least):
-    plan = getattr(B.load(), "_ZN3mbk8wgr_planEbiiiiPi")
-    plan.restype, plan.argtypes = C.c_bool, [C.c_bool] + 4 * [C.c_int] + [C.POINTER(C.c_int)]
-    got = C.c_int(0)
-    assert plan(bf16, Ma, Mb, N, HW, C.byref(got)) == (least > 0)
-    assert got.value >= least
+    got = plan("_ZN3mbk8wgr_planEbiiiiPi", BOOL, *4 * [INT])(bf16, Ma, Mb, N, HW)
+    assert got >= least if least else got is None
 
 
 @pytest.mark.parametrize("N,M,K,H,chunks", [
@@ -79,12 +70,7 @@ def test_weight_gradients_of_4_gib_and_more(bf16, N, Ma, Mb, HW, least):
     (1, 240, 41, 7, None), (1, 1536, 256, 7, None),      # channel counts that it does not take
 ])
 def test_expansion_conv_of_small_launches(N, M, K, H, chunks):
-    plan = getattr(B.load(), "_ZN3mbk12xs_conv_planEiiiiiiPi")
-    plan.restype, plan.argtypes = C.c_bool, 6 * [C.c_int] + [C.POINTER(C.c_int)]
-    got = C.c_int(0)
-    assert plan(N, M, K, H * H, 0, 1, C.byref(got)) == (chunks is not None)
-    if chunks is not None:
-        assert got.value == chunks
+    assert plan("_ZN3mbk12xs_conv_planEiiiiiiPi", *6 * [INT])(N, M, K, H * H, 0, 1) == chunks
 
 
 def test_benchmark_counts_the_bytes_of_the_kernel_that_runs():

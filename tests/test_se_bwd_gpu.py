@@ -6,6 +6,7 @@ import pytest
 from mbconv_inputs import BlockShape, make_block_inputs
 from oracle import oracle as orc
 from parity_util import compare_block, run_gpu_block
+from route_util import se_bwd_tiled
 
 pytestmark = pytest.mark.gpu
 
@@ -15,6 +16,7 @@ pytestmark = pytest.mark.gpu
 def test_gradients_match_oracle(N, C, Cse):
     s = BlockShape(N=N, Cin=C, H=4, W=4, Cexp=C, Cse=Cse, Cout=16, k=3, stride=1, has_expand=False)
     t = make_block_inputs(s, seed=C + Cse)
+    assert se_bwd_tiled(N, C, Cse) == ((C, Cse) not in ((60, 4), (300, 3), (40, 70)))
     print(f"[se bwd] {s}", flush=True)
     res, blk = run_gpu_block(s, t)
     f, b = orc.mbconv_step(s, t)

@@ -6,6 +6,7 @@ import pytest
 from mbconv_inputs import BlockShape, make_block_inputs
 from oracle import oracle as orc
 from parity_util import compare_block, run_gpu_block
+from route_util import block_wgrad_kernels
 
 pytestmark = pytest.mark.gpu
 
@@ -20,6 +21,7 @@ pytestmark = pytest.mark.gpu
 def test_matches_oracle(N, Cin, Cexp, Cout, H, stride):
     s = BlockShape(N=N, Cin=Cin, H=H, W=H, Cexp=Cexp, Cse=8, Cout=Cout, k=3, stride=stride, has_expand=True,
                    residual=False, dtype="bf16")
+    assert block_wgrad_kernels(s) == (("rd" if stride == 2 else "x3"), "x3")
     t = make_block_inputs(s, seed=Cexp)
     print(f"[wgrad bf16] {s}", flush=True)
     res, blk = run_gpu_block(s, t)
