@@ -282,12 +282,13 @@ hipError_t launch_dw_eval_coef(DwEval &ev, hipStream_t st)
 //    (25x25, 222 images 286 / 287; 57x57, 444 images 1484 / 1359); with stride 2 the output is a quarter (17x17, 672
 //    channels, 24 images, 65 k, 66.1 / 64.5, 48, 129 k, 91.7 / 93.0, 95 158 / 167; 64 -> 384 -> 89 on 9x9, bf16, 164 images,
 //    63 k, 143.6 / 146.6);
-//  - 5x5 on fp32 planes of 1024 threads: 64 registers and more, which is one workgroup to a compute unit, not two, with
+//  - dw4 and dw2, 5x5, fp32, planes of 1024 threads: 64 registers and more, which is one workgroup to a compute unit, not two, with
 //    stride 2: 24 -> 144 -> 40 on 72x72, stride 2, 4 images (9 k) 36.6 / 30.8, 16 59.5 / 69.0, 64 162 / 201, 8 -> 48 -> 12 on
 //    104x100 without SE, 17 images (13 k) 37.6 / 40.6; stride 1, 16
 //    images (37 k) 90.8 / 84.9, 64 311 / 326, without SE 16 images 74.8 / 80.3; 42 -> 252 -> 40, a launch ahead, stride 2,
 //    one image (4 k) 28.1 / 26.2, 3 39.2 / 40.4.
-// dw4, dw2 and dwr otherwise, where a wavefront has more pixels: folded is as fast or faster at every size measured.
+// dw_fwd with 1024 threads and 5x5: the folded form is the faster kernel (16 -> 96 -> 16 on 82x82, ReLU6, 61 images 310 / 251;
+// 43 -> 31 on 69x69, stride 2, 64 images 74 / 57).  dw4, dw2 and dwr otherwise, where a wavefront has more pixels: folded is as fast or faster at every size measured.
 bool dw_eval_folds(bool bf16, const DwShape &s, bool se, bool coef_ahead)
 {
     const int saved = (se ? 1 : 0) + (coef_ahead ? 0 : 1);
@@ -299,6 +300,8 @@ bool dw_eval_folds(bool bf16, const DwShape &s, bool se, bool coef_ahead)
     const int items = runs ? s.H * ((s.W + 3) / 4) : s.H * s.W; // and threads to a plane, as the launchers choose them
     const int threads = items <= 256 ? 64 : items <= (runs ? 1024 : 4096) ? 256 : 1024;
     const long long waves = (long long)s.N * s.C * (threads / 64);
+    if (s.k == 5 && threads == 1024 && !runs)
+        return true;
     if (!bf16 && s.k == 5 && threads == 1024)
         return waves <= (se && s.s == 1 ? 48 : coef_ahead ? 4 : 10) * 1024;
     return runs || (se && s.s == 1) || waves <= (saved == 2 ? 48 : 28) * 1024;

@@ -1061,21 +1061,22 @@ bool xs_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt)
         return false;
     bool ok;
     // Where the other kernel is conv_pe (kernels_pv16.hip: planes of a multiple of four pixels, up to 40 input and 384 output
-    // channels), whose workgroups take all rows of 64 pixels and are the later to finish the more rows there are, and
-    // leave BN1 fewer partial sums: up to eight chunks a row, 1280 in all.  (Forward, conv_pe / here, us, at a half, once and
-    // one and a half times that: 24 -> 144 on 28x28 1.12, 1.05, 0.96 times as fast, 40 -> 120 on 56x56 1.07, 1.06, 0.98;
-    // 40 -> 240 on 14x14 at 532, 1065 and 2131 chunks 1.23, 1.12, 1.00; 16 -> 192 on 56x56 at 784 and 1568 1.02, 0.97; 40 -> 384
-    // on 28x28 at 759, 1543 and 3062 1.06, 1.03, 0.86; 8 -> 48 on 56x56, 2646 chunks 48.2 / 48.7.)
+    // channels), which leaves BN1 fewer partial sums: as many as its finalise step adds beside the planes for nothing.
+    // (Forward, times as fast as conv_pe: 24 -> 144 on 28x28 at 588, 1151 and 1739 chunks 1.12, 1.05, 0.96; 16 -> 96 on 56x56 at
+    // 784 and 1176 1.05, 1.03; 8 -> 24 on 112x112 at 1176 and 1960 1.03, 1.01, on 56x56 at 1960 0.97; 40 -> 120 on 56x56 at 980 and
+    // 1960 1.06, 0.98; 40 -> 240 on 14x14 at 1065 and 2131 1.12, 1.00; 16 -> 192 on 56x56 at 784 and 1568 1.02, 0.97; 40 -> 384 on
+    // 28x28 at 759, 1543 and 3062 1.06, 1.03, 0.86.)
     if (wave_conv_kind(M, K, HW))
-        ok = chunks <= std::min(8 * M, 1280);
+        ok = chunks <= 1200;
     // Elsewhere up to one and a half times what is resident at once; beyond, the rows that every workgroup reads again cost
     // more than the latencies (80 -> 480 on 14x14 and 15x15 at 8, 16 and 32 thousand wavefronts 1.02 to 1.04, 1.00, 0.9;
     // 24 -> 144 on 57x57 1.04, 1.02, 1.00).  conv_xw catches up sooner where it has few rows to stage and reads
-    // the pixels once: 64 -> 64 on 14x14, 251, 502 and 998 chunks 1.07, 1.01, 0.92; 32 -> 96 on 27x27, 660 and 1344 1.05, 0.97.
+    // the pixels once: 64 -> 64 on 14x14, 251, 502 and 998 chunks 1.07, 1.01, 0.92; 32 -> 96
+    // on 27x27, 660 and 1344 1.05, 0.97; 56 -> 168 on 17x17, 524, evaluation of the block 49.9 / 48.5 us.
     else {
         int sets;
         const long long waves = chunks * ((M + 15) / 16) * ((K + 31) / 32);
-        ok = waves <= 12 * 1024 && (chunks <= 512 || !xw_conv_plan(N, M, K, HW, pro, epi, &sets));
+        ok = waves <= 12 * 1024 && (chunks <= 600 || !xw_conv_plan(N, M, K, HW, pro, epi, &sets));
     }
     if (!ok)
         return false;

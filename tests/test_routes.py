@@ -23,6 +23,7 @@ class DwShape(C.Structure):
     (16, 144, 72, 5, 2, False, True, False, False),    # 1024 threads, 5x5, fp32: 36864, 2304; bf16
     (1, 144, 72, 5, 2, False, True, False, True),
     (16, 144, 72, 5, 2, True, True, False, True),
+    (61, 96, 82, 5, 1, False, False, False, True),     # (of dw4 and dw2: dw_fwd folds at any size)
     (16, 144, 72, 5, 1, False, True, False, True),
     (64, 144, 72, 5, 1, False, True, False, False),
     (3, 252, 72, 5, 2, False, True, True, False),
@@ -58,14 +59,14 @@ def test_weight_gradients_of_4_gib_and_more(bf16, N, Ma, Mb, HW, least):
 
 
 @pytest.mark.parametrize("N,M,K,H,chunks", [
-    (32, 240, 40, 28, 784), (64, 240, 40, 28, None),     # beside conv_pe: eight chunks a row, 1280 at most
+    (32, 240, 40, 28, 784), (64, 240, 40, 28, None),     # beside conv_pe: 1200 chunks
     (2, 48, 8, 56, 196), (41, 48, 8, 56, None),
-    (11, 144, 24, 56, 1078), (12, 144, 24, 56, None),
+    (12, 144, 24, 56, 1176), (13, 144, 24, 56, None),
     (30, 384, 40, 28, 735), (64, 384, 40, 28, None),
     (17, 240, 40, 27, 388), (18, 240, 40, 27, None),     # odd plane: 12288 wavefronts; so for outputs above conv_pe's
     (11, 400, 40, 28, None), (9, 400, 40, 28, 221),
     (18, 576, 96, 14, 111), (19, 576, 96, 14, None),
-    (83, 64, 64, 14, 509), (85, 64, 64, 14, None),       # few rows: conv_xw from 512 chunks on
+    (97, 64, 64, 14, 595), (99, 64, 64, 14, None),       # few rows: conv_xw from 600 chunks on
     (8, 12, 8, 57, 813), (100, 12, 8, 57, 10154),        # (conv_big: no such line)
     (1, 240, 41, 7, None), (1, 1536, 256, 7, None),      # channel counts that it does not take
 ])
