@@ -6,7 +6,7 @@
 // block, and what bounds a kernel that reads both is memory: 16 -> 96 channels on 803 k pixels are 719 MB,
 // 160 us in this form, 170 with a workgroup per chunk.  But e = W x, and x is here for the weight gradient
 // anyway, so a chunk's e costs matrix-core time only (section "Guided Optimization Case Study:
-// EfficientNet": recompute instead of load): 411 MB, 105 us.
+// EfficientNet": recompute instead of load): 411 MB, 99 us.
 //   - A wavefront owns chunks of 32 pixels (chunk = W*workgroup + wavefront, stride W*grid); nothing crosses
 //     wavefronts inside the loop, so there is no barrier in it.
 //   - Lane (r, g) = (lane % 16, lane / 16) holds pixels 2r and 2r+1, eight bytes per load, sixteen lanes to a
