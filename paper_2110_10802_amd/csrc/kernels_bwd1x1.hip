@@ -18,7 +18,7 @@
 //   - The result has the lane's two pixels of channels 4g .. 4g+3, and that is how dy1 is loaded, so
 //     de = c0*dy1 + (c1*e + c2) is two fma per element.
 //   - Data gradient: these registers, split, are its B operand (the contraction's order is free: W^T lies in
-//     LDS to match); a step's product is complete before it is added (dx 1.3e-7 with one accumulator, now 6.2e-8).
+//     LDS to match); its small products in accumulators of their own (re_mma; dx 1.3e-7 in one, now 7.1e-8).
 //   - Weight gradient: a contraction over pixels, so de and x go through LDS once, [channel][pixel], the
 //     lane's two pixels of a channel as one 32-bit store per plane; large and small products in accumulators of their own
 //     (5.1e-7 together, 1.1e-7 now, for centred channels).
@@ -57,19 +57,23 @@ __device__ __forceinline__ void re_lds_fence()
 __device__ __forceinline__ uint32_t re_lo(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
 __device__ __forceinline__ uint32_t re_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
-// acc0 += a*b0, acc1 += a*b1 over three planes, taking turns, small terms first
+// acc + low += a*b over three planes, for two B operands taking turns.  The small products apart: an MFMA cuts off what of
+// its addend lies below its products' last place, the same way in every pixel.  (In one accumulator, small terms first, the
+// mean over pixels of dx's error is 7.5e-9 of dx, 16 -> 96 channels, and 1.1e-8 where a step is summed before it is added;
+// on fp32 MFMA 7.7e-9; as here 5e-10.  Sums of dx over the pixels that should vanish, the gradient of a bias behind a
+// normalisation, are made of it.)
 __device__ __forceinline__ void re_mma(const bf16x8 (&a)[3], const bf16x8 (&b0)[3], const bf16x8 (&b1)[3],
-                                       f32x4 &acc0, f32x4 &acc1)
+                                       f32x4 &acc0, f32x4 &acc1, f32x4 &low0, f32x4 &low1)
 {
-#define MBK_MMA(i, j)                                                                             \
-    acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b0[j], acc0, 0, 0, 0);                   \
-    acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b1[j], acc1, 0, 0, 0);
-    MBK_MMA(2, 0)
-    MBK_MMA(0, 2)
-    MBK_MMA(1, 1)
-    MBK_MMA(1, 0)
-    MBK_MMA(0, 1)
-    MBK_MMA(0, 0)
+#define MBK_MMA(i, j, p, q)                                                                       \
+    p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b0[j], p, 0, 0, 0);                         \
+    q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b1[j], q, 0, 0, 0);
+    MBK_MMA(2, 0, low0, low1)
+    MBK_MMA(0, 2, low0, low1)
+    MBK_MMA(1, 1, low0, low1)
+    MBK_MMA(1, 0, low0, low1)
+    MBK_MMA(0, 1, low0, low1)
+    MBK_MMA(0, 0, acc0, acc1)
 #undef MBK_MMA
 }
 
@@ -237,7 +241,7 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
         re_lds_fence(); // these reads before the first step's stores
         __builtin_amdgcn_sched_barrier(0);
 
-        f32x4 accd0 = {0.f, 0.f, 0.f, 0.f}, accd1 = accd0;
+        f32x4 accd0 = {0.f, 0.f, 0.f, 0.f}, accd1 = accd0, lowd0 = accd0, lowd1 = accd0;
         f32x2 rs[4];
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
@@ -302,10 +306,7 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
                     b1[pl] = __builtin_bit_cast(bf16x8, hi);
                     aw[pl] = *reinterpret_cast<const bf16x8 *>(Wt + (size_t)(s * 3 + pl) * 512 + lane * 8);
                 }
-                f32x4 t0 = {0.f, 0.f, 0.f, 0.f}, t1 = t0;
-                re_mma(aw, b0, b1, t0, t1);
-                accd0 += t0;
-                accd1 += t1;
+                re_mma(aw, b0, b1, accd0, accd1, lowd0, lowd1);
             }
             re_lds_fence();
 #pragma unroll
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = 4 * g + v;
-            f32x2 o = {accd0[v], accd1[v]};
+            f32x2 o = {accd0[v] + lowd0[v], accd1[v] + lowd1[v]};
             if (a.res)
                 o += rs[v];
             if (okm && row < Cn)
@@ -390,8 +391,8 @@ __global__ __launch_bounds__(512, 2) void bwd1x1_re_kernel(Bwd1x1ReArgs a)
 
 // The shapes of this file: pixel pairs, groups of four wide channels, and enough chunks that the tables pay (both
 // steps of the gradients, bwd1x1_lt / here, us: 16 -> 32 channels, 16 chunks 14.4 / 13.7, 392 16.1 / 14.3, 4214 36.9 / 21.9; 16 ->
-// 64, 196 chunks 15.4 / 16.2, 392 17.0 / 16.3; 16 -> 96, 392 chunks 18.0 / 18.4, 544 20.6 / 18.6, 12544 102 / 64; 16 -> 144, 544
-// 22.3 / 22.4, 4214 51.8 / 42.7; 16 -> 192, 4214 70.7 / 60.2).
+// 64, 196 chunks 15.4 / 16.2, 392 17.0 / 16.3; 16 -> 96, 392 chunks 18.0 / 18.4, 544 20.6 / 18.6, 12544 102 / 64; 16 -> 144,
+// 544 chunks 22.3 / 22.4; the kernels alone, 4232 chunks, 16 -> 144 44.7 / 33.5, 16 -> 192 61.5 / 39.3).
 bool bwd1x1_re_supported(int N, int Cw, int Cn, int HW)
 {
     const long long Q = (long long)N * HW, chunks = (Q + 31) / 32;

@@ -45,7 +45,9 @@ def test_error_is_that_of_values_rounded_once(N, Cin, Cexp, H, mean):
     """Channels that are far from centred: the gradients' relative error against 64 bits is at most four times that of a
     computation that rounds e and de = c0*dy + c1*e + c2 to fp32 once each and is exact otherwise, and 2^-24 for each
     time that a wavefront adds a chunk's product to its accumulators (they are 2048 at most, a chunk 32 pixels).  An
-    error of e that all pixels share would be tens of times as large in the weight gradient."""
+    error of e that all pixels share would be tens of times as large in the weight gradient.  The mean over the pixels of the
+    data gradient's error is an eighth of 2^-25 of it at most: roundings to nearest leave it at their size over the
+    square root of the pixels, a truncation of the same sign in every pixel at some 2^-26."""
     import torch
     from paper_2110_10802_amd import binding as B
     launch = getattr(B.load(), "_ZN3mbk19launch_bwd1x1_fusedEbiiiiRKNS_7OperandEPKvS4_PvS4_PfPiP12ihipStream_t")
@@ -86,3 +88,6 @@ def test_error_is_that_of_values_rounded_once(N, Cin, Cexp, H, mean):
         err, ref = float((got - ex).norm() / ex.norm()), float((on - ex).norm() / ex.norm())
         print(f"  {err:.2e}, rounded once {ref:.2e}", flush=True)
         assert err <= 4 * ref + 2.0 ** -24 * -(-m // (32 * 2048))
+    offset = (dx.double() - exact[1]).mean((0, 2)).square().mean().sqrt() / exact[1].square().mean().sqrt()
+    print(f"  offset {float(offset):.2e}", flush=True)
+    assert float(offset) <= 2.0 ** -28
