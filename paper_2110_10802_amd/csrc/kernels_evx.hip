@@ -1,0 +1,865 @@
+// Evaluation mode, fp32: expansion conv, BN1, activation and depthwise conv in one launch.
+//
+//   d[n][c] = depthwise(act(BN1(W_e x[n]))),   z[n][c] = mean of act(BN2(d[n][c]))
+//
+// With fixed statistics BN1 is an affine map per channel, so nothing keeps the expansion conv's output e, the
+// largest tensor of the block, from staying on the chip.  A workgroup owns 16 expanded channels (the rows of an
+// MFMA tile) and a strip of output rows of one image:
+//   - the strip's input pixels, with the rows that the filter reaches beyond it, are one contiguous range of the
+//     plane; a wavefront takes 16*PX of them at a time, multiplies on fp32 MFMA (A = weights, in registers for the
+//     workgroup's life, B = x straight from memory: lane (r, g) holds PX consecutive pixels of channel 4t + g, and
+//     element j feeds MFMA number j), applies BN1 and the activation and leaves them in an LDS tile with a zero border;
+//   - after one barrier, 16 or 32 threads to a channel convolve runs of four outputs from the tile, store d, and sum
+//     act(BN2(d)) for the squeeze.
+// What bounds it: small launches the chain of one workgroup (a request of 112 -> 672 channels on 14x14: 1.9 us until all loads
+// are issued, 1.3 weights through LDS, 0.7 operands, 1.1 MFMAs, 0.4 into the tile, 1.3 depthwise), large ones the vector
+// work of the two activations and the filter beside the MFMAs, which fp32 MFMAs do not overlap with.  24 -> 144 on 56x56,
+// 32 images, ReLU6: 21.8 + 21.9 us in two launches (e written and read, 116 MB), 34 here.
+#include "mbconv_dev.h"
+#include "mbconv_launch.h"
+#include "mbconv_eval.h"
+
+#include <algorithm>
+
+namespace mbk {
+
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+namespace {
+
+constexpr int kXdRows = 16;     // expanded channels of a workgroup
+constexpr int kXdThreads = 512; // 32 to a channel in the depthwise part
+
+struct XdArgs {
+    int N, K, C, H, W, Ho, Wo, k, s, Cse;
+    int CG, S, R, rin;   // channel groups, strips per image, output rows of a strip, tile rows
+    int NI;              // images side by side in the tile (a power of two; S = 1 where it is not 1)
+    int pitch, ims, chs; // tile: floats per row (the plane's column 0 at 4), image and channel
+    int items, PL;       // (image group, strip) pairs, and how many of them a workgroup takes one after the other
+    int groups;          // ceil(items / PL)
+    int perDie;          // 0: workgroups in order; else the channel groups of an item group on one XCD
+    int rt;              // output rows to a thread: 1 or 2
+    int act;             // store act(BN2(d)) in place of d
+    FastDiv divCG, divS, divW, divHW, divRuns;
+    const float *x, *w, *wdw, *w1;
+    float *d, *z;        // z: [strip][n][c] partial means, or null
+    float *q;            // or, instead: [n][channel group, strip][Cse] partial sums of W1 z
+};
+
+// One row of the window of four outputs, from the plane's column 4*S*j - P on.
+template <int K, int S>
+__device__ __forceinline__ void xd_window(const float *p, float (&o)[3 * S + K])
+{
+    constexpr int P = (K - 1) / 2;
+    const f32x4 m = *reinterpret_cast<const f32x4 *>(p);
+    if (P == 1) {
+        o[0] = p[-1];
+    } else {
+        const f32x2 l = *reinterpret_cast<const f32x2 *>(p - 2);
+        o[0] = l[0];
+        o[1] = l[1];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        o[P + e] = m[e];
+    if (S == 1) {
+        if (P == 1) {
+            o[5] = p[4];
+        } else {
+            const f32x2 r = *reinterpret_cast<const f32x2 *>(p + 4);
+            o[6] = r[0];
+            o[7] = r[1];
+        }
+    } else {
+        const f32x4 m2 = *reinterpret_cast<const f32x4 *>(p + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            o[P + 4 + e] = m2[e];
+        if (P == 2)
+            o[10] = p[8];
+    }
+}
+
+struct XdItem {
+    int n, ni, strip, ho0, hin0, p0, p1; // first image, images, ..., pixels p0 .. p1-1 (of all images of the item)
+};
+template <int KD, int SD>
+__device__ __forceinline__ XdItem xd_item(const XdArgs &a, int item)
+{
+    XdItem t;
+    const int ng = (int)fdiv((uint32_t)item, a.divS);
+    t.n = ng * a.NI;
+    t.ni = min(a.NI, a.N - t.n);
+    t.strip = item - ng * a.S;
+    t.ho0 = t.strip * a.R;
+    t.hin0 = t.ho0 * SD - (KD - 1) / 2;
+    t.p0 = max(t.hin0, 0) * a.W;
+    t.p1 = min(t.hin0 + a.rin, a.H) * a.W + (t.ni - 1) * a.H * a.W;
+    return t;
+}
+
+// The depthwise convolution of one item.  Thread -> (channel, image, runs): RT rows by four columns at a time, so that a
+// row of the tile is read once for all the outputs of the thread that it reaches.
+template <int K, int S, int RT>
+__device__ __forceinline__ void xd_depthwise(const XdArgs &a, const XdItem &it, int cg, const float *tile,
+                                             const float (&wt)[K * K], float *cf, float inv_hw)
+{
+    const int tid = threadIdx.x, ch = tid >> 5, tpi = 32 / a.NI;
+    const int im = a.NI == 1 ? 0 : (tid & 31) / tpi, lt = tid & (tpi - 1);
+    const int c = cg * kXdRows + ch;
+    const bool live = c < a.C && im < it.ni;
+    const float scale = cf[4 * ch + 2], shift = cf[4 * ch + 3];
+    const int rw = (a.Wo + 3) >> 2, rows = min(a.R, a.Ho - it.ho0), runs = (rows + RT - 1) / RT * rw;
+    const float *tc = tile + ch * a.chs + im * a.ims + 4;
+    float *out = a.d + ((size_t)(it.n + (live ? im : 0)) * a.C + min(c, a.C - 1)) * (a.Ho * a.Wo) + it.ho0 * a.Wo;
+    const bool sums = a.z || a.q;
+    float zs = 0.f;
+    for (int i = lt; i < runs; i += tpi) {
+        const int rg = (int)fdiv((uint32_t)i, a.divRuns), j = i - rg * rw, oh = RT * rg;
+        const float *p = tc + 4 * S * j;
+        float o[RT][4];
+#pragma unroll
+        for (int q = 0; q < RT; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                o[q][r] = 0.f;
+        // (rows past the tile, which only outputs past the strip reach, are its last; two rows at a time: the next is on its
+        // way while one is multiplied, and no further ones, which would cost registers)
+        constexpr int NR = (RT - 1) * S + K;
+        const auto at = [&](int ir) { return p + (RT == 1 ? oh * S + ir : min(oh * S + ir, a.rin - 1)) * a.pitch; };
+        const auto taps = [&](int ir, const float (&row)[3 * S + K]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < RT; ++q) {
+                const int u = ir - q * S;
+                if (u >= 0 && u < K) {
+#pragma unroll
+                    for (int v = 0; v < K; ++v)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            o[q][r] = fmaf(wt[u * K + v], row[r * S + v], o[q][r]);
+                }
+            }
+        };
+        float row[2][3 * S + K];
+        xd_window<K, S>(at(0), row[0]);
+#pragma unroll
+        for (int ir = 0; ir < NR; ++ir) {
+            if (ir + 1 < NR)
+                xd_window<K, S>(at(ir + 1), row[(ir + 1) % 2]);
+            if (RT > 1)
+                __builtin_amdgcn_sched_barrier(0);
+            taps(ir, row[ir % 2]);
+            if (RT > 1)
+                __builtin_amdgcn_sched_barrier(0);
+        }
+        const int left = a.Wo - 4 * j; // outputs of a run that exist
+#pragma unroll
+        for (int q = 0; q < RT; ++q) {
+            if (RT > 1 && oh + q >= rows)
+                break;
+            if (a.act) { // (uniform)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    o[q][r] = actf(fmaf(o[q][r], scale, shift));
+                    zs += r < left ? o[q][r] : 0.f; // by selection: what lies past the row is unspecified
+                }
+            }
+            float *po = out + (oh + q) * a.Wo + 4 * j;
+            if (live) {
+                if ((a.Wo & 3) == 0) {
+                    *reinterpret_cast<f32x4 *>(po) = (f32x4){o[q][0], o[q][1], o[q][2], o[q][3]};
+                } else if ((a.Wo & 1) == 0) {
+                    *reinterpret_cast<f32x2 *>(po) = (f32x2){o[q][0], o[q][1]};
+                    if (left > 2)
+                        *reinterpret_cast<f32x2 *>(po + 2) = (f32x2){o[q][2], o[q][3]};
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (r < left)
+                            po[r] = o[q][r];
+                }
+            }
+            if (sums && !a.act) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float v = actf(fmaf(o[q][r], scale, shift));
+                    zs += r < left ? v : 0.f;
+                }
+            }
+        }
+    }
+    if (sums) {
+        if (tpi >= 16) {
+            zs = row16_sum(zs);
+            if (tpi == 32)
+                zs += __shfl_xor(zs, 16, kWave);
+        } else {
+            for (int o = tpi >> 1; o > 0; o >>= 1)
+                zs += __shfl_xor(zs, o, kWave);
+        }
+        zs *= inv_hw;
+        if (lt == 0 && live) {
+            if (a.z)
+                a.z[((size_t)it.strip * a.N + it.n + im) * a.C + c] = zs;
+        }
+        if (a.q && lt == 0) // (channels past the end: zero)
+            cf[64 + im * kXdRows + ch] = live ? zs : 0.f;
+    }
+}
+
+// T: steps of four input channels, 4*TP < K <= 4*T.  PX: pixels to a lane.  KD, SD, RT: xd_depthwise.
+template <int T, int TP, int PX, int KD, int SD, int RT>
+__global__ __launch_bounds__(kXdThreads, T *(PX + 1) > 40 || (KD == 5 && RT == 2) ? 2 : 4) void xd_kernel(XdArgs a, DwEval ev)
+{
+    constexpr int threads = kXdThreads, nw = threads / 64;
+    constexpr int WP = 4 * T + 4;
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ __attribute__((aligned(16))) float cf[4 * kXdRows + 8 * kXdRows]; // {BN1 scale, shift, BN2 scale, shift}
+                                                                               // per channel; plane sums
+    __shared__ float wd[25 * kXdRows]; // depthwise filters
+    __shared__ float w1s[64 * kXdRows];
+    float *wl = lds, *tile = lds + kXdRows * WP;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    int cg, ig;
+    if (a.perDie) {
+        if ((int)blockIdx.x >= ev.main) {
+            dw_eval_extra(ev, (int)blockIdx.x - ev.main, threads);
+            return;
+        }
+        const int j = (int)(blockIdx.x >> 3), q = (int)fdiv((uint32_t)j, a.divCG);
+        cg = j - q * a.CG;
+        ig = 8 * q + (int)(blockIdx.x & 7);
+        if (ig >= a.groups)
+            return;
+    } else {
+        cg = (int)blockIdx.x;
+        ig = (int)blockIdx.y;
+        if (ig >= a.groups) {
+            dw_eval_extra(ev, (ig - a.groups) * a.CG + cg, threads);
+            return;
+        }
+    }
+    const int c0 = cg * kXdRows, K = a.K, HW = a.H * a.W;
+    constexpr int KK = KD * KD;
+    const int last = min((ig + 1) * a.PL, a.items);
+    int item = ig * a.PL;
+    XdItem it = xd_item<KD, SD>(a, item);
+
+    float b[T][PX];
+    // the pixels of one chunk, past the range's end those of its start
+    const auto fetch = [&](const XdItem &t, int chunk) __attribute__((always_inline)) {
+        const int pix = t.p0 + (chunk * 16 + r) * PX;
+        uint32_t pc = (uint32_t)(pix < t.p1 ? pix : t.p0);
+        if (a.NI > 1) // (uniform)
+            pc += fdiv(pc, a.divHW) * (uint32_t)((K - 1) * HW);
+        // (byte offsets from one uniform base: a base for every step would not fit the scalar registers)
+        const char *px = reinterpret_cast<const char *>(a.x + (size_t)t.n * K * HW);
+        const uint32_t step = 16u * (uint32_t)HW, off = 4u * ((uint32_t)(g * HW) + pc);
+#pragma unroll
+        for (int s = 0; s < T; ++s) {
+            const float *q = reinterpret_cast<const float *>(
+                px + (s < TP ? off + (uint32_t)s * step : 4u * ((uint32_t)(min(4 * s + g, K - 1) * HW) + pc)));
+            if (PX == 4) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(q);
+#pragma unroll
+                for (int e = 0; e < PX; ++e)
+                    b[s][e] = v[e];
+            } else if (PX == 2) {
+                const f32x2 v = *reinterpret_cast<const f32x2 *>(q);
+#pragma unroll
+                for (int e = 0; e < PX; ++e)
+                    b[s][e] = v[e];
+            } else {
+                b[s][0] = q[0];
+            }
+        }
+    };
+    // ---- everything that the workgroup needs from memory is requested here ----
+    // weights: 16 rows of K, padded with zeros to 4T; row r, channel 4t + g to [r][g][t]
+    constexpr int WN = (64 * T + threads - 1) / threads;
+    float wv[WN];
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+        const uint32_t idx = (uint32_t)(tid + i * threads), m = idx / (4 * T), kk = idx % (4 * T);
+        wv[i] = a.w[(size_t)min(c0 + (int)m, a.C - 1) * K + min((int)kk, K - 1)];
+    }
+    const float fv = a.wdw[min(c0 * KK + tid, a.C * KK - 1)];
+    // the squeezed layer's weights for these channels, [j][channel]
+    float w1v[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        w1v[i] = a.q ? a.w1[(size_t)min((tid + i * threads) >> 4, a.Cse - 1) * a.C + min(c0 + (tid & 15), a.C - 1)] : 0.f;
+    BnEvalRegs r1 = {}, r2 = {};
+    if (tid < kXdRows) {
+        const int c = min(c0 + tid, a.C - 1);
+        r1 = bn_eval_issue(ev.bn1, c);
+        r2 = bn_eval_issue(ev.bn2, c);
+    }
+    fetch(it, wave);
+    __builtin_amdgcn_sched_barrier(0);
+    // the tile's rows outside the plane
+    const auto border = [&](const XdItem &t) __attribute__((always_inline)) {
+        const int top = max(0, -t.hin0), rows = top + max(0, t.hin0 + a.rin - a.H);
+        for (int i = wave; i < kXdRows * rows; i += nw) {
+            const int rr = i >> 4, row = rr < top ? rr : a.rin - rows + rr;
+            float *p = tile + (i & 15) * a.chs + row * a.pitch;
+            if (4 * lane < a.pitch)
+                for (int im = 0; im < a.NI; ++im)
+                    *reinterpret_cast<f32x4 *>(p + im * a.ims + 4 * lane) = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    border(it);
+    // ---- the tile's zero columns, once ----
+    for (int row = tid; row < kXdRows * a.NI * a.rin; row += threads) {
+        const int rr = row >> 4;
+        float *p = tile + (row & 15) * a.chs + rr * a.pitch;
+        *reinterpret_cast<f32x4 *>(p) = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int c = 4 + a.W; c < a.pitch; ++c)
+            p[c] = 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+        const uint32_t idx = (uint32_t)(tid + i * threads), m = idx / (4 * T), kk = idx % (4 * T);
+        if (idx < 64 * T)
+            wl[m * WP + (kk & 3) * T + (kk >> 2)] = (int)kk < K ? wv[i] : 0.f;
+    }
+    if (tid < kXdRows * KK)
+        wd[tid] = fv;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        w1s[tid + i * threads] = c0 + (tid & 15) < a.C ? w1v[i] : 0.f;
+    if (tid < kXdRows) {
+        const BnEvalCoef k1 = bn_eval_coef(r1, ev.eps), k2 = bn_eval_coef(r2, ev.eps);
+        *reinterpret_cast<f32x4 *>(cf + 4 * tid) = (f32x4){k1.scale, k1.shift, k2.scale, k2.shift};
+    }
+    __syncthreads();
+    float av[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+        av[t] = wl[r * WP + g * T + t];
+    float wt[KK];
+#pragma unroll
+    for (int t = 0; t < KK; ++t)
+        wt[t] = wd[(tid >> 5) * KK + t];
+    float sc[4], sh[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        sc[v] = cf[4 * (4 * g + v)];
+        sh[v] = cf[4 * (4 * g + v) + 1];
+    }
+    for (;;) {
+        const int chunks = (it.p1 - it.p0 + 16 * PX - 1) / (16 * PX);
+        for (int ck = wave; ck < chunks; ck += nw) {
+            // (long contractions a chain of four steps at a time: in one chain every step rounds the whole sum; the fence keeps
+            // the sums from being put off, which takes registers)
+            constexpr int CH = T > 6 ? 4 : T;
+            f32x4 acc[PX], sum[PX];
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                // (past the contraction both operands are zero: what was loaded there may be infinite)
+                const uint32_t ok = t < TP || 4 * t + g < K ? 0xffffffffu : 0u;
+#pragma unroll
+                for (int e = 0; e < PX; ++e) {
+                    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                    acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[t], t < TP ? b[t][e] : and_mask(b[t][e], ok),
+                                                                  t % CH ? acc[e] : zero, 0, 0, 0);
+                    if (t % CH == CH - 1 || t == T - 1)
+                        sum[e] = t < CH ? acc[e] : sum[e] + acc[e];
+                }
+                if (t % CH == CH - 1)
+                    __builtin_amdgcn_sched_barrier(0);
+            }
+            int pix = it.p0 + (ck * 16 + r) * PX;
+            const bool in = pix < it.p1;
+            if (ck + nw < chunks)
+                fetch(it, ck + nw);
+            float *p = tile + 4 * g * a.chs + 4;
+            if (a.NI > 1) { // (uniform)
+                const int im = (int)fdiv((uint32_t)pix, a.divHW);
+                pix -= im * HW;
+                p += im * a.ims;
+            }
+            const int h = (int)fdiv((uint32_t)pix, a.divW), w = pix - h * a.W;
+            p += (h - it.hin0) * a.pitch + w;
+            if (in) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    float y[PX];
+#pragma unroll
+                    for (int e = 0; e < PX; ++e)
+                        y[e] = actf(fmaf(sum[e][v], sc[v], sh[v]));
+                    if (PX == 4)
+                        *reinterpret_cast<f32x4 *>(p + v * a.chs) = (f32x4){y[0], y[PX / 4], y[PX / 2], y[PX - 1]};
+                    else if (PX == 2)
+                        *reinterpret_cast<f32x2 *>(p + v * a.chs) = (f32x2){y[0], y[PX - 1]};
+                    else
+                        p[v * a.chs] = y[0];
+                }
+            }
+        }
+        const XdItem cur = it;
+        ++item;
+        __syncthreads();
+        xd_depthwise<KD, SD, RT>(a, cur, cg, tile, wt, cf, ev.inv_hw);
+        if (a.q) { // (one item to a workgroup; at most 64 squeezed channels and eight images)
+            __syncthreads();
+            const int qj = tid & 63, qi = tid >> 6;
+            if (qj < a.Cse && qi < cur.ni) {
+                float s = 0.f;
+#pragma unroll
+                for (int e = 0; e < kXdRows; ++e)
+                    s = fmaf(w1s[qj * kXdRows + e], cf[64 + qi * kXdRows + e], s);
+                a.q[((size_t)(cur.n + qi) * (a.CG * a.S) + cg * a.S + cur.strip) * a.Cse + qj] = s;
+            }
+        }
+        if (item >= last)
+            return;
+        it = xd_item<KD, SD>(a, item);
+        fetch(it, wave);
+        __syncthreads();
+        border(it);
+    }
+}
+
+constexpr int kXdSteps[] = {4, 6, 10, 16, 20, 28, 48};
+
+// Steps of the contraction (rounded up to one that is built), pixels to a lane
+bool xd_form(int K, int W, int *T, int *PX)
+{
+    for (const int t : kXdSteps)
+        if (K <= 4 * t) {
+            *T = t;
+            *PX = W % 4 == 0 && t <= 16 ? 4 : W % 2 == 0 && t <= 28 ? 2 : 1;
+            return true;
+        }
+    return false;
+}
+
+size_t xd_geometry(const DwShape &s, int T, int S, int NI, XdArgs &a)
+{
+    a.S = S;
+    a.NI = NI;
+    a.R = (s.Ho + S - 1) / S;
+    a.rin = (a.R - 1) * s.s + s.k;
+    a.pitch = (s.s == 1 ? 4 : 8) * ((s.Wo + 3) / 4) + 8;
+    a.ims = a.rin * a.pitch;
+    a.chs = NI * a.ims;
+    if (a.chs % 8 == 0) // channels four apart on the two halves of the banks
+        a.chs += 4;
+    return sizeof(float) * (size_t)kXdRows * (a.chs + 4 * T + 4);
+}
+
+} // namespace
+
+// Strips of an image, and the rest of the plan; false: not a shape of this kernel.
+static bool xd_plan(const DwShape &s, int K, XdArgs &a, int *T, int *PX, size_t *lds)
+{
+    // (long contractions as conv_xs takes them: its rows are what this kernel replaces; odd channel counts are with kernels
+    // on the bf16 matrix cores, whose sums are the more exact ones)
+    if (!xd_form(K, s.W, T, PX) || (*T > 6 && K % 8 != 0))
+        return false;
+    if ((long long)s.N * s.Ho * ((s.C + 15) / 16) >= (1ll << 30))
+        return false;
+    // what the depthwise kernels refuse stays refused (kernels_dw2.hip)
+    if (s.s == 2 && s.W % 4 == 2 && s.H % 2 == 0 && s.H * ((s.W + 3) / 4) > 1024)
+        return false;
+    a.CG = (s.C + kXdRows - 1) / kXdRows;
+    int S = 1, NI = 1;
+    while (S < s.Ho && xd_geometry(s, *T, S, 1, a) > 52 * 1024)
+        ++S;
+    while (S < s.Ho && (long long)s.N * a.CG * S < 128 && (s.Ho + S - 1) / S * s.Wo > 128)
+        ++S;
+    S = (s.Ho + (s.Ho + S - 1) / S - 1) / ((s.Ho + S - 1) / S); // no empty strips
+    // small planes: images side by side until every wavefront has a chunk, where that leaves two workgroups per CU
+    if (S == 1)
+        while (NI < 8 && NI < s.N && NI * s.H * s.W < 6 * 16 * *PX && xd_geometry(s, *T, S, 2 * NI, a) <= 52 * 1024 &&
+               (long long)(s.N + 2 * NI - 1) / (2 * NI) * a.CG >= 512)
+            NI *= 2;
+    *lds = xd_geometry(s, *T, S, NI, a);
+    if (*lds > 60 * 1024)
+        return false;
+    const long long wgs = (long long)((s.N + NI - 1) / NI) * S * a.CG;
+    // Where the line lies (one forward pass, the launches it replaces / this kernel, us).  Long contractions hold a compute
+    // unit with one or two workgroups, and a second round of them loses to kernels whose operands are split once for all rows:
+    // 80 -> 480 on 14x14, 3x3, 16 and 32 images 32.0 / 29.9 and 37.9 / 43.4; 112 -> 672 on 14x14, 5x5, 4 and 8 images 26.0 /
+    // 22.3 and 32.4 / 40.8; 192 -> 1152 on 7x7, 2 and 4 images 27.6 / 22.0 and 29.0 / 35.7.  Up to 24 input channels it is the
+    // faster one at any size (24 -> 144 on 56x56, 3x3, 32 and 128 images 69.8 / 68.4 and 248 / 205; 16 -> 96 on 112x112, 3x3,
+    // stride 2, 64 images 195 / 143), but for 5x5 filters with stride 2 (24 -> 144 on 56x56, 16 and 32 images 36.9 / 32.6 and
+    // 51.1 / 52.5) or on odd widths (16 -> 64 on 127x127, 64 images 480 / 507), rows of an MFMA tile without a channel (8 -> 24
+    // on 108x108, stride 2, 73 images 67.4 / 71.0) and small planes, which leave wavefronts without pixels (24 -> 144, 3x3 on
+    // 14x14, 512 images 80.8 / 82.5, 5x5 on 7x7, 1024 images 73.0 / 82.2).
+    const bool large = 10 * s.C >= 8 * kXdRows * a.CG && (s.k == 3 || (s.s == 1 && s.W % 2 == 0)) && s.H * s.W >= 400;
+    if (wgs > (*T > 20 ? 256 : *T > 6 ? 512 : large ? 1 << 30 : 1024))
+        return false;
+    a.rt = s.s == 1 && a.R * ((s.Wo + 3) / 4) >= 3 * 32 ? 2 : 1;
+    a.items = (s.N + NI - 1) / NI * S;
+    a.PL = 1;
+    if (wgs > 4096) // (the weights staged once for several: 128 images of 56x56 above 215 -> 205 us)
+        a.PL = (int)std::min<long long>((wgs + 4095) / 4096 * 2, 8);
+    a.groups = (a.items + a.PL - 1) / a.PL;
+    a.perDie = a.groups >= 64 ? (a.groups + 7) / 8 * a.CG : 0;
+    return true;
+}
+
+bool eval_expand_dw_plan(const DwShape &s, int K, int *strips)
+{
+    XdArgs a = {};
+    int T, PX;
+    size_t lds;
+    if (!xd_plan(s, K, a, &T, &PX, &lds))
+        return false;
+    *strips = a.S;
+    return true;
+}
+
+// Partial sums per image and squeezed channel that launch_eval_expand_dw writes where it is given `q`; 0: it cannot
+int eval_expand_dw_qparts(const DwShape &s, int K, int Cse)
+{
+    XdArgs a = {};
+    int T, PX;
+    size_t lds;
+    if (Cse > 64 || !xd_plan(s, K, a, &T, &PX, &lds) || a.PL != 1)
+        return 0;
+    return a.CG * a.S;
+}
+
+hipError_t launch_eval_expand_dw(const DwShape &s, int K, const void *x, const void *w_expand, const void *w_dw, void *d,
+                                 float *z, float *q, int Cse, const float *w1, bool act, const DwEval &ev_in, hipStream_t st)
+{
+    XdArgs a = {};
+    int T, PX;
+    size_t lds;
+    if (!xd_plan(s, K, a, &T, &PX, &lds))
+        return hipErrorInvalidValue;
+    a.N = s.N;
+    a.K = K;
+    a.C = s.C;
+    a.H = s.H;
+    a.W = s.W;
+    a.Ho = s.Ho;
+    a.Wo = s.Wo;
+    a.k = s.k;
+    a.s = s.s;
+    a.Cse = Cse;
+    a.divCG = make_div((uint32_t)a.CG);
+    a.divS = make_div((uint32_t)a.S);
+    a.divW = make_div((uint32_t)s.W);
+    a.divHW = make_div((uint32_t)(s.H * s.W));
+    a.divRuns = make_div((uint32_t)((s.Wo + 3) / 4));
+    a.x = (const float *)x;
+    a.w = (const float *)w_expand;
+    a.wdw = (const float *)w_dw;
+    a.w1 = w1;
+    a.d = (float *)d;
+    a.z = q ? nullptr : z;
+    a.q = q;
+    a.act = act;
+    DwEval ev = ev_in;
+    // small launches: channel group, item group (no division ahead of the loads); workgroups past the items are the extra ones
+    const unsigned main = a.perDie ? 8u * (unsigned)a.perDie : (unsigned)(a.groups * a.CG);
+    const unsigned extra = dw_eval_extra_blocks(ev, main, kXdThreads);
+    const dim3 grid = a.perDie ? dim3(main + extra) : dim3(a.CG, a.groups + (extra + a.CG - 1) / a.CG);
+#define MBK_GO(T_, TP_, PX_, K_, S_, RT_)                                                         \
+    if (s.k == K_ && s.s == S_ && a.rt == RT_) {                                                  \
+        hipLaunchKernelGGL((xd_kernel<T_, TP_, PX_, K_, S_, RT_>), grid, dim3(kXdThreads), lds, st, a, ev); \
+        return hipGetLastError();                                                                 \
+    }
+#define MBK_CASE(T_, TP_, PX_)                                                                    \
+    if (T == T_ && PX == PX_) {                                                                   \
+        MBK_GO(T_, TP_, PX_, 3, 1, 1)                                                             \
+        MBK_GO(T_, TP_, PX_, 5, 1, 1)                                                             \
+        MBK_GO(T_, TP_, PX_, 3, 1, 2)                                                             \
+        MBK_GO(T_, TP_, PX_, 5, 1, 2)                                                             \
+        MBK_GO(T_, TP_, PX_, 3, 2, 1)                                                             \
+        MBK_GO(T_, TP_, PX_, 5, 2, 1)                                                             \
+    }
+    MBK_CASE(4, 0, 1) MBK_CASE(4, 0, 2) MBK_CASE(4, 0, 4)
+    MBK_CASE(6, 4, 1) MBK_CASE(6, 4, 2) MBK_CASE(6, 4, 4)
+    MBK_CASE(10, 6, 1) MBK_CASE(10, 6, 2) MBK_CASE(10, 6, 4)
+    MBK_CASE(16, 10, 1) MBK_CASE(16, 10, 2) MBK_CASE(16, 10, 4)
+    MBK_CASE(20, 16, 1) MBK_CASE(20, 16, 2)
+    MBK_CASE(28, 20, 1) MBK_CASE(28, 20, 2)
+    MBK_CASE(48, 28, 1)
+#undef MBK_CASE
+#undef MBK_GO
+    return hipErrorInvalidValue;
+}
+
+
+// ---- projection conv of small launches, with the squeeze-and-excitation gate and BN3 ----
+//
+//   out[n][m] = BN3(sum_k W_p[m][k] act(BN2(d[n][k])) g[n][k]) (+ x),  g = sigmoid(W2 swish(q) + b2)
+//
+// A request's projection conv is a chain of latencies: with a wavefront for every eighth of the contraction and
+// a launch ahead of it for the gate it took 7 to 11 us, and the gate 3 to 6.  A workgroup owns 16 output channels by 16*PX
+// pixels of one image and its wavefronts cut the contraction into slices of 4*T channels, everything that a
+// wavefront needs (its part of W_p, d, W2, the coefficients) being requested before the first use.  q comes as the
+// expansion kernel's partial sums, which the wavefronts share out and add through LDS; the gate of a wavefront's
+// channels is its own work, and so needs no barrier.  The slices' tiles are added in a fixed order.
+// One image, gate and projection in two launches / here: 1152 -> 192 on 7x7 5.7 + 11.3 / 13.2 us, 672 -> 112 on 14x14
+// 4.0 + 9.4 / 7.8, 240 -> 40 on 28x28 2.5 + 6.5 / 4.4, 144 -> 24 on 56x56 2.6 + 7.6 / 5.3; sixteen blocks 349 -> 278 us with
+// both kernels of this file.
+namespace {
+
+constexpr int kXpWaves = 16;
+
+struct XpArgs {
+    int M, K, HW, Cse, parts; // parts == 0: no gate from q
+    const float *w, *d, *bn2, *bn3; // [M][K]; normalisation blocks {scale, shift, ...}
+    const float *q, *b1, *w2, *b2;  // [n][parts][Cse]
+    const float *g;                 // gate [n][K], where there is one in memory
+    const float *res;
+    float *out;
+};
+
+// JR: pieces of 16 squeezed channels (0: no gate from q).  ACT: d is to go through BN2 and the activation (it has not yet).
+template <int T, int PX, int JR, bool ACT>
+__global__ __launch_bounds__(64 * kXpWaves) void xp_kernel(XpArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const int tid = threadIdx.x, lane = tid & 63, KS = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int M = a.M, K = a.K, HW = a.HW;
+    const int m0 = 16 * (int)blockIdx.x, p0 = 16 * PX * (int)blockIdx.y, n = blockIdx.z;
+    f32x4 *part = reinterpret_cast<f32x4 *>(lds);          // [KS][PX][64]
+    float *cs = lds + (size_t)KS * PX * 256 + wave * 16 * T; // the slice's channels: {BN2 scale, shift, gate, b2}
+    float *qs = lds + (size_t)KS * PX * 256 + KS * 16 * T;   // [KS][64]
+
+    // ---- the loads ----
+    constexpr int QU = 8;
+    float qv[QU], b1v = 0.f;
+    constexpr int WR = T / 4 < 3 ? T / 4 : 3; // sixteen channels' W2 at a time in flight
+    f32x4u w2v[WR][JR > 0 ? JR : 1];
+    const int ks0 = 4 * T * wave, part4 = lane & 3;
+    if (JR > 0) {
+        const int j = min(lane, a.Cse - 1);
+#pragma unroll
+        for (int u = 0; u < QU; ++u)
+            qv[u] = a.q[((size_t)n * a.parts + min(wave + u * KS, a.parts - 1)) * a.Cse + j];
+        b1v = a.b1[j];
+    }
+    float cv[T / 4];
+    {
+        const float *pc4 = part4 == 0 ? a.bn2 : part4 == 1 ? a.bn2 + K : part4 == 2 ? (a.g ? a.g + (size_t)n * K : a.bn2) : JR > 0 ? a.b2 : a.bn2;
+#pragma unroll
+        for (int i = 0; i < T / 4; ++i)
+            cv[i] = pc4[min(ks0 + 16 * i + (lane >> 2), K - 1)];
+    }
+    const auto fetch_w2 = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < JR; ++v)
+            w2v[i % WR][v] = *reinterpret_cast<const f32x4u *>(a.w2 + (size_t)min(ks0 + 16 * i + (lane >> 2), K - 1) * a.Cse +
+                                                               min(4 * (part4 + 4 * v), a.Cse - 4));
+    };
+#pragma unroll
+    for (int i = 0; i < WR; ++i)
+        fetch_w2(i);
+    // contraction index of slot (i, e): min(kg, K - 4) + e with kg = ks0 + T g + 4 i; what a slot shares with another one
+    // is masked, in both factors (either may be infinite)
+    f32x4u av[T / 4];
+    float b[T][PX];
+    const int pix = p0 + PX * r;
+    const bool in = pix < HW;
+    const uint32_t pc = (uint32_t)(in ? pix : 0);
+#pragma unroll
+    for (int i = 0; i < T / 4; ++i) {
+        const int kk = min(ks0 + T * g + 4 * i, K - 4);
+        const float *pb = a.d + ((size_t)n * K + kk) * HW + pc;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (PX == 4) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(pb + (size_t)e * HW);
+#pragma unroll
+                for (int c = 0; c < PX; ++c)
+                    b[4 * i + e][c] = v[c];
+            } else if (PX == 2) {
+                const f32x2 v = *reinterpret_cast<const f32x2 *>(pb + (size_t)e * HW);
+#pragma unroll
+                for (int c = 0; c < PX; ++c)
+                    b[4 * i + e][c] = v[c];
+            } else {
+                b[4 * i + e][0] = pb[(size_t)e * HW];
+            }
+        }
+    }
+    const auto fetch_w = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < T / 4; ++i)
+            av[i] = *reinterpret_cast<const f32x4u *>(a.w + (size_t)min(m0 + r, M - 1) * K + min(ks0 + T * g + 4 * i, K - 4));
+    };
+    // (long slices: under the gate's arithmetic, when the registers of its loads are free)
+    constexpr bool kLateW = JR > 0 && T >= 20;
+    if (!kLateW)
+        fetch_w();
+    // of the thread's output: BN3's coefficients and the residual
+    const int orow = tid / (16 * PX), opx = tid % (16 * PX), om = min(m0 + orow, M - 1);
+    const size_t oat = ((size_t)n * M + om) * HW + min(p0 + opx, HW - 1);
+    const float o3 = a.bn3[om], o3s = a.bn3[M + om], ores = a.res ? a.res[oat] : 0.f;
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- the gate ----
+#pragma unroll
+    for (int i = 0; i < T / 4; ++i)
+        cs[64 * i + lane] = JR == 0 && part4 == 2 && !a.g ? 1.f : cv[i];
+    if (JR > 0) {
+        float s = 0.f;
+#pragma unroll
+        for (int u = 0; u < QU; ++u)
+            s += wave + u * KS < a.parts ? qv[u] : 0.f;
+        for (int p = wave + QU * KS; p < a.parts; p += KS)
+            s += a.q[((size_t)n * a.parts + p) * a.Cse + min(lane, a.Cse - 1)];
+        qs[wave * 64 + lane] = s;
+        __syncthreads();
+        if (kLateW)
+            fetch_w();
+        float t = b1v;
+#pragma unroll
+        for (int w = 0; w < kXpWaves; ++w)
+            t += w < KS ? qs[min(w, KS - 1) * 64 + lane] : 0.f;
+        // the squeezed channels of the lane's pieces, from the lanes that hold them
+        const float rq = lane < a.Cse ? swishf(t) : 0.f;
+        float rx[JR > 0 ? JR : 1][4];
+#pragma unroll
+        for (int v = 0; v < JR; ++v)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                rx[v][e] = __shfl(rq, min(4 * (part4 + 4 * v), a.Cse - 4) + e, kWave);
+#pragma unroll
+        for (int i = 0; i < T / 4; ++i) {
+            float acc = 0.f;
+#pragma unroll
+            for (int v = 0; v < JR; ++v) {
+                const int want = 4 * (part4 + 4 * v), at = min(want, a.Cse - 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc = fmaf(at + e >= want ? w2v[i % WR][v][e] : 0.f, at + e >= want ? rx[v][e] : 0.f, acc);
+            }
+            if (i + WR < T / 4)
+                fetch_w2(i + WR);
+            acc += __shfl_xor(acc, 1, kWave);
+            acc += __shfl_xor(acc, 2, kWave);
+            if (part4 == 3) // (the lane that has loaded b2)
+                cs[64 * i + lane - 1] = sigmoidf_fast(acc + cv[i]);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // ---- the slice's product ----
+    // (every instruction with a sum of its own, added in pairs: a chain rounds the whole sum at every step)
+    f32x4 acc[PX][4], sum[PX];
+#pragma unroll
+    for (int i = 0; i < T / 4; ++i) {
+        const int kg = ks0 + T * g + 4 * i, kk = min(kg, K - 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            constexpr f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            const int t = 4 * i + e;
+            const bool ok = kk + e >= kg;
+            const f32x4 k4 = *reinterpret_cast<const f32x4 *>(cs + 4 * max(kk + e - ks0, 0));
+            const float w = ok ? av[i][e] : 0.f;
+#pragma unroll
+            for (int c = 0; c < PX; ++c) {
+                const float v = ok ? (ACT ? actf(fmaf(b[t][c], k4[0], k4[1])) : b[t][c]) * k4[2] : 0.f;
+                acc[c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, v, zero, 0, 0, 0);
+                if (e == 3) {
+                    const f32x4 four = (acc[c][0] + acc[c][1]) + (acc[c][2] + acc[c][3]);
+                    sum[c] = i == 0 ? four : sum[c] + four;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < PX; ++c)
+        part[(wave * PX + c) * 64 + lane] = sum[c];
+    __syncthreads();
+    // ---- the slices added up, BN3 and the residual: thread -> row, pixel ----
+    const auto total = [&](int row, int px) __attribute__((always_inline)) {
+        const float *ps = lds + 4 * ((px % PX) * 64 + (row >> 2) * 16 + px / PX) + (row & 3);
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kXpWaves; ++w)
+            s[w & 3] += w < KS ? ps[min(w, KS - 1) * PX * 256] : 0.f;
+        return (s[0] + s[1]) + (s[2] + s[3]);
+    };
+    if (tid < 256 * PX && m0 + orow < M && p0 + opx < HW)
+        a.out[oat] = fmaf(total(orow, opx), o3, o3s) + ores;
+    for (int o = tid + blockDim.x; o < 256 * PX; o += blockDim.x) { // (fewer threads than outputs)
+        const int row = o / (16 * PX), px = o % (16 * PX), m = m0 + row;
+        if (m < M && p0 + px < HW) {
+            const size_t at = ((size_t)n * M + m) * HW + p0 + px;
+            a.out[at] = fmaf(total(row, px), a.bn3[m], a.bn3[M + m]) + (a.res ? a.res[at] : 0.f);
+        }
+    }
+}
+
+long long xp_groups(int N, int M, int HW, int PX)
+{
+    return (long long)((M + 15) / 16) * ((HW + 16 * PX - 1) / (16 * PX)) * N;
+}
+
+// Steps of four channels to a wavefront, wavefronts, pixels to a lane (as many as leave most compute units a workgroup)
+bool xp_form(int N, int M, int K, int HW, int Cse, int *T, int *KS, int *PX)
+{
+    if (K < 4 || K > kXpWaves * 80 || (Cse && (Cse < 4 || Cse > 64)))
+        return false;
+    for (const int t : {4, 8, 12, 20})
+        if (K <= kXpWaves * 4 * t) {
+            *T = t;
+            *KS = (K + 4 * t - 1) / (4 * t);
+            *PX = 1;
+            if (HW % 2 == 0 && t <= 12 && xp_groups(N, M, HW, 2) >= 128)
+                *PX = 2;
+            if (HW % 4 == 0 && t <= 4 && *KS <= 10 && xp_groups(N, M, HW, 4) >= 128)
+                *PX = 4;
+            return true;
+        }
+    return false;
+}
+
+} // namespace
+
+bool eval_proj_plan(int N, int M, int K, int HW, int Cse, bool act)
+{
+    int T, KS, PX;
+    if (!xp_form(N, M, K, HW, Cse, &T, &KS, &PX) || N > 65535 || HW > 65535)
+        return false;
+    // Up to one workgroup of sixteen wavefronts to a compute unit; beyond, the gate and W_p that every workgroup fetches again
+    // cost more than the launches (the SE stage and the projection conv / this kernel: 672 -> 112 on 14x14, 4 and 8 images 13.0 /
+    // 10.4 and 15.5 / 19.7 us; 480 -> 80, 4 and 8 images 11.8 / 11.5, 12.7 / 15.2; 144 -> 24 on 56x56, 4 images 11.8 / 8.5).
+    // With the activation still to apply, which each of them repeats, somewhat less (306 -> 34 on 16x16, 15 images, 3600
+    // wavefronts, evaluation 23.9 / 24.7).
+    return xp_groups(N, M, HW, PX) * KS <= (act ? 3200 : 4096);
+}
+
+hipError_t launch_eval_proj(int N, int M, int K, int HW, int Cse, const void *w, const void *d, const float *bn2,
+                            const float *bn3, const float *q, int parts, const float *b1, const float *w2,
+                            const float *b2, const float *gate, bool act, const void *res, void *out, hipStream_t st)
+{
+    int T, KS, PX;
+    if (!xp_form(N, M, K, HW, parts ? Cse : 0, &T, &KS, &PX) || (parts && act))
+        return hipErrorInvalidValue;
+    const XpArgs a = {M, K, HW, Cse, parts, (const float *)w, (const float *)d, bn2, bn3, q, b1, w2, b2, gate,
+                      (const float *)res, (float *)out};
+    const dim3 grid((M + 15) / 16, (HW + 16 * PX - 1) / (16 * PX), N);
+    const size_t lds = sizeof(float) * ((size_t)KS * PX * 256 + KS * 16 * T + (parts ? KS * 64 : 0));
+    const int jr = parts ? (Cse + 15) / 16 : 0;
+#define MBK_CASE(T_, PX_, JR_, ACT_)                                                              \
+    if (T == T_ && PX == PX_ && jr == JR_ && act == ACT_) {                                       \
+        hipLaunchKernelGGL((xp_kernel<T_, PX_, JR_, ACT_>), grid, dim3(64 * KS), lds, st, a);     \
+        return hipGetLastError();                                                                 \
+    }
+#define MBK_JR(T_, PX_)                                                                           \
+    MBK_CASE(T_, PX_, 0, true) MBK_CASE(T_, PX_, 0, false) MBK_CASE(T_, PX_, 1, false) MBK_CASE(T_, PX_, 2, false) \
+    MBK_CASE(T_, PX_, 3, false) MBK_CASE(T_, PX_, 4, false)
+    MBK_JR(4, 1) MBK_JR(4, 2) MBK_JR(4, 4)
+    MBK_JR(8, 1) MBK_JR(8, 2)
+    MBK_JR(12, 1) MBK_JR(12, 2)
+    MBK_JR(20, 1)
+#undef MBK_JR
+#undef MBK_CASE
+    return hipErrorInvalidValue;
+}
+
+} // namespace mbk

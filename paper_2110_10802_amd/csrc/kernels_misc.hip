@@ -220,8 +220,10 @@ hipError_t launch_bn_bwd_finalize(int C, int NP, double m, const float *psb, con
 // One workgroup per image.  q = W1 z + b1 (a wavefront per output, lanes stride over C),
 // r = swish(q), g = sigmoid(W2 r + b2) (a thread per channel).
 
+// (PARTS: z is a sum of several arrays)
+template <bool PARTS>
 __global__ __launch_bounds__(256) void se_fwd_kernel(int C, int Cse, const float *__restrict__ z,
-                                                     const float *__restrict__ w1,
+                                                     int nz, const float *__restrict__ w1,
                                                      const float *__restrict__ b1,
                                                      const float *__restrict__ w2,
                                                      const float *__restrict__ b2, float *q,
@@ -230,8 +232,13 @@ __global__ __launch_bounds__(256) void se_fwd_kernel(int C, int Cse, const float
     extern __shared__ float lds[];
     float *zs = lds, *rs = lds + C;
     const int n = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int c = tid; c < C; c += 256)
-        zs[c] = z[(size_t)n * C + c];
+    for (int c = tid; c < C; c += 256) {
+        float v = z[(size_t)n * C + c];
+#pragma unroll 4
+        for (int s = 1; PARTS && s < nz; ++s)
+            v += z[((size_t)s * gridDim.x + n) * C + c];
+        zs[c] = v;
+    }
     __syncthreads();
     for (int j = wave; j < Cse; j += 4) {
         float acc = 0.f;
@@ -266,9 +273,9 @@ __global__ __launch_bounds__(256) void se_fwd_kernel(int C, int Cse, const float
 // end; the elements a piece shares with the one before it are masked, in both factors: either may be
 // infinite.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-template <int CI, int JR>
+template <int CI, int JR, bool PARTS>
 __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int slice,
-                                                           const float *__restrict__ z,
+                                                           const float *__restrict__ z, int nz,
                                                            const float *__restrict__ w1,
                                                            const float *__restrict__ b1,
                                                            const float *__restrict__ w2,
@@ -304,6 +311,11 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
                                                        min(4 * (part + 4 * v), Cse - 4));
     };
     fetch_w2(c);
+#pragma unroll 1
+    for (int s = 1; PARTS && s < nz; ++s)
+#pragma unroll
+        for (int i = 0; i < CI; ++i)
+            zv[i] += *reinterpret_cast<const f32x4u *>(z + ((size_t)s * gridDim.x + n) * C + min(4 * (lane + 64 * i), C - 4));
     __builtin_amdgcn_sched_barrier(0);
     const auto own = [&](int i, int e) { return min(4 * (lane + 64 * i), C - 4) + e >= 4 * (lane + 64 * i); };
 #pragma unroll
@@ -351,7 +363,7 @@ __global__ __launch_bounds__(1024) void se_fwd_wide_kernel(int C, int Cse, int s
     }
 }
 
-hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, const float *w1, const float *b1,
+hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, int nz, const float *w1, const float *b1,
                          const float *w2, const float *b2, float *q, float *g, hipStream_t st)
 {
     // (128 channels and more: 240 -> 10, batch 64, 7.8 -> 4.8 us; 96 -> 4, two images, no faster)
@@ -363,8 +375,12 @@ hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, const float *w1,
         const int slice = (C + G - 1) / G, ci = (C + 255) / 256, jr = (Cse + 15) / 16;
 #define MBK_CASE(CI_, JR_)                                                                        \
     if (ci <= CI_ && jr == JR_) {                                                                 \
-        hipLaunchKernelGGL((se_fwd_wide_kernel<CI_, JR_>), dim3(N, G), dim3(1024), 0, st, C, Cse, \
-                           slice, z, w1, b1, w2, b2, q, g);                                       \
+        if (nz > 1)                                                                               \
+            hipLaunchKernelGGL((se_fwd_wide_kernel<CI_, JR_, true>), dim3(N, G), dim3(1024), 0, st, C, Cse, \
+                               slice, z, nz, w1, b1, w2, b2, q, g);                               \
+        else                                                                                      \
+            hipLaunchKernelGGL((se_fwd_wide_kernel<CI_, JR_, false>), dim3(N, G), dim3(1024), 0, st, C, Cse, \
+                               slice, z, nz, w1, b1, w2, b2, q, g);                               \
         return hipGetLastError();                                                                 \
     }
 #define MBK_CI(CI_) MBK_CASE(CI_, 1) MBK_CASE(CI_, 2) MBK_CASE(CI_, 3) MBK_CASE(CI_, 4)
@@ -377,8 +393,11 @@ hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, const float *w1,
 #undef MBK_CI
 #undef MBK_CASE
     }
-    hipLaunchKernelGGL(se_fwd_kernel, dim3(N), dim3(256), sizeof(float) * (C + Cse), st, C, Cse, z,
-                       w1, b1, w2, b2, q, g);
+    const size_t lds = sizeof(float) * (C + Cse);
+    if (nz > 1)
+        hipLaunchKernelGGL((se_fwd_kernel<true>), dim3(N), dim3(256), lds, st, C, Cse, z, nz, w1, b1, w2, b2, q, g);
+    else
+        hipLaunchKernelGGL((se_fwd_kernel<false>), dim3(N), dim3(256), lds, st, C, Cse, z, nz, w1, b1, w2, b2, q, g);
     return hipGetLastError();
 }
 

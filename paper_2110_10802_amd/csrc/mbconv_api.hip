@@ -313,6 +313,16 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     const auto wimg = [&](int i) -> const void * {
         return P.o_wimg[i] == kAbsent ? nullptr : at<char>(saved, P.o_wimg[i]);
     };
+    // Evaluation mode, fp32: expansion conv and depthwise conv in one launch, nothing of e in memory
+    const DwShape ds = {P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p};
+    int strips = 1;
+    const bool xd = eval && !bf && P.expand && eval_expand_dw_plan(ds, P.Cin, &strips);
+    // ... and, of small launches, the projection conv with everything behind it in another: with the SE stage too where the
+    // first one multiplies the squeeze with W1 (the partial sums go where e would be)
+    const bool xp = eval && !bf && eval_proj_plan(P.N, P.Cout, P.Cexp, P.HWo, P.se ? P.Cse : 0, !xd);
+    int qparts = xd && xp && P.se ? eval_expand_dw_qparts(ds, P.Cin, P.Cse) : 0;
+    if ((size_t)qparts * P.Cse * P.N > P.nE)
+        qparts = 0;
     X3PrepArgs prep = {};
     prep.bf16 = bf;
     {
@@ -320,23 +330,25 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
             if (P.o_wimg[i] != kAbsent)
                 x3_prep_add(prep, w, M, K, sm, sk, at<char>(saved, P.o_wimg[i]));
         };
-        add(0, prm->w_expand, P.Cexp, P.Cin, P.Cin, 1);
-        add(1, prm->w_proj, P.Cout, P.Cexp, P.Cexp, 1);
+        if (!xd)
+            add(0, prm->w_expand, P.Cexp, P.Cin, P.Cin, 1);
+        if (!xp)
+            add(1, prm->w_proj, P.Cout, P.Cexp, P.Cexp, 1);
         if (!eval) {
             add(2, prm->w_proj, P.Cexp, P.Cout, 1, P.Cexp);
             add(3, prm->w_expand, P.Cin, P.Cexp, 1, P.Cin);
         }
     }
-    const bool prep_first = P.o_wimg[0] != kAbsent;
-    float *z = at<float>(saved, P.o_z), *g = at<float>(saved, P.o_g), *q = at<float>(saved, P.o_q);
+    const bool prep_first = P.o_wimg[0] != kAbsent && !xd;
+    // (of more than one strip, the squeeze's parts go where e would be)
+    float *z = at<float>(saved, strips > 1 ? P.o_e : P.o_z), *g = at<float>(saved, P.o_g), *q = at<float>(saved, P.o_q);
     // no squeeze-and-excitation stage: the gate every later prologue multiplies by is one, written by
     // the same launches
-    float *ones = P.se ? nullptr : g;
+    float *ones = P.se || xp ? nullptr : g;
     const size_t ones_count = (size_t)P.N * P.Cexp;
     // Evaluation mode: the depthwise launch brings the coefficients, the pool and the weight images, or a launch ahead of
     // everything else the coefficients and the images (dw_eval_folds).
-    const DwShape ds = {P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p};
-    const bool fold = eval && dw_eval_folds(bf, ds, P.se, prep_first);
+    const bool fold = xd || (eval && dw_eval_folds(bf, ds, P.se, prep_first));
     DwEval ev = {};
     if (eval) {
         if (P.expand)
@@ -364,6 +376,8 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
             const hipError_t pe = prep_first && (!eval || fold) ? launch_x3_prep(prep, st) : hipSuccess;
             if (pe != hipSuccess)
                 return pe;
+            if (xd)
+                return hipSuccess;
             return launch_conv1x1(bf, P.N, P.Cexp, P.Cin, P.HW, prm->w_expand, P.Cin, 1, B, e, EPI_STATS,
                                   nullptr, psum, psq, nullptr, splitk, st, wimg(0));
         };
@@ -388,8 +402,11 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
         MBK_STEP(MBCONV_STEP_BN1_FINALIZE, launch_bn_finalize(P.Cexp, P.NT1, m1, psum, psq, prm->bn1_gamma,
                                    prm->bn1_beta, eps, mom, fin1.run_mean, fin1.run_var, bn1, st));
     // BN1 + Swish + depthwise + BN2 statistics
-    MBK_STEP(MBCONV_STEP_DW_FWD, launch_dw_fwd(bf, ds, dw_in, bn1, prm->w_dw, d, psum2, psq2, a1_store,
-                                               fuse1 ? &fin1 : nullptr, fold ? &ev : nullptr, st));
+    MBK_STEP(MBCONV_STEP_DW_FWD, xd ? launch_eval_expand_dw(ds, P.Cin, x, prm->w_expand, prm->w_dw, d, ev.z,
+                                                            qparts ? at<float>(saved, P.o_e) : nullptr, P.Cse,
+                                                            prm->se_w1, xp, ev, st)
+                                    : launch_dw_fwd(bf, ds, dw_in, bn1, prm->w_dw, d, psum2, psq2, a1_store,
+                                                    fuse1 ? &fin1 : nullptr, fold ? &ev : nullptr, st));
     // BN2 + Swish + SE squeeze, SE excite
     const BnFin fin2 = make_bn_fin(psum2, psq2, prm->bn2_gamma, prm->bn2_beta, run ? run->bn2_mean : nullptr,
                                    run ? run->bn2_var : nullptr, bn2, P.NPdw, eps, mom, m2);
@@ -405,8 +422,15 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
                                       prep_first ? nullptr : &prep, st);
         };
         MBK_STEP(MBCONV_STEP_SE_POOL, pool());
-        MBK_STEP(MBCONV_STEP_SE_FC, launch_se_fwd(P.N, P.Cexp, P.Cse, z, prm->se_w1, prm->se_b1, prm->se_w2, prm->se_b2, q,
+        MBK_STEP(MBCONV_STEP_SE_FC, qparts ? hipSuccess : launch_se_fwd(P.N, P.Cexp, P.Cse, z, strips, prm->se_w1, prm->se_b1, prm->se_w2, prm->se_b2, q,
                               g, st));
+    }
+    if (xp) {
+        MBK_STEP(MBCONV_STEP_PROJ_CONV,
+                 launch_eval_proj(P.N, P.Cout, P.Cexp, P.HWo, P.Cse, prm->w_proj, d, bn2, bn3,
+                                  qparts ? at<float>(saved, P.o_e) : nullptr, qparts, prm->se_b1, prm->se_w2, prm->se_b2,
+                                  P.se && !qparts ? g : nullptr, !xd, P.res ? x : nullptr, out, st));
+        return MBCONV_OK;
     }
     // projection conv on Swish(BN2(d))*g + BN3 statistics
     {

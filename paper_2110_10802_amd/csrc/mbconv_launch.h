@@ -243,6 +243,24 @@ hipError_t launch_dw_fwd(bool bf16, const DwShape &s, const void *e, const float
                          const void *w_dw, void *d, float *psum, float *psq, void *a1_store,
                          const BnFin *fin, const DwEval *ev, hipStream_t st);
 
+// Evaluation mode, fp32: the expansion conv, BN1, activation and the depthwise conv in one launch, e staying on the
+// chip (kernels_evx.hip).  eval_expand_dw_plan: whether the shape is taken, and in how many strips of rows a plane is;
+// the squeeze then comes as that many partial means, z[strip][n][c] (z null: none), or, where `q` is given, multiplied
+// with W1 already, as eval_expand_dw_qparts partial sums q[n][part][Cse] (0: not available).  `act`: d is stored after BN2
+// and the activation.
+bool eval_expand_dw_plan(const DwShape &s, int K, int *strips);
+int eval_expand_dw_qparts(const DwShape &s, int K, int Cse);
+hipError_t launch_eval_expand_dw(const DwShape &s, int K, const void *x, const void *w_expand, const void *w_dw, void *d,
+                                 float *z, float *q, int Cse, const float *w1, bool act, const DwEval &ev, hipStream_t st);
+
+// Evaluation mode, fp32, small launches: out = BN3(W_p (act(BN2(d)) * gate)) (+ res) in one launch, the gate from
+// the `parts` partial sums q of launch_eval_expand_dw, or (parts == 0) read from `gate`, or (that null) one.
+// `act`: whether d is still to go through BN2 and the activation.
+bool eval_proj_plan(int N, int M, int K, int HW, int Cse, bool act);
+hipError_t launch_eval_proj(int N, int M, int K, int HW, int Cse, const void *w, const void *d, const float *bn2,
+                            const float *bn3, const float *q, int parts, const float *b1, const float *w2,
+                            const float *b2, const float *gate, bool act, const void *res, void *out, hipStream_t st);
+
 // Per plane of d: z = mean swish(y2), s3 = sum swish'(y2), s4 = sum swish'(y2)*dhat.
 // With `fin` non-null (only when plane_channel_form says so) the kernel derives bn2 from fin's partial
 // sums and writes it to fin->bn_out, and writes the weight images of `prep` (may be null).
@@ -250,8 +268,8 @@ bool plane_channel_form(int N, int C, int HW);
 hipError_t launch_pool(bool bf16, int N, int C, int HW, const void *d, const float *bn2, float *z,
                        float *s3, float *s4, const BnFin *fin, const X3PrepArgs *prep, hipStream_t st);
 
-// SE excite: q = W1 z + b1, g = sigmoid(W2 swish(q) + b2).
-hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, const float *w1, const float *b1,
+// SE excite: q = W1 z + b1, g = sigmoid(W2 swish(q) + b2); z is the sum of `nz` arrays [n][c], one behind the other.
+hipError_t launch_se_fwd(int N, int C, int Cse, const float *z, int nz, const float *w1, const float *b1,
                          const float *w2, const float *b2, float *q, float *g, hipStream_t st);
 
 // out = p*scale3+shift3 (+ x).

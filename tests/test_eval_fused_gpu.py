@@ -1,0 +1,82 @@
+"""Evaluation mode, fp32: the expansion and depthwise convs in one launch, and the projection conv of small launches with the
+gate and BN3 in another, at the edges of their tiles, slices and rules, against the oracle at the tolerances of parity_util."""
+import ctypes as C
+
+import pytest
+
+from mbconv_inputs import BlockShape
+from route_util import BOOL, INT, plan, rule
+from test_eval_routes_gpu import check
+from test_routes import DwShape
+
+# (N, Cin, Cexp, Cse, Cout, H, W, k, stride): strips of the fused expansion (None: not taken), projection in one launch
+CASES = {
+    "one_image_7x7": ((1, 192, 1152, 48, 192, 7, 7, 5, 1), 1, True),
+    "one_image_14x14": ((1, 112, 672, 28, 112, 14, 14, 5, 1), 2, True),
+    "strips_28x28": ((1, 40, 240, 10, 40, 28, 28, 5, 1), 7, True),
+    "strips_odd_width_stride_2": ((2, 16, 36, 4, 20, 61, 59, 3, 2), 8, True),
+    "strips_112x112_stride_2": ((1, 16, 96, 4, 24, 112, 112, 3, 2), 28, True),
+    "128x126_5x5": ((1, 8, 20, 4, 12, 128, 126, 5, 1), 128, True),
+    "masked_channels": ((3, 23, 50, 5, 17, 15, 14, 3, 1), 2, True),
+    "last_strip_shorter": ((2, 9, 17, 4, 9, 31, 30, 5, 2), 2, True),
+    "images_side_by_side_7x7": ((200, 24, 144, 6, 24, 7, 7, 3, 1), 1, False),
+    "images_side_by_side_4x3": ((600, 16, 96, 4, 16, 4, 3, 5, 1), 1, True),
+    "several_items_to_a_workgroup": ((4200, 8, 16, 4, 8, 20, 20, 3, 1), 1, False),
+    "64_squeezed": ((1, 64, 256, 64, 72, 9, 9, 3, 1), 1, True),
+    "65_squeezed": ((1, 64, 256, 65, 72, 9, 9, 3, 1), 1, False),
+    "3_squeezed": ((1, 16, 64, 3, 24, 9, 9, 3, 1), 1, False),
+    "odd_contraction": ((2, 41, 130, 7, 40, 10, 10, 3, 1), None, True),
+    "1x1_plane": ((2, 16, 30, 4, 16, 1, 1, 3, 1), 1, True),
+    "2x5_plane_stride_2": ((5, 8, 33, 4, 5, 2, 5, 5, 2), 1, True),
+    "longest_slices": ((1, 160, 1280, 33, 16, 5, 5, 3, 1), 1, True),
+}
+
+
+def dw_shape(N, Cexp, H, W, k, s):
+    p = (k - 1) // 2
+    return DwShape(N, Cexp, H, W, (H + 2 * p - k) // s + 1, (W + 2 * p - k) // s + 1, k, s, p)
+
+
+def strips(N, Cin, Cexp, H, W, k, s):
+    fused = plan("_ZN3mbk19eval_expand_dw_planERKNS_7DwShapeEiPi", C.POINTER(DwShape), INT)
+    return fused(C.byref(dw_shape(N, Cexp, H, W, k, s)), Cin)
+
+
+def projection(N, Cout, Cexp, HW, Cse, act):
+    return rule("_ZN3mbk14eval_proj_planEiiiiib", BOOL, *5 * [INT], BOOL)(N, Cout, Cexp, HW, Cse, act)
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_route(name):
+    (N, Cin, Cexp, Cse, Cout, H, W, k, s), want, proj = CASES[name]
+    got = strips(N, Cin, Cexp, H, W, k, s)
+    d = dw_shape(N, Cexp, H, W, k, s)
+    assert got == want
+    assert projection(N, Cout, Cexp, d.Ho * d.Wo, Cse, got is None) == proj
+
+
+@pytest.mark.parametrize("N,Cin,Cexp,H,W,k,s,taken", [
+    (16, 80, 480, 14, 14, 3, 1, True), (18, 80, 480, 14, 14, 3, 1, False),       # 512 workgroups
+    (6, 112, 672, 14, 14, 5, 1, True), (7, 112, 672, 14, 14, 5, 1, False),       # 256
+    (1, 81, 486, 14, 14, 3, 1, False), (1, 200, 1200, 7, 7, 3, 1, False),        # odd, and longer than any
+    (128, 24, 144, 56, 56, 3, 1, True), (64, 24, 144, 56, 56, 5, 2, False),      # up to 24 channels: any size, but
+    (64, 16, 64, 127, 127, 5, 1, False), (73, 8, 24, 108, 108, 3, 2, False), (1024, 24, 144, 7, 7, 5, 1, False),
+    (1, 8, 24, 110, 82, 3, 2, False),                                            # planes that the depthwise kernels refuse
+])
+def test_rule(N, Cin, Cexp, H, W, k, s, taken):
+    assert (strips(N, Cin, Cexp, H, W, k, s) is not None) == taken
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("variant", ["se", "no_se", "relu6", "residual", "no_expand"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_matches_oracle(name, variant):
+    (N, Cin, Cexp, Cse, Cout, H, W, k, s), _, _ = CASES[name]
+    if variant == "residual":
+        if s != 1:
+            pytest.skip("a residual needs stride 1")
+        Cout = Cin
+    expand = variant != "no_expand"
+    check(BlockShape(N=N, Cin=Cin if expand else Cexp, H=H, W=W, Cexp=Cexp, Cse=Cse, Cout=Cout, k=k, stride=s,
+                     has_expand=expand, residual=variant == "residual", has_se=variant not in ("no_se", "relu6"),
+                     activation="relu6" if variant == "relu6" else "swish"), len(name))
