@@ -224,6 +224,11 @@ hipError_t launch_bf_conv1x1(int N, int M, int K, int HW, const void *w, int sAm
                              const Operand &B, void *out, int epi, const void *res, float *psum,
                              float *psq, float *splitk_ws, hipStream_t st);
 
+// kernels_bw.hip
+bool bw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt);
+hipError_t launch_bw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm, int sAk, const void *wimg, const Operand &B,
+                             void *out, int epi, float *psum, float *psq, hipStream_t st);
+
 // kernels_x3.hip
 bool x3_wgrad_plan(bool bf16, int Ma, int Mb, int N, int HW, int *splits);
 hipError_t launch_x3_wgrad(bool bf16, int N, int Ma, int Mb, int HW, const Operand &U, const Operand &V,
@@ -265,12 +270,20 @@ static bool xk_applies(bool bf16, int N, int M, int K, int HW, bool stores_opera
            xk_conv_plan(bf16, N, M, K, HW, pro, nt);
 }
 
+// bf16, short contraction, many rows: weights resident in LDS (conv_bw)
+static bool bw_applies(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi, int *nt)
+{
+    return bf16 && !stores_operand && !wave_conv_kind(M, K, HW) &&
+           !xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, nt) && bw_conv_plan(N, M, K, HW, pro, epi, nt);
+}
+
 // convolutions of the wide blocks that run on the bf16 matrix cores from a weight image
 bool conv1x1_uses_weight_image(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro,
                                int epi)
 {
     int nt;
-    return xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt);
+    return xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt) ||
+           (pro == PRO_BNBWD && bw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt));
 }
 
 // which matrix-core instruction family serves a launch (values of mbconv_engine in mbconv.h)
@@ -300,7 +313,8 @@ int conv1x1_num_partials(bool bf16, int N, int M, int K, int HW, bool stores_ope
     if (kind)
         return wave_conv_num_partials(kind, N, M, HW);
     if (xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
-        xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
+        xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
+        bw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
         return qtiles;
     if (bf16 && !stores_operand && bf_conv_plan(N, M, K, HW, &qtiles, &splits))
         return qtiles;
@@ -314,7 +328,8 @@ size_t conv1x1_splitk_floats(bool bf16, int N, int M, int K, int HW, bool stores
     int qtiles, splits;
     if (stores_operand || wave_conv_kind(M, K, HW) || xs_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
         xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
-        xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
+        xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
+        bw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
         return 0;
     if (bf16 && bf_conv_plan(N, M, K, HW, &qtiles, &splits))
         return bf_conv_splitk_floats(N, M, K, HW);
@@ -338,6 +353,11 @@ hipError_t launch_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w,
                 return hipErrorInvalidValue;
             return launch_xk_conv1x1(bf16, N, M, K, HW, w, sAm, sAk, wimg, B, out, epi, res, psum, psq, st);
         }
+    }
+    {
+        int nt;
+        if (bw_applies(bf16, N, M, K, HW, sc_store != nullptr, B.pro, epi, &nt))
+            return launch_bw_conv1x1(N, M, K, HW, w, sAm, sAk, wimg, B, out, epi, psum, psq, st);
     }
     const int kind = sc_store ? 0 : wave_conv_kind(M, K, HW);
     if (kind)
