@@ -40,7 +40,7 @@ struct XdArgs {
     int perDie;          // 0: workgroups in order; else the channel groups of an item group on one XCD
     int rt;              // output rows to a thread: 1 or 2
     int act;             // store act(BN2(d)) in place of d
-    FastDiv divCG, divS, divW, divHW, divRuns;
+    FastDiv divCG, divS, divW, divHW, divRuns, divRuns4;
     const float *x, *w, *wdw, *w1;
     float *d, *z;        // z: [strip][n][c] partial means, or null
     float *q;            // or, instead: [n][channel group, strip][Cse] partial sums of W1 z
@@ -587,6 +587,393 @@ hipError_t launch_eval_expand_dw(const DwShape &s, int K, const void *x, const v
     return hipErrorInvalidValue;
 }
 
+
+// ---- a block without squeeze-and-excitation in one launch ----
+//
+//   out[n][m] = BN3(sum_c W_p[m][c] act(BN2(depthwise(act(BN1(W_e x[n])))[c]))) (+ x)
+//
+// Without a gate nothing couples the planes, so a workgroup takes its pixels through the whole block, sixteen expanded
+// channels at a time: expansion conv, BN1 and activation into the LDS tile (as above), depthwise conv, BN2 and activation
+// into a second one, and the projection conv's products with those sixteen channels into sums that stay in registers.
+// Neither e nor d exists in memory.  A wavefront has 64 pixels of the strip's input, which it holds in registers for all
+// channels, and 64 of its output; two barriers per sixteen channels.  What bounds it: MFMAs and vector instructions in turn
+// (fp32 MFMAs do not overlap with them), a workgroup to a compute unit: 3.9 us for sixteen channels of 504 pixels.  Held to the
+// 128 registers that would let two share one it spills inside the loop (32 images of 56x56 39.4 -> 43.6 us, 128 153 -> 169).
+// 24 -> 144 -> 24 on 56x56, 32 images: 69.5 us in three launches, 54.7 in two, 39.4 here.
+namespace {
+
+struct XfArgs {
+    XdArgs x;
+    int M, dstr;     // output channels; floats per channel of the second tile
+    const float *wp; // [M][C]
+    const float *res;
+    float *out;
+};
+
+template <int T, int TP, int PX, int KD, int SD, int MT>
+__global__ __launch_bounds__(kXdThreads, 2) void xf_kernel(XfArgs f, DwEval ev)
+{
+    const XdArgs &a = f.x;
+    constexpr int threads = kXdThreads, WP = 4 * T + 4, KK = KD * KD, RT = SD == 1 ? 2 : 1;
+    constexpr int WL = kXdRows * WP, WB = WL + 256 * MT + kXdRows * KK; // floats of one group's weights
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ float cf3[2 * 16 * MT]; // BN3 {scale, shift}
+    float *cf = lds + 2 * WB;          // {BN1 scale, shift, BN2 scale, shift} of every expanded channel
+    float *tile = cf + 4 * kXdRows * a.CG, *dt = tile + kXdRows * a.chs;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int K = a.K, C = a.C, HW = a.H * a.W;
+    const XdItem it = xd_item<KD, SD>(a, blockIdx.x);
+
+    // the wavefront's input pixels: column j of the lane is pixel 4r + j, 32 (j/2) + 2r + j%2 or 16j + r
+    float b[T][4];
+    int toff[4]; // where they go in the tile, -1: nowhere
+#pragma unroll
+    for (int j = 0; j < 4; j += PX) {
+        int pix = it.p0 + 64 * wave + (PX == 4 ? 4 * r : PX == 2 ? 16 * j + 2 * r : 16 * j + r);
+        const bool in = pix < it.p1;
+        pix = in ? pix : it.p0;
+        const int im = a.NI > 1 ? (int)fdiv((uint32_t)pix, a.divHW) : 0, pl = pix - im * HW;
+        const int h = (int)fdiv((uint32_t)pl, a.divW), w = pl - h * a.W;
+#pragma unroll
+        for (int e = 0; e < PX; ++e)
+            toff[j + e] = in ? im * a.ims + (h - it.hin0) * a.pitch + 4 + w + e : -1;
+        const char *px = reinterpret_cast<const char *>(a.x + (size_t)it.n * K * HW);
+        const uint32_t at = (uint32_t)(im * K * HW + pl), off = 4u * ((uint32_t)(g * HW) + at);
+#pragma unroll
+        for (int s = 0; s < T; ++s) {
+            const float *q = reinterpret_cast<const float *>(
+                px + (s < TP ? off + (uint32_t)s * (16u * (uint32_t)HW) : 4u * ((uint32_t)(min(4 * s + g, K - 1) * HW) + at)));
+            if (PX == 4) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(q);
+#pragma unroll
+                for (int e = 0; e < PX; ++e)
+                    b[s][(j + e) % 4] = v[e];
+            } else if (PX == 2) {
+                const f32x2 v = *reinterpret_cast<const f32x2 *>(q);
+#pragma unroll
+                for (int e = 0; e < PX; ++e)
+                    b[s][(j + e) % 4] = v[e];
+            } else {
+                b[s][j] = q[0];
+            }
+        }
+    }
+    // one group's weights: requested (load) and parked (park); W_e as in xd_kernel, W_p and the filters in the order of use
+    constexpr int WN = (64 * T + threads - 1) / threads, PN = (256 * MT + threads - 1) / threads;
+    float wv[WN], pv[PN], fv;
+    const auto load = [&](int cg) __attribute__((always_inline)) {
+        const int c0 = cg * kXdRows;
+#pragma unroll
+        for (int i = 0; i < WN; ++i) {
+            const uint32_t idx = (uint32_t)(tid + i * threads), m = idx / (4 * T), kk = idx % (4 * T);
+            wv[i] = a.w[(size_t)min(c0 + (int)m, C - 1) * K + min((int)kk, K - 1)];
+        }
+#pragma unroll
+        for (int i = 0; i < PN; ++i) { // [row tile][step][lane]
+            const int idx = tid + i * threads, ln = idx & 63, st = (idx >> 6) & 3, m = 16 * (idx >> 8) + (ln & 15);
+            pv[i] = f.wp[(size_t)min(m, f.M - 1) * C + min(c0 + 4 * st + (ln >> 4), C - 1)];
+        }
+        fv = a.wdw[min(c0 * KK + tid, C * KK - 1)];
+    };
+    const auto park = [&](int cg) __attribute__((always_inline)) {
+        float *wl = lds + (cg & 1) * WB;
+#pragma unroll
+        for (int i = 0; i < WN; ++i) {
+            const uint32_t idx = (uint32_t)(tid + i * threads), m = idx / (4 * T), kk = idx % (4 * T);
+            if (idx < 64 * T)
+                wl[m * WP + (kk & 3) * T + (kk >> 2)] = (int)kk < K ? wv[i] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < PN; ++i) {
+            const int idx = tid + i * threads, c = cg * kXdRows + 4 * ((idx >> 6) & 3) + ((idx & 63) >> 4);
+            if (idx < 256 * MT) // (channels past the end: zero)
+                wl[WL + idx] = c < C ? pv[i] : 0.f;
+        }
+        if (tid < kXdRows * KK)
+            wl[WL + 256 * MT + tid] = fv;
+    };
+    load(0);
+    for (int c = tid; c < kXdRows * a.CG; c += threads) {
+        const BnEvalRegs r1 = bn_eval_issue(ev.bn1, min(c, C - 1)), r2 = bn_eval_issue(ev.bn2, min(c, C - 1));
+        const BnEvalCoef k1 = bn_eval_coef(r1, ev.eps), k2 = bn_eval_coef(r2, ev.eps);
+        *reinterpret_cast<f32x4 *>(cf + 4 * c) = (f32x4){k1.scale, k1.shift, k2.scale, k2.shift};
+    }
+    if (tid < 16 * MT) {
+        const BnEvalCoef k3 = bn_eval_coef(bn_eval_issue(ev.bn3, min(tid, f.M - 1)), ev.eps);
+        cf3[2 * tid] = k3.scale;
+        cf3[2 * tid + 1] = k3.shift;
+    }
+    // the tile's zero columns, and its rows outside the plane
+    for (int row = tid; row < kXdRows * a.NI * a.rin; row += threads) {
+        const int rr = row >> 4, h = it.hin0 + rr - (a.NI > 1 ? (int)((uint32_t)rr / (uint32_t)a.rin) * a.rin : 0);
+        float *p = tile + (row & 15) * a.chs + rr * a.pitch;
+        const bool out = h < 0 || h >= a.H;
+        for (int c = 0; c < a.pitch; c += 4)
+            if (out || c == 0 || c + 4 > 4 + a.W)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (out || c == 0 || c + e >= 4 + a.W)
+                        p[c + e] = 0.f;
+    }
+    park(0);
+    __syncthreads();
+
+    const int rw = (a.Wo + 3) >> 2, rows = min(a.R, a.Ho - it.ho0), opx = 4 * rw; // (a row of the second tile: opx)
+    const int ch = tid >> 5, tpi = 32 / a.NI, dim = a.NI == 1 ? 0 : (tid & 31) / tpi, lt = tid & (tpi - 1);
+    const int runs = (a.R + RT - 1) / RT * rw;
+    f32x4 sum[MT][4];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            sum[m][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    constexpr f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    for (int cg = 0; cg < a.CG; ++cg) {
+        const float *wl = lds + (cg & 1) * WB, *wps = wl + WL, *wd = wps + 256 * MT;
+        if (cg + 1 < a.CG)
+            load(cg + 1);
+        // ---- expansion ----
+        {
+            f32x4 acc[4];
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const float av = wl[r * WP + g * T + t];
+                const uint32_t ok = t < TP || 4 * t + g < K ? 0xffffffffu : 0u;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, t < TP ? b[t][j] : and_mask(b[t][j], ok),
+                                                                  t ? acc[j] : zero, 0, 0, 0);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const f32x2 k = *reinterpret_cast<const f32x2 *>(cf + 4 * (cg * kXdRows + 4 * g + v));
+                float *p = tile + (4 * g + v) * a.chs;
+                float y[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    y[j] = actf(fmaf(acc[j][v], k[0], k[1]));
+                if (PX == 4) {
+                    if (toff[0] >= 0)
+                        *reinterpret_cast<f32x4 *>(p + toff[0]) = (f32x4){y[0], y[1], y[2], y[3]};
+                } else if (PX == 2) {
+#pragma unroll
+                    for (int j = 0; j < 4; j += 2)
+                        if (toff[j] >= 0)
+                            *reinterpret_cast<f32x2 *>(p + toff[j]) = (f32x2){y[j], y[j + 1]};
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (toff[j] >= 0)
+                            p[toff[j]] = y[j];
+                }
+            }
+        }
+        __syncthreads();
+        if (cg + 1 < a.CG) // (the other buffer's readers are past this barrier)
+            park(cg + 1);
+        // ---- depthwise ----
+        {
+            float wt[KK];
+#pragma unroll
+            for (int t = 0; t < KK; ++t)
+                wt[t] = wd[ch * KK + t];
+            const f32x2 k2 = *reinterpret_cast<const f32x2 *>(cf + 4 * (cg * kXdRows + ch) + 2);
+            const float *tc = tile + ch * a.chs + dim * a.ims + 4;
+            float *dc = dt + ch * f.dstr + dim * a.R * opx;
+            for (int i = lt; i < runs; i += tpi) {
+                const int rg = (int)fdiv((uint32_t)i, a.divRuns), j = i - rg * rw, oh = RT * rg;
+                const float *p = tc + 4 * SD * j;
+                float o[RT][4];
+#pragma unroll
+                for (int q = 0; q < RT; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        o[q][e] = 0.f;
+#pragma unroll
+                for (int ir = 0; ir < (RT - 1) * SD + KD; ++ir) {
+                    float row[3 * SD + KD];
+                    xd_window<KD, SD>(p + min(oh * SD + ir, a.rin - 1) * a.pitch, row);
+#pragma unroll
+                    for (int q = 0; q < RT; ++q) {
+                        const int u = ir - q * SD;
+                        if (u >= 0 && u < KD) {
+#pragma unroll
+                            for (int v = 0; v < KD; ++v)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+                                    o[q][e] = fmaf(wt[u * KD + v], row[e * SD + v], o[q][e]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < RT; ++q) {
+                    if (oh + q < a.R) {
+                        f32x4 y;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            y[e] = actf(fmaf(o[q][e], k2[0], k2[1]));
+                        *reinterpret_cast<f32x4 *>(dc + (oh + q) * opx + 4 * j) = y;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        // ---- projection: (what lies past a row or a strip gives columns that are not stored) ----
+        f32x4 acc[MT][4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const f32x4 bq = *reinterpret_cast<const f32x4 *>(dt + (4 * s + g) * f.dstr + 64 * wave + 4 * r);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const float av = wps[m * 256 + s * 64 + lane];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bq[j], s ? acc[m][j] : zero, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                sum[m][j] += acc[m][j];
+    }
+    // ---- the lane's four output pixels of its rows ----
+    const int q = 64 * wave + 4 * r, row = (int)fdiv((uint32_t)q, a.divRuns4), col = q - row * opx;
+    const int im = a.NI == 1 ? 0 : (int)((uint32_t)row / (uint32_t)a.R), oh = row - im * a.R;
+    if (im >= it.ni || oh >= rows)
+        return;
+    const int left = a.Wo - col;
+    const size_t HWo = (size_t)a.Ho * a.Wo, base = (size_t)(it.n + im) * f.M * HWo + (size_t)(it.ho0 + oh) * a.Wo + col;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int mm = 16 * m + 4 * g + v;
+            if (mm < f.M) {
+                const float sc = cf3[2 * mm], sh = cf3[2 * mm + 1];
+                const size_t at = base + (size_t)mm * HWo;
+                if ((a.Wo & 3) == 0) {
+                    f32x4 y;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        y[j] = fmaf(sum[m][j][v], sc, sh);
+                    if (f.res)
+                        y += *reinterpret_cast<const f32x4 *>(f.res + at);
+                    *reinterpret_cast<f32x4 *>(f.out + at) = y;
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (j < left)
+                            f.out[at + j] = fmaf(sum[m][j][v], sc, sh) + (f.res ? f.res[at + j] : 0.f);
+                }
+            }
+        }
+}
+
+} // namespace
+
+// Whether the shape is taken; the plan.
+static bool xf_plan(const DwShape &s, int K, int M, XfArgs &f, int *T, int *PX, int *MT, size_t *lds)
+{
+    XdArgs &a = f.x;
+    if (!xd_form(K, s.W, T, PX) || *T > 10 || M > 64 || s.C > 1024)
+        return false;
+    if (s.s == 2 && s.W % 4 == 2 && s.H % 2 == 0 && s.H * ((s.W + 3) / 4) > 1024) // (as in xd_plan)
+        return false;
+    *T = std::max(*T, 6);
+    *MT = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+    a.CG = (s.C + kXdRows - 1) / kXdRows;
+    // strips whose input and output (in runs of four) are at most 64 pixels to a wavefront, or images side by side
+    const int opx = 4 * ((s.Wo + 3) / 4);
+    int S = 1, NI = 1;
+    for (;; ++S) {
+        xd_geometry(s, *T, S, 1, a);
+        if (std::min(a.rin, s.H) * s.W <= 512 && a.R * opx <= 512)
+            break;
+        if (S >= s.Ho)
+            return false;
+    }
+    S = (s.Ho + a.R - 1) / a.R; // no empty strips
+    if (S == 1)
+        while (NI < 8 && NI < s.N && 2 * NI * s.H * s.W <= 512 && 2 * NI * s.Ho * opx <= 512)
+            NI *= 2;
+    xd_geometry(s, *T, S, NI, a);
+    f.dstr = NI * a.R * opx;
+    f.dstr = std::max(f.dstr, 512); // (a wavefront reads its 64 pixels whether they exist or not)
+    f.dstr += 16;
+    const int KK = s.k * s.k, WB = kXdRows * (4 * *T + 4) + 256 * *MT + kXdRows * KK;
+    *lds = sizeof(float) * (size_t)(2 * WB + 4 * kXdRows * a.CG + kXdRows * a.chs + kXdRows * f.dstr);
+    a.items = (s.N + NI - 1) / NI * S;
+    return *lds <= 156 * 1024;
+}
+
+bool eval_block_plan(const DwShape &s, int K, int M)
+{
+    XfArgs f = {};
+    int T, PX, MT;
+    size_t lds;
+    if (!xf_plan(s, K, M, f, &T, &PX, &MT, &lds))
+        return false;
+    // Most compute units have a workgroup, and the strip's input is at most one and a half times its output (one forward
+    // pass, ReLU6, two launches / one, us: 24 -> 144 -> 24 on 56x56, 3x3, 16 images 42 / 38, 32 54.7 / 39.4, 128 205 / 153; 32 ->
+    // 192 -> 32 on 28x28, 3x3, 96 images 69 / 55; 40 -> 240 -> 40 on 14x14, 5x5, 512 images 125 / 104; 24 -> 144 -> 24 on 7x7,
+    // 5x5, 2000 images 91 / 58; twice, 5x5 on 57x57, 124 / 128; stride 2, 16 -> 96 on 112x112, 64 images 113 / 266).
+    return f.x.items >= 160 && s.s == 1 && 2 * std::min(f.x.rin, s.H) <= 3 * f.x.R;
+}
+
+hipError_t launch_eval_block(const DwShape &s, int K, int M, const void *x, const void *w_expand, const void *w_dw,
+                             const void *w_proj, const void *res, void *out, const DwEval &ev, hipStream_t st)
+{
+    XfArgs f = {};
+    int T, PX, MT;
+    size_t lds;
+    if (!xf_plan(s, K, M, f, &T, &PX, &MT, &lds))
+        return hipErrorInvalidValue;
+    XdArgs &a = f.x;
+    a.N = s.N;
+    a.K = K;
+    a.C = s.C;
+    a.H = s.H;
+    a.W = s.W;
+    a.Ho = s.Ho;
+    a.Wo = s.Wo;
+    a.k = s.k;
+    a.s = s.s;
+    a.divS = make_div((uint32_t)a.S);
+    a.divW = make_div((uint32_t)s.W);
+    a.divHW = make_div((uint32_t)(s.H * s.W));
+    a.divRuns = make_div((uint32_t)((s.Wo + 3) / 4));
+    a.divRuns4 = make_div((uint32_t)((s.Wo + 3) / 4 * 4));
+    a.x = (const float *)x;
+    a.w = (const float *)w_expand;
+    a.wdw = (const float *)w_dw;
+    f.M = M;
+    f.wp = (const float *)w_proj;
+    f.res = (const float *)res;
+    f.out = (float *)out;
+#define MBK_GO(T_, TP_, PX_, K_, S_, MT_)                                                         \
+    if (T == T_ && PX == PX_ && s.k == K_ && s.s == S_ && MT == MT_) {                            \
+        auto kern = xf_kernel<T_, TP_, PX_, K_, S_, MT_>;                                         \
+        const hipError_t e_ = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+        if (e_ != hipSuccess)                                                                     \
+            return e_;                                                                            \
+        hipLaunchKernelGGL(kern, dim3(a.items), dim3(kXdThreads), lds, st, f, ev);                \
+        return hipGetLastError();                                                                 \
+    }
+#define MBK_MT(T_, TP_, PX_, K_, S_) MBK_GO(T_, TP_, PX_, K_, S_, 1) MBK_GO(T_, TP_, PX_, K_, S_, 2) \
+    MBK_GO(T_, TP_, PX_, K_, S_, 4)
+#define MBK_KS(T_, TP_, PX_) MBK_MT(T_, TP_, PX_, 3, 1) MBK_MT(T_, TP_, PX_, 5, 1)
+#define MBK_T(T_, TP_) MBK_KS(T_, TP_, 1) MBK_KS(T_, TP_, 2) MBK_KS(T_, TP_, 4)
+    MBK_T(6, 0)
+    MBK_T(10, 6)
+#undef MBK_T
+#undef MBK_KS
+#undef MBK_MT
+#undef MBK_GO
+    return hipErrorInvalidValue;
+}
 
 // ---- projection conv of small launches, with the squeeze-and-excitation gate and BN3 ----
 //

@@ -253,6 +253,11 @@ int eval_expand_dw_qparts(const DwShape &s, int K, int Cse);
 hipError_t launch_eval_expand_dw(const DwShape &s, int K, const void *x, const void *w_expand, const void *w_dw, void *d,
                                  float *z, float *q, int Cse, const float *w1, bool act, const DwEval &ev, hipStream_t st);
 
+// Evaluation mode, fp32, a block without SE stage and with an expansion: all of it in one launch (ev: the normalisations).
+bool eval_block_plan(const DwShape &s, int K, int M);
+hipError_t launch_eval_block(const DwShape &s, int K, int M, const void *x, const void *w_expand, const void *w_dw,
+                             const void *w_proj, const void *res, void *out, const DwEval &ev, hipStream_t st);
+
 // Evaluation mode, fp32, small launches: out = BN3(W_p (act(BN2(d)) * gate)) (+ res) in one launch, the gate from
 // the `parts` partial sums q of launch_eval_expand_dw, or (parts == 0) read from `gate`, or (that null) one.
 // `act`: whether d is still to go through BN2 and the activation.

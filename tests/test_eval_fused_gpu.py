@@ -80,3 +80,39 @@ def test_matches_oracle(name, variant):
     check(BlockShape(N=N, Cin=Cin if expand else Cexp, H=H, W=W, Cexp=Cexp, Cse=Cse, Cout=Cout, k=k, stride=s,
                      has_expand=expand, residual=variant == "residual", has_se=variant not in ("no_se", "relu6"),
                      activation="relu6" if variant == "relu6" else "swish"), len(name))
+
+
+# A block without SE stage in one launch: (N, Cin, Cexp, Cout, H, W, k)
+WHOLE = {
+    "strips_56x56": (21, 24, 144, 24, 56, 56, 3),
+    "strips_odd_width": (41, 23, 50, 17, 39, 37, 3),          # a last strip that is shorter, one pixel to a load
+    "even_width_masked_channels": (55, 9, 33, 33, 30, 34, 3),
+    "36_input_channels_64_rows": (81, 36, 72, 64, 25, 28, 3),
+    "two_images_14x14_5x5": (321, 40, 104, 40, 14, 14, 5),
+    "eight_images_7x7": (1283, 16, 48, 16, 7, 7, 5),
+    "eight_images_5x3": (1281, 11, 17, 5, 5, 3, 3),
+}
+
+
+@pytest.mark.parametrize("N,Cin,Cexp,Cout,H,W,k,s,taken", [
+    (20, 24, 144, 24, 56, 56, 3, 1, True), (19, 24, 144, 24, 56, 56, 3, 1, False),   # 160 workgroups of strips
+    (319, 40, 240, 40, 14, 14, 5, 1, True), (318, 40, 240, 40, 14, 14, 5, 1, False),
+    (64, 41, 246, 40, 28, 28, 3, 1, False), (96, 40, 240, 65, 28, 28, 3, 1, False),
+    (96, 32, 192, 32, 28, 28, 3, 2, False), (40, 24, 144, 30, 57, 57, 5, 1, False),
+])
+def test_rule_of_the_whole_block(N, Cin, Cexp, Cout, H, W, k, s, taken):
+    whole = rule("_ZN3mbk15eval_block_planERKNS_7DwShapeEii", BOOL, C.POINTER(DwShape), INT, INT)
+    assert whole(C.byref(dw_shape(N, Cexp, H, W, k, s)), Cin, Cout) == taken
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("activation", ["relu6", "swish"])
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("name", list(WHOLE))
+def test_whole_block_matches_oracle(name, residual, activation):
+    N, Cin, Cexp, Cout, H, W, k = WHOLE[name]
+    Cout = Cin if residual else Cout
+    whole = rule("_ZN3mbk15eval_block_planERKNS_7DwShapeEii", BOOL, C.POINTER(DwShape), INT, INT)
+    assert whole(C.byref(dw_shape(N, Cexp, H, W, k, 1)), Cin, Cout)
+    check(BlockShape(N=N, Cin=Cin, H=H, W=W, Cexp=Cexp, Cse=1, Cout=Cout, k=k, stride=1, has_expand=True,
+                     residual=residual, has_se=False, activation=activation), len(name))
