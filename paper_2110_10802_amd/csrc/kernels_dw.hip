@@ -1008,7 +1008,7 @@ __global__ __launch_bounds__(1024) void bn_bwd_chan_kernel(PlaneArgs a, BnBwdFin
         }
         f.dbeta[c] = (float)sb;
         f.dgamma[c] = (float)sr;
-        bn_bwd_coef_vals(a.C, c, f.m, sr, sb, gm, mu, rs, f.coef);
+        bn_bwd_coef_vals(a.C, c, f.inv_m, sr, sb, gm, mu, rs, f.coef);
     }
 }
 

@@ -13,7 +13,7 @@ namespace mbk {
 // PREP: the workgroups past the channels' write the weight images of convolutions later in the
 // sequence (a launch of their own cost 4 to 5 us; this one's few workgroups leave the chip empty).
 template <bool PREP>
-__global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double m,
+__global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double inv_m, double unbias,
                                                           const float *__restrict__ psum,
                                                           const float *__restrict__ psq,
                                                           const float *__restrict__ gamma,
@@ -77,11 +77,15 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double 
     s = wave_sum_d(s);
     s2 = wave_sum_d(s2);
     if (lane == 0) {
-        const double mean = s / m;
-        double var = s2 / m - mean * mean;
+        // (no divisions and no square root, as in bn_fin_finish: they are chains of a dozen fp64 instructions each)
+        const double mean = s * inv_m;
+        double var = s2 * inv_m - mean * mean;
         if (var < 0.0)
             var = 0.0;
-        const double rstd = 1.0 / sqrt(var + (double)eps);
+        const double xv = var + (double)eps;
+        double rstd = __builtin_amdgcn_rsq(xv);
+        if (xv > 0.0 && xv < __builtin_inf())
+            rstd = rstd * (1.5 - 0.5 * xv * rstd * rstd);
         const double scale = (double)gm * rstd;
         bn[c] = (float)scale;
         bn[C + c] = (float)((double)bt - mean * scale);
@@ -90,7 +94,7 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double 
         if (run_mean)
             run_mean[c] = (float)((1.0 - (double)momentum) * (double)rm + (double)momentum * mean);
         if (run_var) {
-            const double unbiased = m > 1.0 ? var * m / (m - 1.0) : var;
+            const double unbiased = var * unbias;
             run_var[c] = (float)((1.0 - (double)momentum) * (double)rv + (double)momentum * unbiased);
         }
     }
@@ -102,22 +106,23 @@ hipError_t launch_bn_finalize(int C, int NP, double m, const float *psum, const 
                               float *ones, size_t ones_count, const X3PrepArgs *prep)
 {
     const unsigned own = (unsigned)((C + 3) / 4);
+    const double inv_m = 1.0 / m, unbias = m > 1.0 ? m / (m - 1.0) : 1.0;
     if (prep && prep->tiles)
-        hipLaunchKernelGGL(bn_finalize_kernel<true>, dim3(own + prep->tiles), dim3(256), 0, st, C, NP, m, psum, psq,
+        hipLaunchKernelGGL(bn_finalize_kernel<true>, dim3(own + prep->tiles), dim3(256), 0, st, C, NP, inv_m, unbias, psum, psq,
                            gamma, beta, eps, momentum, run_mean, run_var, bn, ones, ones ? ones_count : 0, *prep);
     else
-        hipLaunchKernelGGL(bn_finalize_kernel<false>, dim3(own), dim3(256), 0, st, C, NP, m, psum, psq, gamma, beta,
+        hipLaunchKernelGGL(bn_finalize_kernel<false>, dim3(own), dim3(256), 0, st, C, NP, inv_m, unbias, psum, psq, gamma, beta,
                            eps, momentum, run_mean, run_var, bn, ones, ones ? ones_count : 0, X3PrepArgs());
     return hipGetLastError();
 }
 
-__device__ __forceinline__ void bn_bwd_coef(int C, int c, double m, double dgamma, double dbeta,
+__device__ __forceinline__ void bn_bwd_coef(int C, int c, double inv_m, double dgamma, double dbeta,
                                             float gamma, const float *bn, float *coef)
 {
-    bn_bwd_coef_vals(C, c, m, dgamma, dbeta, gamma, bn[2 * C + c], bn[3 * C + c], coef);
+    bn_bwd_coef_vals(C, c, inv_m, dgamma, dbeta, gamma, bn[2 * C + c], bn[3 * C + c], coef);
 }
 
-__device__ __forceinline__ void bn_bwd_finalize_body(int block, int C, int NP, double m,
+__device__ __forceinline__ void bn_bwd_finalize_body(int block, int C, int NP, double inv_m,
                                                      const float *__restrict__ psb,
                                                      const float *__restrict__ psr,
                                                      const float *__restrict__ gamma,
@@ -154,11 +159,11 @@ __device__ __forceinline__ void bn_bwd_finalize_body(int block, int C, int NP, d
             dbeta[c] = (float)sb;
         if (dgamma)
             dgamma[c] = (float)sr;
-        bn_bwd_coef_vals(C, c, m, sr, sb, gm, mean, rstd, coef);
+        bn_bwd_coef_vals(C, c, inv_m, sr, sb, gm, mean, rstd, coef);
     }
 }
 
-__global__ __launch_bounds__(256) void bn_bwd_finalize_kernel(int C, int NP, double m,
+__global__ __launch_bounds__(256) void bn_bwd_finalize_kernel(int C, int NP, double inv_m,
                                                               const float *__restrict__ psb,
                                                               const float *__restrict__ psr,
                                                               const float *__restrict__ gamma,
@@ -166,13 +171,13 @@ __global__ __launch_bounds__(256) void bn_bwd_finalize_kernel(int C, int NP, dou
                                                               float *dgamma, float *dbeta,
                                                               float *coef)
 {
-    bn_bwd_finalize_body(blockIdx.x, C, NP, m, psb, psr, gamma, bn, dgamma, dbeta, coef);
+    bn_bwd_finalize_body(blockIdx.x, C, NP, inv_m, psb, psr, gamma, bn, dgamma, dbeta, coef);
 }
 
 // Block without squeeze-and-excitation: one wavefront per channel adds the plane sums of the
 // batch in a fixed order (lane l takes images l, l+64, ...; fp64 butterfly), writes BN2's
 // parameter gradients and backward coefficients, and zeroes the channel's column of dzs.
-__global__ __launch_bounds__(256) void bn2_bwd_nose_kernel(int N, int C, double m,
+__global__ __launch_bounds__(256) void bn2_bwd_nose_kernel(int N, int C, double inv_m,
                                                            const float *__restrict__ A1,
                                                            const float *__restrict__ A2,
                                                            const float *__restrict__ gamma,
@@ -194,7 +199,7 @@ __global__ __launch_bounds__(256) void bn2_bwd_nose_kernel(int N, int C, double 
     if (lane == 0) {
         dbeta[c] = (float)sb;
         dgamma[c] = (float)sr;
-        bn_bwd_coef(C, c, m, sr, sb, gamma[c], bn, coef);
+        bn_bwd_coef(C, c, inv_m, sr, sb, gamma[c], bn, coef);
     }
 }
 
@@ -202,7 +207,7 @@ hipError_t launch_bn2_bwd_nose(int N, int C, double m, const float *A1, const fl
                                const float *gamma, const float *bn, float *dgamma, float *dbeta,
                                float *coef, float *dzs, hipStream_t st)
 {
-    hipLaunchKernelGGL(bn2_bwd_nose_kernel, dim3((C + 3) / 4), dim3(256), 0, st, N, C, m, A1, A2,
+    hipLaunchKernelGGL(bn2_bwd_nose_kernel, dim3((C + 3) / 4), dim3(256), 0, st, N, C, 1.0 / m, A1, A2,
                        gamma, bn, dgamma, dbeta, coef, dzs);
     return hipGetLastError();
 }
@@ -211,7 +216,7 @@ hipError_t launch_bn_bwd_finalize(int C, int NP, double m, const float *psb, con
                                   const float *gamma, const float *bn, float *dgamma,
                                   float *dbeta, float *coef, hipStream_t st)
 {
-    hipLaunchKernelGGL(bn_bwd_finalize_kernel, dim3((C + 3) / 4), dim3(256), 0, st, C, NP, m, psb,
+    hipLaunchKernelGGL(bn_bwd_finalize_kernel, dim3((C + 3) / 4), dim3(256), 0, st, C, NP, 1.0 / m, psb,
                        psr, gamma, bn, dgamma, dbeta, coef);
     return hipGetLastError();
 }
@@ -498,7 +503,7 @@ __global__ __launch_bounds__(256) void se_bwd_batch_kernel(SeBwdArgs a)
             a.db2[c] = sb;
             a.dbeta2[c] = (float)dbeta;
             a.dgamma2[c] = (float)dgamma;
-            bn_bwd_coef(C, c, (double)N * a.HW, dgamma, dbeta, a.gamma2[c], a.bn2, a.coef2);
+            bn_bwd_coef(C, c, a.inv_m, dgamma, dbeta, a.gamma2[c], a.bn2, a.coef2);
         }
         return;
     }
@@ -666,7 +671,7 @@ __global__ __launch_bounds__(256) void se_bwd_sums_kernel(SeBwdArgs a, int chan,
             a.db2[c] = sb;
             a.dbeta2[c] = (float)dbeta;
             a.dgamma2[c] = (float)dgamma;
-            bn_bwd_coef_vals(C, c, (double)N * a.HW, dgamma, dbeta, gm, mean, rstd, a.coef2);
+            bn_bwd_coef_vals(C, c, a.inv_m, dgamma, dbeta, gm, mean, rstd, a.coef2);
         }
         return;
     }
@@ -787,7 +792,7 @@ __global__ __launch_bounds__(256) void reduce_planes_kernel(const float *__restr
 // workgroups add the filter-gradient partials, the others finalise BN1's backward.
 __global__ __launch_bounds__(256) void dw_bwd_finalize_kernel(int nb1, const float *__restrict__ pdw,
                                                               int C, int NP, int inner,
-                                                              float *__restrict__ dw, double m,
+                                                              float *__restrict__ dw, double inv_m,
                                                               const float *__restrict__ psb,
                                                               const float *__restrict__ psr,
                                                               const float *__restrict__ gamma,
@@ -798,7 +803,7 @@ __global__ __launch_bounds__(256) void dw_bwd_finalize_kernel(int nb1, const flo
     if ((int)blockIdx.x < nb1)
         reduce_planes_body(blockIdx.x, pdw, C, NP, inner, dw);
     else
-        bn_bwd_finalize_body(blockIdx.x - nb1, C, NP, m, psb, psr, gamma, bn, dgamma, dbeta, coef);
+        bn_bwd_finalize_body(blockIdx.x - nb1, C, NP, inv_m, psb, psr, gamma, bn, dgamma, dbeta, coef);
 }
 
 hipError_t launch_dw_bwd_finalize(const float *pdw, int C, int NP, int inner, float *dw, double m,
@@ -809,7 +814,7 @@ hipError_t launch_dw_bwd_finalize(const float *pdw, int C, int NP, int inner, fl
     const long long total = (long long)C * inner * 8;
     const int nb1 = (int)((total + 255) / 256), nb2 = (C + 3) / 4;
     hipLaunchKernelGGL(dw_bwd_finalize_kernel, dim3((unsigned)(nb1 + nb2)), dim3(256), 0, st, nb1, pdw,
-                       C, NP, inner, dw, m, psb, psr, gamma, bn, dgamma, dbeta, coef);
+                       C, NP, inner, dw, 1.0 / m, psb, psr, gamma, bn, dgamma, dbeta, coef);
     return hipGetLastError();
 }
 

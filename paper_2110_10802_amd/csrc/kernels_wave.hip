@@ -340,8 +340,8 @@ __global__ __launch_bounds__(512, DG ? 4 : 1) void wgrad_lt_kernel(WgradClArgs a
                 }
                 // c0*dy + c1*raw + c2 (see launch_bn_bwd_finalize): dgamma = sr, dbeta = sb
                 const double c0 = (double)gm * rstd;
-                const double c1 = -c0 * rstd * sr / a.ufin.m;
-                const double c2 = -c0 * sb / a.ufin.m - c1 * mean;
+                const double c1 = -c0 * rstd * sr * a.ufin.inv_m;
+                const double c2 = -c0 * sb * a.ufin.inv_m - c1 * mean;
                 uk0[ta] = (float)c0;
                 uk1[ta] = (float)c1;
                 uk2[ta] = (float)c2;
@@ -630,8 +630,8 @@ __global__ __launch_bounds__(256, NTW == 1 ? 3 : 2) void projbwd_wave_kernel(Wgr
             }
             // c0*dy + c1*raw + c2 (see launch_bn_bwd_finalize): dgamma = sr, dbeta = sb
             const double c0 = (double)gm * rstd;
-            const double c1 = -c0 * rstd * sr / a.ufin.m;
-            const double c2 = -c0 * sb / a.ufin.m - c1 * mean;
+            const double c1 = -c0 * rstd * sr * a.ufin.inv_m;
+            const double c2 = -c0 * sb * a.ufin.inv_m - c1 * mean;
             k0 = (float)c0;
             k1 = (float)c1;
             k2 = (float)c2;

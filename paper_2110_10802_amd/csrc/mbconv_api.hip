@@ -527,7 +527,7 @@ mbconv_status backward_impl(const mbconv_desc *desc, const mbconv_params *prm, c
     // backward: no launch for that step)
     int psplits = 0;
     const bool proj_fused = projbwd_fused_plan(P.N, P.Cexp, P.Cout, P.HWo, &psplits);
-    const BnBwdFin fin3 = {pa, pb, prm->bn3_gamma, bn3, gr->bn3_gamma, gr->bn3_beta, coef3, P.N, m2};
+    const BnBwdFin fin3 = {pa, pb, prm->bn3_gamma, bn3, gr->bn3_gamma, gr->bn3_beta, coef3, P.N, 1.0 / m2};
     const bool chan3 = !proj_fused && bn_bwd_chan_supported(P.N, P.HWo);
     if (chan3)
         MBK_STEP(MBCONV_STEP_BN3_BWD_REDUCE, launch_bn_bwd_chan(bf, P.N, P.Cout, P.HWo, dout, p, bn3, fin3, st));
@@ -619,6 +619,7 @@ mbconv_status backward_impl(const mbconv_desc *desc, const mbconv_params *prm, c
         a.s4 = at<float>(saved, P.o_s4);
         a.gamma2 = prm->bn2_gamma;
         a.bn2 = bn2;
+        a.inv_m = 1.0 / m2;
         a.dt = at<float>(scratch, P.o_dt);
         a.dq = at<float>(scratch, P.o_dq);
         a.dzs = dzs;

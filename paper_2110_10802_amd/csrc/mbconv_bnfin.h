@@ -5,12 +5,28 @@
 
 namespace mbk {
 
+// Sum over the 64 lanes, by the same DPP moves as wave_sum (mbconv_dev.h) and for the same reason: a butterfly of
+// __shfl_xor is two trips through the LDS crossbar per step, some 0.3 us for the two sums of a finalise step, in a
+// chain that nothing else of the launch hides.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add_d(double v)
+{
+    const uint2 b = __builtin_bit_cast(uint2, v);
+    const uint2 t = make_uint2((uint32_t)__builtin_amdgcn_update_dpp(0, (int)b.x, CTRL, ROWS, 0xf, false),
+                               (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b.y, CTRL, ROWS, 0xf, false));
+    return v + __builtin_bit_cast(double, t);
+}
 __device__ __forceinline__ double wave_sum_d(double v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-        v += __shfl_xor(v, o, kWave);
-    return v;
+    v = dpp_add_d<0x128, 0xf>(v); // row_ror:8, 4, 2, 1
+    v = dpp_add_d<0x124, 0xf>(v);
+    v = dpp_add_d<0x122, 0xf>(v);
+    v = dpp_add_d<0x121, 0xf>(v);
+    v = dpp_add_d<0x142, 0xa>(v); // row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
+    v = dpp_add_d<0x143, 0xc>(v);
+    const uint2 b = __builtin_bit_cast(uint2, v);
+    return __builtin_bit_cast(double, make_uint2((uint32_t)__builtin_amdgcn_readlane((int)b.x, 63),
+                                                 (uint32_t)__builtin_amdgcn_readlane((int)b.y, 63)));
 }
 
 // A group of TPP consecutive threads (lane index `lt` within the group) that works on channel c
@@ -133,13 +149,14 @@ __device__ __forceinline__ void bn_fin_finish(const BnFin &f, int C, int c, int 
 }
 
 // dx = gamma*rstd*(dy - dbeta/m - xhat*dgamma/m) with xhat = (raw-mean)*rstd, rewritten as
-// c0*dy + c1*raw + c2 so the consumer's prologue is two fused multiply-adds.
-__device__ __forceinline__ void bn_bwd_coef_vals(int C, int c, double m, double dgamma, double dbeta,
+// c0*dy + c1*raw + c2 so the consumer's prologue is two fused multiply-adds.  (1/m from the host: an fp64 division is
+// a chain of a dozen instructions.)
+__device__ __forceinline__ void bn_bwd_coef_vals(int C, int c, double inv_m, double dgamma, double dbeta,
                                                  float gamma, double mean, double rstd, float *coef)
 {
     const double c0 = (double)gamma * rstd;
-    const double c1 = -c0 * rstd * dgamma / m;
-    const double c2 = -c0 * dbeta / m - c1 * mean;
+    const double c1 = -c0 * rstd * dgamma * inv_m;
+    const double c2 = -c0 * dbeta * inv_m - c1 * mean;
     coef[c] = (float)c0;
     coef[C + c] = (float)c1;
     coef[2 * C + c] = (float)c2;

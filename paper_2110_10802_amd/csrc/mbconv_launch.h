@@ -127,12 +127,12 @@ hipError_t launch_wgrad1x1_pair(bool bf16, int N, int MaA, int MbA, int HWA, con
 //   G[n,c,q] = sum_j w[j*Cw+c] * dp[n,j,q],   dW[j][c] = sum_{n,q} dp[n,j,q] * sc[n,c,q]
 // `fin` (optional): dp's BN-backward coefficients are not read from dp.c0/c1/c2 but derived in
 // the kernel from the per-plane partial sums, as launch_bn_bwd_finalize would (psb/psr: [Cn][NP],
-// m elements per channel); workgroup 0 also stores dgamma, dbeta and the coefficient triple.
+// inv_m: one over the elements per channel); workgroup 0 also stores dgamma, dbeta and the coefficient triple.
 struct BnBwdFin {
     const float *psb, *psr, *gamma, *bn;
     float *dgamma, *dbeta, *coef;
     int NP;
-    double m;
+    double inv_m;
 };
 bool projbwd_fused_plan(int N, int Cw, int Cn, int HW, int *splits);
 hipError_t launch_projbwd_fused(bool bf16, int N, int Cw, int Cn, int HW, const Operand &dp,
@@ -305,6 +305,7 @@ struct SeBwdArgs {
     const float *z, *g, *q, *w1, *w2;
     const float *dg, *A1, *A2, *s3, *s4;
     const float *gamma2, *bn2;
+    double inv_m; // 1/(N*HW)
     float *dt, *dq, *dzs;
     float *dw1, *db1, *dw2, *db2, *dgamma2, *dbeta2, *coef2;
 };
