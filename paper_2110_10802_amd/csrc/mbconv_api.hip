@@ -313,20 +313,27 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
     const auto wimg = [&](int i) -> const void * {
         return P.o_wimg[i] == kAbsent ? nullptr : at<char>(saved, P.o_wimg[i]);
     };
-    // Evaluation mode, fp32: the whole block in one launch where there is no gate to wait for
-    if (eval && !bf && P.expand && !P.se && eval_block_plan({P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p}, P.Cin, P.Cout)) {
+    const DwShape ds = {P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p};
+    // Evaluation mode, fp32: the whole block in one launch where there is no gate to wait for.  Its workgroups read rows of x
+    // (halo, residual) that others have written by then if `out` lies over x; the launches below read x for the last time
+    // element by element, where they write.
+    const char *xb = (const char *)x, *ob = (const char *)out;
+    const bool apart = xb + P.nX * sizeof(float) <= ob || ob + P.nP * sizeof(float) <= xb;
+    if (eval && !bf && P.expand && !P.se && apart && eval_block_plan(ds, P.Cin, P.Cout)) {
         DwEval ev = {};
         ev.bn1 = {P.Cexp, prm->bn1_gamma, prm->bn1_beta, run->bn1_mean, run->bn1_var, bn1};
         ev.bn2 = {P.Cexp, prm->bn2_gamma, prm->bn2_beta, run->bn2_mean, run->bn2_var, bn2};
         ev.bn3 = {P.Cout, prm->bn3_gamma, prm->bn3_beta, run->bn3_mean, run->bn3_var, bn3};
         ev.eps = eps;
-        MBK_STEP(MBCONV_STEP_DW_FWD,
-                 launch_eval_block({P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p}, P.Cin, P.Cout, x, prm->w_expand, prm->w_dw,
-                                   prm->w_proj, P.res ? x : nullptr, out, ev, st));
+        // the steps that this launch has in it are an empty event pair to a probe
+        MBK_STEP(MBCONV_STEP_BN1_FINALIZE, hipSuccess);
+        MBK_STEP(MBCONV_STEP_EXPAND_CONV, hipSuccess);
+        MBK_STEP(MBCONV_STEP_DW_FWD, launch_eval_block(ds, P.Cin, P.Cout, x, prm->w_expand, prm->w_dw, prm->w_proj,
+                                                       P.res ? x : nullptr, out, ev, st));
+        MBK_STEP(MBCONV_STEP_PROJ_CONV, hipSuccess);
         return MBCONV_OK;
     }
     // otherwise: expansion conv and depthwise conv in one launch, nothing of e in memory
-    const DwShape ds = {P.N, P.Cexp, P.H, P.W, P.Ho, P.Wo, P.k, P.s, P.p};
     int strips = 1;
     const bool xd = eval && !bf && P.expand && eval_expand_dw_plan(ds, P.Cin, &strips);
     // ... and, of small launches, the projection conv with everything behind it in another: with the SE stage too where the

@@ -4,7 +4,7 @@ import ctypes as C
 
 import pytest
 
-from mbconv_inputs import BlockShape
+from mbconv_inputs import BlockShape, make_block_inputs
 from route_util import BOOL, INT, plan, rule
 from test_eval_routes_gpu import check
 from test_routes import DwShape
@@ -116,3 +116,37 @@ def test_whole_block_matches_oracle(name, residual, activation):
     assert whole(C.byref(dw_shape(N, Cexp, H, W, k, 1)), Cin, Cout)
     check(BlockShape(N=N, Cin=Cin, H=H, W=W, Cexp=Cexp, Cse=1, Cout=Cout, k=k, stride=1, has_expand=True,
                      residual=residual, has_se=False, activation=activation), len(name))
+
+
+@pytest.mark.gpu
+def test_whole_block_probed_and_in_place():
+    """A probe on any step that the launch has in it is recorded; a call whose output lies over its input is not given to
+    this kernel, whose workgroups read each other's rows."""
+    import torch
+    from bench import HipEvents
+    from paper_2110_10802_amd import binding as B
+    from paper_2110_10802_amd.harness import DeviceBlock
+
+    N, Cin, Cexp, _, H, W, k = WHOLE["strips_56x56"]
+    s = BlockShape(N=N, Cin=Cin, H=H, W=W, Cexp=Cexp, Cse=1, Cout=Cin, k=k, stride=1, has_expand=True, residual=True,
+                   has_se=False, activation="relu6")
+    t = make_block_inputs(s, seed=3)
+    blk = DeviceBlock(s, t)
+    x = blk.to_device(t["x"])
+    want = blk.forward_eval(x).clone()
+    ev = HipEvents()
+    for step in ("bn1_finalize", "expand_conv", "dw_fwd", "proj_conv"):
+        a, b = ev.create(), ev.create()
+        B.mbconv_forward_eval_probed(blk.desc, blk.params, blk.running, x, blk.out, blk.eval_ws, 0,
+                                     B.Probe(B.STEPS[step], a, b))
+        torch.cuda.synchronize()
+        ms = ev.elapsed_ms(a, b)  # (an error if the events were not recorded)
+        assert ms > 0.01 or step != "dw_fwd"
+        ev.destroy(a)
+        ev.destroy(b)
+    for _ in range(2):
+        y = x.clone()
+        B.mbconv_forward_eval(blk.desc, blk.params, blk.running, y, y, blk.eval_ws, 0)
+        torch.cuda.synchronize()
+        # two fp32 evaluations of one block, each within 2e-6 of the result's scale
+        assert float((y - want).abs().max()) <= 1e-5 * float(want.abs().max())
