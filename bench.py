@@ -645,8 +645,14 @@ def run_block(args, config: int, steps: int, warmup: int, with_cpu: bool, distri
         survey[name] = sorted(reps)[1]
     ev.destroy(e0)
     ev.destroy(e1)
-    dominant = args.probe_step or max(
-        (n for n in survey if algorithmic_bytes(shape, n) is not None), key=lambda n: survey[n])
+    bytes_of = step_bytes(shape)
+    if evalm and shape.has_expand and "expand_conv" not in survey:
+        # the depthwise step's launch has the expansion conv (x is read in place of its output, which stays on the chip), or
+        # the whole block
+        elem = 2 if shape.dtype == "bf16" else 4
+        written = shape.Cexp if "proj_conv" in survey else shape.Cout
+        bytes_of["dw_fwd"] = elem * shape.N * (shape.Cin * shape.H * shape.W + written * shape.Ho * shape.Wo)
+    dominant = args.probe_step or max((n for n in survey if n in bytes_of), key=lambda n: survey[n])
     print(f"config {config} per-step ms (untimed survey): " +
           ", ".join(f"{n}={v * 1e3:.1f}us" for n, v in survey.items()), file=sys.stderr)
 
@@ -694,10 +700,10 @@ def run_block(args, config: int, steps: int, warmup: int, with_cpu: bool, distri
             dst.copy_(src)
         torch.cuda.synchronize()
 
-    nbytes = algorithmic_bytes(shape, dominant)
+    nbytes = bytes_of[dominant]
     achieved = nbytes / (kern_ms * 1e-3) / 1e9
     workload = f"config{config}"
-    total_bytes = sum(v for n, v in step_bytes(shape).items() if not evalm or n in survey)
+    total_bytes = sum(v for n, v in bytes_of.items() if not evalm or n in survey)
     net = lambda n: max(survey[n] - overhead_ms, 1e-6)
     result = {
         "metric": "mbconv_eval_fwd_images_per_sec" if evalm else "mbconv_fwd_bwd_images_per_sec",
@@ -727,7 +733,7 @@ def run_block(args, config: int, steps: int, warmup: int, with_cpu: bool, distri
         # kernels lie within 2 us of each other and the survey's order among them varies from run
         # to run, so the line shows all of them whichever one `roofline` names
         "roofline_next": [
-            _roofline_entry(n, algorithmic_bytes(shape, n), net(n))
+            _roofline_entry(n, bytes_of.get(n), net(n))
             for n in sorted((m for m in survey if m != dominant and algorithmic_bytes(shape, m) is not None),
                             key=lambda m: -survey[m])[:3]],
         "step_roofline": {"bound": "hbm", "algorithmic_bytes": total_bytes,
