@@ -160,8 +160,8 @@ mbconv_status mbconv_forward(const mbconv_desc *desc, const mbconv_params *param
  * The _probed variant brackets one step like mbconv_forward_probed; the coefficient blocks of
  * all three normalisations come from one launch attributed to MBCONV_STEP_BN1_FINALIZE
  * (MBCONV_STEP_BN2_FINALIZE when has_expand == 0), the other finalise steps do not occur.
- * A launch may have several steps in it: it is attributed to MBCONV_STEP_DW_FWD, and a probe on
- * one of the others times an empty event pair. */
+ * A launch may have several steps in it: it is attributed to one of them (MBCONV_STEP_DW_FWD or
+ * MBCONV_STEP_PROJ_CONV), and a probe on the others times an empty event pair. */
 mbconv_status mbconv_eval_workspace_size(const mbconv_desc *desc, size_t *workspace_bytes);
 mbconv_status mbconv_forward_eval(const mbconv_desc *desc, const mbconv_params *params,
                                   const mbconv_bn_state *running, const void *x, void *out,
