@@ -469,6 +469,7 @@ static bool xd_plan(const DwShape &s, int K, XdArgs &a, int *T, int *PX, size_t 
     int S = 1, NI = 1;
     while (S < s.Ho && xd_geometry(s, *T, S, 1, a) > 52 * 1024)
         ++S;
+    const int rows = S * std::min(a.rin, s.H); // (rows of e computed, those that strips share more than once)
     while (S < s.Ho && (long long)s.N * a.CG * S < 128 && (s.Ho + S - 1) / S * s.Wo > 128)
         ++S;
     S = (s.Ho + (s.Ho + S - 1) / S - 1) / ((s.Ho + S - 1) / S); // no empty strips
@@ -487,11 +488,24 @@ static bool xd_plan(const DwShape &s, int K, XdArgs &a, int *T, int *PX, size_t 
     // 22.3 and 32.4 / 40.8; 192 -> 1152 on 7x7, 2 and 4 images 27.6 / 22.0 and 29.0 / 35.7.  Up to 24 input channels it is the
     // faster one at any size (24 -> 144 on 56x56, 3x3, 32 and 128 images 69.8 / 68.4 and 248 / 205; 16 -> 96 on 112x112, 3x3,
     // stride 2, 64 images 195 / 143), but for 5x5 filters with stride 2 (24 -> 144 on 56x56, 16 and 32 images 36.9 / 32.6 and
-    // 51.1 / 52.5) or on odd widths (16 -> 64 on 127x127, 64 images 480 / 507), rows of an MFMA tile without a channel (8 -> 24
+    // 51.1 / 52.5), rows of an MFMA tile without a channel (8 -> 24
     // on 108x108, stride 2, 73 images 67.4 / 71.0) and small planes, which leave wavefronts without pixels (24 -> 144, 3x3 on
     // 14x14, 512 images 80.8 / 82.5, 5x5 on 7x7, 1024 images 73.0 / 82.2).
-    const bool large = 10 * s.C >= 8 * kXdRows * a.CG && (s.k == 3 || (s.s == 1 && s.W % 2 == 0)) && s.H * s.W >= 400;
-    if (wgs > (*T > 20 ? 256 : *T > 6 ? 512 : large ? 1 << 30 : 1024))
+    // 5x5 filters with stride 1 have the matrix unit wait for the filter's vector work: up to one workgroup to a compute unit
+    // (24 -> 144, 4 and 16 images of 56x56 28.0 / 21.5 and 51.9 / 55.6, 256 of 28x28 135 / 154).  24x24 is one row too tall for a
+    // strip (256 images, 3x3, 89.2 / 97.9).
+    const bool large = 10 * s.C >= 8 * kXdRows * a.CG && s.k == 3 && s.H * s.W >= 784;
+    if (wgs > (*T > 20 || (s.k == 5 && s.s == 1) ? 256 : *T > 6 ? 512 : large ? 1 << 30 : 1024))
+        return false;
+    // The strips of wide planes are a few rows, and what they compute twice loses first where every compute unit is busy
+    // anyway (16 -> 96 channels, one and eight images: 72x72, 3x3, 1.25 rows for each, 17.8 / 15.0 and 37.2 / 32.1; 96x96, 3x3, 1.4,
+    // 20.2 / 18.5 and 44.2 / 46.0; 128x128, 3x3, 1.7, 25.0 / 24.6 and 62.1 / 65.7; 112x112, 5x5, 3, 23.9 / 29.4 and 60.2 / 73.4;
+    // stride 2: 112x112, 3x3, 1.25, 19.6 / 15.2 and 38.1 / 37.0; 72x72, 5x5, 1.5, 17.9 / 12.0 and 36.9 / 23.9; 112x112, 5x5, 2.5,
+    // 20.7 / 23.3; 24 -> 144, 5x5, 64 images: 48x48, 1.5, 95.8 / 116.7).  Nor, with stride 1, does a last round of workgroups pay that is nearly
+    // empty (two to a compute unit; 24 -> 144, 3x3, 16 images: 48x48, 576, 40.2 / 41.2; 64x64, 1152, 52.5 / 53.4;
+    // 64 images of 20x20, 576, 33.9 / 35.5).
+    const int most = wgs <= 256 || s.s == 2 ? 175 : 130; // per cent
+    if (100 * rows > most * s.H || (s.s == 1 && wgs > 512 && 5 * wgs < 4 * 512 * ((wgs + 511) / 512)))
         return false;
     a.rt = s.s == 1 && a.R * ((s.Wo + 3) / 4) >= 3 * 32 ? 2 : 1;
     a.items = (s.N + NI - 1) / NI * S;
@@ -1216,8 +1230,9 @@ bool eval_proj_plan(int N, int M, int K, int HW, int Cse, bool act)
     // cost more than the launches (the SE stage and the projection conv / this kernel: 672 -> 112 on 14x14, 4 and 8 images 13.0 /
     // 10.4 and 15.5 / 19.7 us; 480 -> 80, 4 and 8 images 11.8 / 11.5, 12.7 / 15.2; 144 -> 24 on 56x56, 4 images 11.8 / 8.5).
     // With the activation still to apply, which each of them repeats, somewhat less (306 -> 34 on 16x16, 15 images, 3600
-    // wavefronts, evaluation 23.9 / 24.7).
-    return xp_groups(N, M, HW, PX) * KS <= (act ? 3200 : 4096);
+    // wavefronts, evaluation 23.9 / 24.7; 96 -> 24 on 128x128, one image,
+    // 3072, 26.2 / 26.9).
+    return xp_groups(N, M, HW, PX) * KS <= (act ? 2600 : 4096);
 }
 
 hipError_t launch_eval_proj(int N, int M, int K, int HW, int Cse, const void *w, const void *d, const float *bn2,

@@ -16,12 +16,13 @@ CASES = {
     "strips_28x28": ((1, 40, 240, 10, 40, 28, 28, 5, 1), 7, True),
     "strips_odd_width_stride_2": ((2, 16, 36, 4, 20, 61, 59, 3, 2), 8, True),
     "strips_112x112_stride_2": ((1, 16, 96, 4, 24, 112, 112, 3, 2), 28, True),
-    "128x126_5x5": ((1, 8, 20, 4, 12, 128, 126, 5, 1), 128, True),
+    "widest_128x128": ((1, 8, 20, 4, 12, 128, 128, 3, 1), 64, True),
+    "128x126_5x5": ((1, 8, 20, 4, 12, 128, 126, 5, 1), None, True),
     "masked_channels": ((3, 23, 50, 5, 17, 15, 14, 3, 1), 2, True),
     "last_strip_shorter": ((2, 9, 17, 4, 9, 31, 30, 5, 2), 2, True),
     "images_side_by_side_7x7": ((200, 24, 144, 6, 24, 7, 7, 3, 1), 1, False),
-    "images_side_by_side_4x3": ((600, 16, 96, 4, 16, 4, 3, 5, 1), 1, True),
-    "several_items_to_a_workgroup": ((4200, 8, 16, 4, 8, 20, 20, 3, 1), 1, False),
+    "images_side_by_side_4x3": ((600, 16, 96, 4, 16, 4, 3, 3, 1), 1, True),
+    "several_items_to_a_workgroup": ((2100, 8, 16, 4, 8, 28, 28, 3, 1), 2, False),
     "64_squeezed": ((1, 64, 256, 64, 72, 9, 9, 3, 1), 1, True),
     "65_squeezed": ((1, 64, 256, 65, 72, 9, 9, 3, 1), 1, False),
     "3_squeezed": ((1, 16, 64, 3, 24, 9, 9, 3, 1), 1, False),
@@ -61,6 +62,8 @@ def test_route(name):
     (1, 81, 486, 14, 14, 3, 1, False), (1, 200, 1200, 7, 7, 3, 1, False),        # odd, and longer than any
     (128, 24, 144, 56, 56, 3, 1, True), (64, 24, 144, 56, 56, 5, 2, False),      # up to 24 channels: any size, but
     (64, 16, 64, 127, 127, 5, 1, False), (73, 8, 24, 108, 108, 3, 2, False), (1024, 24, 144, 7, 7, 5, 1, False),
+    (8, 16, 96, 72, 72, 3, 1, True), (8, 16, 96, 96, 96, 3, 1, False), (1, 16, 96, 96, 96, 3, 1, True),          # rows computed twice
+    (1, 16, 96, 112, 112, 5, 1, False), (8, 16, 96, 72, 72, 5, 2, True), (1, 16, 96, 128, 128, 5, 2, False),
     (1, 8, 24, 110, 82, 3, 2, False),                                            # planes that the depthwise kernels refuse
 ])
 def test_rule(N, Cin, Cexp, H, W, k, s, taken):
