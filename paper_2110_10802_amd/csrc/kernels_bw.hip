@@ -13,8 +13,10 @@
 //     byte permutation per pair of values; with a prologue it is the conversion to bf16 that pairs them) and has the B
 //     operands of v_mfma_f32_16x16x32_bf16, pixel 4r + j feeding instruction j: no LDS store and no barrier in the loop;
 //   - a step's values of the next chunk, or of the step after the next, are requested as soon as its registers are free,
-//     and results leave the same way, eight bytes per lane.
-// The same two, here: 18.3 and 26.3 us.  What bounds it is a wavefront's chain at the two or three workgroups of a
+//     and results leave the same way, eight bytes per lane;
+//   - BN1's statistics leave as one fp32 partial for every chunk, 64 pixels, with the additions of conv_bf in its order (kept in
+//     fp32 over a wavefront's chunks they take 18.8 us instead of 19.5, and lose bits with every chunk).
+// The same two, here: 19.5 and 26.1 us.  What bounds it is a wavefront's chain at the two or three workgroups of a
 // compute unit that the registers allow (16 tiles of sums): 2.9 us until the weights lie in LDS, then 2.5 to 3.5 a chunk.
 #include "mbconv_x3.h"
 
@@ -35,13 +37,38 @@ struct BwArgs {
     const bf16_t *p0, *p1;
     const float *c0, *c1, *c2;
     bf16_t *out;
-    float *psum, *psq; // EPI_STATS: [M][NT]
-    int NT;            // chunk sets (= statistics partials per row)
+    float *psum, *psq; // EPI_STATS: [M][numChunks]
+    int NT;            // chunk sets
     int slabs, perDie;
 };
 
 __device__ __forceinline__ uint32_t bw_lo(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
 __device__ __forceinline__ uint32_t bw_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+template <int CTRL>
+__device__ __forceinline__ float bw_add_dpp(float v)
+{
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+// (by value: a choice between two elements of an array is a choice of addresses to the compiler, and the array in memory)
+__device__ __forceinline__ float bw_pick(bool second, float a, float b) { return second ? b : a; }
+
+// Sums over the 16 lanes of a row of eight values per lane, two of them to each quad: lane r ends with the total of value
+// r % 8.  The additions are those of row16_sum, in its order (so the same bits), but of half as many values after each step
+// but the first.
+__device__ __forceinline__ float bw_sum8(float (&v)[8], int r)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        v[i] = bw_add_dpp<0x124>(bw_add_dpp<0x128>(v[i])); // row_ror:8, row_ror:4
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        v[i] = bw_add_dpp<0x4e>(bw_pick(r & 4, v[i], v[i + 4])); // quad_perm: the lane two further on
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        v[i] = bw_add_dpp<0xb1>(bw_pick(r & 2, v[i], v[i + 2])); // quad_perm: the neighbour
+    return bw_pick(r & 1, v[0], v[1]);
+}
 
 // Workgroups of a compute unit that the registers allow
 constexpr int bw_waves(int pro, int ks) { return pro == PRO_BNBWD && ks <= 4 ? 3 : 2; }
@@ -82,7 +109,6 @@ __global__ __launch_bounds__(256, bw_waves(PRO, KS)) void conv_bw_kernel(BwArgs 
             wreg[s] = *reinterpret_cast<const u32x4 *>(wr + min(32 * s + 8 * sg, K - 8)); // (K % 8 == 0)
     }
     f32x4 *Cl = reinterpret_cast<f32x4 *>(lds16 + KS * 2048); // [32*KS] {c0, c1, c2, -} (PRO_BNBWD), zero past K
-    float *Rd = reinterpret_cast<float *>(lds16 + KS * 2048); // [4][128] (EPI_STATS, at the end)
     f32x4 cv = {0.f, 0.f, 0.f, 0.f};
     if (PRO == PRO_BNBWD) {
         const int kk = min(tid, K - 1);
@@ -135,12 +161,11 @@ __global__ __launch_bounds__(256, bw_waves(PRO, KS)) void conv_bw_kernel(BwArgs 
     }
     __syncthreads(); // the slab, Cl
 
-    float s1[4][4], s2[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            s1[i][v] = s2[i][v] = 0.f;
+    // (the lane's row of the statistics: row tile r / 4, row 4g + r % 4 of it)
+    const int srow = 64 * slab + 16 * (r >> 2) + 4 * g + (r & 3), snum = EPI == EPI_STATS ? (int)(4u * (uint32_t)a.numChunks * (uint32_t)M) : 0;
+    const auto rsum = __builtin_amdgcn_make_buffer_rsrc(a.psum, 0, snum, 0x00020000);
+    const auto rsq = __builtin_amdgcn_make_buffer_rsrc(a.psq, 0, snum, 0x00020000);
+    const uint32_t sv = srow < M ? 4u * (uint32_t)srow * (uint32_t)a.numChunks : kBwNowhere;
     for (; ch < a.numChunks; ch += cStep) {
         uint32_t nbo, noo, nokm;
         locate(ch + cStep < a.numChunks ? ch + cStep : ch, nbo, noo, nokm);
@@ -202,6 +227,7 @@ __global__ __launch_bounds__(256, bw_waves(PRO, KS)) void conv_bw_kernel(BwArgs 
         }
         // rows 64 slab + 16i + 4g + v, the lane's four pixels.  Buffer stores, which drop what lies past the tensor's
         // end: behind a branch around a store the next loads' wait would be one for every store before them.
+        float s1[2], s2[2], p1[8], p2[8];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint32_t ov = okm && 64 * slab + 16 * i + 4 * g < M ? 2u * (oo + mrow) : kBwNowhere; // (M % 8 == 0)
@@ -210,45 +236,30 @@ __global__ __launch_bounds__(256, bw_waves(PRO, KS)) void conv_bw_kernel(BwArgs 
                 const u32x2 o = {bf16_pack2(acc[i][0][v], acc[i][1][v]), bf16_pack2(acc[i][2][v], acc[i][3][v])};
                 __builtin_amdgcn_raw_buffer_store_b64(o, rsrc, (int)ov, (int)(2u * (uint32_t)(16 * i + v) * (uint32_t)HW), 0);
                 if (EPI == EPI_STATS) { // of the values as stored
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const uint32_t x = o[h] & okm;
-                        const float x0 = __uint_as_float(x << 16), x1 = __uint_as_float(x & 0xffff0000u);
-                        s1[i][v] += x0 + x1;
-                        s2[i][v] = fmaf(x0, x0, fmaf(x1, x1, s2[i][v]));
-                    }
+                    const uint32_t xl = o[0] & okm, xh = o[1] & okm;
+                    const float x0 = __uint_as_float(xl << 16), x1 = __uint_as_float(xl & 0xffff0000u);
+                    const float x2 = __uint_as_float(xh << 16), x3 = __uint_as_float(xh & 0xffff0000u);
+                    p1[4 * (i & 1) + v] = ((x0 + x1) + x2) + x3;
+                    p2[4 * (i & 1) + v] = fmaf(x3, x3, fmaf(x2, x2, fmaf(x1, x1, x0 * x0)));
                 }
             }
+            if (EPI == EPI_STATS && i & 1) {
+                s1[i >> 1] = bw_sum8(p1, r);
+                s2[i >> 1] = bw_sum8(p2, r);
+            }
+        }
+        if (EPI == EPI_STATS) { // a partial sum for every 64 pixels, as the tiles leave them: the rest is added in fp64
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, bw_pick(r & 8, s1[0], s1[1])), rsum, (int)sv, 4 * ch, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, bw_pick(r & 8, s2[0], s2[1])), rsq, (int)sv, 4 * ch, 0);
         }
         bo = nbo;
         oo = noo;
         okm = nokm;
     }
-    if (EPI == EPI_STATS) {
-        // lanes of a row hold the same 16 channels: add them, then the wavefronts in order
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float t1 = row16_sum(s1[i][v]), t2 = row16_sum(s2[i][v]);
-                if (r == 0) {
-                    Rd[wv * 128 + 16 * i + 4 * g + v] = t1;
-                    Rd[wv * 128 + 64 + 16 * i + 4 * g + v] = t2;
-                }
-            }
-        __syncthreads();
-        if (tid < 128) {
-            const int mm = 64 * slab + (tid & 63);
-            const float t = (Rd[tid] + Rd[128 + tid]) + (Rd[256 + tid] + Rd[384 + tid]);
-            if (mm < M)
-                (tid < 64 ? a.psum : a.psq)[(size_t)mm * a.NT + cs] = t;
-        }
-    }
 }
 
-// `nt`: chunk sets = statistics partials per row.
-bool bw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt)
+// `sets`: chunk sets, each a workgroup's for every slab of rows.
+bool bw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *sets)
 {
     const long long Q = (long long)N * HW;
     // the shapes that kernels_bf.hip multiplies with bf16 operands, in the roles of a short contraction
@@ -267,7 +278,7 @@ bool bw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt)
         return false;
     // one round of workgroups, with as many chunks to a wavefront as that takes (544 workgroups on 512 places: 22.3 us above)
     const long long wgs = 256 * bw_waves(pro, (K + 31) / 32), rounds = (groups * slabs + wgs - 1) / wgs;
-    *nt = (int)((groups + rounds - 1) / rounds);
+    *sets = (int)((groups + rounds - 1) / rounds);
     return true;
 }
 
@@ -300,7 +311,7 @@ hipError_t launch_bw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm
     a.perDie = (nt >> 3) * a.slabs + ((nt & 7) * a.slabs + 7) / 8;
     const int ks = (K + 31) / 32;
     const dim3 grid((unsigned)(8 * a.perDie));
-    const size_t lds = (size_t)ks * 4096 + std::max((size_t)ks * 512, (size_t)2048);
+    const size_t lds = (size_t)ks * (B.pro == PRO_BNBWD ? 4608 : 4096);
 #define MBK_CASE(KS_, RD_, PRO_, EPI_)                                                            \
     if (ks == KS_ && B.pro == PRO_) {                                                             \
         hipLaunchKernelGGL((conv_bw_kernel<KS_, RD_, PRO_, EPI_>), grid, dim3(256), lds, st, a);  \

@@ -225,7 +225,7 @@ hipError_t launch_bf_conv1x1(int N, int M, int K, int HW, const void *w, int sAm
                              float *psq, float *splitk_ws, hipStream_t st);
 
 // kernels_bw.hip
-bool bw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *nt);
+bool bw_conv_plan(int N, int M, int K, int HW, int pro, int epi, int *sets);
 hipError_t launch_bw_conv1x1(int N, int M, int K, int HW, const void *w, int sAm, int sAk, const void *wimg, const Operand &B,
                              void *out, int epi, float *psum, float *psq, hipStream_t st);
 
@@ -271,10 +271,12 @@ static bool xk_applies(bool bf16, int N, int M, int K, int HW, bool stores_opera
 }
 
 // bf16, short contraction, many rows: weights resident in LDS (conv_bw)
-static bool bw_applies(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi, int *nt)
+// (a statistics partial for every 64 pixels, as from conv_bf, which takes the same shapes)
+static bool bw_applies(bool bf16, int N, int M, int K, int HW, bool stores_operand, int pro, int epi)
 {
+    int n;
     return bf16 && !stores_operand && !wave_conv_kind(M, K, HW) &&
-           !xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, nt) && bw_conv_plan(N, M, K, HW, pro, epi, nt);
+           !xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &n) && bw_conv_plan(N, M, K, HW, pro, epi, &n);
 }
 
 // convolutions of the wide blocks that run on the bf16 matrix cores from a weight image
@@ -283,7 +285,7 @@ bool conv1x1_uses_weight_image(bool bf16, int N, int M, int K, int HW, bool stor
 {
     int nt;
     return xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt) ||
-           (pro == PRO_BNBWD && bw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &nt));
+           (pro == PRO_BNBWD && bw_applies(bf16, N, M, K, HW, stores_operand, pro, epi));
 }
 
 // which matrix-core instruction family serves a launch (values of mbconv_engine in mbconv.h)
@@ -313,8 +315,7 @@ int conv1x1_num_partials(bool bf16, int N, int M, int K, int HW, bool stores_ope
     if (kind)
         return wave_conv_num_partials(kind, N, M, HW);
     if (xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
-        xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
-        bw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
+        xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
         return qtiles;
     if (bf16 && !stores_operand && bf_conv_plan(N, M, K, HW, &qtiles, &splits))
         return qtiles;
@@ -329,7 +330,7 @@ size_t conv1x1_splitk_floats(bool bf16, int N, int M, int K, int HW, bool stores
     if (stores_operand || wave_conv_kind(M, K, HW) || xs_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
         xw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
         xk_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles) ||
-        bw_applies(bf16, N, M, K, HW, stores_operand, pro, epi, &qtiles))
+        bw_applies(bf16, N, M, K, HW, stores_operand, pro, epi))
         return 0;
     if (bf16 && bf_conv_plan(N, M, K, HW, &qtiles, &splits))
         return bf_conv_splitk_floats(N, M, K, HW);
@@ -354,11 +355,8 @@ hipError_t launch_conv1x1(bool bf16, int N, int M, int K, int HW, const void *w,
             return launch_xk_conv1x1(bf16, N, M, K, HW, w, sAm, sAk, wimg, B, out, epi, res, psum, psq, st);
         }
     }
-    {
-        int nt;
-        if (bw_applies(bf16, N, M, K, HW, sc_store != nullptr, B.pro, epi, &nt))
-            return launch_bw_conv1x1(N, M, K, HW, w, sAm, sAk, wimg, B, out, epi, psum, psq, st);
-    }
+    if (bw_applies(bf16, N, M, K, HW, sc_store != nullptr, B.pro, epi))
+        return launch_bw_conv1x1(N, M, K, HW, w, sAm, sAk, wimg, B, out, epi, psum, psq, st);
     const int kind = sc_store ? 0 : wave_conv_kind(M, K, HW);
     if (kind)
         return launch_wave_conv1x1(bf16, kind, N, M, K, HW, w, sAm, sAk, B, out, epi, res, psum,

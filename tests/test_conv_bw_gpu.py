@@ -1,10 +1,12 @@
 """bf16 storage, short contractions with the weights resident in LDS: one to six steps of the contraction, a last step that
 is not full, a last slab of rows and a last chunk of pixels that are not, one chunk and several to a wavefront, against the
 oracle at the tolerances of parity_util; and on which side of its lines a shape is."""
+import numpy as np
 import pytest
 
 from mbconv_inputs import BlockShape, make_block_inputs
 from oracle import oracle as orc
+from paper_2110_10802_amd import binding as B
 from parity_util import compare_block, run_gpu_block
 from route_util import INT, plan
 
@@ -45,3 +47,35 @@ def test_matches_oracle(N, Cin, Cexp, Cout, H, W, stride):
     res, blk = run_gpu_block(s, t)
     f, b = orc.mbconv_step(s, t)
     compare_block(s, t, res, f, b, blk)
+
+
+@pytest.mark.gpu
+def test_statistics_of_many_chunks_are_exact():
+    """The statistics are fp32 sums over 64 pixels, combined in fp64, however many chunks a wavefront has.  Values in [1, 2)
+    of bf16 and their squares are multiples of 2^-7 and 2^-14, so such a sum is exact (64 < 2^7 of them below 2^2 take
+    7 + 2 + 14 = 23 bits) and what is left is fp64's rounding, 2^-53 a step, over a variance of a thousandth of the squares'
+    mean, and the results' own rounding to fp32.  (Eight chunks of a wavefront in one fp32 sum: 1.7e-6.)"""
+    import torch
+    from paper_2110_10802_amd.harness import DeviceBlock
+
+    s = BlockShape(N=1024, Cin=48, H=32, W=32, Cexp=64, Cse=4, Cout=16, k=3, stride=2, has_expand=True, residual=False,
+                   dtype="bf16")
+    assert (s.N * s.H * s.W // 64) / (4 * sets(s.N, s.Cexp, s.Cin, s.H * s.W, NONE)) >= 8  # chunks to a wavefront
+    t = make_block_inputs(BlockShape(**{**s.__dict__, "N": 1}), seed=5)
+    t["w_expand"] = t["w_expand"] * 0 + 0.0078125 * np.sign(t["w_expand"])
+    t["w_expand"][:, 0] = 1.5
+    blk = DeviceBlock(s, t)
+    gen = torch.Generator(device=blk.device).manual_seed(6)
+    x = torch.randn((s.N, s.Cin, s.H, s.W), generator=gen, device=blk.device)
+    x[:, 0] = 1.0
+    blk.forward(x.to(torch.bfloat16))
+    torch.cuda.synchronize()
+    at = B.mbconv_saved_offsets(blk.desc)
+    e = blk.saved[at["e"]:][:2 * s.N * s.Cexp * s.H * s.W].view(torch.bfloat16).view(s.N, s.Cexp, -1)
+    assert float(e.min()) >= 1 and float(e.max()) < 2
+    got = blk.saved[at["bn1"]:][:16 * s.Cexp].view(torch.float32).view(4, s.Cexp).double()
+    mean = torch.stack([e[:, c].double().mean() for c in range(s.Cexp)])
+    var = torch.stack([e[:, c].double().var(unbiased=False) for c in range(s.Cexp)])
+    rstd = 1 / torch.sqrt(var + blk.desc.bn_eps)
+    assert float((got[2] / mean - 1).abs().max()) < 2 ** -23
+    assert float((got[3] / rstd - 1).abs().max()) < 2 ** -23
