@@ -13,7 +13,7 @@ namespace mbk {
 // PREP: the workgroups past the channels' write the weight images of convolutions later in the
 // sequence (a launch of their own cost 4 to 5 us; this one's few workgroups leave the chip empty).
 template <bool PREP>
-__global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double inv_m, double unbias,
+__global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double m,
                                                           const float *__restrict__ psum,
                                                           const float *__restrict__ psq,
                                                           const float *__restrict__ gamma,
@@ -77,15 +77,13 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double 
     s = wave_sum_d(s);
     s2 = wave_sum_d(s2);
     if (lane == 0) {
-        // (no divisions and no square root, as in bn_fin_finish: they are chains of a dozen fp64 instructions each)
-        const double mean = s * inv_m;
-        double var = s2 * inv_m - mean * mean;
+        // Divisions and a square root, although they are chains of a dozen fp64 instructions each: with a rounded 1/m a constant
+        // channel's variance is not zero but its square times 2^-53, which a small eps does not cover.
+        const double mean = s / m;
+        double var = s2 / m - mean * mean;
         if (var < 0.0)
             var = 0.0;
-        const double xv = var + (double)eps;
-        double rstd = __builtin_amdgcn_rsq(xv);
-        if (xv > 0.0 && xv < __builtin_inf())
-            rstd = rstd * (1.5 - 0.5 * xv * rstd * rstd);
+        const double rstd = 1.0 / sqrt(var + (double)eps);
         const double scale = (double)gm * rstd;
         bn[c] = (float)scale;
         bn[C + c] = (float)((double)bt - mean * scale);
@@ -94,7 +92,7 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(int C, int NP, double 
         if (run_mean)
             run_mean[c] = (float)((1.0 - (double)momentum) * (double)rm + (double)momentum * mean);
         if (run_var) {
-            const double unbiased = var * unbias;
+            const double unbiased = m > 1.0 ? var * m / (m - 1.0) : var;
             run_var[c] = (float)((1.0 - (double)momentum) * (double)rv + (double)momentum * unbiased);
         }
     }
@@ -106,12 +104,11 @@ hipError_t launch_bn_finalize(int C, int NP, double m, const float *psum, const 
                               float *ones, size_t ones_count, const X3PrepArgs *prep)
 {
     const unsigned own = (unsigned)((C + 3) / 4);
-    const double inv_m = 1.0 / m, unbias = m > 1.0 ? m / (m - 1.0) : 1.0;
     if (prep && prep->tiles)
-        hipLaunchKernelGGL(bn_finalize_kernel<true>, dim3(own + prep->tiles), dim3(256), 0, st, C, NP, inv_m, unbias, psum, psq,
+        hipLaunchKernelGGL(bn_finalize_kernel<true>, dim3(own + prep->tiles), dim3(256), 0, st, C, NP, m, psum, psq,
                            gamma, beta, eps, momentum, run_mean, run_var, bn, ones, ones ? ones_count : 0, *prep);
     else
-        hipLaunchKernelGGL(bn_finalize_kernel<false>, dim3(own), dim3(256), 0, st, C, NP, inv_m, unbias, psum, psq, gamma, beta,
+        hipLaunchKernelGGL(bn_finalize_kernel<false>, dim3(own), dim3(256), 0, st, C, NP, m, psum, psq, gamma, beta,
                            eps, momentum, run_mean, run_var, bn, ones, ones ? ones_count : 0, X3PrepArgs());
     return hipGetLastError();
 }

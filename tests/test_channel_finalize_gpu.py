@@ -91,3 +91,22 @@ def test_bn2_step_is_a_launch_for_large_batches(shape):
     s = _s(**{**dict(Cin=32, Cexp=1024, Cse=4, Cout=16, residual=False), **shape})
     assert _occurs(s, "bn2_finalize")
     assert not _occurs(s.with_batch(s.N - 1), "bn2_finalize")
+
+
+def test_constant_channel_has_no_variance():
+    """The finalise launch of BN1 (the storing policy's) over 49 equal values: their mean and no variance, so that rstd is
+    1 / sqrt(eps); 1/49 is not a number of 53 bits, and 49 times its nearest one is not 1."""
+    import torch
+    from paper_2110_10802_amd import binding as B
+    from paper_2110_10802_amd.harness import DeviceBlock
+
+    s = _s(N=1, Cin=16, H=7, W=7, Cexp=96, Cse=4, Cout=16, residual=False, eps=1e-12)
+    t = make_block_inputs(s, seed=30)
+    t["w_expand"] = t["w_expand"] * 0 + 64
+    blk = DeviceBlock(s, t, B.MBCONV_STORE)
+    x = torch.ones((s.N, s.Cin, s.H, s.W), device=blk.device)
+    blk.forward(x)
+    torch.cuda.synchronize()
+    mean, rstd = blk.saved_tensor("bn1")[2:]
+    assert (mean == 1024).all()
+    assert abs(rstd * 1e-6 - 1).max() < 1e-6  # (fp32 holds eps to 6e-8)
