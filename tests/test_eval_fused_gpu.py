@@ -153,3 +153,34 @@ def test_whole_block_probed_and_in_place():
         torch.cuda.synchronize()
         # two fp32 evaluations of one block, each within 2e-6 of the result's scale
         assert float((y - want).abs().max()) <= 1e-5 * float(want.abs().max())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Cin", [24, 28, 36, 40])
+def test_whole_block_is_as_exact_as_separate_launches(Cin):
+    """Error against 64 bits (2-norm) of one launch and of the separate ones, which a call takes whose output lies over
+    its input: a chain of MFMAs that is as long as the contraction rounds its whole sum at every step."""
+    import numpy as np
+    import torch
+    from oracle import oracle as orc
+    from paper_2110_10802_amd import binding as B
+    from paper_2110_10802_amd.harness import DeviceBlock
+
+    s = BlockShape(N=128, Cin=Cin, H=28, W=28, Cexp=3 * Cin, Cse=1, Cout=Cin, k=3, stride=1, has_expand=True, residual=True,
+                   has_se=False)
+    whole = rule("_ZN3mbk15eval_block_planERKNS_7DwShapeEii", BOOL, C.POINTER(DwShape), INT, INT)
+    assert whole(C.byref(dw_shape(s.N, s.Cexp, s.H, s.W, s.k, 1)), Cin, Cin)
+    t = make_block_inputs(s, seed=Cin)
+    rng = np.random.default_rng(Cin)
+    for i, c in ((1, s.Cexp), (2, s.Cexp), (3, s.Cout)):
+        t[f"bn{i}_mean"] = (0.3 * rng.standard_normal(c)).astype(np.float32)
+        t[f"bn{i}_var"] = rng.uniform(0.5, 2.0, c).astype(np.float32)
+    blk = DeviceBlock(s, t)
+    x = blk.to_device(t["x"])
+    one = blk.forward_eval(x).clone()
+    B.mbconv_forward_eval(blk.desc, blk.params, blk.running, x, x, blk.eval_ws, 0)
+    torch.cuda.synchronize()
+    ref = torch.from_numpy(np.asarray(orc.mbconv_forward_eval(s, t))).to(blk.device)
+    error = [float((y.double() - ref).norm() / ref.norm()) for y in (one, x)]
+    print(f"[eval] {Cin} channels: one launch {error[0]:.3e}, separate {error[1]:.3e}", flush=True)
+    assert error[0] <= error[1]
