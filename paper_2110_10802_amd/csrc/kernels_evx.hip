@@ -936,11 +936,23 @@ bool eval_block_plan(const DwShape &s, int K, int M)
     size_t lds;
     if (!xf_plan(s, K, M, f, &T, &PX, &MT, &lds))
         return false;
-    // Most compute units have a workgroup, and the strip's input is at most one and a half times its output (one forward
-    // pass, ReLU6, two launches / one, us: 24 -> 144 -> 24 on 56x56, 3x3, 16 images 42 / 38, 32 54.7 / 39.4, 128 205 / 153; 32 ->
-    // 192 -> 32 on 28x28, 3x3, 96 images 69 / 55; 40 -> 240 -> 40 on 14x14, 5x5, 512 images 125 / 104; 24 -> 144 -> 24 on 7x7,
-    // 5x5, 2000 images 91 / 58; twice, 5x5 on 57x57, 124 / 128; stride 2, 16 -> 96 on 112x112, 64 images 113 / 266).
-    return f.x.items >= 160 && s.s == 1 && 2 * std::min(f.x.rin, s.H) <= 3 * f.x.R;
+    // A workgroup takes as long for a strip of a few pixels as for 512, so a round of 256 takes 4 to 6 us for sixteen
+    // channels however much of it is output; the other launches take time by the pixel, and some for being two or three. So:
+    // the share of the rounds' places that have an output pixel, with what those launches cost counted as pixels. Where it
+    // lies is a fit to 844 blocks measured on more than one route; of the 486 it takes thirteen are 2 to 6 % slower than in
+    // separate launches (one forward pass, ReLU6, best other route / one launch, us). 24 -> 144 -> 24 on 56x56, 3x3, 8
+    // workgroups to an image: 10 images 31.5 / 37.7, 13 39.3 / 37.8, 32 56.5 / 38.9, 33 (a second round) 58.5 / 74.2, 48
+    // 76.7 / 74.7, 64 94.5 / 76.4. 32 -> 192 -> 32 on 28x28, 3x3: 56 images 51.6 / 54.2, 72 57.6 / 54.3, 128 84.6 / 55.8,
+    // 160 96.3 / 107, 192 115 / 107. 40 -> 240 -> 40, 5x5: on 14x14, 320 images 86.6 / 100.5, 400 105 / 102; 26x28, 270
+    // images 247 / 288. Rows of the output past a multiple of sixteen count, too: 24 -> 96 -> 39 on 40x40, 5x5, 126 images
+    // 91 / 116, 32 -> 96 -> 37 on 80x80, 35 images 94 / 107. The other launches are slower on rows that are not whole fours:
+    // 32 -> 128 -> 34 on 81x83, 71 images 386 / 315, 28 -> 84 -> 28 on 45x42, 5x5, 315 images 447 / 305. An expanded tensor
+    // of more than the 256 MB of the last cache costs them, too: 40 -> 160 -> 40 on 68x68, 88 images 364 / 289. Few
+    // workgroups leave the chip empty.
+    const long long rounds = (f.x.items + 255) / 256, pixels = (long long)s.N * s.Ho * s.Wo + 4000000 / s.C;
+    const bool large = (long long)s.N * s.C * s.H * s.W > 60000000;
+    const int share = (s.k == 3 ? 55 : 65) + (T > 6 ? 5 : 0) + (M > 32 ? 10 : 0) - (s.W % 4 ? 10 : 0) - (large ? 10 : 0); // per cent
+    return s.s == 1 && f.x.items >= 100 && 100 * pixels >= share * rounds * 256 * 512;
 }
 
 hipError_t launch_eval_block(const DwShape &s, int K, int M, const void *x, const void *w_expand, const void *w_dw,

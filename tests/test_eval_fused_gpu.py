@@ -98,10 +98,15 @@ WHOLE = {
 
 
 @pytest.mark.parametrize("N,Cin,Cexp,Cout,H,W,k,s,taken", [
-    (20, 24, 144, 24, 56, 56, 3, 1, True), (19, 24, 144, 24, 56, 56, 3, 1, False),   # 160 workgroups of strips
-    (319, 40, 240, 40, 14, 14, 5, 1, True), (318, 40, 240, 40, 14, 14, 5, 1, False),
-    (64, 41, 246, 40, 28, 28, 3, 1, False), (96, 40, 240, 65, 28, 28, 3, 1, False),
-    (96, 32, 192, 32, 28, 28, 3, 2, False), (40, 24, 144, 30, 57, 57, 5, 1, False),
+    (15, 24, 144, 24, 56, 56, 3, 1, True), (14, 24, 144, 24, 56, 56, 3, 1, False),   # most of a round's places taken,
+    (33, 24, 144, 24, 56, 56, 3, 1, False), (38, 24, 144, 24, 56, 56, 3, 1, True),   # of a second one, too
+    (363, 40, 240, 40, 16, 16, 3, 1, True), (128, 40, 240, 40, 16, 16, 3, 1, False), (71, 32, 128, 34, 81, 83, 3, 1, True),
+    (132, 32, 192, 23, 24, 24, 3, 1, False), (23, 32, 192, 38, 65, 65, 3, 1, False),  # slower by a third and more
+    (126, 24, 96, 39, 40, 40, 5, 1, False), (270, 40, 240, 40, 26, 28, 5, 1, False), (35, 32, 96, 37, 80, 80, 3, 1, False),
+    (88, 40, 160, 40, 68, 68, 3, 1, True),                                           # an expanded tensor of 260 MB
+    (99, 8, 48, 8, 16, 16, 3, 1, False), (100, 8, 48, 8, 20, 20, 3, 1, True),        # a hundred workgroups
+    (64, 41, 246, 40, 28, 28, 3, 1, False), (128, 40, 240, 65, 28, 28, 3, 1, False),
+    (128, 32, 192, 32, 28, 28, 3, 2, False), (40, 24, 144, 30, 57, 57, 5, 1, False),
 ])
 def test_rule_of_the_whole_block(N, Cin, Cexp, Cout, H, W, k, s, taken):
     whole = rule("_ZN3mbk15eval_block_planERKNS_7DwShapeEii", BOOL, C.POINTER(DwShape), INT, INT)
