@@ -507,6 +507,23 @@ static bool xd_plan(const DwShape &s, int K, XdArgs &a, int *T, int *PX, size_t 
     const int most = wgs <= 256 || s.s == 2 ? 175 : 130; // per cent
     if (100 * rows > most * s.H || (s.s == 1 && wgs > 512 && 5 * wgs < 4 * 512 * ((wgs + 511) / 512)))
         return false;
+    // Rows of whole fours, which the separate launches are fastest on: of long contractions a second workgroup to a compute unit
+    // draws or loses (25 shapes, 0.83 to 1.07 of their time; 80 -> 320 on 12x12, 3x3, 16 images 23.4 / 28.1, 32 -> 192 on
+    // 64x64, 3x3, 4 images 30.5 / 34.4; 80 -> 240 on 28x28, 5x5, stride 2, 9 images 25.0 / 28.6), but for stride 2 with 3x3 or up
+    // to 40 channels (32 -> 192 on 36x36, 3x3, 9 images 28.6 / 19.9, on 72x72, 5x5, 3 images 33.7 / 23.3).
+    const bool fours = s.W % 4 == 0;
+    if (*T > 6 && wgs > 256 && fours && (s.s == 1 || (*T > 10 && s.k == 5)))
+        return false;
+    // The longest, which a compute unit has one workgroup of and which take the steps of 192 channels whatever they have, lose
+    // where wavefronts have a second chunk of pixels to take (160 -> 960 on 12x12, 3x3, 3 images 26.5 / 33.3, on 8x8 21.0 / 17.2;
+    // 144 -> 432 on 16x16, 4 images 21.8 / 25.8; 176 -> 528 on 22x22, 2 images 25.6 / 31.8), unless the launch leaves half of
+    // the compute units idle or the channels are whole 64s (192 -> 1152 on 12x12, 3 images 28.0 / 26.2).
+    const int strip = std::min(a.rin, s.H) * s.W;
+    if (*T > 28 && wgs > 128 && s.s == 1 && K % 64 != 0 && s.H * s.W % 4 == 0 && strip > (fours ? 140 : 200))
+        return false;
+    // (four and eight images side by side, rows of an odd number of pairs: 24 -> 144 on 8x6, 376 images 24.6 / 30.5)
+    if (NI >= 4 && s.s == 1 && s.W % 4 == 2 && wgs > 512)
+        return false;
     a.rt = s.s == 1 && a.R * ((s.Wo + 3) / 4) >= 3 * 32 ? 2 : 1;
     a.items = (s.N + NI - 1) / NI * S;
     a.PL = 1;

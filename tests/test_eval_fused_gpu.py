@@ -64,6 +64,11 @@ def test_route(name):
     (64, 16, 64, 127, 127, 5, 1, False), (73, 8, 24, 108, 108, 3, 2, False), (1024, 24, 144, 7, 7, 5, 1, False),
     (8, 16, 96, 72, 72, 3, 1, True), (8, 16, 96, 96, 96, 3, 1, False), (1, 16, 96, 96, 96, 3, 1, True),          # rows computed twice
     (1, 16, 96, 112, 112, 5, 1, False), (8, 16, 96, 72, 72, 5, 2, True), (1, 16, 96, 128, 128, 5, 2, False),
+    (16, 80, 320, 12, 12, 3, 1, False), (12, 80, 320, 12, 12, 3, 1, True), (4, 32, 192, 64, 64, 3, 1, False),     # a second
+    (17, 80, 320, 14, 14, 3, 1, True), (9, 32, 192, 36, 36, 3, 2, True), (9, 80, 240, 28, 28, 5, 2, False),       # round
+    (3, 160, 960, 12, 12, 3, 1, False), (2, 160, 960, 12, 12, 3, 1, True), (3, 176, 1056, 8, 8, 3, 1, True),      # chunks of
+    (4, 144, 432, 16, 16, 3, 1, False), (2, 176, 528, 22, 22, 3, 1, False), (3, 192, 1152, 12, 12, 3, 1, True),   # the longest
+    (376, 24, 144, 8, 6, 3, 1, False), (376, 24, 144, 8, 8, 3, 1, True),
     (1, 8, 24, 110, 82, 3, 2, False),                                            # planes that the depthwise kernels refuse
 ])
 def test_rule(N, Cin, Cexp, H, W, k, s, taken):
