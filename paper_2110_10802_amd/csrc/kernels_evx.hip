@@ -521,6 +521,14 @@ static bool xd_plan(const DwShape &s, int K, XdArgs &a, int *T, int *PX, size_t 
     const int strip = std::min(a.rin, s.H) * s.W;
     if (*T > 28 && wgs > 128 && s.s == 1 && K % 64 != 0 && s.H * s.W % 4 == 0 && strip > (fours ? 140 : 200))
         return false;
+    // Many channels from 17 to 24, stride 2, on large planes: strips that compute an eighth and more twice lose 2 to 11 % once
+    // the launch is several rounds (24 -> 144, 3x3, 56x56, 64 and 72 images 74.0 / 76.1 and 78.0 / 83.0; 64x64, 64 images 85.2 /
+    // 87.2; 22 -> 132 on 112x112, 17 images 75.0 / 83.9), until the expanded tensor that they save no longer lies in the last
+    // cache (52x52, 92 and 123 images 90 / 94 and 129 / 111).  Strips of less than five rows, which the
+    // tile leaves where a plane is wider, bear more (68x68, 119 %, 26 images 64.7 / 56.9).
+    if (s.s == 2 && *T == 6 && a.CG >= 8 && s.H * s.W >= 2500 && wgs > 1750 && (long long)s.N * s.C * s.H * s.W < 40000000 &&
+        100 * rows >= (a.R >= 5 ? 117 : 125) * s.H)
+        return false;
     // (four and eight images side by side, rows of an odd number of pairs: 24 -> 144 on 8x6, 376 images 24.6 / 30.5)
     if (NI >= 4 && s.s == 1 && s.W % 4 == 2 && wgs > 512)
         return false;

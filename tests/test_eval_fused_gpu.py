@@ -68,6 +68,8 @@ def test_route(name):
     (17, 80, 320, 14, 14, 3, 1, True), (9, 32, 192, 36, 36, 3, 2, True), (9, 80, 240, 28, 28, 5, 2, False),       # round
     (3, 160, 960, 12, 12, 3, 1, False), (2, 160, 960, 12, 12, 3, 1, True), (3, 176, 1056, 8, 8, 3, 1, True),      # chunks of
     (4, 144, 432, 16, 16, 3, 1, False), (2, 176, 528, 22, 22, 3, 1, False), (3, 192, 1152, 12, 12, 3, 1, True),   # the longest
+    (64, 24, 144, 56, 56, 3, 2, False), (64, 24, 144, 48, 48, 3, 2, True), (17, 22, 132, 112, 112, 3, 2, False),  # strips of
+    (26, 24, 144, 68, 68, 3, 2, True), (96, 24, 144, 64, 64, 3, 2, True), (30, 24, 144, 56, 56, 3, 2, True),      # stride 2
     (376, 24, 144, 8, 6, 3, 1, False), (376, 24, 144, 8, 8, 3, 1, True),
     (1, 8, 24, 110, 82, 3, 2, False),                                            # planes that the depthwise kernels refuse
 ])
