@@ -1275,7 +1275,12 @@ bool eval_proj_plan(int N, int M, int K, int HW, int Cse, bool act)
     // With the activation still to apply, which each of them repeats, somewhat less (306 -> 34 on 16x16, 15 images, 3600
     // wavefronts, evaluation 23.9 / 24.7; 96 -> 24 on 128x128, one image,
     // 3072, 26.2 / 26.9).
-    return xp_groups(N, M, HW, PX) * KS <= (act ? 2600 : 4096);
+    // With the activation to apply and four pixels to a lane, one workgroup to a compute unit is all that pays (evaluation, SE: 96
+    // -> 24 on 12x12, 58 images, 348 workgroups, 20.7 / 22.3; 114 -> 38 on 16x16, 25 images, 300, 21.9 / 23.2; 96 -> 38 on 8x8,
+    // 56 images, 168, 19.6 / 18.2; no SE: 48 -> 29 on 48x48, 10 images, 720, 12.1 / 13.5), but for short contractions (24 ->
+    // 10 on 68x68, 11 images, 803, 21.7 / 18.5).
+    const long long groups = xp_groups(N, M, HW, PX);
+    return groups * KS <= (act ? 2600 : 4096) && !(act && PX == 4 && KS > (Cse ? 4 : 2) && groups > 256);
 }
 
 hipError_t launch_eval_proj(int N, int M, int K, int HW, int Cse, const void *w, const void *d, const float *bn2,

@@ -92,6 +92,16 @@ def test_matches_oracle(name, variant):
                      activation="relu6" if variant == "relu6" else "swish"), len(name))
 
 
+@pytest.mark.parametrize("N,Cout,Cexp,HW,Cse,act,taken", [
+    (56, 38, 96, 64, 6, True, True), (58, 24, 96, 144, 6, True, False), (25, 38, 114, 256, 9, True, False),  # 256 workgroups
+    (11, 10, 24, 4624, 6, True, True),                                      # of a short contraction: more
+    (10, 29, 48, 2304, 0, True, False), (29, 21, 32, 324, 0, True, True), (58, 24, 96, 144, 6, False, True),
+    (92, 24, 96, 98, 6, True, False), (26, 24, 96, 98, 6, True, True), (26, 40, 480, 98, 6, True, False),  # 2600 wavefronts
+])
+def test_rule_of_the_projection(N, Cout, Cexp, HW, Cse, act, taken):
+    assert projection(N, Cout, Cexp, HW, Cse, act) == taken
+
+
 # A block without SE stage in one launch: (N, Cin, Cexp, Cout, H, W, k)
 WHOLE = {
     "strips_56x56": (21, 24, 144, 24, 56, 56, 3),
