@@ -331,6 +331,7 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
         MBK_STEP(MBCONV_STEP_DW_FWD, launch_eval_block(ds, P.Cin, P.Cout, x, prm->w_expand, prm->w_dw, prm->w_proj,
                                                        P.res ? x : nullptr, out, ev, st));
         MBK_STEP(MBCONV_STEP_PROJ_CONV, hipSuccess);
+        MBK_STEP(MBCONV_STEP_BN3_APPLY, hipSuccess);
         return MBCONV_OK;
     }
     // otherwise: expansion conv and depthwise conv in one launch, nothing of e in memory
@@ -449,6 +450,7 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
                  launch_eval_proj(P.N, P.Cout, P.Cexp, P.HWo, P.Cse, prm->w_proj, d, bn2, bn3,
                                   qparts ? at<float>(saved, P.o_e) : nullptr, qparts, prm->se_b1, prm->se_w2, prm->se_b2,
                                   P.se && !qparts ? g : nullptr, !xd, P.res ? x : nullptr, out, st));
+        MBK_STEP(MBCONV_STEP_BN3_APPLY, hipSuccess);
         return MBCONV_OK;
     }
     // projection conv on Swish(BN2(d))*g + BN3 statistics
@@ -469,8 +471,10 @@ mbconv_status forward_impl(const mbconv_desc *desc, const mbconv_params *prm, mb
                 return fused == hipErrorNotSupported ? hipSuccess : fused;
             };
             MBK_STEP(MBCONV_STEP_PROJ_CONV, try_fused());
-            if (fused == hipSuccess)
+            if (fused == hipSuccess) {
+                MBK_STEP(MBCONV_STEP_BN3_APPLY, hipSuccess);
                 return MBCONV_OK;
+            }
         }
         void *sc_store = (P.store && !eval) ? at<char>(saved, P.o_sc) : nullptr;
         const auto conv = [&]() -> hipError_t {

@@ -143,12 +143,52 @@ def test_whole_block_matches_oracle(name, residual, activation):
                      residual=residual, has_se=False, activation=activation), len(name))
 
 
+# Every step of an evaluation that another launch may have in it: (N, Cin, Cexp, Cout, H, W, k, SE, bf16), the steps that occur
+PROBED = {
+    "one_launch": ((21, 24, 144, 24, 56, 56, 3, False, False), "bn1_finalize expand_conv dw_fwd proj_conv bn3_apply"),
+    "two_launches": ((1, 24, 144, 40, 56, 56, 3, True, False),
+                     "bn1_finalize expand_conv dw_fwd se_pool se_fc proj_conv bn3_apply"),
+    "no_expansion": ((1, 32, 32, 16, 112, 112, 3, True, False), "bn2_finalize dw_fwd se_pool se_fc proj_conv bn3_apply"),
+    "affine_epilogue": ((128, 112, 672, 112, 14, 14, 5, True, True),
+                        "bn1_finalize expand_conv dw_fwd se_pool se_fc proj_conv bn3_apply"),
+    "odd_channels": ((64, 33, 99, 20, 15, 13, 5, True, False),
+                 "bn1_finalize expand_conv dw_fwd se_pool se_fc proj_conv bn3_apply"),
+}
+
+
 @pytest.mark.gpu
-def test_whole_block_probed_and_in_place():
-    """A probe on any step that the launch has in it is recorded; a call whose output lies over its input is not given to
-    this kernel, whose workgroups read each other's rows."""
+@pytest.mark.parametrize("name", list(PROBED))
+def test_every_step_answers_a_probe(name):
     import torch
     from bench import HipEvents
+    from paper_2110_10802_amd import binding as B
+    from paper_2110_10802_amd.harness import DeviceBlock
+
+    (N, Cin, Cexp, Cout, H, W, k, se, bf16), steps = PROBED[name]
+    s = BlockShape(N=N, Cin=Cin, H=H, W=W, Cexp=Cexp, Cse=8, Cout=Cout, k=k, stride=1, has_expand=Cin != Cexp,
+                   residual=Cin == Cout, has_se=se, dtype="bf16" if bf16 else "f32")
+    t = make_block_inputs(s, seed=3)
+    blk = DeviceBlock(s, t)
+    x = blk.to_device(t["x"])
+    blk.forward_eval(x)
+    ev = HipEvents()
+    for step in steps.split():
+        a, b = ev.create(), ev.create()
+        B.mbconv_forward_eval_probed(blk.desc, blk.params, blk.running, x, blk.out, blk.eval_ws, 0,
+                                     B.Probe(B.STEPS[step], a, b))
+        torch.cuda.synchronize()
+        print(f"[probe] {name} {step}", flush=True)
+        ms = ev.elapsed_ms(a, b)  # (an error if the events were not recorded)
+        assert ms > 0.003 or step != "dw_fwd"
+        ev.destroy(a)
+        ev.destroy(b)
+
+
+@pytest.mark.gpu
+def test_whole_block_in_place():
+    """A call whose output lies over its input is not given to the one-launch kernel, whose workgroups read each other's
+    rows."""
+    import torch
     from paper_2110_10802_amd import binding as B
     from paper_2110_10802_amd.harness import DeviceBlock
 
@@ -159,16 +199,6 @@ def test_whole_block_probed_and_in_place():
     blk = DeviceBlock(s, t)
     x = blk.to_device(t["x"])
     want = blk.forward_eval(x).clone()
-    ev = HipEvents()
-    for step in ("bn1_finalize", "expand_conv", "dw_fwd", "proj_conv"):
-        a, b = ev.create(), ev.create()
-        B.mbconv_forward_eval_probed(blk.desc, blk.params, blk.running, x, blk.out, blk.eval_ws, 0,
-                                     B.Probe(B.STEPS[step], a, b))
-        torch.cuda.synchronize()
-        ms = ev.elapsed_ms(a, b)  # (an error if the events were not recorded)
-        assert ms > 0.01 or step != "dw_fwd"
-        ev.destroy(a)
-        ev.destroy(b)
     for _ in range(2):
         y = x.clone()
         B.mbconv_forward_eval(blk.desc, blk.params, blk.running, y, y, blk.eval_ws, 0)
