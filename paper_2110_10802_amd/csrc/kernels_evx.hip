@@ -649,11 +649,11 @@ struct XfArgs {
     float *out;
 };
 
-template <int T, int TP, int PX, int KD, int SD, int MT>
+template <int T, int TP, int PX, int KD, int MT>
 __global__ __launch_bounds__(kXdThreads, 2) void xf_kernel(XfArgs f, DwEval ev)
 {
     const XdArgs &a = f.x;
-    constexpr int threads = kXdThreads, WP = 4 * T + 4, KK = KD * KD, RT = SD == 1 ? 2 : 1;
+    constexpr int threads = kXdThreads, WP = 4 * T + 4, KK = KD * KD, RT = 2;
     constexpr int WL = kXdRows * WP, WB = WL + 256 * MT + kXdRows * KK; // floats of one group's weights
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ float cf3[2 * 16 * MT]; // BN3 {scale, shift}
@@ -663,7 +663,7 @@ __global__ __launch_bounds__(kXdThreads, 2) void xf_kernel(XfArgs f, DwEval ev)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g = lane >> 4;
     const int K = a.K, C = a.C, HW = a.H * a.W;
-    const XdItem it = xd_item<KD, SD>(a, blockIdx.x);
+    const XdItem it = xd_item<KD, 1>(a, blockIdx.x);
 
     // the wavefront's input pixels: column j of the lane is pixel 4r + j, 32 (j/2) + 2r + j%2 or 16j + r
     float b[T][4];
@@ -829,7 +829,7 @@ __global__ __launch_bounds__(kXdThreads, 2) void xf_kernel(XfArgs f, DwEval ev)
             float *dc = dt + ch * f.dstr + dim * a.R * opx;
             for (int i = lt; i < runs; i += tpi) {
                 const int rg = (int)fdiv((uint32_t)i, a.divRuns), j = i - rg * rw, oh = RT * rg;
-                const float *p = tc + 4 * SD * j;
+                const float *p = tc + 4 * j;
                 float o[RT][4];
 #pragma unroll
                 for (int q = 0; q < RT; ++q)
@@ -837,18 +837,18 @@ __global__ __launch_bounds__(kXdThreads, 2) void xf_kernel(XfArgs f, DwEval ev)
                     for (int e = 0; e < 4; ++e)
                         o[q][e] = 0.f;
 #pragma unroll
-                for (int ir = 0; ir < (RT - 1) * SD + KD; ++ir) {
-                    float row[3 * SD + KD];
-                    xd_window<KD, SD>(p + min(oh * SD + ir, a.rin - 1) * a.pitch, row);
+                for (int ir = 0; ir < RT - 1 + KD; ++ir) {
+                    float row[3 + KD];
+                    xd_window<KD, 1>(p + min(oh + ir, a.rin - 1) * a.pitch, row);
 #pragma unroll
                     for (int q = 0; q < RT; ++q) {
-                        const int u = ir - q * SD;
+                        const int u = ir - q;
                         if (u >= 0 && u < KD) {
 #pragma unroll
                             for (int v = 0; v < KD; ++v)
 #pragma unroll
                                 for (int e = 0; e < 4; ++e)
-                                    o[q][e] = fmaf(wt[u * KD + v], row[e * SD + v], o[q][e]);
+                                    o[q][e] = fmaf(wt[u * KD + v], row[e + v], o[q][e]);
                         }
                     }
                 }
@@ -923,9 +923,8 @@ __global__ __launch_bounds__(kXdThreads, 2) void xf_kernel(XfArgs f, DwEval ev)
 static bool xf_plan(const DwShape &s, int K, int M, XfArgs &f, int *T, int *PX, int *MT, size_t *lds)
 {
     XdArgs &a = f.x;
-    if (!xd_form(K, s.W, T, PX) || *T > 10 || M > 64 || s.C > 1024)
-        return false;
-    if (s.s == 2 && s.W % 4 == 2 && s.H % 2 == 0 && s.H * ((s.W + 3) / 4) > 1024) // (as in xd_plan)
+    // (stride 1: with 2 a strip's input is four times its output, 16 -> 96 on 112x112, 64 images 113 us in two launches / 266)
+    if (!xd_form(K, s.W, T, PX) || *T > 10 || M > 64 || s.C > 1024 || s.s != 1)
         return false;
     *T = std::max(*T, 6);
     *MT = M <= 16 ? 1 : M <= 32 ? 2 : 4;
@@ -977,7 +976,7 @@ bool eval_block_plan(const DwShape &s, int K, int M)
     const long long rounds = (f.x.items + 255) / 256, pixels = (long long)s.N * s.Ho * s.Wo + 4000000 / s.C;
     const bool large = (long long)s.N * s.C * s.H * s.W > 60000000;
     const int share = (s.k == 3 ? 55 : 65) + (T > 6 ? 5 : 0) + (M > 32 ? 10 : 0) - (s.W % 4 ? 10 : 0) - (large ? 10 : 0); // per cent
-    return s.s == 1 && f.x.items >= 100 && 100 * pixels >= share * rounds * 256 * 512;
+    return f.x.items >= 100 && 100 * pixels >= share * rounds * 256 * 512;
 }
 
 hipError_t launch_eval_block(const DwShape &s, int K, int M, const void *x, const void *w_expand, const void *w_dw,
@@ -1010,18 +1009,17 @@ hipError_t launch_eval_block(const DwShape &s, int K, int M, const void *x, cons
     f.wp = (const float *)w_proj;
     f.res = (const float *)res;
     f.out = (float *)out;
-#define MBK_GO(T_, TP_, PX_, K_, S_, MT_)                                                         \
-    if (T == T_ && PX == PX_ && s.k == K_ && s.s == S_ && MT == MT_) {                            \
-        auto kern = xf_kernel<T_, TP_, PX_, K_, S_, MT_>;                                         \
+#define MBK_GO(T_, TP_, PX_, K_, MT_)                                                             \
+    if (T == T_ && PX == PX_ && s.k == K_ && MT == MT_) {                                         \
+        auto kern = xf_kernel<T_, TP_, PX_, K_, MT_>;                                             \
         const hipError_t e_ = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
         if (e_ != hipSuccess)                                                                     \
             return e_;                                                                            \
         hipLaunchKernelGGL(kern, dim3(a.items), dim3(kXdThreads), lds, st, f, ev);                \
         return hipGetLastError();                                                                 \
     }
-#define MBK_MT(T_, TP_, PX_, K_, S_) MBK_GO(T_, TP_, PX_, K_, S_, 1) MBK_GO(T_, TP_, PX_, K_, S_, 2) \
-    MBK_GO(T_, TP_, PX_, K_, S_, 4)
-#define MBK_KS(T_, TP_, PX_) MBK_MT(T_, TP_, PX_, 3, 1) MBK_MT(T_, TP_, PX_, 5, 1)
+#define MBK_MT(T_, TP_, PX_, K_) MBK_GO(T_, TP_, PX_, K_, 1) MBK_GO(T_, TP_, PX_, K_, 2) MBK_GO(T_, TP_, PX_, K_, 4)
+#define MBK_KS(T_, TP_, PX_) MBK_MT(T_, TP_, PX_, 3) MBK_MT(T_, TP_, PX_, 5)
 #define MBK_T(T_, TP_) MBK_KS(T_, TP_, 1) MBK_KS(T_, TP_, 2) MBK_KS(T_, TP_, 4)
     MBK_T(6, 0)
     MBK_T(10, 6)
