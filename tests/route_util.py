@@ -46,3 +46,15 @@ def xs_chunks(s):
 def se_bwd_tiled(N, channels, squeezed):
     """Whether the SE backward's two steps are those with a workgroup per sixteen channels."""
     return rule("_ZN3mbk12se_bwd_tiledEiii", BOOL, INT, INT, INT)(N, channels, squeezed)
+
+
+def bw_form(N, M, K, HW, backward):
+    """How the bf16 convolution with resident weights takes an expansion conv (or a projection conv's data gradient): steps of
+    the contraction, chunks of 64 pixels to a wavefront and pixels in the last chunk; None where another kernel runs."""
+    pro, epi = (2, 0) if backward else (0, 1)
+    sets = plan("_ZN3mbk12bw_conv_planEiiiiiiPi", *6 * [INT])(N, M, K, HW, pro, epi)
+    if sets is None or rule("_ZN3mbk14wave_conv_kindEiii", INT, INT, INT, INT)(M, K, HW) or \
+            plan("_ZN3mbk12xk_conv_planEbiiiiiPi", BOOL, *5 * [INT])(True, N, M, K, HW, pro) is not None:
+        return None
+    chunks = -(-N * HW // 64)
+    return -(-K // 32), -(-chunks // (4 * sets)), (N * HW - 1) % 64 + 1

@@ -8,7 +8,7 @@ from mbconv_inputs import BlockShape, make_block_inputs
 from oracle import oracle as orc
 from paper_2110_10802_amd import binding as B
 from parity_util import compare_block, run_gpu_block
-from route_util import INT, plan
+from route_util import INT, bw_form, plan
 
 NONE, BNBWD, STATS, NO_EPILOGUE = 0, 2, 1, 0
 
@@ -27,21 +27,42 @@ def test_rule(N, M, K, HW, pro, taken):
     assert (sets(N, M, K, HW, pro) is not None) == taken
 
 
+# (N, Cin, Cexp, Cout, H, W, stride): of the expansion conv and of the projection conv's data gradient the steps of the
+# contraction, the chunks to a wavefront and the pixels of the last chunk (None: another kernel)
+# (Inputs for which the storage and the operands leave room below the tolerance: tests/rounding_model.py, 64 bits with those
+# roundings, is 1.1e-2 to 1.8e-2 from the oracle in BN1's gamma gradient, the residue of a sum that cancels.  With 672 expanded
+# channels in place of 648 it is 2.17e-2, and this kernel 2.21e-2.)
+FORMS = {
+    (285, 48, 72, 32, 12, 12, 1): ((2, 1, 16), None),           # two slabs, the second of eight rows
+    (85, 72, 200, 88, 16, 17, 1): ((3, 1, 16), (3, 1, 16)),
+    (53, 112, 456, 104, 14, 14, 1): ((4, 1, 20), (4, 1, 20)),   # the last step half full
+    (42, 152, 608, 136, 14, 14, 1): ((5, 1, 40), (5, 1, 40)),
+    (70, 192, 392, 168, 12, 14, 1): ((6, 1, 48), (6, 1, 48)),
+    (33, 40, 640, 64, 18, 18, 2): ((2, 1, 4), None),            # one pixel run in the last chunk; planes of 81
+    (205, 32, 400, 32, 12, 14, 1): ((1, 2, 8), (1, 2, 8)),      # several chunks to a wavefront, in every form
+    (101, 48, 640, 64, 14, 14, 1): ((2, 2, 20), (2, 2, 20)),
+    (301, 72, 264, 96, 12, 12, 1): ((3, 2, 16), (3, 2, 16)),
+    (93, 104, 648, 120, 14, 14, 1): ((4, 2, 52), (4, 2, 52)),
+    (150, 136, 136, 136, 18, 18, 1): ((5, 2, 24), (5, 2, 24)),
+    (75, 168, 392, 168, 18, 18, 1): ((6, 2, 44), (6, 2, 44)),
+}
+
+
+@pytest.mark.parametrize("shape", list(FORMS), ids=str)
+def test_form(shape):
+    N, Cin, Cexp, Cout, H, W, stride = shape
+    Ho, Wo = -(-H // stride), -(-W // stride)
+    # (up to 32 output channels one kernel may compute both gradients of the projection conv)
+    both = plan("_ZN3mbk18projbwd_fused_planEiiiiPi", *4 * [INT])(N, Cexp, Cout, Ho * Wo) is not None
+    assert (bw_form(N, Cexp, Cin, H * W, False), None if both else bw_form(N, Cexp, Cout, Ho * Wo, True)) == FORMS[shape]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("N,Cin,Cexp,Cout,H,W,stride", [
-    (285, 48, 72, 32, 12, 12, 1),    # two steps and one; two slabs, the second of eight rows
-    (85, 72, 200, 88, 16, 17, 1),    # three
-    (53, 112, 456, 104, 14, 14, 1),  # four, the last half full; several chunks to a wavefront
-    (42, 152, 608, 136, 14, 14, 1),  # five
-    (70, 192, 392, 168, 12, 14, 1),  # six
-    (33, 40, 640, 64, 18, 18, 2),    # the data gradient's planes four times smaller
-])
-def test_matches_oracle(N, Cin, Cexp, Cout, H, W, stride):
+@pytest.mark.parametrize("shape", list(FORMS), ids=str)
+def test_matches_oracle(shape):
+    N, Cin, Cexp, Cout, H, W, stride = shape
     s = BlockShape(N=N, Cin=Cin, H=H, W=W, Cexp=Cexp, Cse=8, Cout=Cout, k=3, stride=stride, has_expand=True,
                    residual=False, dtype="bf16")
-    wave = Cin <= 40  # (the register-direct kernels)
-    assert wave or sets(N, Cexp, Cin, H * W, NONE)
-    assert (s.Ho * s.Wo) % 4 or Cout <= 40 or sets(N, Cexp, Cout, s.Ho * s.Wo, BNBWD)
     t = make_block_inputs(s, seed=Cexp)
     print(f"[conv bw] {s}", flush=True)
     res, blk = run_gpu_block(s, t)
