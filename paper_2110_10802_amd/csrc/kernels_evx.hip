@@ -509,10 +509,13 @@ static bool xd_plan(const DwShape &s, int K, XdArgs &a, int *T, int *PX, size_t 
         return false;
     // Rows of whole fours, which the separate launches are fastest on: of long contractions a second workgroup to a compute unit
     // draws or loses (25 shapes, 0.83 to 1.07 of their time; 80 -> 320 on 12x12, 3x3, 16 images 23.4 / 28.1, 32 -> 192 on
-    // 64x64, 3x3, 4 images 30.5 / 34.4; 80 -> 240 on 28x28, 5x5, stride 2, 9 images 25.0 / 28.6), but for stride 2 with 3x3 or up
-    // to 40 channels (32 -> 192 on 36x36, 3x3, 9 images 28.6 / 19.9, on 72x72, 5x5, 3 images 33.7 / 23.3).
+    // 64x64, 3x3, 4 images 30.5 / 34.4; 80 -> 240 on 28x28, 5x5, stride 2, 9 images 25.0 / 28.6), but for stride 2 with 3x3, and up
+    // to 40 channels stride 2 and planes of one strip (32 -> 192 on 36x36, 3x3, stride 2, 9 images 28.6 / 19.9, on 72x72, 5x5, 3
+    // images 33.7 / 23.3; 40 -> 240 on 16x16, 31 images 24.1 / 21.1, but on 12x12, 40 -> 160, 30 images 19.5 / 22.5).
     const bool fours = s.W % 4 == 0;
-    if (*T > 6 && wgs > 256 && fours && (s.s == 1 || (*T > 10 && s.k == 5)))
+    const int runs = a.R * ((s.Wo + 3) / 4);
+    const bool tail = s.k == 3 && runs > 32 && runs < 43; // a second round of a channel's 32 threads for a few runs
+    if (*T > 6 && wgs > 256 && fours && (*T > 10 ? s.s == 1 || s.k == 5 : s.s == 1 && (S > 1 || tail)))
         return false;
     // The longest, which a compute unit has one workgroup of and which take the steps of 192 channels whatever they have, lose
     // where wavefronts have a second chunk of pixels to take (160 -> 960 on 12x12, 3x3, 3 images 26.5 / 33.3, on 8x8 21.0 / 17.2;
@@ -963,20 +966,20 @@ bool eval_block_plan(const DwShape &s, int K, int M)
     // A workgroup takes as long for a strip of a few pixels as for 512, so a round of 256 takes 4 to 6 us for sixteen
     // channels however much of it is output; the other launches take time by the pixel, and some for being two or three. So:
     // the share of the rounds' places that have an output pixel, with what those launches cost counted as pixels. Where it
-    // lies is a fit to 844 blocks measured on more than one route; of the 486 it takes thirteen are 2 to 6 % slower than in
-    // separate launches (one forward pass, ReLU6, best other route / one launch, us). 24 -> 144 -> 24 on 56x56, 3x3, 8
-    // workgroups to an image: 10 images 31.5 / 37.7, 13 39.3 / 37.8, 32 56.5 / 38.9, 33 (a second round) 58.5 / 74.2, 48
-    // 76.7 / 74.7, 64 94.5 / 76.4. 32 -> 192 -> 32 on 28x28, 3x3: 56 images 51.6 / 54.2, 72 57.6 / 54.3, 128 84.6 / 55.8,
-    // 160 96.3 / 107, 192 115 / 107. 40 -> 240 -> 40, 5x5: on 14x14, 320 images 86.6 / 100.5, 400 105 / 102; 26x28, 270
-    // images 247 / 288. Rows of the output past a multiple of sixteen count, too: 24 -> 96 -> 39 on 40x40, 5x5, 126 images
-    // 91 / 116, 32 -> 96 -> 37 on 80x80, 35 images 94 / 107. The other launches are slower on rows that are not whole fours:
-    // 32 -> 128 -> 34 on 81x83, 71 images 386 / 315, 28 -> 84 -> 28 on 45x42, 5x5, 315 images 447 / 305. An expanded tensor
-    // of more than the 256 MB of the last cache costs them, too: 40 -> 160 -> 40 on 68x68, 88 images 364 / 289. Few
-    // workgroups leave the chip empty.
+    // lies is a fit to 1029 blocks measured on more than one route; of the 604 it takes thirteen are 2 to 12 % slower than
+    // in separate launches (one forward pass, ReLU6, best other route / one launch, us). 24 -> 144 -> 24 on 56x56, 3x3, 8
+    // workgroups to an image: 10 images 31.5 / 37.7, 13 39.3 / 37.8, 16 38.7 / 37.9, 32 56.5 / 38.9, 33 (a second round)
+    // 58.5 / 74.2, 48 76.7 / 74.7, 64 94.5 / 76.4. 32 -> 192 -> 32 on 28x28, 3x3: 56 images 51.6 / 54.2, 72 57.6 / 54.3, 128
+    // 84.6 / 55.8, 160 96.3 / 107, 192 115 / 107. 40 -> 240 -> 40, 5x5: on 14x14, 320 images 86.6 / 100.5, 400 105 / 102;
+    // 26x28, 270 images 247 / 288. Rows of the output past a multiple of sixteen count, too: 24 -> 96 -> 39 on 40x40, 5x5,
+    // 126 images 91 / 116, 32 -> 96 -> 37 on 80x80, 35 images 94 / 107. The other launches are slower on rows that are not
+    // whole fours: 32 -> 128 -> 34 on 81x83, 71 images 386 / 315, 28 -> 84 -> 28 on 45x42, 5x5, 315 images 447 / 305. An
+    // expanded tensor of more than the 256 MB of the last cache costs them, too: 40 -> 160 -> 40 on 68x68, 88 images 364 /
+    // 289. Few workgroups leave the chip empty (24 -> 72 -> 36 on 22x22, 67 images, 134 workgroups, 22.8 / 32.7).
     const long long rounds = (f.x.items + 255) / 256, pixels = (long long)s.N * s.Ho * s.Wo + 4000000 / s.C;
     const bool large = (long long)s.N * s.C * s.H * s.W > 60000000;
-    const int share = (s.k == 3 ? 55 : 65) + (T > 6 ? 5 : 0) + (M > 32 ? 10 : 0) - (s.W % 4 ? 10 : 0) - (large ? 10 : 0); // per cent
-    return f.x.items >= 100 && 100 * pixels >= share * rounds * 256 * 512;
+    const int share = (s.k == 3 ? 60 : T > 6 ? 70 : 65) + (M > 32 ? 10 : 0) - (s.W % 4 ? 10 : 0) - (large ? 10 : 0); // per cent
+    return f.x.items >= (M > 32 ? 160 : 100) && 100 * pixels >= share * rounds * 256 * 512;
 }
 
 hipError_t launch_eval_block(const DwShape &s, int K, int M, const void *x, const void *w_expand, const void *w_dw,

@@ -65,7 +65,7 @@ def test_route(name):
     (8, 16, 96, 72, 72, 3, 1, True), (8, 16, 96, 96, 96, 3, 1, False), (1, 16, 96, 96, 96, 3, 1, True),          # rows computed twice
     (1, 16, 96, 112, 112, 5, 1, False), (8, 16, 96, 72, 72, 5, 2, True), (1, 16, 96, 128, 128, 5, 2, False),
     (16, 80, 320, 12, 12, 3, 1, False), (12, 80, 320, 12, 12, 3, 1, True), (4, 32, 192, 64, 64, 3, 1, False),     # a second
-    (17, 80, 320, 14, 14, 3, 1, True), (9, 32, 192, 36, 36, 3, 2, True), (9, 80, 240, 28, 28, 5, 2, False),       # round
+    (17, 80, 320, 14, 14, 3, 1, True), (31, 40, 240, 16, 16, 3, 1, True), (30, 40, 160, 12, 12, 3, 1, False), (9, 32, 192, 36, 36, 3, 2, True), (9, 80, 240, 28, 28, 5, 2, False),       # round
     (3, 160, 960, 12, 12, 3, 1, False), (2, 160, 960, 12, 12, 3, 1, True), (3, 176, 1056, 8, 8, 3, 1, True),      # chunks of
     (4, 144, 432, 16, 16, 3, 1, False), (2, 176, 528, 22, 22, 3, 1, False), (3, 192, 1152, 12, 12, 3, 1, True),   # the longest
     (64, 24, 144, 56, 56, 3, 2, False), (64, 24, 144, 48, 48, 3, 2, True), (17, 22, 132, 112, 112, 3, 2, False),  # strips of
@@ -115,13 +115,13 @@ WHOLE = {
 
 
 @pytest.mark.parametrize("N,Cin,Cexp,Cout,H,W,k,s,taken", [
-    (15, 24, 144, 24, 56, 56, 3, 1, True), (14, 24, 144, 24, 56, 56, 3, 1, False),   # most of a round's places taken,
-    (33, 24, 144, 24, 56, 56, 3, 1, False), (38, 24, 144, 24, 56, 56, 3, 1, True),   # of a second one, too
+    (17, 24, 144, 24, 56, 56, 3, 1, True), (16, 24, 144, 24, 56, 56, 3, 1, False),   # most of a round's places taken,
+    (33, 24, 144, 24, 56, 56, 3, 1, False), (42, 24, 144, 24, 56, 56, 3, 1, True),   # of a second one, too
     (363, 40, 240, 40, 16, 16, 3, 1, True), (128, 40, 240, 40, 16, 16, 3, 1, False), (71, 32, 128, 34, 81, 83, 3, 1, True),
     (132, 32, 192, 23, 24, 24, 3, 1, False), (23, 32, 192, 38, 65, 65, 3, 1, False),  # slower by a third and more
     (126, 24, 96, 39, 40, 40, 5, 1, False), (270, 40, 240, 40, 26, 28, 5, 1, False), (35, 32, 96, 37, 80, 80, 3, 1, False),
     (88, 40, 160, 40, 68, 68, 3, 1, True),                                           # an expanded tensor of 260 MB
-    (99, 8, 48, 8, 16, 16, 3, 1, False), (100, 8, 48, 8, 20, 20, 3, 1, True),        # a hundred workgroups
+    (99, 8, 48, 8, 16, 16, 3, 1, False), (100, 8, 48, 8, 20, 20, 3, 1, True), (67, 24, 72, 36, 22, 22, 3, 1, False),        # a hundred workgroups
     (64, 41, 246, 40, 28, 28, 3, 1, False), (128, 40, 240, 65, 28, 28, 3, 1, False),
     (128, 32, 192, 32, 28, 28, 3, 2, False), (40, 24, 144, 30, 57, 57, 5, 1, False),
 ])
