@@ -14,7 +14,8 @@
 // What bounds it: small launches the chain of one workgroup (a request of 112 -> 672 channels on 14x14: 1.9 us until all loads
 // are issued, 1.3 weights through LDS, 0.7 operands, 1.1 MFMAs, 0.4 into the tile, 1.3 depthwise), large ones the vector
 // work of the two activations and the filter beside the MFMAs, which fp32 MFMAs do not overlap with.  24 -> 144 on 56x56,
-// 32 images, ReLU6: 21.8 + 21.9 us in two launches (e written and read, 116 MB), 34 here.
+// 32 images: 21.8 + 21.9 us in two launches (e written and read, 116 MB), 34 here with ReLU6; with Swish 21.1 + 22.2 and 42.4,
+// VALUBusy 50 %.
 #include "mbconv_dev.h"
 #include "mbconv_launch.h"
 #include "mbconv_eval.h"
